@@ -11,7 +11,7 @@
 // recompute that the value-only rule of Sec. 2.5.1 would need.
 #include <algorithm>
 
-#include "bigrows.h"
+#include "longev.h"
 
 #ifndef INK_EV_INLINE_WIDE
 #define INK_EV_INLINE_WIDE 1       // inline recompute of exposed rows: 0 never, 1 rows of 64 lanes and short launches, 2 also 32 lanes, 3 always
@@ -105,6 +105,11 @@ template <bool IS_MIN, int LPR> __device__ __forceinline__ void reduce_groups_i(
       merge2i<IS_MIN>(ov, oi, os, oj, bv.v[c], bi.v[c], sv.v[c], si.v[c]);
     }
   }
+}
+template <int LPR> __device__ __forceinline__ int reduce_flags(int fl) {
+#pragma unroll
+  for (int off = LPR; off < kWave; off <<= 1) fl |= __shfl_xor(fl, off, kWave);
+  return fl;
 }
 
 // Selection over neighbours ids[j0 .. j1) of one row, by the whole wave.  On return every lane
@@ -429,16 +434,17 @@ template <bool IS_MIN> struct EvAcc {
 //    mask of its own: it never becomes a candidate, and as "new value of the holder" it is a reset;
 //  * an inserted edge cannot name the old holder or runner-up (it was no neighbour), so the id
 //    tests need no kind;
-//  * the runner-up among the candidates is max(cs, min(r, cv)) (mirrored for min) whichever of the
-//    two wins;
+//  * the runner-up among the candidates is the middle one of (r, cv, cs), whichever of the first two
+//    wins, because cs never beats cv;
 //  * TIES false (wave-uniform): the candidates so far are changed sources in ascending id order (the order the
 //    events are created in), so on equal values the earlier one keeps the dimension and the id
 //    comparison is skipped.  The caller sets TIES from a target's first inserted edge on.
-// v_max_f32 / v_min_f32 as they are: the library forms first canonicalise both operands (two more
-// instructions each), which matters in a loop whose time follows its instruction count.  No NaN
-// reaches them (inputs are finite, the sentinels are infinities).
-__device__ __forceinline__ float vmax(float a, float b) { float d; asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b)); return d; }
-__device__ __forceinline__ float vmin(float a, float b) { float d; asm("v_min_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b)); return d; }
+// v_med3_f32 as it is: no NaN reaches it (inputs are finite, the sentinels are infinities).
+__device__ __forceinline__ float vmed3(float a, float b, float c) {
+  float d;
+  asm("v_med3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
 
 template <bool IS_MIN, int U>
 __device__ __forceinline__ void consume_batch(const EvBatch<U> &b, const Cached<IS_MIN> &k, EvAcc<IS_MIN> &s, bool TIES) {
@@ -463,19 +469,39 @@ __device__ __forceinline__ void consume_batch(const EvBatch<U> &b, const Cached<
     }
 #pragma unroll
     for (int c = 0; c < 4; c++) {
-      s.cs.v[c] = IS_MIN ? vmin(s.cs.v[c], vmax(r[c], s.cv.v[c])) : vmax(s.cs.v[c], vmin(r[c], s.cv.v[c]));
+      s.cs.v[c] = vmed3(r[c], s.cv.v[c], s.cs.v[c]);
       s.cv.v[c] = first[c] ? r[c] : s.cv.v[c];
       s.ci.v[c] = first[c] ? id : s.ci.v[c];
     }
   }
 }
 
+// Rows that a launch lists for the kernels after it.  A list has one global counter, and a wave that
+// takes a slot waits for its answer: 131 k exposed rows took 0.4 of 2.4 ms (655 k targets) that way.
+// So a wave keeps its rows in a register, one per lane, and takes their slots together at its end or
+// when the register is full.
+struct RowSink {
+  int n = 0, id = 0;
+  __device__ __forceinline__ void flush(int32_t *list, int32_t *n_list) {
+    if (n == 0) return;
+    int base = 0;
+    if (lane_id() == 0) base = atomicAdd(n_list, n);
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (lane_id() < n) list[base + lane_id()] = id;
+    n = 0;
+  }
+  __device__ __forceinline__ void push(int v, int32_t *list, int32_t *n_list) {     // whole wave, wave-uniform arguments
+    if (lane_id() == n) id = v;
+    if (++n == kWave) flush(list, n_list);
+  }
+};
+
 // The decision for target v once its events are reduced (the lane groups still hold partial
 // results), the recompute of an exposed row of moderate length, and the store.
 template <bool IS_MIN, int LPR, bool INLINE>
 __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cached<IS_MIN> &k, EvAcc<IS_MIN> &s,
                                               bool lane_on, int q, uint64_t *chg, int32_t *big_list, int32_t *exp_list,
-                                              Counters *cnt) {
+                                              RowSink &exp, Counters *cnt) {
   const int l = lane_id();
   const F4 &ov = k.ov; const I4 &oi = k.oi; const F4 &ou = k.ou; const I4 &o2 = k.o2;
   F4 &cv = s.cv; I4 &ci = s.ci; F4 &cs = s.cs;
@@ -483,8 +509,7 @@ __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cac
   unsigned fl = 0u;
 #pragma unroll
   for (int c = 0; c < 4; c++) fl |= ((unsigned)s.reset[c] << c) | ((unsigned)s.inv2[c] << (4 + c));
-#pragma unroll
-  for (int off = LPR; off < kWave; off <<= 1) fl |= (unsigned)__shfl_xor((int)fl, off, kWave);
+  fl = (unsigned)reduce_flags<LPR>((int)fl);
   bool reset[4], inv2[4];
 #pragma unroll
   for (int c = 0; c < 4; c++) { reset[c] = (fl >> c) & 1u; inv2[c] = (fl >> (4 + c)) & 1u; }
@@ -550,7 +575,7 @@ __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cac
     }
   }
   if (exposed) {
-    int deg = a.in_deg[v];
+    const int deg = __builtin_amdgcn_readfirstlane(a.in_deg[v]);
     if (l == 0) {
       if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_EXPOSED], 1ull);
       atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER], (unsigned long long)deg);
@@ -571,10 +596,9 @@ __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cac
       if (deg > a.big_deg) {
         big_list[atomicAdd(&cnt->v[C_NBIG], 1)] = v;
         atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER_LONG], (unsigned long long)deg);
-      } else {
-        exp_list[atomicAdd(&cnt->v[C_NEXP], 1)] = v;
       }
     }
+    if (!INLINE && deg <= a.big_deg) exp.push(v, exp_list, &cnt->v[C_NEXP]);
     return;
   }
   // each half of the cached row is rewritten only if it changed: most targets keep their bound and
@@ -604,13 +628,41 @@ __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cac
 // form is 3 % faster (waves that recompute leave their neighbours in the block waiting), on rows of
 // 256 floats the inline form saves 0.1 of 0.9 ms of aggregation, and on short launches it saves a
 // launch.  The launcher picks per call.
+// The events [e0, e1) of target v into s and the target's cached row into c; every lane group keeps
+// its own partial result.
+template <bool IS_MIN, int LPR>
+__device__ __forceinline__ void reduce_events(const AggArgs &a, int v, const uint32_t *ev, int e0, int e1, bool lane_on, int q,
+                                              Cached<IS_MIN> &c, EvAcc<IS_MIN> &s) {
+  constexpr int G = kWave / LPR;
+  constexpr int U = INK_EV_U;
+  const int l = lane_id();
+  load_cached<IS_MIN>(a, v, lane_on, q, c);
+  s.init();
+  bool ties = false;
+  for (int eb = e0; eb < e1; eb += kWave) {
+    const int ee = eb + l;
+    const uint32_t mine = ee < e1 ? ev[ee] : kEvNone;
+    const int cntw = e1 - eb < kWave ? e1 - eb : kWave;
+    // wave-uniform: from the first inserted edge of the window on, equal values are settled by id
+    const uint64_t adds = __ballot(ee < e1 && (mine >> kEvKindShift) == EV_ADD);
+    s.any_del |= __ballot(ee < e1 && (mine >> kEvKindShift) != EV_ADD) != 0ull;
+    const int first_add = adds ? __builtin_ctzll(adds) : kWave;
+    for (int it = 0; it < cntw; it += G * U) {
+      EvBatch<U> bx;
+      issue_batch<IS_MIN, LPR, U>(a, mine, it, cntw, lane_on, q, bx);
+      ties |= it + G * U > first_add;
+      consume_batch<IS_MIN, U>(bx, c, s, ties);
+    }
+  }
+}
+
 template <bool IS_MIN, int LPR, bool INLINE>
 __global__ __launch_bounds__(256) void k_agg_events(AggArgs a, const int32_t *targets, const int32_t *seg,
                                                     const int32_t *n_targets_p, const uint32_t *ev, uint64_t *chg,
-                                                    int32_t *big_list, int32_t *exp_list, Counters *cnt, int ev_block) {
-  constexpr int G = kWave / LPR;
-  constexpr int U = INK_EV_U;
+                                                    int32_t *big_list, int32_t *exp_list, Counters *cnt, int ev_block,
+                                                    LongEvents lng) {
   static_assert(kEvBlock + 2 <= kWave, "a lane per target and bound of the block");
+  RowSink exp;
   const int l = lane_id();
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
@@ -626,29 +678,101 @@ __global__ __launch_bounds__(256) void k_agg_events(AggArgs a, const int32_t *ta
     for (int t = 0; t < kt; t++) {
       const int v = __builtin_amdgcn_readlane(my_t, t);
       const int e0 = __builtin_amdgcn_readlane(my_s, t), e1 = __builtin_amdgcn_readlane(my_s, t + 1);
+      if (e1 - e0 > lng.limit) { list_long_segment(lng, w0 + t, e1 - e0, cnt); continue; }
       Cached<IS_MIN> c;
-      load_cached<IS_MIN>(a, v, lane_on, q, c);
       EvAcc<IS_MIN> s;
-      s.init();
-      bool ties = false;
-      for (int eb = e0; eb < e1; eb += kWave) {
-        const int ee = eb + l;
-        const uint32_t mine = ee < e1 ? ev[ee] : kEvNone;
-        const int cntw = e1 - eb < kWave ? e1 - eb : kWave;
-        // wave-uniform: from the first inserted edge of the window on, equal values are settled by id
-        const uint64_t adds = __ballot(ee < e1 && (mine >> kEvKindShift) == EV_ADD);
-        s.any_del |= __ballot(ee < e1 && (mine >> kEvKindShift) != EV_ADD) != 0ull;
-        const int first_add = adds ? __builtin_ctzll(adds) : kWave;
-        for (int it = 0; it < cntw; it += G * U) {
-          EvBatch<U> bx;
-          issue_batch<IS_MIN, LPR, U>(a, mine, it, cntw, lane_on, q, bx);
-          ties |= it + G * U > first_add;
-          consume_batch<IS_MIN, U>(bx, c, s, ties);
-        }
-      }
-      finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, big_list, exp_list, cnt);
+      reduce_events<IS_MIN, LPR>(a, v, ev, e0, e1, lane_on, q, c, s);
+      finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, big_list, exp_list, exp, cnt);
     }
   }
+  if constexpr (!INLINE) exp.flush(exp_list, &cnt->v[C_NEXP]);
+}
+
+// What the waves of a long segment's chunk hand on, per dimension: best candidate, its source, the
+// runner-up candidate value, and the flags (bit 0 reset, bit 1 runner-up invalid, bit 2 any_del).
+struct EvPart { float *v; int32_t *i; float *s; int32_t *f; };
+
+// One workgroup per chunk of a long segment: its waves take a quarter of the events each.
+template <bool IS_MIN, int LPR>
+__global__ __launch_bounds__(256) void k_ev_partial(AggArgs a, const int32_t *targets, const int32_t *seg, const uint32_t *ev,
+                                                    LongEvents lng, EvPart part, const Counters *cnt) {
+  constexpr int NW = 4;
+  __shared__ float sv[NW][kWave * 4], ss[NW][kWave * 4];
+  __shared__ int si[NW][kWave * 4], sf[NW][kWave * 4];
+  const int l = lane_id(), w = threadIdx.x / kWave;
+  const int q = l % LPR;
+  const bool lane_on = 4 * q < a.wd;
+  const int total = cnt->v[C_NEVCH];
+  for (int ch = blockIdx.x; ch < total; ch += gridDim.x) {
+    int e0, e1;
+    const int v = targets[long_chunk(lng, ch, seg, e0, e1)];
+    const int len = e1 - e0;
+    Cached<IS_MIN> c;
+    EvAcc<IS_MIN> s;
+    reduce_events<IS_MIN, LPR>(a, v, ev, e0 + len * w / NW, e0 + len * (w + 1) / NW, lane_on, q, c, s);
+    reduce_groups<IS_MIN, LPR>(s.cv, s.ci, s.cs);
+    int fl[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      fl[k] = reduce_flags<LPR>((int)s.reset[k] | ((int)s.inv2[k] << 1) | ((int)s.any_del << 2));
+      sv[w][l * 4 + k] = s.cv.v[k]; si[w][l * 4 + k] = s.ci.v[k]; ss[w][l * 4 + k] = s.cs.v[k]; sf[w][l * 4 + k] = fl[k];
+    }
+    __syncthreads();
+    if (w == 0 && lane_on && l < LPR) {
+      for (int ww = 1; ww < NW; ww++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+          merge2<IS_MIN>(sv[ww][l * 4 + k], si[ww][l * 4 + k], ss[ww][l * 4 + k], s.cv.v[k], s.ci.v[k], s.cs.v[k]);
+          fl[k] |= sf[ww][l * 4 + k];
+        }
+      const int64_t o = (int64_t)ch * a.wd + 4 * q;
+      *reinterpret_cast<float4 *>(part.v + o) = make_float4(s.cv.v[0], s.cv.v[1], s.cv.v[2], s.cv.v[3]);
+      *reinterpret_cast<int4 *>(part.i + o) = make_int4(s.ci.v[0], s.ci.v[1], s.ci.v[2], s.ci.v[3]);
+      *reinterpret_cast<float4 *>(part.s + o) = make_float4(s.cs.v[0], s.cs.v[1], s.cs.v[2], s.cs.v[3]);
+      *reinterpret_cast<int4 *>(part.f + o) = make_int4(fl[0], fl[1], fl[2], fl[3]);
+    }
+    __syncthreads();
+  }
+}
+
+// One wave per long segment: its lane groups take the chunks in turn, then the target is decided.
+template <bool IS_MIN, int LPR, bool INLINE>
+__global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targets, const int32_t *seg, LongEvents lng,
+                                                 EvPart part, uint64_t *chg, int32_t *big_list, int32_t *exp_list,
+                                                 Counters *cnt) {
+  constexpr int G = kWave / LPR;
+  RowSink exp;
+  const int l = lane_id(), q = l % LPR, g = l / LPR;
+  const bool lane_on = 4 * q < a.wd;
+  const int n = cnt->v[C_NEVL];
+  for (int i = blockIdx.x; i < n; i += gridDim.x) {
+    const LongSeg L = lng.list[i];
+    const int v = targets[L.target];
+    const int nch = (seg[L.target + 1] - seg[L.target] + kEvChunk - 1) / kEvChunk;
+    Cached<IS_MIN> c;
+    load_cached<IS_MIN>(a, v, lane_on, q, c);
+    EvAcc<IS_MIN> s;
+    s.init();
+    int fl = 0;
+    if (lane_on)
+      for (int p = g; p < nch; p += G) {
+        const int64_t o = (int64_t)(L.base + p) * a.wd + 4 * q;
+        const float4 pv = ld4(part.v + o), ps = ld4(part.s + o);
+        const int4 pi = *reinterpret_cast<const int4 *>(part.i + o), pf = *reinterpret_cast<const int4 *>(part.f + o);
+        const float xv[4] = {pv.x, pv.y, pv.z, pv.w}, xs[4] = {ps.x, ps.y, ps.z, ps.w};
+        const int xi[4] = {pi.x, pi.y, pi.z, pi.w}, xf[4] = {pf.x, pf.y, pf.z, pf.w};
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+          merge2<IS_MIN>(xv[k], xi[k], xs[k], s.cv.v[k], s.ci.v[k], s.cs.v[k]);
+          s.reset[k] |= (xf[k] & 1) != 0;
+          s.inv2[k] |= (xf[k] & 2) != 0;
+          fl |= xf[k];
+        }
+      }
+    s.any_del = __ballot((fl & 4) != 0) != 0ull;
+    finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, big_list, exp_list, exp, cnt);
+  }
+  if constexpr (!INLINE) exp.flush(exp_list, &cnt->v[C_NEXP]);
 }
 
 // ------------------------------------------------------------------ host side
@@ -699,29 +823,43 @@ static hipError_t full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targets
   return run_big<IS_MIN, LPR>(c, a, chg, compare, big_block_threads(n_targets), n_targets);
 }
 
+template <bool IS_MIN, int LPR, bool INLINE>
+static hipError_t launch_events(ink_ctx *c, const AggArgs &a, const int32_t *targets, const int32_t *seg, int64_t n_targets,
+                                const int32_t *n_targets_dev, const uint32_t *ev, const EventBounds &eb, uint64_t *chg) {
+  KernelTimer kt(c, a.layer, INK_K_AGG_EVENTS);
+  const bool latency = latency_mode(n_targets);
+  // few targets per wave visit while the launch has fewer blocks than the chip has waves to spread them over
+  const int ev_block = (int)std::max<int64_t>(1, std::min<int64_t>(kEvBlock, n_targets / 32768));
+  int64_t blocks = std::min<int64_t>(((n_targets + ev_block - 1) / ev_block + 3) / 4, INK_EVENT_GRID);
+  LongEvents lng{nullptr, nullptr, latency ? kEvLongLatency : kEvLong};
+  INK_TRY(ensure_long_events(c, eb, a.wd, true, &lng));
+  int32_t *big_list = c->big_list.as<int32_t>(), *exp_list = c->exp_list.as<int32_t>();
+  hipLaunchKernelGGL((k_agg_events<IS_MIN, LPR, INLINE>), dim3((unsigned)blocks), dim3(256), 0, c->stream, a, targets, seg,
+                     n_targets_dev, ev, chg, big_list, exp_list, c->d_cnt, ev_block, lng);
+  if (eb.max_seg > lng.limit) {      // otherwise no segment can be long
+    EvPart part{c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>()};
+    hipLaunchKernelGGL((k_ev_partial<IS_MIN, LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(eb.n_events, lng.limit), 8192)),
+                       dim3(256), 0, c->stream, a, targets, seg, ev, lng, part, (const Counters *)c->d_cnt);
+    hipLaunchKernelGGL((k_ev_final<IS_MIN, LPR, INLINE>), dim3((unsigned)std::min<int64_t>(long_ev_rows(eb.n_events, lng.limit), 8192)),
+                       dim3(64), 0, c->stream, a, targets, seg, lng, part, chg, big_list, exp_list, c->d_cnt);
+  }
+  return hipGetLastError();
+}
+
 // n_targets may be an upper bound: the kernel stops at the device-side count n_targets_dev.
-// Exposed rows are listed by the event kernel and recomputed by the two launches after it.
+// Exposed rows are listed by the event kernels and recomputed by the two launches after them.
 template <bool IS_MIN, int LPR>
 static hipError_t events_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targets, const int32_t *seg,
-                           int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev, uint64_t *chg) {
+                           int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev, const EventBounds &eb,
+                           uint64_t *chg) {
   if (n_targets <= 0) return hipSuccess;
   AggArgs a = a_in;
   a.big_deg = big_threshold(n_targets, LPR, kBigDeg);
   INK_TRY(ensure_big_buffers(c, a.wd, true));
   INK_TRY(c->exp_list.reserve((size_t)n_targets * 4));
-  const int ev_block = latency_mode(n_targets) ? 1 : kEvBlock;
-  int64_t blocks = std::min<int64_t>(((n_targets + ev_block - 1) / ev_block + 3) / 4, INK_EVENT_GRID);
   const bool inline_exposed = INK_EV_INLINE_WIDE == 0 ? false : (LPR >= (INK_EV_INLINE_WIDE == 1 ? 64 : (INK_EV_INLINE_WIDE == 2 ? 32 : 16)) || latency_mode(n_targets));
-  {
-    KernelTimer kt(c, a.layer, INK_K_AGG_EVENTS);
-    if (inline_exposed)
-      hipLaunchKernelGGL((k_agg_events<IS_MIN, LPR, true>), dim3((unsigned)blocks), dim3(256), 0, c->stream, a, targets, seg,
-                         n_targets_dev, ev, chg, c->big_list.as<int32_t>(), c->exp_list.as<int32_t>(), c->d_cnt, ev_block);
-    else
-      hipLaunchKernelGGL((k_agg_events<IS_MIN, LPR, false>), dim3((unsigned)blocks), dim3(256), 0, c->stream, a, targets, seg,
-                         n_targets_dev, ev, chg, c->big_list.as<int32_t>(), c->exp_list.as<int32_t>(), c->d_cnt, ev_block);
-    INK_TRY(hipGetLastError());
-  }
+  if (inline_exposed) INK_TRY((launch_events<IS_MIN, LPR, true>(c, a, targets, seg, n_targets, n_targets_dev, ev, eb, chg)));
+  else INK_TRY((launch_events<IS_MIN, LPR, false>(c, a, targets, seg, n_targets, n_targets_dev, ev, eb, chg)));
   if (!inline_exposed) {
     KernelTimer kt(c, a.layer, INK_K_AGG_EXPOSED);
     int64_t rb = std::min<int64_t>((n_targets + 3) / 4, latency_mode(n_targets) ? 2048 : 16384);
@@ -753,8 +891,9 @@ hipError_t agg_select_full(ink_ctx *c, const AggArgs &a, const int32_t *targets,
 }
 
 hipError_t agg_select_events(ink_ctx *c, const AggArgs &a, const int32_t *targets, const int32_t *seg,
-                             int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, uint64_t *chg) {
-  DISPATCH(events_t, c, a, targets, seg, n_targets, n_targets_dev, ev_val, chg);
+                             int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, const EventBounds &eb,
+                             uint64_t *chg) {
+  DISPATCH(events_t, c, a, targets, seg, n_targets, n_targets_dev, ev_val, eb, chg);
 }
 
 }  // namespace ink

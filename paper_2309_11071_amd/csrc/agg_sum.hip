@@ -7,7 +7,7 @@
 // groups are combined in a fixed pattern: results are reproducible run to run.
 #include <algorithm>
 
-#include "bigrows.h"
+#include "longev.h"
 
 namespace ink {
 
@@ -198,22 +198,17 @@ __global__ void k_delta_rows(const float *M, int ldm, const int32_t *F, int nF, 
   if (i < nF) f_delta[i * ld_old + k] = __fsub_rn(M[(int64_t)F[i] * ldm + k], f_old[i * ld_old + k]);
 }
 
+struct SumSources {             // the changed sources of the layer and their rows
+  const int32_t *F; int nF;
+  const float *f_old, *f_delta; int ld_old;
+};
+
+// adds the events [e0, e1) of one target to acc: lane group g takes e0 + g, e0 + g + G, ... in order
 template <int LPR>
-__global__ __launch_bounds__(256) void k_sum_events(AggArgs a, const int32_t *targets, const int32_t *seg,
-                                                    const int32_t *n_targets_p, const uint32_t *ev, const int32_t *F,
-                                                    int nF, const float *f_old, const float *f_delta, int ld_old,
-                                                    uint64_t *chg, Counters *cnt) {
+__device__ __forceinline__ void sum_event_range(const AggArgs &a, const uint32_t *ev, int e0, int e1, const SumSources &src,
+                                                bool lane_on, int q, S4 &acc) {
   constexpr int G = kWave / LPR;
-  const int l = lane_id();
-  const int q = l % LPR, g = l / LPR;
-  const bool lane_on = 4 * q < a.wd;
-  int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  if (wid >= *n_targets_p) return;
-  int v = targets[wid];
-  int e0 = seg[wid], e1 = seg[wid + 1];
-  S4 acc;
-#pragma unroll
-  for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
+  const int l = lane_id(), g = l / LPR;
   for (int eb = e0; eb < e1; eb += kWave) {
     int ee = eb + l;
     uint32_t mine = ee < e1 ? ev[ee] : 0xFFFFFFFFu;
@@ -233,12 +228,12 @@ __global__ __launch_bounds__(256) void k_sum_events(AggArgs a, const int32_t *ta
           uint32_t kind = x >> kEvKindShift;
           int id = (int)(x & kEvIdMask);
           if (kind == EV_CHG) {          // id = position of the source in F: add (new - old)
-            p[u] = f_delta + (int64_t)id * ld_old + 4 * q;
+            p[u] = src.f_delta + (int64_t)id * src.ld_old + 4 * q;
           } else if (kind == EV_ADD) {
             p[u] = a.M + (int64_t)id * a.ldm + 4 * q;
           } else {                        // removed edge: subtract what the source contributed before
-            int pos = nF > 0 ? find_in(F, nF, id) : -1;
-            p[u] = pos >= 0 ? f_old + (int64_t)pos * ld_old + 4 * q : a.M + (int64_t)id * a.ldm + 4 * q;
+            int pos = src.nF > 0 ? find_in(src.F, src.nF, id) : -1;
+            p[u] = pos >= 0 ? src.f_old + (int64_t)pos * src.ld_old + 4 * q : a.M + (int64_t)id * a.ldm + 4 * q;
             neg[u] = true;
           }
           r[u] = ldf4(p[u]);
@@ -257,7 +252,11 @@ __global__ __launch_bounds__(256) void k_sum_events(AggArgs a, const int32_t *ta
       }
     }
   }
-  sum_groups<LPR>(acc);
+}
+
+// cached row of v plus acc, stored if it changed
+template <int LPR>
+__device__ __forceinline__ void add_to_row(const AggArgs &a, int v, bool lane_on, int q, const S4 &acc, uint64_t *chg, Counters *cnt) {
   S4 nv;
 #pragma unroll
   for (int c = 0; c < 4; c++) nv.v[c] = 0.f;
@@ -267,7 +266,82 @@ __global__ __launch_bounds__(256) void k_sum_events(AggArgs a, const int32_t *ta
     nv.v[2] = __fadd_rn(o.z, acc.v[2]); nv.v[3] = __fadd_rn(o.w, acc.v[3]);
   }
   bool ch = store_sum<LPR>(a.A, a.ld, a.d, v, lane_on, q, nv, true);
-  if (ch && l == 0) { mark_bit_s(chg, v); if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull); }
+  if (ch && lane_id() == 0) { mark_bit_s(chg, v); if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull); }
+}
+
+template <int LPR>
+__global__ __launch_bounds__(256) void k_sum_events(AggArgs a, const int32_t *targets, const int32_t *seg,
+                                                    const int32_t *n_targets_p, const uint32_t *ev, SumSources src,
+                                                    uint64_t *chg, Counters *cnt, LongEvents lng) {
+  const int q = lane_id() % LPR;
+  const bool lane_on = 4 * q < a.wd;
+  int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+  if (wid >= *n_targets_p) return;
+  int e0 = __builtin_amdgcn_readfirstlane(seg[wid]), e1 = __builtin_amdgcn_readfirstlane(seg[wid + 1]);
+  if (e1 - e0 > lng.limit) { list_long_segment(lng, (int)wid, e1 - e0, cnt); return; }
+  S4 acc;
+#pragma unroll
+  for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
+  sum_event_range<LPR>(a, ev, e0, e1, src, lane_on, q, acc);
+  sum_groups<LPR>(acc);
+  add_to_row<LPR>(a, targets[wid], lane_on, q, acc, chg, cnt);
+}
+
+// one workgroup per chunk of a long segment, its waves take a quarter of the events each
+template <int LPR>
+__global__ __launch_bounds__(256) void k_sum_ev_partial(AggArgs a, const int32_t *seg, const uint32_t *ev, SumSources src,
+                                                        LongEvents lng, float *part, const Counters *cnt) {
+  constexpr int NW = 4;
+  __shared__ float sv[NW][kWave * 4];
+  const int l = lane_id(), w = threadIdx.x / kWave;
+  const int q = l % LPR;
+  const bool lane_on = 4 * q < a.wd;
+  const int total = cnt->v[C_NEVCH];
+  for (int ch = blockIdx.x; ch < total; ch += gridDim.x) {
+    int e0, e1;
+    long_chunk(lng, ch, seg, e0, e1);
+    const int len = e1 - e0;
+    S4 acc;
+#pragma unroll
+    for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
+    sum_event_range<LPR>(a, ev, e0 + len * w / NW, e0 + len * (w + 1) / NW, src, lane_on, q, acc);
+    sum_groups<LPR>(acc);
+#pragma unroll
+    for (int c = 0; c < 4; c++) sv[w][l * 4 + c] = acc.v[c];
+    __syncthreads();
+    if (w == 0 && lane_on && l < LPR) {
+      for (int ww = 1; ww < NW; ww++)
+#pragma unroll
+        for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], sv[ww][l * 4 + c]);
+      *reinterpret_cast<float4 *>(part + (int64_t)ch * a.wd + 4 * q) = make_float4(acc.v[0], acc.v[1], acc.v[2], acc.v[3]);
+    }
+    __syncthreads();
+  }
+}
+
+// one wave per long segment: its lane groups take the chunks in turn
+template <int LPR>
+__global__ __launch_bounds__(64) void k_sum_ev_final(AggArgs a, const int32_t *targets, const int32_t *seg, LongEvents lng,
+                                                     const float *part, uint64_t *chg, Counters *cnt) {
+  constexpr int G = kWave / LPR;
+  const int l = lane_id(), q = l % LPR, g = l / LPR;
+  const bool lane_on = 4 * q < a.wd;
+  const int n = cnt->v[C_NEVL];
+  for (int i = blockIdx.x; i < n; i += gridDim.x) {
+    const LongSeg L = lng.list[i];
+    const int nch = (seg[L.target + 1] - seg[L.target] + kEvChunk - 1) / kEvChunk;
+    S4 acc;
+#pragma unroll
+    for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
+    if (lane_on)
+      for (int p = g; p < nch; p += G) {
+        const float4 x = ldf4(part + (int64_t)(L.base + p) * a.wd + 4 * q);
+        acc.v[0] = __fadd_rn(acc.v[0], x.x); acc.v[1] = __fadd_rn(acc.v[1], x.y);
+        acc.v[2] = __fadd_rn(acc.v[2], x.z); acc.v[3] = __fadd_rn(acc.v[3], x.w);
+      }
+    sum_groups<LPR>(acc);
+    add_to_row<LPR>(a, targets[L.target], lane_on, q, acc, chg, cnt);
+  }
 }
 
 static int lanes_per_row(int ld) { return ld <= 64 ? 16 : (ld <= 128 ? 32 : 64); }
@@ -304,12 +378,21 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
 
 template <int LPR>
 static hipError_t sum_events_t(ink_ctx *c, const AggArgs &a, const int32_t *targets, const int32_t *seg,
-                               int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev, const int32_t *F,
-                               int nF, const float *f_old, const float *f_delta, int ld_old, uint64_t *chg) {
+                               int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev, const EventBounds &eb,
+                               const SumSources &src, uint64_t *chg) {
   if (n_targets <= 0) return hipSuccess;
   KernelTimer kt(c, a.layer, INK_K_AGG_EVENTS);
+  LongEvents lng{nullptr, nullptr, latency_mode(n_targets) ? kEvLongLatency : kEvLong};
+  INK_TRY(ensure_long_events(c, eb, a.wd, false, &lng));
   hipLaunchKernelGGL((k_sum_events<LPR>), dim3((unsigned)((n_targets + 3) / 4)), dim3(256), 0, c->stream, a, targets,
-                     seg, n_targets_dev, ev, F, nF, f_old, f_delta, ld_old, chg, c->d_cnt);
+                     seg, n_targets_dev, ev, src, chg, c->d_cnt, lng);
+  if (eb.max_seg > lng.limit) {      // otherwise no segment can be long
+    float *part = c->big_part_v.as<float>();
+    hipLaunchKernelGGL((k_sum_ev_partial<LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(eb.n_events, lng.limit), 8192)),
+                       dim3(256), 0, c->stream, a, seg, ev, src, lng, part, (const Counters *)c->d_cnt);
+    hipLaunchKernelGGL((k_sum_ev_final<LPR>), dim3((unsigned)std::min<int64_t>(long_ev_rows(eb.n_events, lng.limit), 8192)),
+                       dim3(64), 0, c->stream, a, targets, seg, lng, (const float *)part, chg, c->d_cnt);
+  }
   return hipGetLastError();
 }
 
@@ -323,12 +406,13 @@ hipError_t agg_sum_full(ink_ctx *c, const AggArgs &a, const int32_t *targets, in
 }
 
 hipError_t agg_sum_events(ink_ctx *c, const AggArgs &a, const int32_t *targets, const int32_t *seg,
-                          int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, const int32_t *F,
-                          int nF, const float *f_old, const float *f_delta, int ld_old, uint64_t *chg) {
+                          int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, const EventBounds &eb,
+                          const int32_t *F, int nF, const float *f_old, const float *f_delta, int ld_old, uint64_t *chg) {
+  const SumSources src{F, nF, f_old, f_delta, ld_old};
   switch (lanes_per_row(a.wd)) {
-    case 16: return sum_events_t<16>(c, a, targets, seg, n_targets, n_targets_dev, ev_val, F, nF, f_old, f_delta, ld_old, chg);
-    case 32: return sum_events_t<32>(c, a, targets, seg, n_targets, n_targets_dev, ev_val, F, nF, f_old, f_delta, ld_old, chg);
-    default: return sum_events_t<64>(c, a, targets, seg, n_targets, n_targets_dev, ev_val, F, nF, f_old, f_delta, ld_old, chg);
+    case 16: return sum_events_t<16>(c, a, targets, seg, n_targets, n_targets_dev, ev_val, eb, src, chg);
+    case 32: return sum_events_t<32>(c, a, targets, seg, n_targets, n_targets_dev, ev_val, eb, src, chg);
+    default: return sum_events_t<64>(c, a, targets, seg, n_targets, n_targets_dev, ev_val, eb, src, chg);
   }
 }
 

@@ -797,7 +797,7 @@ extern "C" void ink_destroy(ink_ctx *c) {
   if (c->bm_a) (void)hipFree(c->bm_a);
   for (DevBuf *b : {&c->ws.blk, &c->ws.hist, &c->ws.tmpk, &c->ws.tmpv, &c->b_raw, &c->b_misc, &c->b_uniq, &c->b_del_s,
                     &c->b_del_d, &c->b_ins_s, &c->b_ins_d, &c->f_list[0], &c->f_list[1], &c->f_old[0], &c->f_old[1],
-                    &c->f_pref, &c->ev_key, &c->ev_val, &c->t_list, &c->t_seg, &c->c_list, &c->c_flag, &c->c_idx, &c->c_old,
+                    &c->f_pref, &c->ev_key, &c->ev_val, &c->t_list, &c->t_seg, &c->evl_list, &c->evl_owner, &c->c_list, &c->c_flag, &c->c_idx, &c->c_old,
                     &c->b_touch_in,
                     &c->u_ev, &c->u_rows, &c->u_key, &c->u_val, &c->u_uniq, &c->u_seg, &c->u_flag, &c->u_idx, &c->u_list, &c->exp_list, &c->big_list, &c->big_part_v, &c->big_part_i, &c->big_part_s, &c->big_part_j, &c->big_pref, &c->f_delta, &c->stage0, &c->stage1, &c->res_ids, &c->res_emb})
     b->release();
@@ -1056,16 +1056,17 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
       API_TRY(c->f_delta.reserve((size_t)nF * ld_old * 4));
       API_TRY(agg_sum_delta_rows(c, a, F, (int)nF, f_old, c->f_delta.as<float>(), ld_old));
     }
+    const EventBounds eb{nE, nF + n_seed};      // a source or a changed edge names a target once
     for (int b = 0; b < agg_blocks(a); b++) {
       AggArgs ab = agg_block(a, b);
       int c0 = b * kAggBlock;
-      if (b > 0) API_TRY(hipMemsetAsync(&dc->v[C_NBIG], 0, 2 * sizeof(int32_t), s));   // long and exposed row lists
+      if (b > 0) API_TRY(hipMemsetAsync(&dc->v[C_NBIG], 0, 4 * sizeof(int32_t), s));   // lists of long rows, exposed rows and long segments
       if (c->is_select)
         API_TRY(agg_select_events(c, ab, c->t_list.as<int32_t>(), c->t_seg.as<int32_t>(), nT, &dc->v[C_NT],
-                                  c->ev_val.as<uint32_t>(), bm));
+                                  c->ev_val.as<uint32_t>(), eb, bm));
       else
         API_TRY(agg_sum_events(c, ab, c->t_list.as<int32_t>(), c->t_seg.as<int32_t>(), nT, &dc->v[C_NT],
-                               c->ev_val.as<uint32_t>(), F, (int)nF, f_old ? f_old + c0 : nullptr,
+                               c->ev_val.as<uint32_t>(), eb, F, (int)nF, f_old ? f_old + c0 : nullptr,
                                c->f_delta.as<float>() ? c->f_delta.as<float>() + c0 : nullptr, ld_old, bm));
     }
   }

@@ -97,8 +97,17 @@ struct HostCounters {
 // (C_NEXP: exposed rows of moderate length listed for the recompute, next to the long ones in C_NBIG)
 // touched nodes and block chunks of the out side (single-workgroup graph stage), and two 64-bit
 // slots (pool tops handed to the apply kernels).  Slot 0 flags a malformed update batch.
-enum { C_ERR = 0, C_NEV = 1, C_NT, C_NBIG, C_NEXP, C_NC, C_NEXT, C_NCHUNK, C_NOPS, C_TMP0, C_TMP1, C_TMP2, C_TMP3,
-       C_OT, C_OCH, C_TOP64 = 16, C_TOP64B = 18 };
+// (C_NEVL, C_NEVCH: targets with a long event segment and the chunks of those segments)
+enum { C_ERR = 0, C_NEV = 1, C_NT, C_NBIG, C_NEXP, C_NEVL, C_NEVCH, C_NC, C_NEXT, C_NCHUNK, C_NOPS, C_TMP0, C_TMP1,
+       C_TMP2, C_TMP3, C_OT, C_OCH, C_TOP64 = 18, C_TOP64B = 20 };
+
+// A target with more than this many events is reduced by many waves (longev.h) instead of one.
+// 128 makes the lists and partial rows of a large launch cost more than the chains they cut (17 M
+// events: 2.0 against 1.75 ms), 512 leaves visible chains in mid-size ones (470 k events: 0.25
+// against 0.21 ms).
+constexpr int kEvLong = 256;          // large launches
+constexpr int kEvLongLatency = 128;   // launches of few targets, where one wave's chain is the launch's time
+constexpr int kEvChunk = 256;         // events of such a segment per workgroup
 
 }  // namespace ink
 
@@ -159,6 +168,7 @@ struct ink_ctx {
   ink::DevBuf b_touch_in;            // destinations touched by the current batch
   int64_t n_touched_in = 0;
   ink::DevBuf exp_list;              // exposed rows of moderate length, listed by the event kernel
+  ink::DevBuf evl_list, evl_owner;   // targets with long event segments, and the owner of each chunk of them
   ink::DevBuf big_list, big_part_v, big_part_i, big_part_s, big_part_j, big_pref;   // cooperative re-gather of long rows
   ink::DevBuf stage0, stage1;        // transform staging
   ink::DevBuf res_ids, res_emb;      // result of the last batch
@@ -224,15 +234,17 @@ struct AggArgs {
 // alpha changed in bitmap `chg` (may be null); big rows go through the cooperative path
 hipError_t agg_select_full(ink_ctx *c, const AggArgs &a, const int32_t *targets, int64_t n_targets,
                            uint64_t *chg);
+struct EventBounds { int64_t n_events, max_seg; };    // events of the layer; most events one target can have
 // n_targets may be an upper bound of the device-side count *n_targets_dev
 hipError_t agg_select_events(ink_ctx *c, const AggArgs &a, const int32_t *targets, const int32_t *seg,
-                             int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, uint64_t *chg);
+                             int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, const EventBounds &eb,
+                             uint64_t *chg);
 // sum-type aggregators (agg_sum.hip): A holds the plain sum of message rows.  F (ascending ids)
 // and f_old (their previous message rows, row stride ld_old) describe the changed sources.
 hipError_t agg_sum_full(ink_ctx *c, const AggArgs &a, const int32_t *targets, int64_t n_targets, uint64_t *chg);
 hipError_t agg_sum_events(ink_ctx *c, const AggArgs &a, const int32_t *targets, const int32_t *seg,
-                          int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, const int32_t *F,
-                          int nF, const float *f_old, const float *f_delta, int ld_old, uint64_t *chg);
+                          int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, const EventBounds &eb,
+                          const int32_t *F, int nF, const float *f_old, const float *f_delta, int ld_old, uint64_t *chg);
 // f_delta[i] = M[F[i]] - f_old[i] (row stride ld_old): what a kept edge of changed source i adds
 hipError_t agg_sum_delta_rows(ink_ctx *c, const AggArgs &a, const int32_t *F, int nF, const float *f_old,
                               float *f_delta, int ld_old);
