@@ -44,15 +44,6 @@ __device__ __forceinline__ void seed_event(int i, const int32_t *del_s, const in
   }
 }
 
-// deletions go to [0, n_del), insertions behind the n_chg events of the changed sources
-__global__ void k_seed_events(const int32_t *del_s, const int32_t *del_d, const int32_t *ins_s, const int32_t *ins_d,
-                              int n_del, int n_ins, int64_t n_chg, uint32_t *key, uint32_t *val) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_del + n_ins) return;
-  const int64_t p = i < n_del ? i : i + n_chg;
-  seed_event((int)i, del_s, del_d, ins_s, ins_d, n_del, &key[p], &val[p]);
-}
-
 // out-edges of a changed source that exist in both snapshots: the block minus the ids appended
 // by this batch
 struct KeptOutDeg {
@@ -81,31 +72,64 @@ __device__ __forceinline__ void expand_event(int e, const int32_t *F, int nF, co
   *val = (EV_CHG << kEvKindShift) | (uint32_t)(payload_index ? lo : u);
 }
 
-// A wave creates kExpandPerWave consecutive events.  It finds the sources of its first and last
-// event with two wave-wide searches (64 probes per round); a lane then looks for the source of each
-// of its events only between those two, usually one or two candidates, instead of searching the
-// whole prefix array once per event.
-constexpr int kExpandPerWave = 4 * kWave;
-__global__ __launch_bounds__(256) void k_expand_events(const int32_t *F, int nF, const int32_t *pref, int n_ev,
-                                                       const int64_t *off, const int32_t *ids, uint32_t *key,
-                                                       uint32_t *val, int payload_index) {
-  const int l = lane_id();
-  const int64_t wv = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int64_t e_base = wv * kExpandPerWave;
-  if (e_base >= n_ev) return;
-  const int e_end = (int)(e_base + kExpandPerWave < n_ev ? e_base + kExpandPerWave : n_ev);
-  const int lo = wave_last_le(pref, nF, (int)e_base);                      // pref[0] = 0 <= every event
-  const int hi = lo + wave_last_le(pref + lo, nF - lo, e_end - 1);         // pref[lo] <= e_base <= e_end - 1
-  for (int e = (int)e_base + l; e < e_end; e += kWave) {
-    int a = lo, b = hi;
-    while (a < b) {
-      int mid = (a + b + 1) >> 1;
-      if (pref[mid] <= e) a = mid; else b = mid - 1;
-    }
-    const int u = F[a];
-    key[e] = (uint32_t)ids[off[u] + (e - pref[a])];
-    val[e] = (EV_CHG << kEvKindShift) | (uint32_t)(payload_index ? a : u);
+// Changed edges and changed sources of a layer: what its events are made from.
+struct EventInputs {
+  const int32_t *del_s, *del_d, *ins_s, *ins_d; int n_del, n_ins;
+  const int32_t *F; int nF; const int32_t *pref; int n_chg;      // changed sources, prefix and total of their kept out-edges
+  const int64_t *off; const int32_t *ids; int payload_index;
+};
+
+// All events of a layer, one tile of the sort per workgroup, which also counts the tile's digits for the
+// first sort pass (the keys are not read again for it).  A wave creates ITEMS * 64 consecutive events: it
+// finds the sources of its first and last propagated event with two wave-wide searches (64 probes per
+// round); a lane then looks for the source of each of its events only between those two, usually a
+// few candidates, instead of searching the whole prefix array once per event.
+template <int D, int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_make_events(EventInputs in, uint32_t *key, uint32_t *val, int32_t *hist, int nb) {
+  __shared__ int h[1 << D];
+  tile_hist_clear<D>(h);
+  const int l = lane_id(), w = threadIdx.x / kWave;
+  const int64_t n = (int64_t)in.n_del + in.n_chg + in.n_ins;
+  const int64_t e_base = ((int64_t)blockIdx.x * kSortWaves + w) * (ITEMS * kWave);
+  const int64_t e_end = e_base + ITEMS * kWave < n ? e_base + ITEMS * kWave : n;
+  // the wave's propagated events [c0, c1)
+  const int64_t c0 = (e_base > in.n_del ? e_base : in.n_del) - in.n_del;
+  const int64_t c1 = (e_end < in.n_del + (int64_t)in.n_chg ? e_end : in.n_del + (int64_t)in.n_chg) - in.n_del;
+  int lo = 0, hi = 0;
+  if (c0 < c1) {
+    lo = wave_last_le(in.pref, in.nF, (int)c0);                                   // pref[0] = 0 <= every event
+    hi = lo + wave_last_le(in.pref + lo, in.nF - lo, (int)(c1 - 1));              // pref[lo] <= c0 <= c1 - 1
   }
+#pragma unroll 4
+  for (int k = 0; k < ITEMS; k++) {
+    const int64_t e = e_base + k * kWave + l;
+    if (e >= e_end) break;
+    uint32_t kk, vv;
+    if (e < in.n_del) seed_event((int)e, in.del_s, in.del_d, in.ins_s, in.ins_d, in.n_del, &kk, &vv);
+    else if (e < in.n_del + (int64_t)in.n_chg) {
+      const int c = (int)(e - in.n_del);
+      int a = lo, b = hi;
+      while (a < b) {
+        const int mid = (a + b + 1) >> 1;
+        if (in.pref[mid] <= c) a = mid; else b = mid - 1;
+      }
+      const int u = in.F[a];
+      kk = (uint32_t)in.ids[in.off[u] + (c - in.pref[a])];
+      vv = (EV_CHG << kEvKindShift) | (uint32_t)(in.payload_index ? a : u);
+    } else seed_event((int)(e - in.n_chg), in.del_s, in.del_d, in.ins_s, in.ins_d, in.n_del, &kk, &vv);
+    key[e] = kk;
+    val[e] = vv;
+    atomicAdd(&h[kk & ((1 << D) - 1)], 1);
+  }
+  tile_hist_store<D>(h, hist, nb);
+}
+
+static void make_events(const SortPlan &p, const EventInputs &in, uint32_t *key, uint32_t *val, int32_t *hist, hipStream_t s) {
+#define INK_MAKE(D, I) hipLaunchKernelGGL((k_make_events<D, I>), dim3(p.tiles), dim3(kSortThreads), 0, s, in, key, val, hist, p.tiles)
+  if (p.digit_bits == 8) { if (p.items == 4) INK_MAKE(8, 4); else INK_MAKE(8, 12); }
+  else if (p.digit_bits == 9) { if (p.items == 4) INK_MAKE(9, 4); else INK_MAKE(9, 12); }
+  else { if (p.items == 4) INK_MAKE(11, 4); else INK_MAKE(11, 12); }
+#undef INK_MAKE
 }
 
 // The counters reach the host through pinned host memory: one wave writes the slots and the
@@ -1017,20 +1041,23 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
 #undef INK_SMALL_GROUP
     API_TRY(hipGetLastError());
   } else {
+    const SortPlan sp = sort_plan(nE, c->id_bits);
+    API_TRY(sort_reserve(c->ws, sp));
+    API_TRY(c->ws.tmpk.reserve((size_t)nE * 4));
+    API_TRY(c->ws.tmpv.reserve((size_t)nE * 4));
     {
       Prof p(c, INK_T_EVENTS);
-      if (n_seed > 0)
-        hipLaunchKernelGGL(k_seed_events, grid1(n_seed), dim3(256), 0, s, (const int32_t *)c->del_src,
-                           (const int32_t *)c->del_dst, (const int32_t *)c->ins_src, (const int32_t *)c->ins_dst,
-                           (int)n_del, (int)n_ins, (int64_t)n_chg, key, val);
-      if (n_chg > 0)
-        hipLaunchKernelGGL(k_expand_events, grid1(n_chg, 256 / kWave * kExpandPerWave), dim3(256), 0, s, F, (int)nF,
-                           (const int32_t *)c->f_pref.as<int32_t>(), (int)n_chg, (const int64_t *)c->gout.off,
-                           (const int32_t *)c->gout.ids, key + n_del, val + n_del, c->is_select ? 0 : 1);
+      make_events(sp, EventInputs{c->del_src, c->del_dst, c->ins_src, c->ins_dst, (int)n_del, (int)n_ins, F, (int)nF,
+                                  c->f_pref.as<int32_t>(), (int)n_chg, c->gout.off, c->gout.ids, c->is_select ? 0 : 1},
+                  key, val, c->ws.hist.as<int32_t>(), s);
       API_TRY(hipGetLastError());
     }
     Prof p(c, INK_T_GROUP);
-    { KernelTimer kt(c, l, INK_K_SORT); API_TRY(radix_sort_pairs(c->ws, key, val, nE, c->id_bits, s)); }
+    {
+      KernelTimer kt(c, l, INK_K_SORT);
+      API_TRY(radix_sort_planned(c->ws, sp, key, val, c->ws.tmpk.as<uint32_t>(), c->ws.tmpv.as<uint32_t>(), nE, true, s));
+      if (sp.passes & 1) { std::swap(c->ev_key, c->ws.tmpk); std::swap(c->ev_val, c->ws.tmpv); }     // the sorted pair stays where it is
+    }
     API_TRY(segment_heads(c->ws, key, nE, c->t_list.as<int32_t>(), c->t_seg.as<int32_t>(), &dc->v[C_NT], s));
     if (nE > kNoSyncEvents) {
       API_TRY(read_counters(c));

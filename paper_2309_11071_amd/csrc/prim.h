@@ -272,6 +272,36 @@ __global__ __launch_bounds__(kOneWgThreads) void k_tile_scan_one(F f, W w, int64
   if (total && threadIdx.x == 0) *total = carry;
 }
 
+// Second launch of a scan of up to kSumOwnLimit tiles: every workgroup adds up the sums of the tiles before
+// it (at most 16 k words from the caches), so the block sums need no scan launch of their own.
+constexpr int kSumOwnLimit = 16384;
+template <class F, class W, int ITEMS>
+__global__ __launch_bounds__(kScanThreads) void k_tile_apply_sum(F f, W w, int64_t n, const int32_t *blk, int32_t *total) {
+  __shared__ int sm[kScanThreads / kWave + 1];
+  int before = 0;
+  for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanThreads) before += blk[i];
+  int base_sum;
+  (void)block_excl_scan(before, sm, &base_sum);
+  int64_t base = (int64_t)blockIdx.x * (kScanThreads * ITEMS) + (int64_t)threadIdx.x * ITEMS;
+  int v[ITEMS];
+  int s = 0;
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    int64_t i = base + k;
+    v[k] = i < n ? f(i) : 0;
+    s += v[k];
+  }
+  int tot;
+  int ex = base_sum + block_excl_scan(s, sm, &tot);
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    int64_t i = base + k;
+    if (i < n) w(i, v[k], ex);
+    ex += v[k];
+  }
+  if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = base_sum + tot;
+}
+
 // ONE_WG: only for functors that do O(1) work per item
 template <class F, class W, int ITEMS = kScanItems, bool ONE_WG = false>
 inline hipError_t tile_scan(PrimWorkspace &ws, F f, W w, int64_t n, int32_t *total, hipStream_t s) {
@@ -292,6 +322,10 @@ inline hipError_t tile_scan(PrimWorkspace &ws, F f, W w, int64_t n, int32_t *tot
   INK_TRY(ws.blk.reserve((size_t)nb * sizeof(int32_t)));
   int32_t *blk = ws.blk.as<int32_t>();
   hipLaunchKernelGGL((k_tile_reduce<F, ITEMS>), dim3(nb), dim3(kScanThreads), 0, s, f, n, blk);
+  if (nb <= kSumOwnLimit) {
+    hipLaunchKernelGGL((k_tile_apply_sum<F, W, ITEMS>), dim3(nb), dim3(kScanThreads), 0, s, f, w, n, (const int32_t *)blk, total);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((k_scan_blk<0>), dim3(1), dim3(kScanThreads), 0, s, blk, nb, total);
   hipLaunchKernelGGL((k_tile_apply<F, W, ITEMS>), dim3(nb), dim3(kScanThreads), 0, s, f, w, n,
                      (const int32_t *)blk, (int32_t *)nullptr);
@@ -316,6 +350,28 @@ hipError_t bitmap_to_list(PrimWorkspace &ws, uint64_t *words, int64_t n_bits, in
 // n_dev (optional): device-side number of valid keys, n is then an upper bound
 hipError_t segment_heads(PrimWorkspace &ws, const uint32_t *keys, int64_t n, int32_t *uniq,
                          int32_t *seg, int32_t *count, hipStream_t s, const int32_t *n_dev = nullptr);
+
+// The passes of a device-wide sort of n pairs by the low `bits` bits of their keys.
+constexpr int kSortThreads = 256;
+constexpr int kSortWaves = kSortThreads / kWave;
+struct SortPlan { int passes, digit_bits, items, tiles; };      // items: keys per thread; a tile is items * 256 keys
+SortPlan sort_plan(int64_t n, int bits);
+hipError_t sort_reserve(PrimWorkspace &ws, const SortPlan &p);  // ws.hist for p
+// Sorts; keys / vals and the alternate buffers trade places after every pass, keys / vals return the
+// sorted pair.  have_first_hist: the tiles' digit counts of the first pass are in ws.hist already
+// (tile_hist_* in the kernel that made the keys).
+hipError_t radix_sort_planned(PrimWorkspace &ws, const SortPlan &p, uint32_t *&keys, uint32_t *&vals, uint32_t *key_alt,
+                              uint32_t *val_alt, int64_t n, bool have_first_hist, hipStream_t s);
+
+// digit counts of one tile, collected in LDS: clear (ends with a barrier), count with LDS atomics, store
+template <int D> __device__ __forceinline__ void tile_hist_clear(int *h) {
+  for (int i = threadIdx.x; i < (1 << D); i += kSortThreads) h[i] = 0;
+  __syncthreads();
+}
+template <int D> __device__ __forceinline__ void tile_hist_store(const int *h, int32_t *hist, int nb) {
+  __syncthreads();
+  for (int i = threadIdx.x; i < (1 << D); i += kSortThreads) hist[(int64_t)i * nb + blockIdx.x] = h[i];
+}
 
 // stable sort of (key, val) pairs by the low `bits` bits of key, in place (uses ws.tmpk / tmpv)
 hipError_t radix_sort_pairs(PrimWorkspace &ws, uint32_t *keys, uint32_t *vals, int64_t n, int bits,

@@ -1,4 +1,6 @@
 // Scan, compaction and radix sort kernels (gfx950, wave64).
+#include <algorithm>
+
 #include "prim.h"
 
 namespace ink {
@@ -71,109 +73,138 @@ hipError_t segment_heads(PrimWorkspace &ws, const uint32_t *keys, int64_t n, int
 }
 
 // ---------------------------------------------------------------- stable LSD radix sort
-constexpr int kSortThreads = 256;
-constexpr int kSortWaves = kSortThreads / kWave;
-#ifndef INK_SORT_ITEMS
-#define INK_SORT_ITEMS 12     // measured on 3.4 x 10^7 pairs: 8 -> 1.25 ms, 12 -> 1.18 ms, 16 -> 1.18 ms
-#endif
-constexpr int kSortItems = INK_SORT_ITEMS;                    // keys per thread
-constexpr int kSortTile = kSortThreads * kSortItems;          // keys per workgroup
+// Three launches a pass: digit counts per tile, one workgroup per digit turns them into exclusive
+// prefixes over the tiles (and the digit's total), the scatter adds the prefix over the digits'
+// totals itself.  Nothing waits for another workgroup.
 
 // hist[d * nb + b] = number of keys of tile b with digit d
-__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint32_t *keys, int64_t n, int shift,
-                                                              int32_t *hist, int nb) {
-  __shared__ int h[kRadix];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  int64_t base = (int64_t)blockIdx.x * kSortTile;
+template <int D, int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint32_t *keys, int64_t n, int shift, int32_t *hist, int nb) {
+  __shared__ int h[1 << D];
+  tile_hist_clear<D>(h);
+  const int64_t base = (int64_t)blockIdx.x * (kSortThreads * ITEMS);
 #pragma unroll
-  for (int k = 0; k < kSortItems; k++) {
+  for (int k = 0; k < ITEMS; k++) {
     int64_t i = base + k * kSortThreads + threadIdx.x;
-    if (i < n) atomicAdd(&h[(keys[i] >> shift) & (kRadix - 1)], 1);
+    if (i < n) atomicAdd(&h[(keys[i] >> shift) & ((1 << D) - 1)], 1);
   }
-  __syncthreads();
-  hist[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
+  tile_hist_store<D>(h, hist, nb);
 }
 
-// Each wave owns a contiguous run of kSortItems * 64 keys of the tile and walks it in rounds of
+// row d of hist (nb entries) -> its exclusive prefix; total[d] = its sum.  One workgroup per digit.
+__global__ __launch_bounds__(kSortThreads) void k_digit_scan(int32_t *hist, int nb, int32_t *total) {
+  __shared__ int sm[kSortWaves + 1];
+  int32_t *row = hist + (int64_t)blockIdx.x * nb;
+  int carry = 0;
+  for (int b0 = 0; b0 < nb; b0 += kSortThreads * kScanItems) {
+    const int b = b0 + threadIdx.x * kScanItems;
+    int x[kScanItems], s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; k++) { x[k] = b + k < nb ? row[b + k] : 0; s += x[k]; }
+    int tot;
+    int ex = carry + block_excl_scan<kSortThreads>(s, sm, &tot);
+#pragma unroll
+    for (int k = 0; k < kScanItems; k++) { if (b + k < nb) row[b + k] = ex; ex += x[k]; }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+
+// Each wave owns a contiguous run of ITEMS * 64 keys of the tile and walks it in rounds of
 // 64 consecutive keys, so ranks follow the input order (stability).  The pairs are first put in
 // digit order inside LDS and written out from there, so that neighbouring lanes store to
 // neighbouring addresses (runs of one digit) instead of 64 unrelated ones per instruction.
+template <int D, int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t *keys, const uint32_t *vals,
                                                                  uint32_t *okeys, uint32_t *ovals, int64_t n,
-                                                                 int shift, const int32_t *hist_scanned, int nb) {
-  static_assert(kSortThreads == kRadix, "one thread per digit");
-  __shared__ int cnt[kSortWaves][kRadix];      // per-wave digit counts, then the wave's first slot of the digit in the tile
-  __shared__ int tile_first[kRadix];           // first slot of the digit in the tile
-  __shared__ int64_t out_first[kRadix];        // first position of the tile's keys of the digit in the output
-  __shared__ uint32_t skey[kSortTile], sval[kSortTile];
+                                                                 int shift, const int32_t *hist_scanned,
+                                                                 const int32_t *digit_total, int nb) {
+  constexpr int ND = 1 << D, DPT = ND / kSortThreads, TILE = kSortThreads * ITEMS;
+  static_assert(DPT >= 1 && TILE < 65536, "digits per thread; tile positions are 16-bit");
+  __shared__ uint16_t cnt[kSortWaves][ND];     // per-wave digit counts, then the wave's first slot of the digit in the tile
+  __shared__ int out_delta[ND];                // output position of a key minus its slot in the tile
+  __shared__ uint32_t skey[TILE], sval[TILE];
   __shared__ int sm[kSortWaves + 1];
-  int w = threadIdx.x / kWave, l = lane_id();
-  for (int i = threadIdx.x; i < kSortWaves * kRadix; i += kSortThreads) (&cnt[0][0])[i] = 0;
+  const int w = threadIdx.x / kWave, l = lane_id();
+  for (int i = threadIdx.x; i < kSortWaves * ND / 2; i += kSortThreads) reinterpret_cast<uint32_t *>(&cnt[0][0])[i] = 0;
   __syncthreads();
-  const int64_t tbase = (int64_t)blockIdx.x * kSortTile;
-  int64_t wbase = tbase + (int64_t)w * (kSortItems * kWave);
-  uint32_t key[kSortItems], val[kSortItems];
-  int rank[kSortItems];
+  const int64_t tbase = (int64_t)blockIdx.x * TILE;
+  const int64_t wbase = tbase + (int64_t)w * (ITEMS * kWave);
+  uint32_t key[ITEMS], val[ITEMS];
+  int rank[ITEMS];
 #pragma unroll
-  for (int k = 0; k < kSortItems; k++) {
+  for (int k = 0; k < ITEMS; k++) {
     int64_t i = wbase + k * kWave + l;
     bool ok = i < n;
     key[k] = ok ? keys[i] : 0xFFFFFFFFu;
     val[k] = ok ? vals[i] : 0;
-    int dg = ok ? (int)((key[k] >> shift) & (kRadix - 1)) : kRadix;   // kRadix = "no key"
+  }
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const bool ok = wbase + k * kWave + l < n;
+    const int dg = (int)((key[k] >> shift) & (ND - 1));
     // lanes holding the same digit
     uint64_t same = __ballot(ok);
 #pragma unroll
-    for (int b = 0; b < kRadixBits; b++) {
+    for (int b = 0; b < D; b++) {
       uint64_t m = __ballot((dg >> b) & 1);
       same &= ((dg >> b) & 1) ? m : ~m;
     }
-    uint64_t lt = (l == 0) ? 0ull : (~0ull >> (kWave - l));
-    int before = __popcll(same & lt);
+    const uint64_t lt = (l == 0) ? 0ull : (~0ull >> (kWave - l));
+    const int before = __popcll(same & lt);
     int prev = 0;
     if (ok) prev = cnt[w][dg];                 // all lanes of a digit group read the same value
     rank[k] = prev + before;
     // the last lane of each group publishes the new count (after every lane has read)
-    bool leader = ok && ((same >> l) >> 1) == 0;
-    if (leader) cnt[w][dg] = prev + before + 1;
+    const bool leader = ok && ((same >> l) >> 1) == 0;
+    if (leader) cnt[w][dg] = (uint16_t)(prev + before + 1);
   }
   __syncthreads();
-  // thread t handles digit t: its total in the tile, the exclusive prefix over digits, the waves' slots
+  // thread t handles digits t DPT ...: their totals in the tile, the exclusive prefix over digits (of the
+  // tile and of the whole input), the waves' first slots
   {
-    const int d = threadIdx.x;
-    int tot = 0;
+    const int d0 = threadIdx.x * DPT;
+    int tot[DPT], all[DPT], st = 0, sa = 0;
 #pragma unroll
-    for (int i = 0; i < kSortWaves; i++) tot += cnt[i][d];
-    int all;
-    int first = block_excl_scan<kSortThreads>(tot, sm, &all);
-    tile_first[d] = first;
-    out_first[d] = (int64_t)hist_scanned[(int64_t)d * nb + blockIdx.x];
-    int run = first;
+    for (int j = 0; j < DPT; j++) {
+      tot[j] = 0;
 #pragma unroll
-    for (int i = 0; i < kSortWaves; i++) {
-      int c = cnt[i][d];
-      cnt[i][d] = run;
-      run += c;
+      for (int i = 0; i < kSortWaves; i++) tot[j] += cnt[i][d0 + j];
+      all[j] = digit_total[d0 + j];
+      st += tot[j]; sa += all[j];
+    }
+    int dummy;
+    int first = block_excl_scan<kSortThreads>(st, sm, &dummy);
+    int base = block_excl_scan<kSortThreads>(sa, sm, &dummy);
+#pragma unroll
+    for (int j = 0; j < DPT; j++) {
+      out_delta[d0 + j] = base + hist_scanned[(int64_t)(d0 + j) * nb + blockIdx.x] - first;
+      int run = first;
+#pragma unroll
+      for (int i = 0; i < kSortWaves; i++) {
+        const int c = cnt[i][d0 + j];
+        cnt[i][d0 + j] = (uint16_t)run;
+        run += c;
+      }
+      first += tot[j];
+      base += all[j];
     }
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kSortItems; k++) {
-    int64_t i = wbase + k * kWave + l;
-    if (i < n) {
-      int dg = (key[k] >> shift) & (kRadix - 1);
-      int slot = cnt[w][dg] + rank[k];
+  for (int k = 0; k < ITEMS; k++) {
+    if (wbase + k * kWave + l < n) {
+      const int dg = (key[k] >> shift) & (ND - 1);
+      const int slot = cnt[w][dg] + rank[k];
       skey[slot] = key[k];
       sval[slot] = val[k];
     }
   }
   __syncthreads();
-  const int in_tile = (int)(n - tbase < kSortTile ? n - tbase : kSortTile);
+  const int in_tile = (int)(n - tbase < TILE ? n - tbase : TILE);
   for (int s = threadIdx.x; s < in_tile; s += kSortThreads) {
-    uint32_t kk = skey[s];
-    int dg = (kk >> shift) & (kRadix - 1);
-    int64_t pos = out_first[dg] + (s - tile_first[dg]);
+    const uint32_t kk = skey[s];
+    const int64_t pos = (uint32_t)(out_delta[(kk >> shift) & (ND - 1)] + s);
     okeys[pos] = kk;
     ovals[pos] = sval[s];
   }
@@ -181,11 +212,10 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t *
 
 // Whole sort in one workgroup: the same stable digit ranking, all passes in LDS, one launch.
 // Keys live in registers between the ranking and the scatter of a pass, so one LDS copy of the
-// pairs is enough.  THREADS x ITEMS pairs at most: 256 x {1,4,16} for short lists, 1024 x 16
-// (128 KB of pairs) up to kSmallSort.
+// pairs is enough.  THREADS x ITEMS pairs at most; beyond kSmallSort one workgroup is slower than the
+// device-wide passes (10 000 pairs: 38 us, against 19 us for two of them).
 constexpr int kWideThreads = 1024;
-constexpr int kSmallItems = 16;
-constexpr int kSmallSort = kWideThreads * kSmallItems;     // 16384 pairs
+constexpr int kSmallSort = 4096;
 
 template <int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_small_sort(uint32_t *keys, uint32_t *vals, int n, int passes) {
@@ -193,6 +223,55 @@ __global__ __launch_bounds__(THREADS) void k_small_sort(uint32_t *keys, uint32_t
   for (int i = threadIdx.x; i < n; i += THREADS) { S.sk[i] = keys[i]; S.sv[i] = vals[i]; }
   small_sort_lds<THREADS, ITEMS>(S, n, passes);
   for (int i = threadIdx.x; i < n; i += THREADS) { keys[i] = S.sk[i]; vals[i] = S.sv[i]; }
+}
+
+SortPlan sort_plan(int64_t n, int bits) {
+  // Few pairs: their passes are launch-bound and stay in the caches, so wide digits; many pairs: digits
+  // that leave runs long enough for whole cache lines in a tile of 3072.  Measured per sort: 312 k pairs of
+  // 21 bits: three 8-bit passes 43 us, two 11-bit passes 27 us.
+  SortPlan p;
+  const int widest = n <= (1 << 20) ? 11 : 9;
+  p.passes = (bits + widest - 1) / widest;
+  const int d = (bits + p.passes - 1) / p.passes;
+  p.digit_bits = d <= 8 ? 8 : (d <= 9 ? 9 : 11);
+  p.items = n <= (1 << 18) ? 4 : 12;          // short sorts need the smaller tiles to fill the chip
+  p.tiles = nblocks(n, kSortThreads * p.items);
+  return p;
+}
+
+hipError_t sort_reserve(PrimWorkspace &ws, const SortPlan &p) {
+  return ws.hist.reserve(((size_t)(1 << p.digit_bits) * (p.tiles + 1)) * sizeof(int32_t));
+}
+
+template <int D, int ITEMS>
+static void radix_pass(const SortPlan &p, int pass, bool have_hist, const uint32_t *ka, const uint32_t *va, uint32_t *kb,
+                       uint32_t *vb, int64_t n, int32_t *hist, hipStream_t s) {
+  const int shift = pass * p.digit_bits;
+  int32_t *total = hist + ((int64_t)p.tiles << D);
+  if (!have_hist)
+    hipLaunchKernelGGL((k_radix_hist<D, ITEMS>), dim3(p.tiles), dim3(kSortThreads), 0, s, ka, n, shift, hist, p.tiles);
+  hipLaunchKernelGGL(k_digit_scan, dim3(1 << D), dim3(kSortThreads), 0, s, hist, p.tiles, total);
+  hipLaunchKernelGGL((k_radix_scatter<D, ITEMS>), dim3(p.tiles), dim3(kSortThreads), 0, s, ka, va, kb, vb, n, shift,
+                     (const int32_t *)hist, (const int32_t *)total, p.tiles);
+}
+
+hipError_t radix_sort_planned(PrimWorkspace &ws, const SortPlan &p, uint32_t *&keys, uint32_t *&vals, uint32_t *key_alt,
+                              uint32_t *val_alt, int64_t n, bool have_first_hist, hipStream_t s) {
+  INK_TRY(sort_reserve(ws, p));
+  int32_t *hist = ws.hist.as<int32_t>();
+  for (int pass = 0; pass < p.passes; pass++) {
+    const bool hh = have_first_hist && pass == 0;
+#define INK_PASS(D) \
+  (p.items == 4 ? radix_pass<D, 4>(p, pass, hh, keys, vals, key_alt, val_alt, n, hist, s) \
+                : radix_pass<D, 12>(p, pass, hh, keys, vals, key_alt, val_alt, n, hist, s))
+    if (p.digit_bits == 8) INK_PASS(8);
+    else if (p.digit_bits == 9) INK_PASS(9);
+    else INK_PASS(11);
+#undef INK_PASS
+    std::swap(keys, key_alt);
+    std::swap(vals, val_alt);
+  }
+  return hipGetLastError();
 }
 
 hipError_t radix_sort_pairs(PrimWorkspace &ws, uint32_t *keys, uint32_t *vals, int64_t n, int bits,
@@ -204,32 +283,20 @@ hipError_t radix_sort_pairs(PrimWorkspace &ws, uint32_t *keys, uint32_t *vals, i
       hipLaunchKernelGGL((k_small_sort<256, 1>), dim3(1), dim3(256), 0, s, keys, vals, (int)n, passes);
     else if (n <= 1024)
       hipLaunchKernelGGL((k_small_sort<256, 4>), dim3(1), dim3(256), 0, s, keys, vals, (int)n, passes);
-    else if (n <= 4096)
-      hipLaunchKernelGGL((k_small_sort<kWideThreads, 4>), dim3(1), dim3(kWideThreads), 0, s, keys, vals, (int)n, passes);
     else
-      hipLaunchKernelGGL((k_small_sort<kWideThreads, kSmallItems>), dim3(1), dim3(kWideThreads), 0, s, keys, vals, (int)n, passes);
+      hipLaunchKernelGGL((k_small_sort<kWideThreads, 4>), dim3(1), dim3(kWideThreads), 0, s, keys, vals, (int)n, passes);
     return hipGetLastError();
   }
-  int nb = nblocks(n, kSortTile);
-  INK_TRY(ws.hist.reserve((size_t)kRadix * nb * sizeof(int32_t)));
+  const SortPlan p = sort_plan(n, bits);
   INK_TRY(ws.tmpk.reserve((size_t)n * sizeof(uint32_t)));
   INK_TRY(ws.tmpv.reserve((size_t)n * sizeof(uint32_t)));
-  int32_t *hist = ws.hist.as<int32_t>();
-  uint32_t *ka = keys, *va = vals, *kb = ws.tmpk.as<uint32_t>(), *vb = ws.tmpv.as<uint32_t>();
-  for (int p = 0; p < passes; p++) {
-    int shift = p * kRadixBits;
-    hipLaunchKernelGGL(k_radix_hist, dim3(nb), dim3(kSortThreads), 0, s, (const uint32_t *)ka, n, shift, hist, nb);
-    INK_TRY(scan_excl_i32(ws, hist, hist, (int64_t)kRadix * nb, nullptr, s));
-    hipLaunchKernelGGL(k_radix_scatter, dim3(nb), dim3(kSortThreads), 0, s, (const uint32_t *)ka,
-                       (const uint32_t *)va, kb, vb, n, shift, (const int32_t *)hist, nb);
-    uint32_t *t = ka; ka = kb; kb = t;
-    t = va; va = vb; vb = t;
+  uint32_t *k = keys, *v = vals;
+  INK_TRY(radix_sort_planned(ws, p, k, v, ws.tmpk.as<uint32_t>(), ws.tmpv.as<uint32_t>(), n, false, s));
+  if (k != keys) {
+    INK_TRY(hipMemcpyAsync(keys, k, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+    INK_TRY(hipMemcpyAsync(vals, v, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
   }
-  if (ka != keys) {
-    INK_TRY(hipMemcpyAsync(keys, ka, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    INK_TRY(hipMemcpyAsync(vals, va, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-  }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 }  // namespace ink
