@@ -132,24 +132,6 @@ static void make_events(const SortPlan &p, const EventInputs &in, uint32_t *key,
 #undef INK_MAKE
 }
 
-// The counters reach the host through pinned host memory: one wave writes the slots and the
-// stripe totals, then a sequence number that the host polls.  A blocking stream synchronisation
-// costs an interrupt round trip per read-back, and a short batch has four of them.  The loads
-// bypass the L1 so that a workgroup may publish what its own threads stored before a barrier.
-__device__ __forceinline__ void publish_wave(const Counters *d, HostCounters *h, uint32_t *h_seq, uint32_t seq) {
-  const int l = lane_id();
-  if (l < 32) h->v[l] = __hip_atomic_load(&d->v[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-  for (int w = 0; w < ST_N; w++) {
-    unsigned long long t = __hip_atomic_load(&d->stripe[l][w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, kWave);
-    if (l == 0) h->total[w] = t;
-  }
-  __threadfence_system();
-  if (l == 0) __hip_atomic_store(h_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-static_assert(kStripes == kWave, "one stripe per lane");
-
 __global__ __launch_bounds__(64) void k_publish(const Counters *d, HostCounters *h, uint32_t *h_seq, uint32_t seq) {
   publish_wave(d, h, h_seq, seq);
 }
@@ -472,8 +454,6 @@ static ink_status seal(ink_ctx *c, ink_status st) {
 }
 static const char *kBrokenMsg = "the context is unusable after a failed update (INK_E_OOM / INK_E_DEVICE): destroy it";
 
-static hipError_t wait_published(ink_ctx *c, uint32_t seq);
-
 static hipError_t alloc_table(Table &t, int64_t n, int d) {
   // rows start on 64-byte boundaries: a gathered row then touches the fewest cache lines (config 2,
   // 41-wide rows: 176 -> 192 bytes per row and 5 % less aggregation time; 128-byte alignment loses
@@ -527,22 +507,22 @@ hipError_t ink::read_counters(ink_ctx *c) {
   hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, c->stream, (const Counters *)c->d_cnt, c->h_cnt, c->h_seq, seq);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return wait_published(c, seq);
+  return wait_published(c, c->h_seq, seq);
 }
 
 // waits until the record with this sequence number has arrived: a short spin, then the blocking wait
-static hipError_t wait_published(ink_ctx *c, uint32_t seq) {
+hipError_t ink::wait_published(ink_ctx *c, const uint32_t *h_seq, uint32_t seq) {
   hipError_t e;
   const auto t0 = std::chrono::steady_clock::now();
   for (int spin = 0;; spin++) {
-    if (__atomic_load_n(c->h_seq, __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+    if (__atomic_load_n(h_seq, __ATOMIC_ACQUIRE) == seq) return hipSuccess;
     if ((spin & 63) == 63 &&
         std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > 150.0)
       break;
   }
   e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return e;
-  return __atomic_load_n(c->h_seq, __ATOMIC_ACQUIRE) == seq ? hipSuccess : hipErrorUnknown;
+  return __atomic_load_n(h_seq, __ATOMIC_ACQUIRE) == seq ? hipSuccess : hipErrorUnknown;
 }
 
 static const Table &msg_table(ink_ctx *c, int l) {   // m_l: h_{l-1} (aggregate first) or GCN's scaled h_{l-1} W_l
@@ -707,7 +687,7 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
   c->profile = opts ? opts->profile : 0;
   c->pool_reserve = opts ? opts->pool_reserve : 0;
   if (opts && opts->small_batch_limit != 0)
-    c->small_batch = opts->small_batch_limit < 0 ? 0 : std::min<int64_t>(opts->small_batch_limit, 4096);
+    c->small_batch = opts->small_batch_limit < 0 ? 0 : std::min<int64_t>(opts->small_batch_limit, kShortBatch);
   c->batch_dev = dev || (opts && opts->batch_mem == INK_MEM_DEVICE);
   if (opts && opts->dense_threshold != 0.f) c->dense_frac = opts->dense_threshold < 0.f ? 1e30 : opts->dense_threshold;
   memset(&c->stats, 0, sizeof(c->stats));
@@ -729,17 +709,25 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
   CREATE_TRY(hipMemset(c->new_out, 0, (size_t)nc * 4));
   CREATE_TRY(hipMalloc(&c->d_cnt, sizeof(Counters)));
   CREATE_TRY(hipMemset(c->d_cnt, 0, sizeof(Counters)));
-  CREATE_TRY(hipHostMalloc((void **)&c->h_cnt, sizeof(HostCounters) + 64, hipHostMallocCoherent));
-  memset(c->h_cnt, 0, sizeof(HostCounters) + 64);
-  c->h_seq = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(c->h_cnt) + sizeof(HostCounters));
+  CREATE_TRY(hipMalloc(&c->d_gcnt, sizeof(Counters)));
+  CREATE_TRY(hipMemset(c->d_gcnt, 0, sizeof(Counters)));
+  {   // one pinned allocation: layer record + sequence number, graph record + sequence number, batch staging
+    static_assert(sizeof(HostCounters) == 192, "records and sequence numbers on their own cache lines");
+    char *h = nullptr;
+    CREATE_TRY(hipHostMalloc((void **)&h, 512 + kPinnedBatch * sizeof(ink_edge_update), hipHostMallocCoherent));
+    memset(h, 0, 512);
+    c->h_cnt = reinterpret_cast<HostCounters *>(h);
+    c->h_seq = reinterpret_cast<uint32_t *>(h + 192);
+    c->h_gcnt = reinterpret_cast<HostCounters *>(h + 256);
+    c->h_gseq = reinterpret_cast<uint32_t *>(h + 448);
+    c->h_batch = reinterpret_cast<ink_edge_update *>(h + 512);
+  }
   size_t bmw = ((size_t)nc + 63) / 64;
   CREATE_TRY(hipMalloc(&c->bm_a, bmw * 8));
   CREATE_TRY(hipMemset(c->bm_a, 0, bmw * 8));
   if (opts && opts->max_batch > 0) {       // size the batch staging up front
-    CREATE_TRY(c->b_raw.reserve((size_t)opts->max_batch * sizeof(ink_edge_update)));
-    const size_t per = (((size_t)opts->max_batch + 64) * 4 + 255) / 256 * 256;
-    CREATE_TRY(c->b_misc.reserve(per * 28));
-    for (DevBuf *b : {&c->b_del_s, &c->b_del_d, &c->b_ins_s, &c->b_ins_d, &c->b_touch_in, &c->b_uniq}) CREATE_TRY(b->reserve(per));
+    if (!c->batch_dev) CREATE_TRY(c->b_raw.reserve((size_t)opts->max_batch * sizeof(ink_edge_update)));
+    CREATE_TRY(graph_reserve(c, opts->max_batch));
     CREATE_TRY(c->c_list.reserve((size_t)nc * 4));
   }
   CREATE_TRY(c->big_list.reserve((size_t)(c->gin.pool_cap / kBigDeg + 4096) * 4));
@@ -817,6 +805,7 @@ extern "C" void ink_destroy(ink_ctx *c) {
   for (auto *vec : {&c->H, &c->A, &c->ARG, &c->UB, &c->ARG2, &c->XW, &c->Msc, &c->USER}) for (auto &t : *vec) if (t.p) (void)hipFree(t.p);
   if (c->cnorm) (void)hipFree(c->cnorm);
   if (c->d_cnt) (void)hipFree(c->d_cnt);
+  if (c->d_gcnt) (void)hipFree(c->d_gcnt);
   if (c->h_cnt) (void)hipHostFree(c->h_cnt);
   if (c->bm_a) (void)hipFree(c->bm_a);
   for (DevBuf *b : {&c->ws.blk, &c->ws.hist, &c->ws.tmpk, &c->ws.tmpv, &c->b_raw, &c->b_misc, &c->b_uniq, &c->b_del_s,
@@ -1216,7 +1205,7 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, int nxt, bool keep_old, i
     *result_done = true;
   }
   API_TRY(hipGetLastError());
-  if (small) API_TRY(wait_published(c, published));
+  if (small) API_TRY(wait_published(c, c->h_seq, published));
   else API_TRY(read_counters(c));
   *nF2 = c->h_cnt->v[C_NEXT];
   if (want_events) *n_chg = (uint32_t)c->h_cnt->v[C_NEV];
@@ -1360,10 +1349,17 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
   int64_t n_ins = 0, n_del = 0;
   if (n > 0) {
     Prof p(c, INK_T_GRAPH);
-    API_TRY(c->b_raw.reserve((size_t)n * sizeof(ink_edge_update)));
-    API_TRY(hipMemcpyAsync(c->b_raw.p, upd, (size_t)n * sizeof(ink_edge_update),
-                           c->batch_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
-    ink_status st = graph_apply_batch(c, n, &n_ins, &n_del);
+    // a device batch is read where it is; a short host batch from pinned memory, by the one kernel that reads it
+    const void *raw = upd;
+    if (!c->batch_dev) {
+      if (n <= kPinnedBatch) { memcpy(c->h_batch, upd, (size_t)n * sizeof(ink_edge_update)); raw = c->h_batch; }
+      else {
+        API_TRY(c->b_raw.reserve((size_t)n * sizeof(ink_edge_update)));
+        API_TRY(hipMemcpyAsync(c->b_raw.p, upd, (size_t)n * sizeof(ink_edge_update), hipMemcpyHostToDevice, s));
+        raw = c->b_raw.p;
+      }
+    }
+    ink_status st = graph_apply_batch(c, raw, n, &n_ins, &n_del);
     if (st != INK_OK) return st;
   }
   out->n_applied_ins = n_ins; out->n_applied_del = n_del; out->n_noop = n - n_ins - n_del;

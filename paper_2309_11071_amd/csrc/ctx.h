@@ -74,6 +74,9 @@ struct DevLayer {
   float *W2 = nullptr; int K2 = 0, K2p = 0, N2 = 0, N2p = 0; float *b2 = nullptr;   // GIN second linear
 };
 
+constexpr int64_t kShortBatch = 16384;     // largest batch of the short form of the graph stage
+constexpr int64_t kPinnedBatch = 1024;     // host batches up to this size are read by the device from pinned memory
+
 constexpr int kStripes = 64;
 enum { ST_EXPOSED = 0, ST_REGATHER, ST_ACHG, ST_NODEL, ST_NOEFFECT, ST_COVERED, ST_REGATHER_LONG, ST_PAD7, ST_N };
 struct Counters {            // device-written, host-read through pinned memory
@@ -98,8 +101,30 @@ struct HostCounters {
 // touched nodes and block chunks of the out side (single-workgroup graph stage), and two 64-bit
 // slots (pool tops handed to the apply kernels).  Slot 0 flags a malformed update batch.
 // (C_NEVL, C_NEVCH: targets with a long event segment and the chunks of those segments)
+// The graph stage of short batches has a block of its own (ink_ctx::d_gcnt): next to the slots above it holds
+// the pool space each side needs (stripe 0, words 0 and 1), the effective ops as the out side sees them, the effective ops
+// of the in side whether or not the apply kernel may run (C_GINS, C_GDEL) and whether it may (C_OK).
 enum { C_ERR = 0, C_NEV = 1, C_NT, C_NBIG, C_NEXP, C_NEVL, C_NEVCH, C_NC, C_NEXT, C_NCHUNK, C_NOPS, C_TMP0, C_TMP1,
-       C_TMP2, C_TMP3, C_OT, C_OCH, C_TOP64 = 18, C_TOP64B = 20 };
+       C_TMP2, C_TMP3, C_OT, C_OCH, C_TOP64 = 18, C_TOP64B = 20,
+       C_OINS = 22, C_ODEL, C_GINS, C_GDEL, C_OK };
+
+// The counters reach the host through pinned host memory: one wave writes the slots and the
+// stripe totals, then a sequence number that the host polls.  A blocking stream synchronisation
+// costs an interrupt round trip per read-back, and a short batch has four of them.  The loads
+// bypass the L1 so that a workgroup may publish what its own threads stored before a barrier.
+static_assert(kStripes == kWave, "one stripe per lane");
+__device__ __forceinline__ void publish_wave(const Counters *d, HostCounters *h, uint32_t *h_seq, uint32_t seq) {
+  const int l = lane_id();
+  if (l < 32) h->v[l] = __hip_atomic_load(&d->v[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int w = 0; w < ST_N; w++) {
+    unsigned long long t = __hip_atomic_load(&d->stripe[l][w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, kWave);
+    if (l == 0) h->total[w] = t;
+  }
+  __threadfence_system();
+  if (l == 0) __hip_atomic_store(h_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // A target with more than this many events is reduced by many waves (longev.h) instead of one.
 // 128 makes the lists and partial rows of a large launch cost more than the chains they cut (17 M
@@ -146,7 +171,11 @@ struct ink_ctx {
   ink::HostCounters *h_cnt = nullptr;   // pinned host mirror, written by the publish kernel
   uint32_t *h_seq = nullptr;         // (same allocation) sequence number of the last published copy
   uint32_t pub_seq = 0;
-  int64_t small_batch = 4096;        // batches up to this size take the single-workgroup graph stage
+  ink::Counters *d_gcnt = nullptr;   // the graph stage's own block, its pinned mirror and sequence number
+  ink::HostCounters *h_gcnt = nullptr;
+  uint32_t *h_gseq = nullptr;
+  ink_edge_update *h_batch = nullptr;   // pinned staging of short host batches
+  int64_t small_batch = 16384;       // batches up to this size take the short form of the graph stage
   uint64_t *bm_a = nullptr;          // node bitmaps (n bits each)
 
   // batch buffers (grown on demand)
@@ -206,10 +235,12 @@ struct KernelTimer : Prof {
 
 // ---- graph store (graph.hip)
 hipError_t graph_build(ink_ctx *c, const int64_t *rowptr_h, const int32_t *col_h);
-// applies a validated batch already on the device in c->b_raw; fills Delta E lists and counts
-ink_status graph_apply_batch(ink_ctx *c, int64_t n, int64_t *n_ins, int64_t *n_del);
+// applies a batch in memory the device can read (ink_edge_update records); fills Delta E lists and counts
+ink_status graph_apply_batch(ink_ctx *c, const void *raw, int64_t n, int64_t *n_ins, int64_t *n_del);
+hipError_t graph_reserve(ink_ctx *c, int64_t max_batch);   // batch buffers for that many entries
 ink_status graph_add_nodes(ink_ctx *c, int64_t n_new);   // empty edge blocks for nodes n .. n + n_new - 1 (before n grows)
 hipError_t read_counters(ink_ctx *c);        // device counters -> c->h_cnt, waits for them
+hipError_t wait_published(ink_ctx *c, const uint32_t *h_seq, uint32_t seq);   // until that record has arrived
 hipError_t graph_end_batch(ink_ctx *c);     // clears per-batch marks (new_out)
 hipError_t graph_export(ink_ctx *c, int64_t *rowptr_h, int32_t *col_h);
 
