@@ -767,11 +767,11 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
       CREATE_TRY(upload_padded(S.W_neigh, S.in_dim, S.out_dim, L.K1p, L.N1p, 0, L.W1, dev));
       CREATE_TRY(upload_vec(S.bias, S.out_dim, &L.b1, dev));
     } else if (c->kind == INK_MODEL_SAGE) {
-      L.K1 = 2 * S.in_dim; L.K1p = round_up(L.K1, 32); L.N1 = S.out_dim; L.N1p = round_up(L.N1, 32);
+      L.K1 = 2 * xform_self_row(S.in_dim); L.K1p = round_up(L.K1, 32); L.N1 = S.out_dim; L.N1p = round_up(L.N1, 32);
       CREATE_TRY(hipMalloc(&L.W1, (size_t)L.K1p * L.N1p * 4));
       CREATE_TRY(hipMemset(L.W1, 0, (size_t)L.K1p * L.N1p * 4));
       CREATE_TRY(upload_padded(S.W_neigh, S.in_dim, S.out_dim, L.K1p, L.N1p, 0, L.W1, dev));
-      CREATE_TRY(upload_padded(S.W_self, S.in_dim, S.out_dim, L.K1p, L.N1p, S.in_dim, L.W1, dev));
+      CREATE_TRY(upload_padded(S.W_self, S.in_dim, S.out_dim, L.K1p, L.N1p, xform_self_row(S.in_dim), L.W1, dev));
       CREATE_TRY(upload_vec(S.bias, S.out_dim, &L.b1, dev));
     } else {   // GIN
       L.K1 = S.in_dim; L.K1p = round_up(L.K1, 32); L.N1 = S.mlp_hidden; L.N1p = round_up(L.N1, 32);

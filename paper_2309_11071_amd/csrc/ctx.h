@@ -306,6 +306,8 @@ struct XformArgs {
   const float *user; int ld_user;      // per-node term added after the bias, before the activation (to_table only), null: none
 };
 hipError_t xform_run(ink_ctx *c, const XformArgs &x);
+// SAGE: row of the padded weight matrix where W_self starts (both halves of the input at multiples of 4)
+__host__ __device__ inline int xform_self_row(int in_dim) { return (in_dim + 3) & ~3; }
 // position of W[k][col] in the padded device copy: k-chunks of 32, inside a chunk one row of 32 per
 // column holding first the 16 even then the 16 odd k (the order the MFMA steps consume them)
 inline size_t xform_weight_index(int k, int col, int Np) {

@@ -6,6 +6,8 @@
 // starting from +0 (the MFMA unit applies its two k-steps in that order), independent of the
 // tile or row slot it is computed in, so a row's result never depends on which other rows share
 // the launch.  Zero-padded k-steps leave the accumulator unchanged.
+#include <algorithm>
+
 #include "ctx.h"
 
 namespace ink {
@@ -14,107 +16,76 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 
 constexpr int KT = 32;       // k-chunk staged in LDS
 
-__device__ __forceinline__ float agg_value(const XformArgs &x, int64_t row, int k) {
-  float a = x.A[row * x.lda + k];
-  if (x.mean_deg) { int dg = x.mean_deg[row]; a = __fdiv_rn(a, (float)(dg > 0 ? dg : 1)); }
-  return a;
-}
-
-template <int MODE>
-__device__ __forceinline__ float fetch_x(const XformArgs &x, int64_t row, int k) {
-  if (MODE == 0) {           // SAGE: [alpha | h_prev]
-    if (k < x.d_in) return agg_value(x, row, k);
-    if (k < 2 * x.d_in) return x.Hp[row * x.ldh + (k - x.d_in)];
-    return 0.f;
-  } else if (MODE == 1) {    // GIN: (1 + eps) h_prev + alpha
-    if (k < x.d_in) return __fadd_rn(__fmul_rn(1.0f + x.eps, x.Hp[row * x.ldh + k]), agg_value(x, row, k));
-    return 0.f;
-  } else if (MODE == 3) {    // GCN: h = act(c_v (S + own scaled message) + b); also stored as h_l
-    if (k >= x.d_in) return 0.f;
-    float v = __fmul_rn(x.cnorm[row], __fadd_rn(x.A[row * x.lda + k], x.Hp[row * x.ldh + k]));
-    if (x.in_bias) v = __fadd_rn(v, x.in_bias[k]);
-    if (x.in_user) v = __fadd_rn(v, x.in_user[row * x.ld_in_user + k]);
-    if (x.in_relu) v = v > 0.f ? v : 0.f;
-    if (x.h_store) x.h_store[row * x.ld_hs + k] = v;
-    return v;
-  } else {                   // dense rows
-    if (k < x.d_in) return x.Hp[row * x.ldh + k];
-    return 0.f;
-  }
-}
-
 __device__ __forceinline__ void ld4v(const float *p, float out[4]) {
   float4 v = *reinterpret_cast<const float4 *>(p);
   out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
 }
 
-// four consecutive inputs k .. k + 3 (k a multiple of 4) of one row; 16-byte loads when the group
-// lies inside one table row, element-wise otherwise.  Results are identical to fetch_x.
+// Four consecutive inputs k .. k + 3 (k a multiple of 4) of one row in two parts: issue_x4 loads what they
+// are made of, finish_x4 combines it where the values are used, so that loads stay in flight across
+// other work.  Always 16-byte loads: table rows are padded with zeros to 16 floats, SAGE's two halves
+// start at multiples of 4 (xform_self_row), and a group past a row's end reads the row's start instead.
+template <int MODE> struct RawX { float4 a; };
+template <> struct RawX<1> { float4 a, b; };
+template <> struct RawX<3> { float4 a, b; };
+
 template <int MODE>
-__device__ __forceinline__ void fetch_x4(const XformArgs &x, int64_t row, int k, float out[4]) {
-  if (MODE == 0) {
-    if ((x.d_in & 3) == 0 && k + 3 < 2 * x.d_in) {
-      if (k < x.d_in) {
-        ld4v(x.A + row * x.lda + k, out);
-        if (x.mean_deg) {
-          int dg = x.mean_deg[row];
-          float dv = (float)(dg > 0 ? dg : 1);
-#pragma unroll
-          for (int i = 0; i < 4; i++) out[i] = __fdiv_rn(out[i], dv);
-        }
-      } else {
-        ld4v(x.Hp + row * x.ldh + (k - x.d_in), out);
-      }
-      return;
-    }
-  } else if (MODE == 1) {
-    if (k + 3 < x.lda && k + 3 < x.ldh) {
-      float a[4], h[4];
-      ld4v(x.A + row * x.lda + k, a);
-      ld4v(x.Hp + row * x.ldh + k, h);
-      float dv = 1.f;
-      if (x.mean_deg) { int dg = x.mean_deg[row]; dv = (float)(dg > 0 ? dg : 1); }
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        float av = x.mean_deg ? __fdiv_rn(a[i], dv) : a[i];
-        out[i] = k + i < x.d_in ? __fadd_rn(__fmul_rn(1.0f + x.eps, h[i]), av) : 0.f;
-      }
-      return;
-    }
-  } else if (MODE == 3) {
-    if (k + 3 < x.lda && k + 3 < x.ldh && !x.in_user) {      // rows with a user term take the element-wise path
-      float a[4], h[4];
-      ld4v(x.A + row * x.lda + k, a);
-      ld4v(x.Hp + row * x.ldh + k, h);
-      float cv = x.cnorm[row];
-      float b[4] = {0.f, 0.f, 0.f, 0.f};
-      if (x.in_bias) {       // one 16-byte load when the group lies inside the bias vector
-        if (k + 3 < x.d_in) ld4v(x.in_bias + k, b);
-        else
-#pragma unroll
-          for (int i = 0; i < 4; i++) if (k + i < x.d_in) b[i] = x.in_bias[k + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        float v = __fmul_rn(cv, __fadd_rn(a[i], h[i]));
-        if (x.in_bias && k + i < x.d_in) v = __fadd_rn(v, b[i]);
-        if (x.in_relu) v = v > 0.f ? v : 0.f;
-        out[i] = k + i < x.d_in ? v : 0.f;
-      }
-      if (x.h_store && k + 3 < x.ld_hs)
-        *reinterpret_cast<float4 *>(x.h_store + row * x.ld_hs + k) = make_float4(out[0], out[1], out[2], out[3]);
-      return;
-    }
-  } else {
-    if ((x.ldh & 3) == 0 && k + 3 < x.ldh) {
-      ld4v(x.Hp + row * x.ldh + k, out);
-#pragma unroll
-      for (int i = 0; i < 4; i++) out[i] = k + i < x.d_in ? out[i] : 0.f;
-      return;
-    }
+__device__ __forceinline__ void issue_x4(const XformArgs &x, int64_t row, int k, RawX<MODE> &r) {
+  if constexpr (MODE == 0) {           // SAGE: [alpha | h_prev]
+    const int d4 = xform_self_row(x.d_in);
+    const int ks = k - d4 < d4 ? k - d4 : 0;
+    const float *p = k < d4 ? x.A + row * x.lda + k : x.Hp + row * x.ldh + ks;
+    r.a = *reinterpret_cast<const float4 *>(p);
+  } else if constexpr (MODE == 2) {    // dense rows
+    r.a = *reinterpret_cast<const float4 *>(x.Hp + row * x.ldh + (k < x.ldh ? k : 0));
+  } else {                             // GIN: (1 + eps) h_prev + alpha; GCN: act(c_v (S + own scaled message) + b)
+    r.a = *reinterpret_cast<const float4 *>(x.A + row * x.lda + (k < x.lda ? k : 0));
+    r.b = *reinterpret_cast<const float4 *>(x.Hp + row * x.ldh + (k < x.ldh ? k : 0));
   }
+}
+// per-row scalar of the combination: degree (mean) or c_v (GCN)
+template <int MODE> __device__ __forceinline__ float row_scalar(const XformArgs &x, int64_t row) {
+  if (MODE == 3) return x.cnorm[row];
+  if ((MODE == 0 || MODE == 1) && x.mean_deg) { const int dg = x.mean_deg[row]; return (float)(dg > 0 ? dg : 1); }
+  return 1.f;
+}
+// store_h: GCN also writes the combined row as h_l
+template <int MODE>
+__device__ __forceinline__ void finish_x4(const XformArgs &x, int64_t row, int k, float sc, bool store_h, const RawX<MODE> &r, float v[4]) {
+  v[0] = r.a.x; v[1] = r.a.y; v[2] = r.a.z; v[3] = r.a.w;
+  if constexpr (MODE == 0) {
+    const int d4 = xform_self_row(x.d_in);
+    if (x.mean_deg && k < d4)
 #pragma unroll
-  for (int i = 0; i < 4; i++) out[i] = fetch_x<MODE>(x, row, k + i);
+      for (int i = 0; i < 4; i++) v[i] = __fdiv_rn(v[i], sc);
+    if (k >= 2 * d4 || d4 != x.d_in)       // past the input, or in the padding of an aggregated row (anything may stand there)
+#pragma unroll
+      for (int i = 0; i < 4; i++) v[i] = k < 2 * d4 && (k < d4 ? k : k - d4) + i < x.d_in ? v[i] : 0.f;
+  } else if constexpr (MODE == 1) {
+    const float h[4] = {r.b.x, r.b.y, r.b.z, r.b.w};
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const float a = x.mean_deg ? __fdiv_rn(v[i], sc) : v[i];
+      v[i] = k + i < x.d_in ? __fadd_rn(__fmul_rn(1.0f + x.eps, h[i]), a) : 0.f;
+    }
+  } else if constexpr (MODE == 2) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) v[i] = k + i < x.d_in ? v[i] : 0.f;
+  } else {
+    const float h[4] = {r.b.x, r.b.y, r.b.z, r.b.w};
+    float b[4], u[4];
+    if (x.in_bias) ld4v(x.in_bias + k, b);
+    if (x.in_user) ld4v(x.in_user + row * x.ld_in_user + (k < x.ld_in_user ? k : 0), u);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      float t = __fmul_rn(sc, __fadd_rn(v[i], h[i]));
+      if (x.in_bias) t = __fadd_rn(t, b[i]);
+      if (x.in_user) t = __fadd_rn(t, u[i]);
+      if (x.in_relu) t = t > 0.f ? t : 0.f;
+      v[i] = k + i < x.d_in ? t : 0.f;
+    }
+    if (x.h_store && store_h && k < x.ld_hs) *reinterpret_cast<float4 *>(x.h_store + row * x.ld_hs + k) = make_float4(v[0], v[1], v[2], v[3]);
+  }
 }
 
 // LDS layouts (floats): X tile [BM][2][16] with row stride XS, W tile [Np][2][16] with row stride
@@ -197,6 +168,11 @@ __device__ __forceinline__ void xform_epilogue(const XformArgs &x, const f16v *a
   }
 }
 
+// Bound by memory as much as by the matrix cores: 655k SAGE rows 256 -> 121 are 1.3 GB and 41 GFLOP, .27 ms
+// of either, and take .46 ms (.48 with a scalar path for rows of odd width and loads that waited where they
+// were issued); the two products of 1.25M GIN rows 128 -> 128 -> 172 take .76 ms (.85) for 3.4 GB.  What keeps it
+// there is the number of waves in flight: prefetching the weights as well, or 128 rows per workgroup, costs
+// registers and LDS and measured .46 - .7 ms; keeping the weights in LDS for a persistent workgroup .52 ms.
 // BM = rows per workgroup (64 or 128), NT = number of 32-column tiles (Np / 32), NW = waves per
 // workgroup.  With RT = BM / 32 row tiles, wave w works on row tile w % RT and on the column tiles
 // w / RT, w / RT + NW / RT, ...
@@ -239,56 +215,29 @@ __global__ __launch_bounds__(NW * 64) void k_xform(XformArgs x) {
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[i][r] = 0.f;
   __syncthreads();
-  // thread -> row t / 4, 8 consecutive k of the X chunk; the next chunk's values are fetched into
-  // registers before the MFMA phase so that the gather latency overlaps it
+  // thread -> row t / 4, 8 consecutive k of the X chunk
   const bool xstage = t < XTHR;
   const int xr = (t % XTHR) / (KT / KPT), xks = (t % (KT / KPT)) * KPT;
   const int64_t xrow = xstage ? srow[xr] : -1;
-  float xv[KPT];
-  auto fetch_chunk = [&](int k0) {
+  // the loads of the next chunk are issued a whole iteration before their values are combined and
+  // staged, so the gather latency overlaps the barriers, the weight staging and the MFMAs of the chunk between
+  RawX<MODE> raw[KPT / 4];
+  const float sc = xrow >= 0 ? row_scalar<MODE>(x, xrow) : 1.f;
+  auto issue = [&](int k0) {
+    if (xrow >= 0) {
+#pragma unroll
+      for (int kk = 0; kk < KPT; kk += 4) issue_x4<MODE>(x, xrow, k0 + xks + kk, raw[kk / 4]);
+    }
+  };
+  issue(0);
+  for (int k0 = 0; k0 < x.Kp; k0 += KT) {
+    float xv[KPT];
 #pragma unroll
     for (int kk = 0; kk < KPT; kk++) xv[kk] = 0.f;
     if (xrow >= 0) {
 #pragma unroll
-      for (int kk = 0; kk < KPT; kk += 4) fetch_x4<MODE>(x, xrow, k0 + xks + kk, xv + kk);
+      for (int kk = 0; kk < KPT; kk += 4) finish_x4<MODE>(x, xrow, k0 + xks + kk, sc, true, raw[kk / 4], xv + kk);
     }
-  };
-  // GCN rows whose width is a multiple of the chunk: the loads of the next chunk are issued a
-  // whole iteration before their values are scaled, biased, stored as h and staged, so the
-  // gather latency overlaps the barriers, the weight staging and the MFMAs of the chunk between
-  const bool raw3 = MODE == 3 && x.d_in == x.Kp && x.lda >= x.Kp && x.ldh >= x.Kp && (!x.h_store || x.ld_hs >= x.Kp) && !x.in_user;
-  float ra[KPT], rh[KPT], rb[KPT];
-  const float cv3 = (raw3 && xrow >= 0) ? x.cnorm[xrow] : 0.f;
-  auto issue3 = [&](int k0) {
-    if (xrow < 0) return;
-#pragma unroll
-    for (int kk = 0; kk < KPT; kk += 4) {
-      int k = k0 + xks + kk;
-      ld4v(x.A + xrow * x.lda + k, ra + kk);
-      ld4v(x.Hp + xrow * x.ldh + k, rh + kk);
-      if (x.in_bias) ld4v(x.in_bias + k, rb + kk);
-    }
-  };
-  auto finish3 = [&](int k0) {
-#pragma unroll
-    for (int kk = 0; kk < KPT; kk++) xv[kk] = 0.f;
-    if (xrow < 0) return;
-#pragma unroll
-    for (int kk = 0; kk < KPT; kk++) {
-      float v = __fmul_rn(cv3, __fadd_rn(ra[kk], rh[kk]));
-      if (x.in_bias) v = __fadd_rn(v, rb[kk]);
-      if (x.in_relu) v = v > 0.f ? v : 0.f;
-      xv[kk] = v;
-    }
-    if (x.h_store) {
-#pragma unroll
-      for (int kk = 0; kk < KPT; kk += 4)
-        *reinterpret_cast<float4 *>(x.h_store + xrow * x.ld_hs + k0 + xks + kk) = make_float4(xv[kk], xv[kk + 1], xv[kk + 2], xv[kk + 3]);
-    }
-  };
-  if (raw3) issue3(0); else fetch_chunk(0);
-  for (int k0 = 0; k0 < x.Kp; k0 += KT) {
-    if (raw3) finish3(k0);
     if (xstage) {   // even k first, then odd k
       float *xp = Xs + xr * XS + (xks >> 1);
       if constexpr (KPT == 8) {
@@ -305,9 +254,8 @@ __global__ __launch_bounds__(NW * 64) void k_xform(XformArgs x) {
 #pragma unroll
       for (int i = t; i < n4; i += NTHR) *reinterpret_cast<float4 *>(Ws + (i >> 3) * XS + (i & 7) * 4) = src[i];
     }
-    if (raw3 && k0 + KT < x.Kp) issue3(k0 + KT);
+    if (k0 + KT < x.Kp) issue(k0 + KT);
     __syncthreads();
-    if (!raw3 && k0 + KT < x.Kp) fetch_chunk(k0 + KT);
     // this wave owns TPW column tiles, or one fewer when the last one would lie past NT
     if (ct0 + (TPW - 1) * CS < NT) mfma_chunk<TPW, CS>(Xs, Ws, rt, ct0, l, acc);
     else if (TPW > 1) mfma_chunk<(TPW > 1 ? TPW - 1 : 1), CS>(Xs, Ws, rt, ct0, l, acc);
