@@ -142,7 +142,7 @@ struct ink_ctx {
   int64_t pool_reserve = 0;
   int64_t n_cap = 0;          // node capacity: every per-node array has this many entries (>= n)
   int64_t big_hint[INK_MAX_LAYERS + 1] = {0};   // chunks of long rows seen by the last update at each layer
-  double dense_frac = 0.75;          // events / edges above which a layer re-aggregates every node
+  double dense_frac = 0;             // events / edges above which a layer re-aggregates every node; 0: by aggregator and width
   int id_bits = 1;
   int kind = 0, agg = 0, n_layers = 0, mem = 0, profile = 0;
   float eps = 0.f, slack = 0.25f;

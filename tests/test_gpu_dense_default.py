@@ -1,0 +1,30 @@
+"""Where the default dense_threshold lies: the fraction of the edges on either side of which a layer groups its
+events or re-aggregates every node, by aggregator, width and event count."""
+import numpy as np
+import pytest
+
+import synth
+from util import Harness
+from test_gpu_edge_cases import tiny_model
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("agg,d,n,sources,dense", [
+    ("max", 64, 4000, 1400, 0), ("max", 64, 4000, 1401, 1), ("min", 65, 4000, 1800, 0), ("min", 65, 4000, 1801, 1),
+    ("max", 20, 1200, 819, 0), ("max", 20, 1200, 820, 1), ("sum", 64, 4000, 2999, 0), ("mean", 20, 4000, 3001, 1)])
+def test_default_threshold(agg, d, n, sources, dense):
+    rng = np.random.default_rng(n + sources)
+    v = np.arange(n)
+    src = np.repeat(v, 5)                                   # 5 out-edges each: 5 events per changed row
+    dst = (src + 1 + 7 * np.tile(np.arange(5), n)) % n
+    src, dst = synth.keys_to_edges(np.unique(synth.edge_keys(src.astype(np.int32), dst.astype(np.int32))))
+    exact = agg in ("max", "min")
+    X = rng.integers(-3, 4, size=(n, d)).astype(np.float32)
+    h = Harness(graph=(n, src, dst), X=X, model=tiny_model("sage", agg, (d, 12, 6), seed=d), precision="f32" if exact else "f64")
+    ids = np.sort(rng.choice(n, size=sources, replace=False)).astype(np.int32)
+    h.feature_step(ids, X[ids] + 1, exact=exact)
+    L = h.ink.stats()["layers"][0]
+    assert L["n_events"] == 5 * sources and L["dense"] == dense
+    h.check_state(exact=exact)
+    h.ink.close()
