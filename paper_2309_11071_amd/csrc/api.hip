@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "bigrows.h"
+#include "events.h"
 
 using namespace ink;
 
@@ -29,49 +30,6 @@ static inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 static inline dim3 grid1(int64_t n, int per = 256) { return dim3((unsigned)std::max<int64_t>(1, (n + per - 1) / per)); }
 
 // ------------------------------------------------------------------------------------ kernels
-// The events of a layer are created in this order: removed edges, changed sources (by ascending
-// source, each over its kept out-edges), inserted edges.  The grouping is stable, so every target
-// sees its events in that order: among the events that carry a row, the changed sources come first
-// and in ascending id order, which is what lets the max / min kernel drop the id comparison of ties
-// until the first inserted edge shows up (consume_batch in agg.hip).
-// seed i of the applied edge changes: deletions first, then insertions; key = target
-__device__ __forceinline__ void seed_event(int i, const int32_t *del_s, const int32_t *del_d, const int32_t *ins_s,
-                                           const int32_t *ins_d, int n_del, uint32_t *key, uint32_t *val) {
-  if (i < n_del) { *key = (uint32_t)del_d[i]; *val = (EV_DEL << kEvKindShift) | (uint32_t)del_s[i]; }
-  else {
-    int j = i - n_del;
-    *key = (uint32_t)ins_d[j]; *val = (EV_ADD << kEvKindShift) | (uint32_t)ins_s[j];
-  }
-}
-
-// out-edges of a changed source that exist in both snapshots: the block minus the ids appended
-// by this batch
-struct KeptOutDeg {
-  const int32_t *F; const int32_t *deg; const int32_t *new_out;
-  const int32_t *n_dev;      // optional device-side length of F (the launch may cover more)
-  __device__ int operator()(int64_t i) const {
-    if (n_dev && i >= *n_dev) return 0;
-    int u = F[i];
-    return deg[u] - new_out[u];
-  }
-};
-struct StorePref { int32_t *p; __device__ void operator()(int64_t i, int, int ex) const { p[i] = ex; } };
-
-// propagated event e: source = the changed node owning it, target = its e-th kept out-neighbour.
-// payload_index: store the position in F instead of the node id.
-__device__ __forceinline__ void expand_event(int e, const int32_t *F, int nF, const int32_t *pref, const int64_t *off,
-                                             const int32_t *ids, int payload_index, uint32_t *key, uint32_t *val) {
-  int lo = 0, hi = nF - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (pref[mid] <= e) lo = mid; else hi = mid - 1;
-  }
-  int u = F[lo];
-  int p = e - pref[lo];
-  *key = (uint32_t)ids[off[u] + p];
-  *val = (EV_CHG << kEvKindShift) | (uint32_t)(payload_index ? lo : u);
-}
-
 // Changed edges and changed sources of a layer: what its events are made from.
 struct EventInputs {
   const int32_t *del_s, *del_d, *ins_s, *ins_d; int n_del, n_ins;
@@ -711,16 +669,22 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
   CREATE_TRY(hipMemset(c->d_cnt, 0, sizeof(Counters)));
   CREATE_TRY(hipMalloc(&c->d_gcnt, sizeof(Counters)));
   CREATE_TRY(hipMemset(c->d_gcnt, 0, sizeof(Counters)));
-  {   // one pinned allocation: layer record + sequence number, graph record + sequence number, batch staging
+  {   // one pinned allocation: layer record + sequence number, graph record + sequence number, one more per layer, batch staging
     static_assert(sizeof(HostCounters) == 192, "records and sequence numbers on their own cache lines");
     char *h = nullptr;
-    CREATE_TRY(hipHostMalloc((void **)&h, 512 + kPinnedBatch * sizeof(ink_edge_update), hipHostMallocCoherent));
-    memset(h, 0, 512);
+    constexpr size_t kRecords = 256 * (INK_MAX_LAYERS + 2);
+    CREATE_TRY(hipHostMalloc((void **)&h, kRecords + kPinnedBatch * sizeof(ink_edge_update), hipHostMallocCoherent));
+    memset(h, 0, kRecords);
     c->h_cnt = reinterpret_cast<HostCounters *>(h);
     c->h_seq = reinterpret_cast<uint32_t *>(h + 192);
     c->h_gcnt = reinterpret_cast<HostCounters *>(h + 256);
     c->h_gseq = reinterpret_cast<uint32_t *>(h + 448);
-    c->h_batch = reinterpret_cast<ink_edge_update *>(h + 512);
+    for (int l = 1; l <= INK_MAX_LAYERS; l++) {
+      c->h_one[l] = reinterpret_cast<HostCounters *>(h + 256 * (l + 1));
+      c->h_oseq[l] = reinterpret_cast<uint32_t *>(h + 256 * (l + 1) + 192);
+    }
+    c->h_batch = reinterpret_cast<ink_edge_update *>(h + kRecords);
+    CREATE_TRY(hipMalloc(&c->d_chain, sizeof(Chain)));
   }
   size_t bmw = ((size_t)nc + 63) / 64;
   CREATE_TRY(hipMalloc(&c->bm_a, bmw * 8));
@@ -806,6 +770,7 @@ extern "C" void ink_destroy(ink_ctx *c) {
   if (c->cnorm) (void)hipFree(c->cnorm);
   if (c->d_cnt) (void)hipFree(c->d_cnt);
   if (c->d_gcnt) (void)hipFree(c->d_gcnt);
+  if (c->d_chain) (void)hipFree(c->d_chain);
   if (c->h_cnt) (void)hipHostFree(c->h_cnt);
   if (c->bm_a) (void)hipFree(c->bm_a);
   for (DevBuf *b : {&c->ws.blk, &c->ws.hist, &c->ws.tmpk, &c->ws.tmpv, &c->b_raw, &c->b_misc, &c->b_uniq, &c->b_del_s,
@@ -1102,26 +1067,26 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
 }
 
 // fills the layer's statistics from the counters of the last read-back
-static void layer_stats_from_counters(ink_ctx *c, int l) {
+static void layer_stats_from_counters(ink_ctx *c, int l, const HostCounters *h) {
   ink_layer_stats &S = c->stats.layer[l - 1];
   if (S.dense) {
     S.n_targets = c->n; S.n_exposed = c->n; S.n_regather_nb = c->n_edges_now;
-    S.n_regather_nb_long = (int64_t)c->h_cnt->sum(ST_REGATHER_LONG);
+    S.n_regather_nb_long = (int64_t)h->sum(ST_REGATHER_LONG);
     return;
   }
-  c->big_hint[l] = c->h_cnt->v[C_NCHUNK];
-  S.n_targets = c->h_cnt->v[C_NT];
+  c->big_hint[l] = h->v[C_NCHUNK];
+  S.n_targets = h->v[C_NT];
   if (c->affected_mode) {
-    S.n_exposed = S.n_targets; S.n_regather_nb = (int64_t)c->h_cnt->sum(ST_REGATHER);
+    S.n_exposed = S.n_targets; S.n_regather_nb = (int64_t)h->sum(ST_REGATHER);
     return;
   }
-  S.n_exposed = (int64_t)c->h_cnt->sum(ST_EXPOSED);
-  S.n_regather_nb = (int64_t)c->h_cnt->sum(ST_REGATHER);
-  S.n_regather_nb_long = (int64_t)c->h_cnt->sum(ST_REGATHER_LONG);
-  S.n_alpha_changed = (int64_t)c->h_cnt->sum(ST_ACHG);
-  S.n_no_deletion = (int64_t)c->h_cnt->sum(ST_NODEL);
-  S.n_deletion_no_effect = (int64_t)c->h_cnt->sum(ST_NOEFFECT);
-  S.n_covered = (int64_t)c->h_cnt->sum(ST_COVERED);
+  S.n_exposed = (int64_t)h->sum(ST_EXPOSED);
+  S.n_regather_nb = (int64_t)h->sum(ST_REGATHER);
+  S.n_regather_nb_long = (int64_t)h->sum(ST_REGATHER_LONG);
+  S.n_alpha_changed = (int64_t)h->sum(ST_ACHG);
+  S.n_no_deletion = (int64_t)h->sum(ST_NODEL);
+  S.n_deletion_no_effect = (int64_t)h->sum(ST_NOEFFECT);
+  S.n_covered = (int64_t)h->sum(ST_COVERED);
 }
 
 // bitmap (plus extra id lists) -> ascending row list in c->c_list; returns the count, or, with
@@ -1224,7 +1189,7 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, int nxt, bool keep_old, i
   return INK_OK;
 }
 
-// Layers 1..k for the sources F_1 = f_list[cur] (nF ids whose layer-1 message changed, n_chg events
+// Layers first..k for the sources F_first = f_list[cur] (nF ids whose layer-1 message changed, n_chg events
 // along their kept out-edges) and the applied edge changes; D (nD ids) are nodes whose in-degree
 // changed (normalised aggregators).  Fills the result for layer k.
 // Rows that have to be re-transformed at a layer for a reason of their own (their user term changed):
@@ -1237,12 +1202,12 @@ struct LayerRows {
 
 static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cur, int64_t n_ins, int64_t n_del,
                                    const int32_t *D_all, int64_t nD_all, ink_update_result *out,
-                                   const LayerRows *own = nullptr) {
+                                   const LayerRows *own = nullptr, int first = 1, bool events_done = false) {
   hipStream_t s = c->stream;
   const int64_t n_seed = n_ins + n_del;
   const bool gcn = c->kind == INK_MODEL_GCN;
   const bool keep_old = !c->is_select && !c->affected_mode;   // delta updates subtract the old message rows
-  for (int l = 1; l <= c->n_layers && (n_seed > 0 || nF > 0 || (own && l <= own->last_layer)); l++) {
+  for (int l = first; l <= c->n_layers && (n_seed > 0 || nF > 0 || (own && l <= own->last_layer)); l++) {
     ink_layer_stats &S = c->stats.layer[l - 1];
     const int32_t *D = D_all;
     int64_t nD = nD_all;
@@ -1252,8 +1217,14 @@ static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cu
     }
     const int32_t *F = c->f_list[cur].as<int32_t>();
     int ld_msg = msg_table(c, l).ld;
-    ink_status st = layer_aggregate(c, l, F, nF, n_chg, keep_old ? c->f_old[cur].as<float>() : nullptr, ld_msg,
-                                    n_ins, n_del);
+    ink_status st = INK_OK;
+    if (l == first && events_done) {       // begun by layer_one: the long exposed rows are left
+      Prof p(c, INK_T_AGG);
+      S.n_sources = nF; S.n_events = n_seed + n_chg;
+      API_TRY(agg_select_long_rows(c, agg_args(c, l), std::min<int64_t>(S.n_events, c->n), c->bm_a));
+    } else {
+      st = layer_aggregate(c, l, F, nF, n_chg, keep_old ? c->f_old[cur].as<float>() : nullptr, ld_msg, n_ins, n_del);
+    }
     if (st != INK_OK) return st;
     // rows to transform: aggregate changed; own message changed (self term); degree changed.
     // A layer with few events keeps the row count on the device: the transform and the emission
@@ -1267,7 +1238,7 @@ static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cu
     st = collect_rows(c, F, nF, D, nD, &nC, bound, n_t_bound, &flags_cleared);
     if (st != INK_OK) return st;
     const int32_t *nC_dev = lazy ? &c->d_cnt->v[C_NC] : nullptr;
-    if (!lazy) { S.n_transformed = nC; layer_stats_from_counters(c, l); }
+    if (!lazy) { S.n_transformed = nC; layer_stats_from_counters(c, l, c->h_cnt); }
     int nxt = cur ^ 1;
     int64_t nF2 = 0, n_chg2 = 0;
     bool result_done = false;
@@ -1298,7 +1269,7 @@ static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cu
     } else if (lazy) {
       API_TRY(read_counters(c));
     }
-    if (lazy) { S.n_transformed = c->h_cnt->v[C_NC]; layer_stats_from_counters(c, l); }
+    if (lazy) { S.n_transformed = c->h_cnt->v[C_NC]; layer_stats_from_counters(c, l, c->h_cnt); }
     S.n_changed = nF2;
     nF = nF2;
     n_chg = n_chg2;
@@ -1315,6 +1286,80 @@ static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cu
         out->embeddings = c->res_emb.as<float>();
       }
     }
+  }
+  return INK_OK;
+}
+
+// Whether layers of this context can run in one workgroup (layer_one.hip): SAGE with max or min, rows of at most 256
+// floats, and a graph whose dense fallback starts above the layer's event limit.  Profiling times the separate stages.
+static bool layer_one_possible(const ink_ctx *c, int64_t n_batch) {
+  if (c->kind != INK_MODEL_SAGE || !c->is_select || c->affected_mode || c->profile || c->n_edges_now <= n_batch) return false;
+  for (int l = 1; l <= c->n_layers; l++)
+    if (c->A[l].d > kAggBlock || kOneEvents > dense_fraction(c, kOneEvents, c->A[l].d) * (double)(c->n_edges_now - n_batch)) return false;
+  return true;
+}
+
+static hipError_t layer_one_launch(ink_ctx *c, int l) {
+  const DevLayer &L = c->layers[l - 1];
+  OneLayer p;
+  memset(&p, 0, sizeof(p));
+  p.a = agg_args(c, l);
+  p.a.big_deg = agg_select_long_degree(p.a, kOneEvents);
+  INK_TRY(agg_select_reserve(c, p.a));
+  p.g = c->d_gcnt; p.chain = c->d_chain; p.cnt = c->d_cnt;
+  p.del_s = c->del_src; p.del_d = c->del_dst; p.ins_s = c->ins_src; p.ins_d = c->ins_dst;
+  p.F = c->f_list[(l - 1) & 1].as<int32_t>(); p.F_next = c->f_list[l & 1].as<int32_t>(); p.pref = c->f_pref.as<int32_t>();
+  p.out_off = c->gout.off; p.out_ids = c->gout.ids; p.out_deg = c->gout.deg; p.new_out = c->new_out;
+  p.touched_src = c->b_uniq.as<int32_t>();
+  p.t_list = c->t_list.as<int32_t>(); p.big_list = c->big_list.as<int32_t>(); p.bm = c->bm_a;
+  p.Hp = c->H[l - 1].f(); p.ldh = c->H[l - 1].ld; p.d_in = L.in_dim;
+  p.W = L.W1; p.Kp = L.K1p; p.Np = L.N1p; p.bias = L.b1; p.n_out = L.out_dim; p.relu = L.act == INK_ACT_RELU;
+  p.user = c->USER[l].f(); p.ld_user = c->USER[l].ld;
+  p.out = c->H[l].f(); p.ld_out = c->H[l].ld;
+  p.layer = l; p.last = l == c->n_layers;
+  p.res = c->res_emb.as<float>();
+  p.h = c->h_one[l]; p.h_seq = c->h_oseq[l]; p.seq = c->one_seq[l] = ++c->pub_seq;
+  return layer_one(c, p);
+}
+
+// Behind the graph stage, before its record is awaited: as many layers as ran in one workgroup last time.
+static hipError_t layer_one_begin(ink_ctx *c) {
+  const size_t rows = 2 * kOneEvents;
+  for (DevBuf *b : {&c->f_list[0], &c->f_list[1], &c->t_list, &c->f_pref}) INK_TRY(b->reserve((rows + 2) * 4));
+  INK_TRY(c->res_emb.reserve(rows * c->H[c->n_layers].d * 4));
+  const int depth = std::max(1, std::min(c->one_hint, c->n_layers));
+  for (int l = 1; l <= depth; l++) INK_TRY(layer_one_launch(c, l));
+  return hipSuccess;
+}
+
+// The records of those layers; further layers the same way while they are small.  *l_next: first layer not done, with
+// its sources in f_list[(*l_next - 1) & 1]; *events_done: its events are.
+static ink_status layer_one_finish(ink_ctx *c, int64_t n_seed, int *l_next, bool *events_done, int64_t *nF, int64_t *n_chg,
+                                   ink_update_result *out) {
+  int launched = std::max(1, std::min(c->one_hint, c->n_layers)), l = 1;
+  for (; l <= c->n_layers; l++) {
+    if (n_seed == 0 && *nF == 0) break;                   // nothing left to propagate
+    if (l > launched) {
+      if (*n_chg > kOneEvents || n_seed + *n_chg > kOneEvents || *nF > kOneEvents) break;
+      API_TRY(layer_one_launch(c, l));
+      launched = l;
+    }
+    API_TRY(wait_published(c, c->h_oseq[l], c->one_seq[l]));
+    const HostCounters *h = c->h_one[l];
+    if (h->v[C_ONE] != kOneDone) { *events_done = h->v[C_ONE] == kOneEventsDone; break; }
+    ink_layer_stats &S = c->stats.layer[l - 1];
+    S.n_sources = *nF; S.n_events = n_seed + *n_chg;
+    layer_stats_from_counters(c, l, h);
+    S.n_transformed = h->v[C_NC];
+    S.n_changed = *nF = h->v[C_NEXT];
+    *n_chg = (uint32_t)h->v[C_NEV];
+  }
+  if (n_seed > 0) c->one_hint = l - 1;
+  *l_next = l;
+  if (l > c->n_layers) {
+    c->n_touched_src = 0;                                 // the last layer has cleared the marks
+    out->n_changed = *nF;
+    if (*nF > 0) { out->changed_ids = c->f_list[c->n_layers & 1].as<int32_t>(); out->embeddings = c->res_emb.as<float>(); }
   }
   return INK_OK;
 }
@@ -1359,6 +1404,7 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
   memset(&c->stats, 0, sizeof(c->stats));
   c->stats.n_layers = c->n_layers;
   int64_t n_ins = 0, n_del = 0;
+  bool one = false;            // the first layers may have run in one workgroup each
   if (n > 0) {
     Prof p(c, INK_T_GRAPH);
     // a device batch is read where it is; a short host batch from pinned memory, by the one kernel that reads it
@@ -1371,7 +1417,8 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
         raw = c->b_raw.p;
       }
     }
-    ink_status st = graph_apply_batch(c, raw, n, &n_ins, &n_del);
+    one = n <= kOneEvents && n <= c->small_batch && layer_one_possible(c, n);
+    ink_status st = graph_apply_batch(c, raw, n, &n_ins, &n_del, one ? layer_one_begin : nullptr);
     if (st != INK_OK) return st;
   }
   out->n_applied_ins = n_ins; out->n_applied_del = n_del; out->n_noop = n - n_ins - n_del;
@@ -1402,12 +1449,19 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
     ink_status st = emit_changed(c, nD, cur, true, ld, true, &nF, &n_chg);
     if (st != INK_OK) return st;
   }
-  {
-    ink_status st = propagate_layers(c, nF, n_chg, cur, n_ins, n_del, D, nD, out);
+  int first = 1;
+  bool events_done = false;
+  if (one) {
+    ink_status st = layer_one_finish(c, n_seed, &first, &events_done, &nF, &n_chg, out);
+    if (st != INK_OK) return st;
+    cur = (first - 1) & 1;
+  }
+  if (first <= c->n_layers) {
+    ink_status st = propagate_layers(c, nF, n_chg, cur, n_ins, n_del, D, nD, out, nullptr, first, events_done);
     if (st != INK_OK) return st;
   }
   API_TRY(graph_end_batch(c));
-  API_TRY(hipStreamSynchronize(s));
+  if (first <= c->n_layers) API_TRY(hipStreamSynchronize(s));     // otherwise the last record covers everything
   prof_collect(c);
   c->stats.ms_total = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - t0).count();
   return INK_OK;

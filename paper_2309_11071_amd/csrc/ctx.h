@@ -77,6 +77,11 @@ struct DevLayer {
 constexpr int64_t kShortBatch = 16384;     // largest batch of the short form of the graph stage
 constexpr int64_t kPinnedBatch = 1024;     // host batches up to this size are read by the device from pinned memory
 
+// A layer of at most this many events can run in one workgroup (layer_one.hip), which leaves in slot C_ONE how far it came.
+constexpr int kOneEvents = 32;
+enum { kOneNothing = 0, kOneEventsDone, kOneDone };
+struct Chain { int32_t done, n_f, n_ev, pad; };   // device: last layer done that way, its changed rows and the events they propagate
+
 constexpr int kStripes = 64;
 enum { ST_EXPOSED = 0, ST_REGATHER, ST_ACHG, ST_NODEL, ST_NOEFFECT, ST_COVERED, ST_REGATHER_LONG, ST_PAD7, ST_N };
 struct Counters {            // device-written, host-read through pinned memory
@@ -106,7 +111,7 @@ struct HostCounters {
 // of the in side whether or not the apply kernel may run (C_GINS, C_GDEL) and whether it may (C_OK).
 enum { C_ERR = 0, C_NEV = 1, C_NT, C_NBIG, C_NEXP, C_NEVL, C_NEVCH, C_NC, C_NEXT, C_NCHUNK, C_NOPS, C_TMP0, C_TMP1,
        C_TMP2, C_TMP3, C_OT, C_OCH, C_TOP64 = 18, C_TOP64B = 20,
-       C_OINS = 22, C_ODEL, C_GINS, C_GDEL, C_OK };
+       C_OINS = 22, C_ODEL, C_GINS, C_GDEL, C_OK, C_ONE = 31 };
 
 // The counters reach the host through pinned host memory: one wave writes the slots and the
 // stripe totals, then a sequence number that the host polls.  A blocking stream synchronisation
@@ -174,6 +179,11 @@ struct ink_ctx {
   ink::Counters *d_gcnt = nullptr;   // the graph stage's own block, its pinned mirror and sequence number
   ink::HostCounters *h_gcnt = nullptr;
   uint32_t *h_gseq = nullptr;
+  ink::Chain *d_chain = nullptr;
+  ink::HostCounters *h_one[INK_MAX_LAYERS + 1] = {nullptr};   // records of the layers that ran in one workgroup, and
+  uint32_t *h_oseq[INK_MAX_LAYERS + 1] = {nullptr};           // their sequence numbers (pinned)
+  uint32_t one_seq[INK_MAX_LAYERS + 1] = {0};                 // what to wait for
+  int one_hint = INK_MAX_LAYERS;     // layers that ran that way in the last update that could
   ink_edge_update *h_batch = nullptr;   // pinned staging of short host batches
   int64_t small_batch = 16384;       // batches up to this size take the short form of the graph stage
   uint64_t *bm_a = nullptr;          // node bitmaps (n bits each)
@@ -236,7 +246,9 @@ struct KernelTimer : Prof {
 // ---- graph store (graph.hip)
 hipError_t graph_build(ink_ctx *c, const int64_t *rowptr_h, const int32_t *col_h);
 // applies a batch in memory the device can read (ink_edge_update records); fills Delta E lists and counts
-ink_status graph_apply_batch(ink_ctx *c, const void *raw, int64_t n, int64_t *n_ins, int64_t *n_del);
+// `queued` is called once its launches are enqueued and before it waits for their record, if the batch takes the short form
+ink_status graph_apply_batch(ink_ctx *c, const void *raw, int64_t n, int64_t *n_ins, int64_t *n_del,
+                             hipError_t (*queued)(ink_ctx *) = nullptr);
 hipError_t graph_reserve(ink_ctx *c, int64_t max_batch);   // batch buffers for that many entries
 ink_status graph_add_nodes(ink_ctx *c, int64_t n_new);   // empty edge blocks for nodes n .. n + n_new - 1 (before n grows)
 hipError_t read_counters(ink_ctx *c);        // device counters -> c->h_cnt, waits for them
@@ -270,6 +282,10 @@ struct EventBounds { int64_t n_events, max_seg; };    // events of the layer; mo
 hipError_t agg_select_events(ink_ctx *c, const AggArgs &a, const int32_t *targets, const int32_t *seg,
                              int64_t n_targets, const int32_t *n_targets_dev, const uint32_t *ev_val, const EventBounds &eb,
                              uint64_t *chg);
+// the long exposed rows that the event stage of a layer listed (at most n_targets), as agg_select_events ends
+hipError_t agg_select_long_rows(ink_ctx *c, const AggArgs &a, int64_t n_targets, uint64_t *chg);
+hipError_t agg_select_reserve(ink_ctx *c, const AggArgs &a);      // its buffers, before the list is filled
+int agg_select_long_degree(const AggArgs &a, int64_t n_targets);   // rows with more neighbours are listed
 // sum-type aggregators (agg_sum.hip): A holds the plain sum of message rows.  F (ascending ids)
 // and f_old (their previous message rows, row stride ld_old) describe the changed sources.
 hipError_t agg_sum_full(ink_ctx *c, const AggArgs &a, const int32_t *targets, int64_t n_targets, uint64_t *chg);
@@ -308,10 +324,29 @@ struct XformArgs {
 hipError_t xform_run(ink_ctx *c, const XformArgs &x);
 // SAGE: row of the padded weight matrix where W_self starts (both halves of the input at multiples of 4)
 __host__ __device__ inline int xform_self_row(int in_dim) { return (in_dim + 3) & ~3; }
-// position of W[k][col] in the padded device copy: k-chunks of 32, inside a chunk one row of 32 per
-// column holding first the 16 even then the 16 odd k (the order the MFMA steps consume them)
+// ---- a small layer in one workgroup (layer_one.hip)
+struct OneLayer {
+  AggArgs a;                                       // with big_deg of a short launch
+  const Counters *g; Chain *chain; Counters *cnt;  // graph stage's counters; the chain; this layer's counters
+  const int32_t *del_s, *del_d, *ins_s, *ins_d;    // applied edge changes
+  const int32_t *F; int32_t *F_next, *pref;        // changed sources of this layer and of the next; prefix of their kept out-edges
+  const int64_t *out_off; const int32_t *out_ids, *out_deg; int32_t *new_out; const int32_t *touched_src;
+  int32_t *t_list, *big_list; uint64_t *bm;
+  const float *Hp; int ldh; int d_in;              // SAGE transform
+  const float *W; int Kp, Np; const float *bias; int n_out, relu;
+  const float *user; int ld_user;
+  float *out; int ld_out;
+  int layer, last;
+  float *res;                                      // last layer: the changed rows, packed
+  HostCounters *h; uint32_t *h_seq; uint32_t seq;
+};
+hipError_t layer_one(ink_ctx *c, const OneLayer &p);
+// position of W[k][col] in the padded device copy: k-chunks of 32, in a chunk one tile per 32 columns, in the order
+// in which a wave loads its operands of the tile's 16 two-k steps: lane (k % 2) * 32 + col % 32 needs k % 32 / 2 = 0 .. 15,
+// four of them per 16-byte load, and the 64 lanes of a load are contiguous
 inline size_t xform_weight_index(int k, int col, int Np) {
-  return (size_t)(k / 32) * 32 * Np + (size_t)col * 32 + (size_t)(k & 1) * 16 + (size_t)((k % 32) >> 1);
+  const int lane = (k & 1) * 32 + col % 32, step = (k % 32) >> 1;
+  return (size_t)(k / 32) * 32 * Np + (size_t)(col / 32) * 1024 + (size_t)(step / 4) * 256 + (size_t)lane * 4 + (size_t)(step % 4);
 }
 
 }  // namespace ink

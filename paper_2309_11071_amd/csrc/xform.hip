@@ -91,8 +91,7 @@ __device__ __forceinline__ void finish_x4(const XformArgs &x, int64_t row, int k
 // LDS layouts (floats): X tile [BM][2][16] with row stride XS, W tile [Np][2][16] with row stride
 // XS.  Index [.][p][s] holds k = k0 + 2 s + p, so the 16 values a lane feeds to the 16 MFMA steps
 // of a chunk (lanes 0-31 take the even k, lanes 32-63 the odd k) are contiguous: four 16-byte LDS
-// reads.  The stride of 36 floats spreads 16 lanes x 4 banks over all 64 banks.  The weights are
-// stored in global memory already in this order (see xform_weight_index).
+// reads.  The stride of 36 floats spreads 16 lanes x 4 banks over all 64 banks.
 constexpr int XS = 36;
 
 // Compute phase of one k-chunk for the NTW column tiles ct0, ct0 + 2, ... of this wave: all LDS
@@ -248,11 +247,12 @@ __global__ __launch_bounds__(NW * 64) void k_xform(XformArgs x) {
         *reinterpret_cast<float2 *>(xp + 16) = make_float2(xv[1], xv[3]);
       }
     }
-    {   // stage the W chunk: global [Np][32] in LDS order -> rows of stride XS
+    {   // stage the W chunk (xform_weight_index) -> rows of stride XS
       const float4 *src = reinterpret_cast<const float4 *>(x.W + (int64_t)k0 * Np);
       constexpr int n4 = KT * Np / 4;
 #pragma unroll
-      for (int i = t; i < n4; i += NTHR) *reinterpret_cast<float4 *>(Ws + (i >> 3) * XS + (i & 7) * 4) = src[i];
+      for (int i = t; i < n4; i += NTHR)
+        *reinterpret_cast<float4 *>(Ws + ((i >> 8) * 32 + (i & 31)) * XS + ((i >> 5) & 1) * 16 + ((i >> 6) & 3) * 4) = src[i];
     }
     if (k0 + KT < x.Kp) issue(k0 + KT);
     __syncthreads();
