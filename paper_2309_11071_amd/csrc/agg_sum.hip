@@ -8,6 +8,7 @@
 #include <algorithm>
 
 #include "longev.h"
+#include "rowload.h"
 
 namespace ink {
 
@@ -36,38 +37,46 @@ template <int LPR> __device__ __forceinline__ void sum_groups(S4 &a) {
 }
 template <int LPR> __device__ __forceinline__ bool lane_in_groups() { return lane_id() < (kWave / LPR) * LPR; }
 
+// U rows per lane group added in order; FULL: every slot is a row, otherwise empty ones add +0 (a sum that starts at
+// +0 is never -0, so that is the identity)
+template <int LPR, int U, bool FULL>
+__device__ __forceinline__ void add_batch(const RowTable<LPR> &tab, int win, int it, int cnt, S4 &acc) {
+  constexpr int G = kWave / LPR;
+  int id[U];
+  float4 row[U];
+  tab.template load_batch<U>(win, it, FULL ? kWave - 1 : cnt - 1, id, row);
+#pragma unroll
+  for (int u = 0; u < U; u++) {
+    const float x[4] = {row[u].x, row[u].y, row[u].z, row[u].w};
+    const bool on = FULL || it + u * G + tab.g < cnt;
+#pragma unroll
+    for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], on ? x[c] : 0.f);
+  }
+}
+
 // sum of rows M[ids[j]] for j in [j0, j1): group g takes j0 + g, j0 + g + G, ... in order
 template <int LPR>
 __device__ __forceinline__ void sum_range(const int32_t *ids, int64_t j0, int64_t j1, const float *M, int ldm,
                                           bool lane_on, int q, S4 &acc) {
-  constexpr int G = kWave / LPR;
+  constexpr int G = kWave / LPR, W = G * LPR == kWave ? kWave : G * (kWave / G);    // ids per window, a multiple of G
+  constexpr int U = LPR <= 16 ? INK_U_SUM16 : (LPR == 32 ? INK_U_SUM32 : INK_U_SUM64);
   const int l = lane_id();
-  const int g = l / LPR;
+  const RowTable<LPR> tab(M, ldm, lane_on, q);
 #pragma unroll
   for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
-  for (int64_t jb = j0; jb < j1; jb += kWave) {
-    int64_t jj = jb + l;
-    int myid = jj < j1 ? ids[jj] : -1;
-    int cnt = (int)((j1 - jb) < kWave ? (j1 - jb) : kWave);
-    constexpr int U = LPR <= 16 ? INK_U_SUM16 : (LPR == 32 ? INK_U_SUM32 : INK_U_SUM64);
-    for (int it = 0; it < cnt; it += G * U) {
-      int id[U];
-      float4 row[U];
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        int k = it + u * G + g;
-        id[u] = __shfl(myid, k < kWave ? k : 0, kWave);
-        if (k >= cnt) id[u] = -1;
-        if (id[u] >= 0 && lane_on) row[u] = ldf4(M + (int64_t)id[u] * ldm + 4 * q);
-      }
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        if (id[u] >= 0 && lane_on) {
-          acc.v[0] = __fadd_rn(acc.v[0], row[u].x); acc.v[1] = __fadd_rn(acc.v[1], row[u].y);
-          acc.v[2] = __fadd_rn(acc.v[2], row[u].z); acc.v[3] = __fadd_rn(acc.v[3], row[u].w);
-        }
-      }
+  const int32_t *p = ids + j0;
+  const int n = __builtin_amdgcn_readfirstlane((int)(j1 - j0));
+  int win = n > 0 ? p[l < n ? l : n - 1] : 0;
+  for (int jb = 0; jb < n; jb += W) {
+    const int cnt = n - jb < W ? n - jb : W, ahead = jb + W + l;
+    const int next = jb + W < n ? p[ahead < n ? ahead : n - 1] : 0;
+    for (int it = 0; it < cnt;) {
+      const int left = cnt - it;
+      if (left >= G * U) { add_batch<LPR, U, true>(tab, win, it, cnt, acc); it += G * U; }
+      else if (left > G * U / 4) { add_batch<LPR, U / 2, false>(tab, win, it, cnt, acc); it += G * U / 2; }
+      else { add_batch<LPR, U / 4, false>(tab, win, it, cnt, acc); it += G * U / 4; }
     }
+    win = next;
   }
   sum_groups<LPR>(acc);
 }

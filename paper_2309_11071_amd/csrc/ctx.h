@@ -14,7 +14,8 @@ namespace ink {
 #ifndef INK_BIG_DEG
 #define INK_BIG_DEG 256
 #endif
-// neighbour rows in flight per lane group while gathering, by aggregator family and lanes per row
+// neighbour rows in flight per lane group while gathering, by aggregator family and lanes per row.  8 where the registers
+// allow: for max / min over rows of 128 floats 8 take 84 registers and cost 3 % (625k nodes, inference: 5.15 against 4.99 ms).
 #ifndef INK_U_SEL16
 #define INK_U_SEL16 4
 #endif
@@ -22,16 +23,16 @@ namespace ink {
 #define INK_U_SEL32 4
 #endif
 #ifndef INK_U_SEL64
-#define INK_U_SEL64 4
+#define INK_U_SEL64 8
 #endif
 #ifndef INK_U_SUM16
 #define INK_U_SUM16 8       // narrow rows are cheap in registers: 8 loads in flight measured 3.5 % faster than 4
 #endif
 #ifndef INK_U_SUM32
-#define INK_U_SUM32 4
+#define INK_U_SUM32 8
 #endif
 #ifndef INK_U_SUM64
-#define INK_U_SUM64 4
+#define INK_U_SUM64 8
 #endif
 #ifndef INK_BIG_CHUNK
 #define INK_BIG_CHUNK 1024

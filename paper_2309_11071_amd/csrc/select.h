@@ -2,6 +2,7 @@
 // gather of a row's neighbours, the reduction of a target's events and the decision what they change.
 #pragma once
 #include "longev.h"
+#include "rowload.h"
 
 namespace ink {
 
@@ -93,6 +94,27 @@ template <int LPR> __device__ __forceinline__ int reduce_flags(int fl) {
   return fl;
 }
 
+// U rows per lane group into the running (best, runner-up) pairs; FULL: every slot is a row
+template <bool IS_MIN, int LPR, bool ASC, int U, bool FULL>
+__device__ __forceinline__ void take_batch(const RowTable<LPR> &tab, int win, int it, int cnt, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
+  constexpr int G = kWave / LPR;
+  int id[U];
+  float4 row[U];
+  tab.template load_batch<U>(win, it, FULL ? kWave - 1 : cnt - 1, id, row);
+#pragma unroll
+  for (int u = 0; u < U; u++) {
+    float x[4] = {row[u].x, row[u].y, row[u].z, row[u].w};
+    if (!FULL) {      // an empty slot offers the worst value under the largest id: it takes no place
+      const bool on = it + u * G + tab.g < cnt;
+      id[u] = on ? id[u] : 0x7fffffff;
+#pragma unroll
+      for (int c = 0; c < 4; c++) x[c] = on ? x[c] : worst<IS_MIN>();
+    }
+#pragma unroll
+    for (int c = 0; c < 4; c++) take2i<IS_MIN, ASC>(x[c], id[u], bv.v[c], bi.v[c], sv.v[c], si.v[c]);
+  }
+}
+
 // Selection over neighbours ids[j0 .. j1) of one row, by the whole wave.  On return every lane
 // holds the best (value, id) and the runner-up value of its 4 dimensions over the range;
 // (worst, INT_MAX, worst) if empty.
@@ -100,35 +122,24 @@ template <bool IS_MIN, int LPR, bool ASC>
 __device__ __forceinline__ void gather_range_t(const int32_t *ids, int64_t j0, int64_t j1, const float *M,
                                                int ldm, bool lane_on, int q, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
   constexpr int G = kWave / LPR;
+  constexpr int U = LPR == 16 ? INK_U_SEL16 : (LPR == 32 ? INK_U_SEL32 : INK_U_SEL64);
   const int l = lane_id();
-  const int g = l / LPR;
+  const RowTable<LPR> tab(M, ldm, lane_on, q);
 #pragma unroll
   for (int c = 0; c < 4; c++) { bv.v[c] = worst<IS_MIN>(); bi.v[c] = 0x7fffffff; sv.v[c] = worst<IS_MIN>(); si.v[c] = 0x7fffffff; }
-  for (int64_t jb = j0; jb < j1; jb += kWave) {
-    int64_t jj = jb + l;
-    int myid = jj < j1 ? ids[jj] : -1;
-    int cnt = (int)((j1 - jb) < kWave ? (j1 - jb) : kWave);
-    constexpr int U = LPR == 16 ? INK_U_SEL16 : (LPR == 32 ? INK_U_SEL32 : INK_U_SEL64);
-    for (int it = 0; it < cnt; it += G * U) {
-      int id[U];
-      float4 row[U];
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        int k = it + u * G + g;
-        id[u] = __shfl(myid, k < kWave ? k : 0, kWave);
-        if (k >= cnt) id[u] = -1;
-        if (id[u] >= 0 && lane_on) row[u] = ld4(M + (int64_t)id[u] * ldm + 4 * q);
-      }
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        if (id[u] >= 0 && lane_on) {
-          take2i<IS_MIN, ASC>(row[u].x, id[u], bv.v[0], bi.v[0], sv.v[0], si.v[0]);
-          take2i<IS_MIN, ASC>(row[u].y, id[u], bv.v[1], bi.v[1], sv.v[1], si.v[1]);
-          take2i<IS_MIN, ASC>(row[u].z, id[u], bv.v[2], bi.v[2], sv.v[2], si.v[2]);
-          take2i<IS_MIN, ASC>(row[u].w, id[u], bv.v[3], bi.v[3], sv.v[3], si.v[3]);
-        }
-      }
+  const int32_t *p = ids + j0;
+  const int n = __builtin_amdgcn_readfirstlane((int)(j1 - j0));
+  int win = n > 0 ? p[l < n ? l : n - 1] : 0;
+  for (int jb = 0; jb < n; jb += kWave) {
+    const int cnt = n - jb < kWave ? n - jb : kWave, ahead = jb + kWave + l;
+    const int next = jb + kWave < n ? p[ahead < n ? ahead : n - 1] : 0;
+    for (int it = 0; it < cnt;) {
+      const int left = cnt - it;
+      if (left >= G * U) { take_batch<IS_MIN, LPR, ASC, U, true>(tab, win, it, cnt, bv, bi, sv, si); it += G * U; }
+      else if (left > G * U / 4) { take_batch<IS_MIN, LPR, ASC, U / 2, false>(tab, win, it, cnt, bv, bi, sv, si); it += G * U / 2; }
+      else { take_batch<IS_MIN, LPR, ASC, U / 4, false>(tab, win, it, cnt, bv, bi, sv, si); it += G * U / 4; }
     }
+    win = next;
   }
   reduce_groups_i<IS_MIN, LPR>(bv, bi, sv, si);
 }
