@@ -124,7 +124,8 @@ __global__ __launch_bounds__(NW * kWave) void k_big_partial(AggArgs a, const int
   }
 }
 
-// one wave per big row: reduce its partial rows and store
+// One wave per big row: its lane groups take the partial rows in turn, U of them in flight, then the row is stored.  (One
+// row after the other made a hub's chain the launch's time: 45 us on 12.5M edges and rows of 128 floats, now 21.)
 template <bool IS_MIN, int LPR>
 __global__ __launch_bounds__(64) void k_big_final(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
                                                   const int32_t *pref, const float *part_v, const int32_t *part_i,
@@ -133,6 +134,8 @@ __global__ __launch_bounds__(64) void k_big_final(AggArgs a, const int32_t *big_
   const int l = lane_id();
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
+  constexpr int G = kWave / LPR, U = 4;
+  const int g = l / LPR, qo = lane_on ? 4 * q : 0;
   const int n_big = *n_big_p;
   for (int i = blockIdx.x; i < n_big; i += gridDim.x) {
     int v = big_list[i];
@@ -141,14 +144,29 @@ __global__ __launch_bounds__(64) void k_big_final(AggArgs a, const int32_t *big_
     for (int c = 0; c < 4; c++) {
       bv.v[c] = worst<IS_MIN>(); bi.v[c] = 0x7fffffff; s2.v[c] = worst<IS_MIN>(); j2.v[c] = 0x7fffffff;
     }
-    if (lane_on && l < LPR) {
-      for (int p = pref[i]; p < pref[i + 1]; p++) {
-        int64_t o = (int64_t)p * a.wd + 4 * q;
+    const int p0 = pref[i], p1 = pref[i + 1];
+    for (int pb = p0; pb < p1; pb += G * U) {
+      float4 xv[U], xs[U];
+      int4 xi[U], xj[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        const int p = pb + u * G + g;
+        const int64_t o = (int64_t)(p < p1 ? p : p1 - 1) * a.wd + qo;
+        xv[u] = ld4(part_v + o); xi[u] = *reinterpret_cast<const int4 *>(part_i + o);
+        xs[u] = ld4(part_s + o); xj[u] = *reinterpret_cast<const int4 *>(part_j + o);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        const bool on = pb + u * G + g < p1;        // a partial row past the end is empty: it takes no place
+        const float yv[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w}, ys[4] = {xs[u].x, xs[u].y, xs[u].z, xs[u].w};
+        const int yi[4] = {xi[u].x, xi[u].y, xi[u].z, xi[u].w}, yj[4] = {xj[u].x, xj[u].y, xj[u].z, xj[u].w};
 #pragma unroll
         for (int c = 0; c < 4; c++)
-          merge2i<IS_MIN>(part_v[o + c], part_i[o + c], part_s[o + c], part_j[o + c], bv.v[c], bi.v[c], s2.v[c], j2.v[c]);
+          merge2i<IS_MIN>(on ? yv[c] : worst<IS_MIN>(), on ? yi[c] : 0x7fffffff, on ? ys[c] : worst<IS_MIN>(),
+                          on ? yj[c] : 0x7fffffff, bv.v[c], bi.v[c], s2.v[c], j2.v[c]);
       }
     }
+    reduce_groups_i<IS_MIN, LPR>(bv, bi, s2, j2);
     finish_empty<IS_MIN>(bv, bi, s2, j2);
     RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
     F4 dum; I4 dumi;

@@ -169,20 +169,32 @@ __global__ __launch_bounds__(64) void k_sum_big_final(AggArgs a, const int32_t *
                                                       int compare) {
   const int l = lane_id();
   const int q = l % LPR;
-  const bool lane_on = 4 * q < a.wd;
+  const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
+  constexpr int G = kWave / LPR, U = 8;
+  const int g = l / LPR < G ? l / LPR : G - 1, qo = lane_on ? 4 * q : 0;
   const int n_big = *n_big_p;
   for (int i = blockIdx.x; i < n_big; i += gridDim.x) {
     int v = big_list[i];
     S4 acc;
 #pragma unroll
     for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
-    if (lane_on && l < LPR) {
-      for (int p = pref[i]; p < pref[i + 1]; p++) {
-        int64_t o = (int64_t)p * a.wd + 4 * q;
+    const int p0 = pref[i], p1 = pref[i + 1];
+    for (int pb = p0; pb < p1; pb += G * U) {       // lane groups take the chunks in turn, U of them in flight
+      float4 x[U];
 #pragma unroll
-        for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], part[o + c]);
+      for (int u = 0; u < U; u++) {
+        const int p = pb + u * G + g;
+        x[u] = ldf4(part + (int64_t)(p < p1 ? p : p1 - 1) * a.wd + qo);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        const bool on = pb + u * G + g < p1;
+        const float y[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+        for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], on ? y[c] : 0.f);
       }
     }
+    sum_groups<LPR>(acc);
     bool ch = store_sum<LPR>(a.A, a.ld, a.d, v, lane_on, q, acc, compare != 0);
     if (ch && chg && l == 0) mark_bit_s(chg, v);
   }
