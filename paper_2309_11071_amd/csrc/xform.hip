@@ -134,7 +134,8 @@ __device__ __forceinline__ void xform_epilogue(const XformArgs &x, const f16v *a
     if (col >= x.n_out) continue;
     float bias = x.bias ? x.bias[col] : 0.f;
     float oldv[16];
-    if (x.to_table) {      // all loads of the cached values first, then compare and store
+    const bool compare = x.to_table && (x.row_changed || x.old_rows);     // a whole inference only stores
+    if (compare) {         // all loads of the cached values first, then compare and store
 #pragma unroll
       for (int r = 0; r < 16; r++) {
         int rl = rt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
@@ -152,12 +153,12 @@ __device__ __forceinline__ void xform_epilogue(const XformArgs &x, const f16v *a
       if (x.out_scale) v = __fmul_rn(v, x.out_scale[sout[rl]]);
       if (x.relu) v = v > 0.f ? v : 0.f;
       int64_t j = r0 + rl;
-      if (x.to_table) {
+      if (compare) {
         float old = oldv[r];
         if (x.old_rows) x.old_rows[j * x.ld_old + col] = old;
         if (__float_as_uint(old) != __float_as_uint(v)) { x.out[sout[rl] * x.ld_out + col] = v; schg[rl] = 1; }
       } else {
-        x.out[j * x.ld_out + col] = v;
+        x.out[(x.to_table ? sout[rl] : j) * x.ld_out + col] = v;
       }
     }
   }
