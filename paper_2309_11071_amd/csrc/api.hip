@@ -249,6 +249,85 @@ __global__ void k_mark_nodes(const int32_t *list, int n, uint64_t *bm) {
   if (i < n) { int v = list[i]; atomicOr((unsigned long long *)&bm[v >> 6], 1ull << (v & 63)); }
 }
 
+// The changed rows of a long layer: their positions, their ids and the prefix of the events they propagate, in one scan
+// over the row flags (two launches).  A tile's sum packs both counts: rows in the upper, events in the lower 32 bits
+// (a layer has less than 2^31 events).  Compaction, gather of the ids and prefix were five launches; the six scans of a
+// batch of 10000 on 1.25M nodes took 140 us that way and take 112, a batch of 100 passes in 1.63 instead of 1.67 ms.
+struct EmitRows {
+  const uint8_t *flag; const int32_t *rows;      // flags are read 8 at a time: room for 7 past n
+  const int32_t *deg, *new_out;                  // deg null: no events wanted
+  int64_t n;
+  __device__ __forceinline__ unsigned long long flags8(int64_t base) const {
+    if (base >= n) return 0;
+    const unsigned long long f = *reinterpret_cast<const unsigned long long *>(flag + base);
+    return n - base >= 8 ? f : f & ((1ull << (8 * (n - base))) - 1);
+  }
+  __device__ __forceinline__ int events(int u) const { return deg ? kept_out_degree(deg, new_out, u) : 0; }
+};
+constexpr int kEmitThreads = 256, kEmitTile = kEmitThreads * 8;
+
+__device__ __forceinline__ unsigned long long block_excl_scan64(unsigned long long x, unsigned long long *sm, unsigned long long *total) {
+  const int l = lane_id(), w = threadIdx.x / kWave;
+  unsigned long long inc = x;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const unsigned long long y = __shfl_up(inc, o, kWave);
+    if (l >= o) inc += y;
+  }
+  __syncthreads();                 // sm may still be read by the scan before
+  if (l == kWave - 1) sm[w] = inc;
+  __syncthreads();
+  unsigned long long before = 0, all = 0;
+#pragma unroll
+  for (int i = 0; i < kEmitThreads / kWave; i++) { if (i < w) before += sm[i]; all += sm[i]; }
+  *total = all;
+  return before + inc - x;
+}
+
+// u[k]: id of row base + k, v[k]: its packed count (0 if its flag is not set)
+__device__ __forceinline__ unsigned long long emit_items(const EmitRows &e, int64_t base, int u[8], unsigned long long v[8]) {
+  const unsigned long long f = e.flags8(base);
+  unsigned long long s = 0;
+#pragma unroll
+  for (int k = 0; k < 8; k++) {
+    u[k] = 0; v[k] = 0;
+    if ((f >> (8 * k)) & 0xFF) { u[k] = e.rows[base + k]; v[k] = (1ull << 32) + (unsigned)e.events(u[k]); }
+    s += v[k];
+  }
+  return s;
+}
+
+__global__ __launch_bounds__(kEmitThreads) void k_emit_count(EmitRows e, unsigned long long *tile) {
+  __shared__ unsigned long long sm[kEmitThreads / kWave];
+  int u[8]; unsigned long long v[8], tot;
+  (void)block_excl_scan64(emit_items(e, (int64_t)blockIdx.x * kEmitTile + threadIdx.x * 8, u, v), sm, &tot);
+  if (threadIdx.x == 0) tile[blockIdx.x] = tot;
+}
+
+__global__ __launch_bounds__(kEmitThreads) void k_emit_write(EmitRows e, const unsigned long long *tile, int32_t *idx, int32_t *ids,
+                                                             int32_t *pref, int32_t *n_rows, int32_t *n_events) {
+  __shared__ unsigned long long sm[kEmitThreads / kWave];
+  unsigned long long part = 0, before, tot;
+  for (int i = threadIdx.x; i < (int)blockIdx.x; i += kEmitThreads) part += tile[i];
+  (void)block_excl_scan64(part, sm, &before);
+  const int64_t base = (int64_t)blockIdx.x * kEmitTile + threadIdx.x * 8;
+  int u[8]; unsigned long long v[8];
+  unsigned long long at = before + block_excl_scan64(emit_items(e, base, u, v), sm, &tot);
+#pragma unroll
+  for (int k = 0; k < 8; k++) {
+    if (!v[k]) continue;
+    const int p = (int)(at >> 32);
+    idx[p] = (int32_t)(base + k);
+    ids[p] = u[k];
+    if (e.deg) pref[p] = (int32_t)(uint32_t)at;
+    at += v[k];
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    *n_rows = (int32_t)((before + tot) >> 32);
+    if (e.deg) *n_events = (int32_t)(uint32_t)(before + tot);
+  }
+}
+
 __global__ void k_gather_i32(const int32_t *table, const int32_t *idx, int n, const int32_t *n_dev, int32_t *out) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n_dev) n = *n_dev;
@@ -1168,21 +1247,20 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, int nxt, bool keep_old, i
     else INK_SMALL_EMIT(1024, 4);
 #undef INK_SMALL_EMIT
   } else {
-    API_TRY(compact_flags_u8(c->ws, c->c_flag.as<uint8_t>(), nC, c->c_idx.as<int32_t>(), &dc->v[C_NEXT], s));
-    hipLaunchKernelGGL(k_gather_i32, grid1(nC), dim3(256), 0, s, (const int32_t *)c->c_list.as<int32_t>(),
-                       (const int32_t *)c->c_idx.as<int32_t>(), 0, (const int32_t *)&dc->v[C_NEXT],
-                       c->f_list[nxt].as<int32_t>());
+    if (want_events) API_TRY(c->f_pref.reserve((size_t)(nC + 1) * 4));
+    const int tiles = nblocks(nC, kEmitTile);
+    API_TRY(c->ws.blk.reserve((size_t)tiles * sizeof(unsigned long long)));
+    unsigned long long *tile = c->ws.blk.as<unsigned long long>();
+    const EmitRows e{c->c_flag.as<uint8_t>(), c->c_list.as<int32_t>(), want_events ? c->gout.deg : nullptr, c->new_out, nC};
+    hipLaunchKernelGGL(k_emit_count, dim3(tiles), dim3(kEmitThreads), 0, s, e, tile);
+    hipLaunchKernelGGL(k_emit_write, dim3(tiles), dim3(kEmitThreads), 0, s, e, (const unsigned long long *)tile,
+                       c->c_idx.as<int32_t>(), c->f_list[nxt].as<int32_t>(), c->f_pref.as<int32_t>(), &dc->v[C_NEXT], &dc->v[C_NEV]);
   }
   if (keep_old) {
     API_TRY(c->f_old[nxt].reserve((size_t)nC * ld * 4));
     hipLaunchKernelGGL(k_gather_rows_ld, grid1(nC * (ld / 4)), dim3(256), 0, s, (const float *)c->c_old.as<float>(), ld,
                        (const int32_t *)c->c_idx.as<int32_t>(), (int64_t)0, (const int32_t *)&dc->v[C_NEXT],
                        c->f_old[nxt].as<float>());
-  }
-  if (want_events && !small) {
-    API_TRY(c->f_pref.reserve((size_t)(nC + 1) * 4));
-    API_TRY(tile_scan(c->ws, KeptOutDeg{c->f_list[nxt].as<int32_t>(), c->gout.deg, c->new_out, &dc->v[C_NEXT]},
-                      StorePref{c->f_pref.as<int32_t>()}, nC, &dc->v[C_NEV], s));
   }
   if (result && (size_t)nC * result->d * 4 <= kEagerResultBytes) {
     API_TRY(c->res_emb.reserve((size_t)nC * result->d * 4));

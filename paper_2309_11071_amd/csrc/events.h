@@ -19,18 +19,8 @@ __device__ __forceinline__ void seed_event(int i, const int32_t *del_s, const in
   }
 }
 
-// out-edges of a changed source that exist in both snapshots: the block minus the ids appended
-// by this batch
-struct KeptOutDeg {
-  const int32_t *F; const int32_t *deg; const int32_t *new_out;
-  const int32_t *n_dev;      // optional device-side length of F (the launch may cover more)
-  __device__ int operator()(int64_t i) const {
-    if (n_dev && i >= *n_dev) return 0;
-    int u = F[i];
-    return deg[u] - new_out[u];
-  }
-};
-struct StorePref { int32_t *p; __device__ void operator()(int64_t i, int, int ex) const { p[i] = ex; } };
+// out-edges of a changed source that exist in both snapshots: the block minus the ids appended by this batch
+__device__ __forceinline__ int kept_out_degree(const int32_t *deg, const int32_t *new_out, int u) { return deg[u] - new_out[u]; }
 
 // propagated event e: source = the changed node owning it, target = its e-th kept out-neighbour.
 // payload_index: store the position in F instead of the node id.
