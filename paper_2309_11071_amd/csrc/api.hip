@@ -1270,7 +1270,9 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, int nxt, bool keep_old, i
     *result_done = true;
   }
   API_TRY(hipGetLastError());
-  if (small) API_TRY(wait_published(c, c->h_seq, published));
+  // with the result gathered, one record after it ends the call: no synchronisation of the stream on top
+  c->drained = result_done && *result_done;
+  if (small && !c->drained) API_TRY(wait_published(c, c->h_seq, published));
   else API_TRY(read_counters(c));
   *nF2 = c->h_cnt->v[C_NEXT];
   if (want_events) *n_chg = (uint32_t)c->h_cnt->v[C_NEV];
@@ -1295,6 +1297,7 @@ static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cu
   const int64_t n_seed = n_ins + n_del;
   const bool gcn = c->kind == INK_MODEL_GCN;
   const bool keep_old = !c->is_select && !c->affected_mode;   // delta updates subtract the old message rows
+  c->drained = false;
   for (int l = first; l <= c->n_layers && (n_seed > 0 || nF > 0 || (own && l <= own->last_layer)); l++) {
     ink_layer_stats &S = c->stats.layer[l - 1];
     const int32_t *D = D_all;
@@ -1376,6 +1379,11 @@ static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cu
     }
   }
   return INK_OK;
+}
+
+// The end of a call: what propagate_layers left running, if anything (profiling reads events recorded after the record).
+static hipError_t finish_stream(ink_ctx *c) {
+  return c->drained && !c->profile ? hipSuccess : hipStreamSynchronize(c->stream);
 }
 
 // Whether layers of this context can run in one workgroup (layer_one.hip): SAGE with max or min, rows of at most 256
@@ -1549,7 +1557,7 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
     if (st != INK_OK) return st;
   }
   API_TRY(graph_end_batch(c));
-  if (first <= c->n_layers) API_TRY(hipStreamSynchronize(s));     // otherwise the last record covers everything
+  if (first <= c->n_layers) API_TRY(finish_stream(c));     // otherwise the last record covers everything
   prof_collect(c);
   c->stats.ms_total = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - t0).count();
   return INK_OK;
@@ -1645,7 +1653,7 @@ static ink_status update_features_impl(ink_ctx *c, const int32_t *node_ids, cons
   if (st != INK_OK) return st;
   st = propagate_layers(c, nF, n_chg, cur, 0, 0, nullptr, 0, out);
   if (st != INK_OK) return st;
-  API_TRY(hipStreamSynchronize(s));
+  API_TRY(finish_stream(c));
   prof_collect(c);
   c->stats.ms_total = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - t0).count();
   return INK_OK;
@@ -1764,7 +1772,7 @@ static ink_status apply_user_events_impl(ink_ctx *c, const ink_user_event *event
   LayerRows own{last, user_rows_of, &u};
   ink_status st = propagate_layers(c, 0, 0, 0, 0, 0, nullptr, 0, out, &own);
   if (st != INK_OK) return st;
-  API_TRY(hipStreamSynchronize(s));
+  API_TRY(finish_stream(c));
   prof_collect(c);
   c->stats.ms_total = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - t0).count();
   return INK_OK;

@@ -155,6 +155,7 @@ struct ink_ctx {
   bool batch_dev = false;
   bool affected_mode = false;        // current call is the affected-area recompute baseline
   bool is_select = true, is_min = false, inferred = false, own_stream = false;
+  bool drained = false;              // the last record read back covers everything the call launched
   bool broken = false;               // an updating call failed on the device side: state may be half-written
   hipStream_t stream = nullptr;
   int device = 0;                    // HIP device the context lives on
