@@ -42,9 +42,14 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
   const bool lane_on = 4 * q < a.wd;
   if (n_targets_dev) { int64_t nd = *n_targets_dev; n_targets = nd < n_targets ? nd : n_targets; }
   const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kWave);
-  for (int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave; wid < n_targets; wid += stride) {
-    int v = targets ? targets[wid] : (int)wid;
-    int deg = a.in_deg[v];
+  // wave-uniform, so that the row's place and length are scalar loads that are under way together; with that the kernel
+  // has 64 registers, 8 waves per SIMD (inference of 625k nodes, 3 layers of 128: 4.80 -> 4.69 ms)
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  for (int64_t wid = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave; wid < n_targets; wid += stride) {
+    const int v = targets ? targets[wid] : (int)wid;
+    const int deg = a.in_deg[v];
+    const int64_t off = a.in_off[v];
+    const bool asc = a.in_asc[v] != 0;
     if ((flags & FULL_COUNT_GATHER) && l == 0)
       atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER], (unsigned long long)deg);
     if ((flags & FULL_COUNT_LONG) && deg > a.big_deg && l == 0)     // few rows: also tallied when every row is recomputed
@@ -53,20 +58,22 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
       if (l == 0) big_list[atomicAdd(n_big, 1)] = v;
       continue;
     }
-    int64_t off = a.in_off[v];
     F4 bv; I4 bi; F4 sv; I4 si;
-    gather_range<IS_MIN, LPR>(a.in_ids + off, 0, deg, a.M, a.ldm, lane_on, q, a.in_asc[v] != 0, bv, bi, sv, si);
+    gather_range<IS_MIN, LPR>(a.in_ids + off, 0, deg, a.M, a.ldm, lane_on, q, asc, bv, bi, sv, si);
     finish_empty<IS_MIN>(bv, bi, sv, si);
     RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
     F4 dum; I4 dumi;
     bool ch;
     if (flags & FULL_COMPARE) ch = store_row<LPR>(o, v, lane_on, q, bv, bi, sv, si, false, dum, dumi);
     else {
+      const int64_t o4 = (int64_t)v * a.ld + 4 * q;       // every lane group has the row: the first two store half of the tables each
       if (lane_on && l < LPR) {
-        *reinterpret_cast<float4 *>(a.A + (int64_t)v * a.ld + 4 * q) = make_float4(bv.v[0], bv.v[1], bv.v[2], bv.v[3]);
-        *reinterpret_cast<int4 *>(a.ARG + (int64_t)v * a.ld + 4 * q) = make_int4(bi.v[0], bi.v[1], bi.v[2], bi.v[3]);
-        *reinterpret_cast<float4 *>(a.UB + (int64_t)v * a.ld + 4 * q) = make_float4(sv.v[0], sv.v[1], sv.v[2], sv.v[3]);
-        *reinterpret_cast<int4 *>(a.ARG2 + (int64_t)v * a.ld + 4 * q) = make_int4(si.v[0], si.v[1], si.v[2], si.v[3]);
+        *reinterpret_cast<float4 *>(a.A + o4) = make_float4(bv.v[0], bv.v[1], bv.v[2], bv.v[3]);
+        *reinterpret_cast<int4 *>(a.ARG + o4) = make_int4(bi.v[0], bi.v[1], bi.v[2], bi.v[3]);
+      }
+      if (lane_on && (LPR == kWave || l / LPR == 1)) {
+        *reinterpret_cast<float4 *>(a.UB + o4) = make_float4(sv.v[0], sv.v[1], sv.v[2], sv.v[3]);
+        *reinterpret_cast<int4 *>(a.ARG2 + o4) = make_int4(si.v[0], si.v[1], si.v[2], si.v[3]);
       }
       ch = false;
     }

@@ -112,10 +112,12 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
   const int l = lane_id();
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
-  int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+  // wave-uniform, so that the row's place and length are scalar loads that are under way together
+  const int64_t wid = (int64_t)blockIdx.x * (blockDim.x / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   if (wid >= n_targets) return;
-  int v = targets ? targets[wid] : (int)wid;
-  int deg = a.in_deg[v];
+  const int v = targets ? targets[wid] : (int)wid;
+  const int deg = a.in_deg[v];
+  const int64_t off = a.in_off[v];
   if (targets && l == 0) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER], (unsigned long long)deg);
   if (deg > a.big_deg && l == 0)      // few rows: also tallied when every row is recomputed
     atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER_LONG], (unsigned long long)deg);
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
     return;
   }
   S4 acc;
-  sum_range<LPR>(a.in_ids + a.in_off[v], 0, deg, a.M, a.ldm, lane_on, q, acc);
+  sum_range<LPR>(a.in_ids + off, 0, deg, a.M, a.ldm, lane_on, q, acc);
   bool ch = store_sum<LPR>(a.A, a.ld, a.d, v, lane_on, q, acc, compare != 0);
   if (ch && chg && l == 0) mark_bit_s(chg, v);
 }
