@@ -492,12 +492,19 @@ static ink_status fail(ink_ctx *c, ink_status st, const std::string &msg) {
   return st;
 }
 
+// What a failing call had enqueued by then may read the caller's arrays: it has ended before the call returns.
+static ink_status drain(ink_ctx *c, ink_status st) {
+  (void)hipStreamSynchronize(c->stream);
+  return st;
+}
+
 // An updating call that fails on the device side (allocation or HIP error) may have rewritten part of
 // the graph store or of the cache: the context is then marked unusable and every later call but
 // ink_last_error / ink_destroy returns INK_E_STATE.
 static ink_status seal(ink_ctx *c, ink_status st) {
-  if (st == INK_E_OOM || st == INK_E_DEVICE) c->broken = true;
-  return st;
+  if (st != INK_E_OOM && st != INK_E_DEVICE) return st;
+  c->broken = true;
+  return drain(c, st);
 }
 static const char *kBrokenMsg = "the context is unusable after a failed update (INK_E_OOM / INK_E_DEVICE): destroy it";
 
@@ -1515,7 +1522,7 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
     }
     one = n <= kOneEvents && n <= c->small_batch && layer_one_possible(c, n);
     ink_status st = graph_apply_batch(c, raw, n, &n_ins, &n_del, one ? layer_one_begin : nullptr);
-    if (st != INK_OK) return st;
+    if (st != INK_OK) return drain(c, st);       // behind the record that tells of a bad entry stand launches that do nothing for it
   }
   out->n_applied_ins = n_ins; out->n_applied_del = n_del; out->n_noop = n - n_ins - n_del;
   c->n_edges_now += n_ins - n_del;
@@ -1617,8 +1624,8 @@ static ink_status update_features_impl(ink_ctx *c, const int32_t *node_ids, cons
       hipLaunchKernelGGL(k_any_out_of_range, grid1(n), dim3(256), 0, s, (const uint32_t *)ids, n, (uint32_t)c->n, &dc->v[C_TMP1]);
     API_TRY(hipGetLastError());
     API_TRY(read_counters(c));
-    if (c->h_cnt->v[C_TMP1]) return fail(c, INK_E_RANGE, "ink_update_features: node id out of range");
-    if (c->h_cnt->v[C_TMP0]) return fail(c, INK_E_ARG, "ink_update_features: a node id appears more than once");
+    if (c->h_cnt->v[C_TMP1]) return drain(c, fail(c, INK_E_RANGE, "ink_update_features: node id out of range"));
+    if (c->h_cnt->v[C_TMP0]) return drain(c, fail(c, INK_E_ARG, "ink_update_features: a node id appears more than once"));
     API_TRY(c->c_flag.reserve((size_t)n + 64));
     API_TRY(c->c_idx.reserve((size_t)n * 4));
     API_TRY(c->c_list.reserve((size_t)c->n * 4));
