@@ -24,7 +24,10 @@
  *     unusable, every later call on it returns INK_E_STATE, and it must be destroyed.
  *     ink_last_error() gives a readable message.
  *   - One context = one HIP stream; calls on one context must not overlap.  All calls are
- *     synchronous: on return the work is complete.
+ *     synchronous: on return the work is complete, what was passed in is no longer read and results
+ *     can be used on any stream.  A successful update ends with a record that the device writes to the
+ *     host when everything else is done: its last kernel, which writes nothing after that record, may for
+ *     a moment still show as running on the stream.  A call that returns an error leaves nothing running.
  *   - Node ids are int32 in [0, n_nodes); the graph is a simple directed graph without self
  *     loops.  Edge batches never change n_nodes (the paper's update stream holds edges only,
  *     Sec. 2.1); it grows only through ink_add_nodes, up to ink_options.node_capacity.

@@ -342,7 +342,9 @@ __global__ __launch_bounds__(kOneThreads) void k_layer_one(OneLayer p) {
     }
   }
   if (t == 0) cnt->v[C_ONE] = status;
-  __threadfence_block();
+  // The record of the last layer ends the call, and the result may then be read on any stream: every wave waits here until
+  // its own stores have reached the L2 (a barrier alone lets them be under way), and wave 0 writes them back from there.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (w == 0) {                                 // publish_wave, for counters whose stripes but the first are 0
     if (l < 32) p.h->v[l] = __hip_atomic_load(&cnt->v[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -1,4 +1,5 @@
-"""What a caller may rely on when a call returns: after a rejected batch nothing is left running on the stream."""
+"""What a caller may rely on when a call returns: the result is there for every stream, and after a rejected batch
+nothing is left running on the context's own."""
 import numpy as np
 import pytest
 
@@ -62,4 +63,33 @@ def test_rejected_features_leave_nothing_running(ids):
             ink.update_features_device(t.data_ptr(), rows.data_ptr(), 2)
         running += not stream.query()
     assert running == 0
+    ink.close()
+
+
+class Rows:
+    def __init__(self, ptr, shape, typestr):
+        self.__cuda_array_interface__ = dict(data=(ptr, False), shape=shape, typestr=typestr, version=3)
+
+
+@pytest.mark.parametrize("size", [1, 200])       # layers of one workgroup, whose last writes the record itself; separate stages
+@pytest.mark.parametrize("width", [8, 256])
+def test_result_is_there_for_another_stream(size, width):
+    import torch
+    n = 3000
+    ink, _ = device_context(n, (16, 16, width))
+    other = torch.cuda.Stream()
+    rng = np.random.default_rng(width)
+    s, d = rng.integers(0, n, size), rng.integers(0, n, size)
+    s[0], d[0] = 3, 9                             # not an edge of the graph
+    batches = [device_batch(np.full(size, op), s, d) for op in (0, 1)]
+    for i in range(100):
+        t, m = batches[i % 2]
+        r = ink.apply_updates_device(t.data_ptr(), m)
+        k = r["n_changed"]
+        assert k > 0
+        with torch.cuda.stream(other):
+            ids = torch.as_tensor(Rows(r["changed_ids_ptr"], (k,), "<i4"), device="cuda").clone()
+            rows = torch.as_tensor(Rows(r["embeddings_ptr"], (k, width), "<f4"), device="cuda").clone()
+        other.synchronize()
+        assert np.array_equal(rows.cpu().numpy().view(np.uint32), ink.get_layer(2, 0)[ids.cpu().numpy()].view(np.uint32))
     ink.close()
