@@ -59,7 +59,7 @@ template <int LPR>
 __device__ __forceinline__ void sum_range(const int32_t *ids, int64_t j0, int64_t j1, const float *M, int ldm,
                                           bool lane_on, int q, S4 &acc) {
   constexpr int G = kWave / LPR, W = G * LPR == kWave ? kWave : G * (kWave / G);    // ids per window, a multiple of G
-  constexpr int U = LPR <= 16 ? INK_U_SUM16 : (LPR == 32 ? INK_U_SUM32 : INK_U_SUM64);
+  constexpr int U = INK_U_SUM;
   const int l = lane_id();
   const RowTable<LPR> tab(M, ldm, lane_on, q);
 #pragma unroll

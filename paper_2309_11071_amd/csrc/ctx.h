@@ -14,8 +14,8 @@ namespace ink {
 #ifndef INK_BIG_DEG
 #define INK_BIG_DEG 256
 #endif
-// neighbour rows in flight per lane group while gathering, by aggregator family and lanes per row.  8 where the registers
-// allow: for max / min over rows of 128 floats 8 take 84 registers and cost 3 % (625k nodes, inference: 5.15 against 4.99 ms).
+// neighbour rows in flight per lane group while gathering, by aggregator family and, for max / min, lanes per row.  8 where the
+// registers allow: for max / min over rows of 128 floats 8 take 84 and cost 3 % (625k nodes, inference: 5.15 against 4.99 ms).
 #ifndef INK_U_SEL16
 #define INK_U_SEL16 4
 #endif
@@ -25,14 +25,8 @@ namespace ink {
 #ifndef INK_U_SEL64
 #define INK_U_SEL64 8
 #endif
-#ifndef INK_U_SUM16
-#define INK_U_SUM16 8       // narrow rows are cheap in registers: 8 loads in flight measured 3.5 % faster than 4
-#endif
-#ifndef INK_U_SUM32
-#define INK_U_SUM32 8
-#endif
-#ifndef INK_U_SUM64
-#define INK_U_SUM64 8
+#ifndef INK_U_SUM
+#define INK_U_SUM 8         // sums are cheap in registers: 8 loads in flight measured 3.5 % faster than 4 on narrow rows
 #endif
 #ifndef INK_BIG_CHUNK
 #define INK_BIG_CHUNK 1024
@@ -248,7 +242,7 @@ struct KernelTimer : Prof {
 // ---- graph store (graph.hip)
 hipError_t graph_build(ink_ctx *c, const int64_t *rowptr_h, const int32_t *col_h);
 // applies a batch in memory the device can read (ink_edge_update records); fills Delta E lists and counts
-// `queued` is called once its launches are enqueued and before it waits for their record, if the batch takes the short form
+// `queued` is called once its launch is enqueued and before it waits for the record, if the batch may take the one-workgroup form
 ink_status graph_apply_batch(ink_ctx *c, const void *raw, int64_t n, int64_t *n_ins, int64_t *n_del,
                              hipError_t (*queued)(ink_ctx *) = nullptr);
 hipError_t graph_reserve(ink_ctx *c, int64_t max_batch);   // batch buffers for that many entries

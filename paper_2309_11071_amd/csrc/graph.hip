@@ -1084,8 +1084,7 @@ static ink_status graph_apply_one(ink_ctx *c, const RawUpdate *raw, int64_t n, i
   return INK_OK;
 }
 
-static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n64, int64_t *n_ins_out, int64_t *n_del_out,
-                                    hipError_t (*queued)(ink_ctx *)) {
+static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n64, int64_t *n_ins_out, int64_t *n_del_out) {
   hipStream_t s = c->stream;
   const int n = (int)n64;
   const size_t per = ((size_t)(n + 64) * 4 + 255) & ~(size_t)255;
@@ -1128,7 +1127,6 @@ static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n6
     return hipGetLastError();
   };
   INK_TRYS(apply(&g->v[C_OK]));
-  if (queued) INK_TRYS(queued(c));
   INK_TRYS(wait_published(c, c->h_gseq, seq));
   const int32_t *v = c->h_gcnt->v;
   ink_status st = short_error(c, v);
@@ -1158,10 +1156,9 @@ ink_status graph_apply_batch(ink_ctx *c, const void *raw_v, int64_t n, int64_t *
   if (n <= kOneEvents && n <= c->small_batch) {
     bool done = false;
     ink_status st = graph_apply_one(c, raw, n, n_ins_out, n_del_out, queued, &done);
-    if (st != INK_OK || done) return st;
-    queued = nullptr;        // what it enqueued did nothing
+    if (st != INK_OK || done) return st;      // otherwise what `queued` enqueued did nothing
   }
-  if (n <= c->small_batch) return graph_apply_short(c, raw, n, n_ins_out, n_del_out, queued);
+  if (n <= c->small_batch) return graph_apply_short(c, raw, n, n_ins_out, n_del_out);
   size_t per = ((size_t)(n + 64) * 4 + 255) & ~(size_t)255;
   INK_TRYS(c->b_misc.reserve(per * 28));
   INK_TRYS(c->b_del_s.reserve(per)); INK_TRYS(c->b_del_d.reserve(per));

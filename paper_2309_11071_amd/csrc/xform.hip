@@ -49,9 +49,9 @@ template <int MODE> __device__ __forceinline__ float row_scalar(const XformArgs 
   if ((MODE == 0 || MODE == 1) && x.mean_deg) { const int dg = x.mean_deg[row]; return (float)(dg > 0 ? dg : 1); }
   return 1.f;
 }
-// store_h: GCN also writes the combined row as h_l
+// GCN also writes the combined row as h_l
 template <int MODE>
-__device__ __forceinline__ void finish_x4(const XformArgs &x, int64_t row, int k, float sc, bool store_h, const RawX<MODE> &r, float v[4]) {
+__device__ __forceinline__ void finish_x4(const XformArgs &x, int64_t row, int k, float sc, const RawX<MODE> &r, float v[4]) {
   v[0] = r.a.x; v[1] = r.a.y; v[2] = r.a.z; v[3] = r.a.w;
   if constexpr (MODE == 0) {
     const int d4 = xform_self_row(x.d_in);
@@ -84,7 +84,7 @@ __device__ __forceinline__ void finish_x4(const XformArgs &x, int64_t row, int k
       if (x.in_relu) t = t > 0.f ? t : 0.f;
       v[i] = k + i < x.d_in ? t : 0.f;
     }
-    if (x.h_store && store_h && k < x.ld_hs) *reinterpret_cast<float4 *>(x.h_store + row * x.ld_hs + k) = make_float4(v[0], v[1], v[2], v[3]);
+    if (x.h_store && k < x.ld_hs) *reinterpret_cast<float4 *>(x.h_store + row * x.ld_hs + k) = make_float4(v[0], v[1], v[2], v[3]);
   }
 }
 
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(NW * 64) void k_xform(XformArgs x) {
     for (int kk = 0; kk < KPT; kk++) xv[kk] = 0.f;
     if (xrow >= 0) {
 #pragma unroll
-      for (int kk = 0; kk < KPT; kk += 4) finish_x4<MODE>(x, xrow, k0 + xks + kk, sc, true, raw[kk / 4], xv + kk);
+      for (int kk = 0; kk < KPT; kk += 4) finish_x4<MODE>(x, xrow, k0 + xks + kk, sc, raw[kk / 4], xv + kk);
     }
     if (xstage) {   // even k first, then odd k
       float *xp = Xs + xr * XS + (xks >> 1);
