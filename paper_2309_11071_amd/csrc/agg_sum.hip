@@ -370,7 +370,7 @@ __global__ __launch_bounds__(64) void k_sum_ev_final(AggArgs a, const int32_t *t
 }
 
 static int lanes_per_row(int ld) { return ld <= 64 ? 16 : (ld <= 128 ? 32 : 64); }
-// full re-aggregation only: narrow rows take 12 lanes (config 2, layer 2: 4.5 % less aggregation time)
+// full re-aggregation only: narrow rows take 12 lanes (rows of 41 floats, 233k nodes / 114M edges: 4.5 % less aggregation time)
 static int lanes_per_row_full(int ld) { return ld <= 48 ? 12 : lanes_per_row(ld); }
 
 template <int LPR>

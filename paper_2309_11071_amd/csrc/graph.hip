@@ -607,8 +607,7 @@ __device__ __forceinline__ void clear_graph_slots(Counters *g, int err) {
 }
 
 // Distinct nodes of the sorted op list (node of op i: node(i), n ops), the start of each node's ops plus the
-// closing offset, the prefix of the chunk counts of their blocks, and both totals.  s_u: LDS for the
-// THREADS nodes of a round.
+// closing offset, the prefix of the chunk counts of their blocks, and both totals.  sm: LDS of the scans.
 template <int THREADS, class NodeAt>
 __device__ __forceinline__ void heads_and_chunks(NodeAt node, int n, const ShortSide &o, int *sm, Counters *g) {
   int n_uniq = 0;

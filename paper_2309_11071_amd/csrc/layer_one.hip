@@ -41,7 +41,7 @@ struct OneLds {
   };
 };
 
-// Orders n (<= kOneEvents) events by target, equal targets in creation order: eight threads count an event's rank.
+// Orders n (<= kOneEvents) events by target, equal targets in creation order: 32 threads count an event's rank.
 __device__ __forceinline__ void sort_events(OneLds &S, int n) {
   constexpr int P = kOneThreads / kOneEvents;
   const int i = threadIdx.x / P, p = threadIdx.x % P;
@@ -107,7 +107,7 @@ __device__ __forceinline__ void recompute_long_row(OneLds &S, const AggArgs &a, 
   if (__syncthreads_or(vchg) && t == 0) { mark_bit(chg, v); atomicAdd(&cnt->stripe[0][ST_ACHG], 1ull); }
 }
 
-// Distinct ascending ids of cand[0 .. n) -> rows, their number -> n_c (n <= kOneRows, four threads a candidate).
+// Distinct ascending ids of cand[0 .. n) -> rows, their number -> n_c (n <= kOneRows, 16 threads a candidate).
 __device__ __forceinline__ void sort_rows(OneLds &S, int n) {
   constexpr int P = kOneThreads / kOneRows;
   const int i = threadIdx.x / P, p = threadIdx.x % P;

@@ -1,7 +1,7 @@
-"""The graph-store update has two forms: short batches (at most 4096 entries) run in one workgroup
-per direction with one host read-back, longer ones through the device-wide primitives.  Both must
-leave the same store, the same Delta E and hence the same result; each is checked against the
-oracle, and against the other bit for bit."""
+"""The graph-store update has a short form (at most 16384 entries, both directions together, one host
+read-back) and a long one through the device-wide primitives.  Both must leave the same store, the
+same Delta E and hence the same result; each is checked against the oracle, and against the other bit
+for bit."""
 import numpy as np
 import pytest
 
