@@ -1047,16 +1047,26 @@ constexpr int64_t kSmallLayer = 4096;           // events / rows up to which a l
 constexpr int64_t kBitmapOneLaunch = 16384;     // nodes up to which the bitmap scan is a single launch
 constexpr int64_t kNoSyncEvents = 1 << 18;     // below this the target count stays on the device
 
-// Events as a fraction of the edges above which re-aggregating every node costs less than grouping the events.
-// A re-aggregated edge costs one cached row read; an event its creation, a place in the sort, its row, and the exposed
-// rows it leaves.  Measured for max on 25M edges and rows of 128 floats: even at .5 (12.0M events 8.2 against 8.8 ms
-// a pass, 14.3M 11.9 against 10.3); for 64 floats at .35.  Sums stay at .75 although they would be even at .15 to .6:
-// a sum formed anew differs in its last bits from the one kept, so nodes that no event touches would be reported as
-// changed.  Layers of the one-workgroup path pay for launches, not for events.
-static double dense_fraction(const ink_ctx *c, int64_t n_events, int width) {
-  if (c->dense_frac != 0) return c->dense_frac;
-  if (n_events <= kSmallLayer || (c->agg != INK_AGG_MAX && c->agg != INK_AGG_MIN)) return 0.75;
-  return width <= 64 ? 0.35 : 0.45;
+// Events of a layer above which re-aggregating every node costs less than grouping the events.  An edge re-aggregated
+// costs one cached row read; an event its creation, a place in the sort, its row, and the exposed rows it leaves.  A node
+// re-aggregated costs its four table rows: a graph of some 300k nodes holds them in the caches, a larger one pays about
+// 2.5 events a node.  Measured for max, edge batches, last of three layers: the fraction of the edges at which both ways
+// take the same time (rule in brackets), rows of 64 / 128 / 256 floats:
+//   5M nodes, 10 edges each    -         / .66 (.69) / -              5M, 20 edges    .51 (.47) / -         / -
+//   2.5M, 10 edges             .71 (.57) / -         / -              2.5M, 20 edges  -         / .58 (.56) / -
+//   1.25M, 8 edges             .73 (.59) / .67 (.69) / -              1.25M, 20 edges .47 (.45) / .53 (.55) / -
+//   800k, 10 edges             .57 (.51) / .54 (.61) / -              600k, 20 edges  .38 (.41) / -         / .53 (.51)
+//   450k, 14 edges             .43 (.41) / .40 (.51) / .51 (.51)      300k, 8 edges   .38 (.35) / -         / .37 (.45)
+// and below .3 at 100k nodes and fewer.  Without the nodes in the rule 3265 updates on 1.25M nodes with 8 edges each
+// (rows of 64 floats, .36) took 2.11 instead of 1.57 ms.  Where 60 % and more of the targets are exposed (features drawn
+// anew) both ways are even at .15 to .4 already, but how many will be is not known here.  Sums stay at .75 of the edges
+// although they would be even at .15 to .6: a sum formed anew differs in its last bits from the one kept, so nodes that
+// no event touches would be reported as changed.  Layers of the one-workgroup path pay for launches, not for events.
+static double dense_line(const ink_ctx *c, int64_t n_events, int width, int64_t n_edges) {
+  const double edges = (double)std::max<int64_t>(n_edges, 1);
+  if (c->dense_frac != 0) return c->dense_frac * edges;
+  if (n_events <= kSmallLayer || (c->agg != INK_AGG_MAX && c->agg != INK_AGG_MIN)) return 0.75 * edges;
+  return std::min(0.75 * edges, (width <= 64 ? 0.35 : 0.45) * edges + 2.5 * std::max(0, c->n - 300000));
 }
 
 static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t nF, int64_t n_chg, const float *f_old,
@@ -1070,7 +1080,7 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
   int64_t nE = n_seed + n_chg;
   S.n_events = nE;
   uint64_t *bm = c->bm_a;
-  bool dense = nE > 0 && (double)nE > dense_fraction(c, nE, a.d) * (double)std::max<int64_t>(c->n_edges_now, 1);
+  bool dense = nE > 0 && (double)nE > dense_line(c, nE, a.d, c->n_edges_now);
   S.dense = dense;
   const bool small = !dense && nE > 0 && nE <= kSmallLayer;
   if (!small) API_TRY(hipMemsetAsync(dc, 0, sizeof(Counters), s));
@@ -1398,7 +1408,7 @@ static hipError_t finish_stream(ink_ctx *c) {
 static bool layer_one_possible(const ink_ctx *c, int64_t n_batch) {
   if (c->kind != INK_MODEL_SAGE || !c->is_select || c->affected_mode || c->profile || c->n_edges_now <= n_batch) return false;
   for (int l = 1; l <= c->n_layers; l++)
-    if (c->A[l].d > kAggBlock || kOneEvents > dense_fraction(c, kOneEvents, c->A[l].d) * (double)(c->n_edges_now - n_batch)) return false;
+    if (c->A[l].d > kAggBlock || kOneEvents > dense_line(c, kOneEvents, c->A[l].d, c->n_edges_now - n_batch)) return false;
   return true;
 }
 

@@ -1,5 +1,5 @@
 """Where the default dense_threshold lies: the fraction of the edges on either side of which a layer groups its
-events or re-aggregates every node, by aggregator, width and event count."""
+events or re-aggregates every node, by aggregator, width, event count, and for large graphs by node."""
 import numpy as np
 import pytest
 
@@ -27,4 +27,24 @@ def test_default_threshold(agg, d, n, sources, dense):
     L = h.ink.stats()["layers"][0]
     assert L["n_events"] == 5 * sources and L["dense"] == dense
     h.check_state(exact=exact)
+    h.ink.close()
+
+
+@pytest.mark.parametrize("n,fan,d,sources,dense", [
+    (300_000, 2, 4, 105_000, 0), (300_000, 2, 4, 105_001, 1),     # the nodes do not count yet: .35
+    (700_000, 5, 4, 445_000, 0), (700_000, 5, 4, 445_001, 1),     # .35 of 3.5 M edges + 2.5 x 400 000 nodes
+    (400_000, 4, 68, 242_500, 0), (400_000, 4, 68, 242_501, 1),   # .45 of 1.6 M edges + 2.5 x 100 000 nodes
+    (1_200_000, 3, 4, 900_000, 0), (1_200_000, 3, 4, 900_001, 1)])   # at most .75
+def test_default_threshold_of_large_graphs(n, fan, d, sources, dense):
+    v = np.arange(n)
+    dst = (np.repeat(v, fan) + 1 + 7 * np.tile(np.arange(fan), n)) % n
+    src, dst = synth.keys_to_edges(np.unique(synth.edge_keys(np.repeat(v, fan).astype(np.int32), dst.astype(np.int32))))
+    rng = np.random.default_rng(n)
+    X = rng.integers(-3, 4, size=(n, d)).astype(np.float32)
+    h = Harness(graph=(n, src, dst), X=X, model=tiny_model("sage", "max", (d, 3), seed=d), precision="f32")
+    ids = np.sort(rng.choice(n, size=sources, replace=False)).astype(np.int32)
+    h.feature_step(ids, X[ids] + 1)
+    L = h.ink.stats()["layers"][0]
+    assert L["n_events"] == fan * sources and L["dense"] == dense
+    h.check_state()
     h.ink.close()
