@@ -1052,7 +1052,9 @@ constexpr int64_t kNoSyncEvents = 1 << 18;     // below this the target count st
 // re-aggregated costs its four table rows: a graph of some 300k nodes holds them in the caches, a larger one pays about
 // 2.5 events a node.  Measured for max, edge batches, last of three layers: the fraction of the edges at which both ways
 // take the same time (rule in brackets), rows of 64 / 128 / 256 floats:
-//   5M nodes, 10 edges each    -         / .66 (.69) / -              5M, 20 edges    .51 (.47) / -         / -
+//   20M nodes, 10 edges each   .69 (.60) / -         / -              20M, 20 edges   -         / .48 (.57) / -
+//   10M, 10 edges              -         / .65 (.69) / -              10M, 20 edges   .51 (.47) / -         / -
+//   5M, 10 edges               -         / .66 (.69) / -              5M, 20 edges    .51 (.47) / .53 (.57) / -
 //   2.5M, 10 edges             .71 (.57) / -         / -              2.5M, 20 edges  -         / .58 (.56) / -
 //   1.25M, 8 edges             .73 (.59) / .67 (.69) / -              1.25M, 20 edges .47 (.45) / .53 (.55) / -
 //   800k, 10 edges             .57 (.51) / .54 (.61) / -              600k, 20 edges  .38 (.41) / -         / .53 (.51)
