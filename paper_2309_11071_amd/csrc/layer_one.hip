@@ -8,7 +8,7 @@
 // 128 floats (of which the transform 6, the event 2 to 4) and 12 to 30 for five, bound by the chain of dependent memory
 // accesses.  The layers of an update are enqueued behind each other and behind the graph stage without waiting
 // for the host: a layer reads its size on the device and does nothing if the layer before did not finish or if it is
-// too large itself.  One edge on 1.25M vertices, three layers: 235 -> 88 us an update.
+// too large itself.  One edge on 1.25M vertices, three layers of one event each: 255 -> 90 us an update.
 //   * at most kOneEvents events: 16 waves take 4 us for 16 targets, most of it instructions that the CU's four SIMDs
 //     share, so 100 targets (28 us, and 18 to transform them) are no faster than the launches of the general path
 //   * exposed rows with many neighbours are recomputed here while they are at most kOneGather floats (2 MB, about
