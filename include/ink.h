@@ -116,7 +116,8 @@ typedef struct {
                             fallback Sec. 5.1 argues for when updates are not sparse);
                             0 = default: 0.75; for max and min, in layers of more than 4096 events,
                             0.45 (0.35 for rows of at most 64 floats) plus 2.5 events for every
-                            node beyond 300 000, but at most 0.75; negative = never */
+                            node beyond 300 000 (for wider rows: in batches of edge updates), but
+                            at most 0.75; negative = never */
   int32_t batch_mem;     /* ink_mem of the `updates` array of ink_apply_updates when it differs from
                             `mem` (e.g. host-built graph, device-resident update stream): the
                             effective location is device if either field says INK_MEM_DEVICE */

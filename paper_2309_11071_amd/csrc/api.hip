@@ -1060,15 +1060,19 @@ constexpr int64_t kNoSyncEvents = 1 << 18;     // below this the target count st
 //   800k, 10 edges             .57 (.51) / .54 (.61) / -              600k, 20 edges  .38 (.41) / -         / .53 (.51)
 //   450k, 14 edges             .43 (.41) / .40 (.51) / .51 (.51)      300k, 8 edges   .38 (.35) / -         / .37 (.45)
 // and below .3 at 100k nodes and fewer.  Without the nodes in the rule 3265 updates on 1.25M nodes with 8 edges each
-// (rows of 64 floats, .36) took 2.11 instead of 1.57 ms.  Where 60 % and more of the targets are exposed (features drawn
-// anew) both ways are even at .15 to .4 already, but how many will be is not known here.  Sums stay at .75 of the edges
-// although they would be even at .15 to .6: a sum formed anew differs in its last bits from the one kept, so nodes that
-// no event touches would be reported as changed.  Layers of the one-workgroup path pay for launches, not for events.
-static double dense_line(const ink_ctx *c, int64_t n_events, int width, int64_t n_edges) {
+// (rows of 64 floats, .36) took 2.11 instead of 1.57 ms.  5 to 20 % of those targets were exposed.  New feature rows
+// expose 20 to 50 % in the second layer, which makes events dearer, above all of wide rows: even at .62 / .52 / - on
+// 1.25M nodes with 8 edges, .42 / .40 / - with 20, .63 / - / - on 2.5M with 10, - / .55 / - on 5M with 10, so without edge
+// updates the nodes count for rows of at most 64 floats only.  (In the first layer, where 80 % and more are exposed, both
+// ways are even at .15 to .4.)  Sums stay at .75 of the edges although they would be even at .15 to .6: a sum formed anew
+// differs in its last bits from the one kept, so nodes that no event touches would be reported as changed.  Layers of the
+// one-workgroup path pay for launches, not for events.
+static double dense_line(const ink_ctx *c, int64_t n_events, int width, int64_t n_edges, bool edge_updates) {
   const double edges = (double)std::max<int64_t>(n_edges, 1);
   if (c->dense_frac != 0) return c->dense_frac * edges;
   if (n_events <= kSmallLayer || (c->agg != INK_AGG_MAX && c->agg != INK_AGG_MIN)) return 0.75 * edges;
-  return std::min(0.75 * edges, (width <= 64 ? 0.35 : 0.45) * edges + 2.5 * std::max(0, c->n - 300000));
+  const double nodes = width <= 64 || edge_updates ? 2.5 * std::max(0, c->n - 300000) : 0.;
+  return std::min(0.75 * edges, (width <= 64 ? 0.35 : 0.45) * edges + nodes);
 }
 
 static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t nF, int64_t n_chg, const float *f_old,
@@ -1082,7 +1086,7 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
   int64_t nE = n_seed + n_chg;
   S.n_events = nE;
   uint64_t *bm = c->bm_a;
-  bool dense = nE > 0 && (double)nE > dense_line(c, nE, a.d, c->n_edges_now);
+  bool dense = nE > 0 && (double)nE > dense_line(c, nE, a.d, c->n_edges_now, n_seed > 0);
   S.dense = dense;
   const bool small = !dense && nE > 0 && nE <= kSmallLayer;
   if (!small) API_TRY(hipMemsetAsync(dc, 0, sizeof(Counters), s));
@@ -1410,7 +1414,7 @@ static hipError_t finish_stream(ink_ctx *c) {
 static bool layer_one_possible(const ink_ctx *c, int64_t n_batch) {
   if (c->kind != INK_MODEL_SAGE || !c->is_select || c->affected_mode || c->profile || c->n_edges_now <= n_batch) return false;
   for (int l = 1; l <= c->n_layers; l++)
-    if (c->A[l].d > kAggBlock || kOneEvents > dense_line(c, kOneEvents, c->A[l].d, c->n_edges_now - n_batch)) return false;
+    if (c->A[l].d > kAggBlock || kOneEvents > dense_line(c, kOneEvents, c->A[l].d, c->n_edges_now - n_batch, true)) return false;
   return true;
 }
 

@@ -33,7 +33,7 @@ def test_default_threshold(agg, d, n, sources, dense):
 @pytest.mark.parametrize("n,fan,d,sources,dense", [
     (300_000, 2, 4, 105_000, 0), (300_000, 2, 4, 105_001, 1),     # the nodes do not count yet: .35
     (700_000, 5, 4, 445_000, 0), (700_000, 5, 4, 445_001, 1),     # .35 of 3.5 M edges + 2.5 x 400 000 nodes
-    (400_000, 4, 68, 242_500, 0), (400_000, 4, 68, 242_501, 1),   # .45 of 1.6 M edges + 2.5 x 100 000 nodes
+    (400_000, 4, 68, 180_000, 0), (400_000, 4, 68, 180_001, 1),   # wide rows, no edge update: .45
     (1_200_000, 3, 4, 900_000, 0), (1_200_000, 3, 4, 900_001, 1)])   # at most .75
 def test_default_threshold_of_large_graphs(n, fan, d, sources, dense):
     v = np.arange(n)
@@ -46,5 +46,18 @@ def test_default_threshold_of_large_graphs(n, fan, d, sources, dense):
     h.feature_step(ids, X[ids] + 1)
     L = h.ink.stats()["layers"][0]
     assert L["n_events"] == fan * sources and L["dense"] == dense
+    h.check_state()
+    h.ink.close()
+
+
+@pytest.mark.parametrize("n,dense", [(300_000, 1), (302_399, 1), (302_401, 0), (400_000, 0)])
+def test_default_threshold_of_edge_updates(n, dense):
+    """60 000 events on 120 000 edges: .45 of them, and 6000 more from 302 400 nodes on."""
+    v = np.arange(60_000, dtype=np.int32)
+    X = np.random.default_rng(n).integers(-3, 4, size=(n, 68)).astype(np.float32)
+    h = Harness(graph=(n, v, v + 1), X=X, model=tiny_model("sage", "max", (68, 3), seed=5), precision="f32")
+    h.step(np.zeros(60_000, np.uint8), v, v + 9)
+    L = h.ink.stats()["layers"][0]
+    assert L["n_events"] == 60_000 and L["dense"] == dense
     h.check_state()
     h.ink.close()
