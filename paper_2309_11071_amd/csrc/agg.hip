@@ -68,12 +68,12 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
     else {
       const int64_t o4 = (int64_t)v * a.ld + 4 * q;       // every lane group has the row: the first two store half of the tables each
       if (lane_on && l < LPR) {
-        *reinterpret_cast<float4 *>(a.A + o4) = make_float4(bv.v[0], bv.v[1], bv.v[2], bv.v[3]);
-        *reinterpret_cast<int4 *>(a.ARG + o4) = make_int4(bi.v[0], bi.v[1], bi.v[2], bi.v[3]);
+        store_past(a.A + o4, bv.v);
+        store_past(a.ARG + o4, bi.v);
       }
       if (lane_on && (LPR == kWave || l / LPR == 1)) {
-        *reinterpret_cast<float4 *>(a.UB + o4) = make_float4(sv.v[0], sv.v[1], sv.v[2], sv.v[3]);
-        *reinterpret_cast<int4 *>(a.ARG2 + o4) = make_int4(si.v[0], si.v[1], si.v[2], si.v[3]);
+        store_past(a.UB + o4, sv.v);
+        store_past(a.ARG2 + o4, si.v);
       }
       ch = false;
     }
@@ -343,7 +343,11 @@ static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compa
   return hipGetLastError();
 }
 
-constexpr int64_t kFullGrid = 1 << 20;     // workgroups of a recompute launch (4 rows each per stride)
+// Workgroups of a recompute launch, whose waves stride over the rows.  With a wave per row half of the chip's places
+// for waves stood empty (3.8 of 8 per SIMD: a workgroup waits until all its places are free, and its rows differ in
+// length), with as many waves as the chip holds the last long rows are a tail: inference of 625k nodes, 3 layers of
+// 128 floats, 2048 / 4096 / 16384 / 65536 workgroups / a wave per row 4.89 / 4.60 / 4.53 / 4.59 / 4.71 ms.
+constexpr int64_t kFullGrid = 16384;
 
 template <bool IS_MIN, int LPR>
 static hipError_t full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targets, int64_t n_targets, uint64_t *chg) {

@@ -151,6 +151,14 @@ __device__ __forceinline__ void gather_range(const int32_t *ids, int64_t j0, int
   else gather_range_t<IS_MIN, LPR, false>(ids, j0, j1, M, ldm, lane_on, q, bv, bi, sv, si);
 }
 
+// 16 bytes of a table row that nothing reads again before it has left the caches: past them, so that they keep the
+// gathered rows.
+template <typename T> __device__ __forceinline__ void store_past(T *p, const T v[4]) {
+  typedef T t4 __attribute__((ext_vector_type(4)));
+  const t4 x = {v[0], v[1], v[2], v[3]};
+  __builtin_nontemporal_store(x, reinterpret_cast<t4 *>(p));
+}
+
 struct RowOut {
   float *A; int32_t *ARG; float *UB; int32_t *ARG2; int ld; int d;
 };
@@ -165,8 +173,8 @@ __device__ __forceinline__ bool store_row(const RowOut &o, int v, bool lane_on, 
   bool writer = lane_on && l < LPR;
   bool vchg = false, ichg = false;
   if (writer) {    // bound and runner-up are rewritten unconditionally (they never decide whether a row "changed")
-    *reinterpret_cast<float4 *>(o.UB + (int64_t)v * o.ld + 4 * q) = make_float4(sv.v[0], sv.v[1], sv.v[2], sv.v[3]);
-    *reinterpret_cast<int4 *>(o.ARG2 + (int64_t)v * o.ld + 4 * q) = make_int4(si.v[0], si.v[1], si.v[2], si.v[3]);
+    store_past(o.UB + (int64_t)v * o.ld + 4 * q, sv.v);
+    store_past(o.ARG2 + (int64_t)v * o.ld + 4 * q, si.v);
   }
   if (writer) {
     F4 cv = ov; I4 ci = oi;
