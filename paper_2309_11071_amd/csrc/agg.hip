@@ -42,8 +42,9 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
   const bool lane_on = 4 * q < a.wd;
   if (n_targets_dev) { int64_t nd = *n_targets_dev; n_targets = nd < n_targets ? nd : n_targets; }
   const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kWave);
-  // wave-uniform, so that the row's place and length are scalar loads that are under way together; with that the kernel
-  // has 64 registers, 8 waves per SIMD (inference of 625k nodes, 3 layers of 128: 4.80 -> 4.69 ms)
+  // wave-uniform, so that the row's place and length are scalar loads that are under way together (inference of 625k
+  // nodes, 3 layers of 128: 4.80 -> 4.69 ms).  79 registers, 6 waves per SIMD: held to 64 the kernel keeps addresses in
+  // scratch and takes a third longer
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   for (int64_t wid = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave; wid < n_targets; wid += stride) {
     const int v = targets ? targets[wid] : (int)wid;
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
       continue;
     }
     F4 bv; I4 bi; F4 sv; I4 si;
-    gather_range<IS_MIN, LPR>(a.in_ids + off, 0, deg, a.M, a.ldm, lane_on, q, asc, bv, bi, sv, si);
+    gather_range<IS_MIN, LPR>(a.in_ids + off, 0, deg, a.M, a.ldm, lane_on, q, a.nonneg, asc, bv, bi, sv, si);
     finish_empty<IS_MIN>(bv, bi, sv, si);
     RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
     F4 dum; I4 dumi;
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(NW * kWave) void k_big_partial(AggArgs a, const int
     int64_t len = j1 - j0;
     int64_t w0 = j0 + len * w / nw, w1 = j0 + len * (w + 1) / nw;
     F4 bv; I4 bi; F4 s2; I4 j2;
-    gather_range<IS_MIN, LPR>(a.in_ids + off, w0, w1, a.M, a.ldm, lane_on, q, a.in_asc[v] != 0, bv, bi, s2, j2);
+    gather_range<IS_MIN, LPR>(a.in_ids + off, w0, w1, a.M, a.ldm, lane_on, q, a.nonneg, a.in_asc[v] != 0, bv, bi, s2, j2);
 #pragma unroll
     for (int c = 0; c < 4; c++) {
       sv[w][l * 4 + c] = bv.v[c]; si[w][l * 4 + c] = bi.v[c]; ss[w][l * 4 + c] = s2.v[c]; sj[w][l * 4 + c] = j2.v[c];

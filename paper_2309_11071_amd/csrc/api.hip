@@ -594,6 +594,7 @@ static AggArgs agg_args(ink_ctx *c, int l) {       // layer l in 1..k
   a.ARG2 = c->is_select ? c->ARG2[l].i() : nullptr;
   a.wd = round_up(a.d, 4);
   a.is_min = c->is_min;
+  a.nonneg = l > 1 && c->kind != INK_MODEL_GCN && c->layers[l - 2].act == INK_ACT_RELU;
   a.big_deg = kBigDeg;
   a.big_grid = 2 * c->big_hint[l] + 1024;
   a.count_cond = 1;

@@ -16,6 +16,9 @@ namespace ink {
 #endif
 // neighbour rows in flight per lane group while gathering, by aggregator family and, for max / min, lanes per row.  8 where the
 // registers allow: for max / min over rows of 128 floats 8 take 84 and cost 3 % (625k nodes, inference: 5.15 against 4.99 ms).
+#ifndef INK_U_SEL8
+#define INK_U_SEL8 4
+#endif
 #ifndef INK_U_SEL16
 #define INK_U_SEL16 4
 #endif
@@ -264,6 +267,7 @@ struct AggArgs {
   int d;                            // columns handled by this launch (<= 256; wider rows go block by block)
   int wd;                           // d rounded up to 4
   bool is_min;
+  bool nonneg;                      // no message has its sign bit set (the layer before ends in ReLU, which gives +0 for every other value)
   int big_deg;                      // rows with more in-neighbours go to the chunked cooperative path
   int64_t big_grid;                 // workgroups to launch for the chunk kernel (it strides if there are more chunks)
   int layer;                        // 1-based layer the launch belongs to (per-kernel timing)

@@ -65,7 +65,7 @@ __device__ __forceinline__ void recompute_long_row(OneLds &S, const AggArgs &a, 
   const int64_t deg = a.in_deg[v];
   F4 bv; I4 bi; F4 sv; I4 si;
   gather_range<IS_MIN, LPR>(a.in_ids + a.in_off[v], deg * w / kOneWaves, deg * (w + 1) / kOneWaves, a.M, a.ldm, lane_on, q,
-                            a.in_asc[v] != 0, bv, bi, sv, si);
+                            a.nonneg, a.in_asc[v] != 0, bv, bi, sv, si);
   auto put = [&](int slot) {
     if (l < LPR)
 #pragma unroll

@@ -34,13 +34,11 @@ template <bool IS_MIN> __device__ __forceinline__ void merge2(float ov, int oi, 
   sv = best_of<IS_MIN>(loser, best_of<IS_MIN>(sv, os));
 }
 // ... and with the runner-up's id si (lowest id among the non-holders that have the value sv)
-// ASC: the caller feeds ids in ascending order, so on equal values the entry seen first keeps its
-// place and the id comparisons drop out (8 instead of 12 vector instructions per value; the
-// re-gather is bound by them, not by memory, on wide rows)
-template <bool IS_MIN, bool ASC>
-__device__ __forceinline__ void take2i(float x, int id, float &bv, int &bi, float &sv, int &si) {
-  const bool first = better<IS_MIN>(x, bv) || (!ASC && x == bv && id < bi);
-  const bool second = better<IS_MIN>(x, sv) || (!ASC && x == sv && id < si);
+// asc: the caller feeds ids in ascending order, and equal values leave the entry seen first its place
+template <bool IS_MIN>
+__device__ __forceinline__ void take2i(float x, int id, bool asc, float &bv, int &bi, float &sv, int &si) {
+  const bool first = better<IS_MIN>(x, bv) || (!asc && x == bv && id < bi);
+  const bool second = better<IS_MIN>(x, sv) || (!asc && x == sv && id < si);
   const float nsv = first ? bv : (second ? x : sv);
   const int nsi = first ? bi : (second ? id : si);
   bv = first ? x : bv;
@@ -94,39 +92,105 @@ template <int LPR> __device__ __forceinline__ int reduce_flags(int fl) {
   return fl;
 }
 
-// U rows per lane group into the running (best, runner-up) pairs; FULL: every slot is a row
-template <bool IS_MIN, int LPR, bool ASC, int U, bool FULL>
-__device__ __forceinline__ void take_batch(const RowTable<LPR> &tab, int win, int it, int cnt, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
+// ---- the gather of a recompute: best and runner-up of every dimension, each with its id
+// An entry (value x, id) is one double: the bits of x on top, below them the id, coded so that among equal values the
+// lower id is the better double.  Doubles are then ordered as entries are selected, and an entry takes three
+// instructions (best, the worse of it and the old best, runner-up) next to the one or two to three that make the double;
+// value and id compared apart took 12, or 8 where the ids are known to ascend.  The vector instructions were half of the
+// time of a recompute (SQ_ACTIVE_INST_VALU: 51 % for short rows, 57 % for long ones) and more where lists no longer
+// ascend: 10000 updates on 1.25M nodes and rows of 128 floats 4.42 -> 4.19 ms, on 612k nodes, hubs and rows of 256
+// 1.49 -> 1.28, inference of 625k nodes 4.51 -> 4.38.
+template <bool IS_MIN> __device__ __forceinline__ double first_of(double x, double y) {
+  double r;
+  if constexpr (IS_MIN) asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+  else asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+  return r;
+}
+template <bool IS_MIN> __device__ __forceinline__ double last_of(double x, double y) { return first_of<!IS_MIN>(x, y); }
+// no entry: worse than any (a finite double beyond those of the infinities)
+template <bool IS_MIN> __device__ __forceinline__ constexpr int no_entry() { return IS_MIN ? 0x7fe00000 : (int)0xffe00000; }
+
+template <bool IS_MIN> struct Top2 {
+  double b[4], s[4];
+  __device__ __forceinline__ void init() {
+#pragma unroll
+    for (int c = 0; c < 4; c++) b[c] = s[c] = __hiloint2double(no_entry<IS_MIN>(), 0);
+  }
+  __device__ __forceinline__ void take(int c, double e) {
+    s[c] = first_of<IS_MIN>(s[c], last_of<IS_MIN>(b[c], e));
+    b[c] = first_of<IS_MIN>(b[c], e);
+  }
+};
+// NONNEG: no value has its sign bit set.  Otherwise -0 counts as +0 (which of them an entry has is looked up in the end).
+template <bool IS_MIN, bool NONNEG> __device__ __forceinline__ double entry(float x, int id, bool on) {
+  int hi, lo;
+  if constexpr (NONNEG) { hi = __float_as_int(x); lo = IS_MIN ? id : ~id; }
+  else {
+    hi = __float_as_int(__fadd_rn(x, 0.f));
+    const int sign = hi >> 31;
+    lo = IS_MIN ? id ^ sign : ~(id ^ sign);
+  }
+  return __hiloint2double(on ? hi : no_entry<IS_MIN>(), lo);
+}
+template <bool IS_MIN> __device__ __forceinline__ int entry_id(double e) {
+  const int lo = __double2loint(e), sign = __double2hiint(e) >> 31;
+  return IS_MIN ? lo ^ sign : ~(lo ^ sign);
+}
+template <bool IS_MIN> __device__ __forceinline__ bool is_entry(double e) { return __double2hiint(e) != no_entry<IS_MIN>(); }
+
+// x of this lane and of the lane OFF away, in any order
+template <int OFF> __device__ __forceinline__ void both(uint32_t x, uint32_t &p, uint32_t &r) {
+  if constexpr (OFF == 32) { const auto t = __builtin_amdgcn_permlane32_swap(x, x, false, false); p = t[0]; r = t[1]; }
+  else if constexpr (OFF == 16) { const auto t = __builtin_amdgcn_permlane16_swap(x, x, false, false); p = t[0]; r = t[1]; }
+  else { static_assert(OFF == 8, "half a row of 16 lanes"); p = x; r = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false); }
+}
+template <int OFF> __device__ __forceinline__ void both(double x, double &p, double &r) {
+  uint32_t pl, rl, ph, rh;
+  both<OFF>((uint32_t)__double2loint(x), pl, rl);
+  both<OFF>((uint32_t)__double2hiint(x), ph, rh);
+  p = __hiloint2double((int)ph, (int)pl);
+  r = __hiloint2double((int)rh, (int)rl);
+}
+template <bool IS_MIN, int OFF> __device__ __forceinline__ void merge_lanes(Top2<IS_MIN> &t) {
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    double b0, b1, s0, s1;
+    both<OFF>(t.b[c], b0, b1);
+    both<OFF>(t.s[c], s0, s1);
+    t.b[c] = first_of<IS_MIN>(b0, b1);
+    t.s[c] = first_of<IS_MIN>(first_of<IS_MIN>(s0, s1), last_of<IS_MIN>(b0, b1));
+  }
+}
+// over the lane groups of a wave: every lane ends with the result for its 4 dimensions
+template <bool IS_MIN, int LPR> __device__ __forceinline__ void merge_groups(Top2<IS_MIN> &t) {
+  if constexpr (LPR <= 8) merge_lanes<IS_MIN, 8>(t);
+  if constexpr (LPR <= 16) merge_lanes<IS_MIN, 16>(t);
+  if constexpr (LPR <= 32) merge_lanes<IS_MIN, 32>(t);
+}
+
+// U rows per lane group; FULL: every slot is a row
+template <bool IS_MIN, int LPR, bool NONNEG, int U, bool FULL>
+__device__ __forceinline__ void take_batch(const RowTable<LPR> &tab, int win, int it, int cnt, Top2<IS_MIN> &t) {
   constexpr int G = kWave / LPR;
   int id[U];
   float4 row[U];
   tab.template load_batch<U>(win, it, FULL ? kWave - 1 : cnt - 1, id, row);
 #pragma unroll
   for (int u = 0; u < U; u++) {
-    float x[4] = {row[u].x, row[u].y, row[u].z, row[u].w};
-    if (!FULL) {      // an empty slot offers the worst value under the largest id: it takes no place
-      const bool on = it + u * G + tab.g < cnt;
-      id[u] = on ? id[u] : 0x7fffffff;
+    const float x[4] = {row[u].x, row[u].y, row[u].z, row[u].w};
+    const bool on = FULL || it + u * G + tab.g < cnt;
 #pragma unroll
-      for (int c = 0; c < 4; c++) x[c] = on ? x[c] : worst<IS_MIN>();
-    }
-#pragma unroll
-    for (int c = 0; c < 4; c++) take2i<IS_MIN, ASC>(x[c], id[u], bv.v[c], bi.v[c], sv.v[c], si.v[c]);
+    for (int c = 0; c < 4; c++) t.take(c, entry<IS_MIN, NONNEG>(x[c], id[u], on));
   }
 }
 
-// Selection over neighbours ids[j0 .. j1) of one row, by the whole wave.  On return every lane
-// holds the best (value, id) and the runner-up value of its 4 dimensions over the range;
-// (worst, INT_MAX, worst) if empty.
-template <bool IS_MIN, int LPR, bool ASC>
-__device__ __forceinline__ void gather_range_t(const int32_t *ids, int64_t j0, int64_t j1, const float *M,
-                                               int ldm, bool lane_on, int q, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
+// Best and runner-up of the rows ids[j0 .. j1) by the whole wave, per lane group
+template <bool IS_MIN, int LPR, bool NONNEG>
+__device__ __forceinline__ void gather_top2(const int32_t *ids, int64_t j0, int64_t j1, const RowTable<LPR> &tab, Top2<IS_MIN> &t) {
   constexpr int G = kWave / LPR;
-  constexpr int U = LPR == 16 ? INK_U_SEL16 : (LPR == 32 ? INK_U_SEL32 : INK_U_SEL64);
+  constexpr int U = LPR == 8 ? INK_U_SEL8 : LPR == 16 ? INK_U_SEL16 : (LPR == 32 ? INK_U_SEL32 : INK_U_SEL64);
   const int l = lane_id();
-  const RowTable<LPR> tab(M, ldm, lane_on, q);
-#pragma unroll
-  for (int c = 0; c < 4; c++) { bv.v[c] = worst<IS_MIN>(); bi.v[c] = 0x7fffffff; sv.v[c] = worst<IS_MIN>(); si.v[c] = 0x7fffffff; }
+  t.init();
   const int32_t *p = ids + j0;
   const int n = __builtin_amdgcn_readfirstlane((int)(j1 - j0));
   int win = n > 0 ? p[l < n ? l : n - 1] : 0;
@@ -135,20 +199,71 @@ __device__ __forceinline__ void gather_range_t(const int32_t *ids, int64_t j0, i
     const int next = jb + kWave < n ? p[ahead < n ? ahead : n - 1] : 0;
     for (int it = 0; it < cnt;) {
       const int left = cnt - it;
-      if (left >= G * U) { take_batch<IS_MIN, LPR, ASC, U, true>(tab, win, it, cnt, bv, bi, sv, si); it += G * U; }
-      else if (left > G * U / 4) { take_batch<IS_MIN, LPR, ASC, U / 2, false>(tab, win, it, cnt, bv, bi, sv, si); it += G * U / 2; }
-      else { take_batch<IS_MIN, LPR, ASC, U / 4, false>(tab, win, it, cnt, bv, bi, sv, si); it += G * U / 4; }
+      if (left >= G * U) { take_batch<IS_MIN, LPR, NONNEG, U, true>(tab, win, it, cnt, t); it += G * U; }
+      else if (left > G * U / 4) { take_batch<IS_MIN, LPR, NONNEG, U / 2, false>(tab, win, it, cnt, t); it += G * U / 2; }
+      else { take_batch<IS_MIN, LPR, NONNEG, U / 4, false>(tab, win, it, cnt, t); it += G * U / 4; }
     }
     win = next;
   }
+}
+
+// The same entry by entry, for rows in whose result an infinity or a NaN stands that the doubles do not order as values
+// are: a NaN takes no place, the worst infinity takes one only in lists not known to be ascending (asc).
+template <bool IS_MIN, int LPR>
+__device__ __forceinline__ void gather_slow(const int32_t *ids, int64_t j0, int64_t j1, const RowTable<LPR> &tab, bool asc,
+                                            F4 &bv, I4 &bi, F4 &sv, I4 &si) {
+#pragma unroll
+  for (int c = 0; c < 4; c++) { bv.v[c] = worst<IS_MIN>(); bi.v[c] = 0x7fffffff; sv.v[c] = worst<IS_MIN>(); si.v[c] = 0x7fffffff; }
+#pragma unroll 1
+  for (int64_t j = j0 + tab.g; j < j1; j += kWave / LPR) {
+    const int id = ids[j];
+    const float4 r = tab.load(id);
+    const float x[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int c = 0; c < 4; c++) take2i<IS_MIN>(x[c], id, asc, bv.v[c], bi.v[c], sv.v[c], si.v[c]);
+  }
   reduce_groups_i<IS_MIN, LPR>(bv, bi, sv, si);
 }
-// asc (wave-uniform): ids[j0 .. j1) are ascending, as they are for every node no op has touched yet
+
+// Selection over neighbours ids[j0 .. j1) of one row, by the whole wave.  On return every lane holds the best and the
+// runner-up (value, id) of its 4 dimensions over the range; (worst, INT_MAX) where there is none.  nonneg, asc (both
+// wave-uniform): the table has no value with its sign bit set; the ids are ascending.
 template <bool IS_MIN, int LPR>
-__device__ __forceinline__ void gather_range(const int32_t *ids, int64_t j0, int64_t j1, const float *M, int ldm,
-                                             bool lane_on, int q, bool asc, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
-  if (asc) gather_range_t<IS_MIN, LPR, true>(ids, j0, j1, M, ldm, lane_on, q, bv, bi, sv, si);
-  else gather_range_t<IS_MIN, LPR, false>(ids, j0, j1, M, ldm, lane_on, q, bv, bi, sv, si);
+__device__ __forceinline__ void gather_range(const int32_t *ids, int64_t j0, int64_t j1, const float *M, int ldm, bool lane_on,
+                                             int q, bool nonneg, bool asc, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
+  const RowTable<LPR> tab(M, ldm, lane_on, q);
+  Top2<IS_MIN> t;
+  if (nonneg) gather_top2<IS_MIN, LPR, true>(ids, j0, j1, tab, t);
+  else gather_top2<IS_MIN, LPR, false>(ids, j0, j1, tab, t);
+  merge_groups<IS_MIN, LPR>(t);
+  bool odd = false, zero = false;
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    const double e[2] = {t.b[c], t.s[c]};
+    float v[2]; int id[2];
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      const int hi = __double2hiint(e[k]);
+      const bool has = is_entry<IS_MIN>(e[k]);
+      v[k] = has ? __int_as_float(hi) : worst<IS_MIN>();
+      id[k] = has ? entry_id<IS_MIN>(e[k]) : 0x7fffffff;
+      odd |= has && !better<IS_MIN>(v[k], worst<IS_MIN>());
+      zero |= hi == 0;
+    }
+    bv.v[c] = v[0]; bi.v[c] = id[0]; sv.v[c] = v[1]; si.v[c] = id[1];
+  }
+  if (!nonneg) {
+    if (__ballot(zero && lane_on) != 0ull) {        // the sign of a zero
+      const float *m = M + 4 * q;
+#pragma unroll
+      for (int c = 0; c < 4; c++)
+        if (lane_on) {
+          if (bv.v[c] == 0.f) bv.v[c] = m[(int64_t)bi.v[c] * ldm + c];
+          if (sv.v[c] == 0.f) sv.v[c] = m[(int64_t)si.v[c] * ldm + c];
+        }
+    }
+  }
+  if (__ballot(odd && lane_on) != 0ull) gather_slow<IS_MIN, LPR>(ids, j0, j1, tab, asc, bv, bi, sv, si);
 }
 
 // 16 bytes of a table row that nothing reads again before it has left the caches: past them, so that they keep the
@@ -443,7 +558,7 @@ __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cac
     if constexpr (INLINE) {      // rows of moderate length are recomputed on the spot
       if (deg <= a.big_deg) {
         F4 bv; I4 bi; F4 sv; I4 si;
-        gather_range<IS_MIN, LPR>(a.in_ids + a.in_off[v], 0, deg, a.M, a.ldm, lane_on, q, a.in_asc[v] != 0, bv, bi, sv, si);
+        gather_range<IS_MIN, LPR>(a.in_ids + a.in_off[v], 0, deg, a.M, a.ldm, lane_on, q, a.nonneg, a.in_asc[v] != 0, bv, bi, sv, si);
         finish_empty<IS_MIN>(bv, bi, sv, si);
         RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
         const bool ch = store_row<LPR>(o, v, lane_on, q, bv, bi, sv, si, true, ov, oi);
