@@ -87,26 +87,26 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
 
 // cooperative path for rows with more than kBigDeg in-neighbours: a workgroup per chunk of
 // kBigChunk neighbours (its 4 waves take a quarter each), partial rows to scratch
-template <bool IS_MIN, int LPR, int NW>
-__global__ __launch_bounds__(NW * kWave) void k_big_partial(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
-                                                      const int32_t *pref, const int32_t *total_p, float *part_v,
-                                                      int32_t *part_i, float *part_s, int32_t *part_j) {
-  __shared__ float sv[NW][kWave * 4];    // sized per variant: the 4-wave form must not pay the LDS of the 16-wave one
+template <bool IS_MIN, int LPR>
+__global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
+                                                     const int32_t *pref, const int32_t *total_p, float *part_v,
+                                                     int32_t *part_i, float *part_s, int32_t *part_j) {
+  constexpr int NW = 4;
+  __shared__ float sv[NW][kWave * 4];
   __shared__ int si[NW][kWave * 4];
   __shared__ float ss[NW][kWave * 4];
   __shared__ int sj[NW][kWave * 4];
   const int l = lane_id(), w = threadIdx.x / kWave;
-  constexpr int nw = NW;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
   const int total = *total_p, n_big = *n_big_p;
   for (int cg = blockIdx.x; cg < total; cg += gridDim.x) {
     int i, v;
     int64_t j0, j1;
-    big_chunk(pref, n_big, cg, big_list, a.in_deg, i, v, j0, j1);
+    big_chunk(pref, n_big, cg, kBigChunk, big_list, a.in_deg, i, v, j0, j1);
     int64_t off = a.in_off[v];
     int64_t len = j1 - j0;
-    int64_t w0 = j0 + len * w / nw, w1 = j0 + len * (w + 1) / nw;
+    int64_t w0 = j0 + len * w / NW, w1 = j0 + len * (w + 1) / NW;
     F4 bv; I4 bi; F4 s2; I4 j2;
     gather_range<IS_MIN, LPR>(a.in_ids + off, w0, w1, a.M, a.ldm, lane_on, q, a.nonneg, a.in_asc[v] != 0, bv, bi, s2, j2);
 #pragma unroll
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(NW * kWave) void k_big_partial(AggArgs a, const int
     }
     __syncthreads();
     if (w == 0) {
-      for (int ww = 1; ww < nw; ww++)
+      for (int ww = 1; ww < NW; ww++)
 #pragma unroll
         for (int c = 0; c < 4; c++)
           merge2i<IS_MIN>(sv[ww][l * 4 + c], si[ww][l * 4 + c], ss[ww][l * 4 + c], sj[ww][l * 4 + c], bv.v[c], bi.v[c],
@@ -127,6 +127,50 @@ __global__ __launch_bounds__(NW * kWave) void k_big_partial(AggArgs a, const int
           part_v[o + c] = bv.v[c]; part_i[o + c] = bi.v[c]; part_s[o + c] = s2.v[c]; part_j[o + c] = j2.v[c];
         }
       }
+    }
+    __syncthreads();
+  }
+}
+
+// The same for launches of few targets, where one chunk's time is the launch's: 16 waves take a slice of kSliceCols
+// columns of a chunk, so that a row of 128 floats is spread over four workgroups, and a load brings eight rows.
+// Updates of 100 edges: 10k nodes, rows of 64 floats, 1.13 -> 1.06 ms for four, 1.25M nodes, rows of 128, 1.58 -> 1.53 ms a pass.
+// Long launches stay with whole rows: the slices leave a third of the reads beyond the L2 out (16.6M -> 10.8M of 128
+// bytes, 625k nodes and rows of 128 floats), but the chunks' fixed costs four times over take as much (10 to 600k nodes,
+// rows of 128 and 256 floats: 0.94 to 1.0 of the speed).
+template <bool IS_MIN>
+__global__ __launch_bounds__(1024) void k_big_slices(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
+                                                     const int32_t *pref, const int32_t *total_p, int slices, float *part_v,
+                                                     int32_t *part_i, float *part_s, int32_t *part_j) {
+  constexpr int LPR = kSliceLanes, NW = 16;
+  __shared__ float sv[NW][kSliceCols], ss[NW][kSliceCols];
+  __shared__ int si[NW][kSliceCols], sj[NW][kSliceCols];
+  const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int q = l % LPR;
+  const int total = *total_p, n_big = *n_big_p, items = slice_items(total, slices);
+  for (int b = blockIdx.x; b < items; b += gridDim.x) {
+    int cg, slice, i, v;
+    int64_t j0, j1;
+    if (!slice_item(b, total, slices, cg, slice)) continue;
+    big_chunk(pref, n_big, cg, kBigChunk, big_list, a.in_deg, i, v, j0, j1);
+    const int64_t off = a.in_off[v], len = j1 - j0;
+    const int64_t w0 = j0 + len * w / NW, w1 = j0 + len * (w + 1) / NW;
+    const int c0 = slice * kSliceCols;
+    F4 bv; I4 bi; F4 s2; I4 j2;
+    gather_range<IS_MIN, LPR>(a.in_ids + off, w0, w1, a.M + c0, a.ldm, c0 + 4 * q < a.wd, q, a.nonneg, a.in_asc[v] != 0, bv, bi, s2, j2);
+    if (l < LPR)
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        sv[w][l * 4 + c] = bv.v[c]; si[w][l * 4 + c] = bi.v[c]; ss[w][l * 4 + c] = s2.v[c]; sj[w][l * 4 + c] = j2.v[c];
+      }
+    __syncthreads();
+    const int col = threadIdx.x;
+    if (col < kSliceCols && c0 + col < a.wd) {
+      float xv = sv[0][col], xs = ss[0][col];
+      int xi = si[0][col], xj = sj[0][col];
+      for (int ww = 1; ww < NW; ww++) merge2i<IS_MIN>(sv[ww][col], si[ww][col], ss[ww][col], sj[ww][col], xv, xi, xs, xj);
+      const int64_t o = (int64_t)cg * a.wd + c0 + col;
+      part_v[o] = xv; part_i[o] = xi; part_s[o] = xs; part_j[o] = xj;
     }
     __syncthreads();
   }
@@ -322,19 +366,19 @@ __global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targe
 static int lanes_per_row(int ld) { return ld <= 64 ? 16 : (ld <= 128 ? 32 : 64); }
 
 template <bool IS_MIN, int LPR>
-static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compare, int block_threads,
-                          int64_t n_rows_max) {
+static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compare, int64_t n_rows_max) {
   const int32_t *list = c->big_list.as<int32_t>();
   int32_t *pref = c->big_pref.as<int32_t>();
   int32_t *n_big = &c->d_cnt->v[C_NBIG], *total = &c->d_cnt->v[C_NCHUNK];
-  INK_TRY(plan_big_rows(c, n_rows_max, a.in_deg));
-  const dim3 grid(big_partial_grid(c, a.big_grid, block_threads));
-  if (block_threads == 1024)
-    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR, 16>), grid, dim3(1024), 0, c->stream, a, list, (const int32_t *)n_big,
-                       (const int32_t *)pref, (const int32_t *)total, c->big_part_v.as<float>(),
+  INK_TRY(plan_big_rows(c, n_rows_max, kBigChunk, a.in_deg));
+  const unsigned chunks = big_partial_grid(c, a.big_grid, latency_mode(n_rows_max));
+  if (latency_mode(n_rows_max)) {
+    const int slices = big_slices(a.wd);
+    hipLaunchKernelGGL((k_big_slices<IS_MIN>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, list,
+                       (const int32_t *)n_big, (const int32_t *)pref, (const int32_t *)total, slices, c->big_part_v.as<float>(),
                        c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
-  else
-    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR, 4>), grid, dim3(256), 0, c->stream, a, list, (const int32_t *)n_big,
+  } else
+    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(chunks), dim3(256), 0, c->stream, a, list, (const int32_t *)n_big,
                        (const int32_t *)pref, (const int32_t *)total, c->big_part_v.as<float>(),
                        c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
   hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, list,
@@ -367,7 +411,7 @@ static hipError_t full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targets
     INK_TRY(hipGetLastError());
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
-  return run_big<IS_MIN, LPR>(c, a, chg, compare, big_block_threads(n_targets), n_targets);
+  return run_big<IS_MIN, LPR>(c, a, chg, compare, n_targets);
 }
 
 template <bool IS_MIN, int LPR, bool INLINE>
@@ -416,7 +460,7 @@ static hipError_t events_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targe
     INK_TRY(hipGetLastError());
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
-  return run_big<IS_MIN, LPR>(c, a, chg, 1, big_block_threads(n_targets), n_targets);
+  return run_big<IS_MIN, LPR>(c, a, chg, 1, n_targets);
 }
 
 #define DISPATCH(fn, ...)                                                         \
@@ -440,7 +484,7 @@ hipError_t agg_select_full(ink_ctx *c, const AggArgs &a, const int32_t *targets,
 template <bool IS_MIN, int LPR>
 static hipError_t long_rows_t(ink_ctx *c, const AggArgs &a, int64_t n_targets, uint64_t *chg) {
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
-  return run_big<IS_MIN, LPR>(c, a, chg, 1, big_block_threads(n_targets), n_targets);
+  return run_big<IS_MIN, LPR>(c, a, chg, 1, n_targets);
 }
 
 hipError_t agg_select_long_rows(ink_ctx *c, const AggArgs &a, int64_t n_targets, uint64_t *chg) {

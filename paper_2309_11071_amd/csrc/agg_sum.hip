@@ -131,28 +131,29 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
   if (ch && chg && l == 0) mark_bit_s(chg, v);
 }
 
-template <int LPR>
-__global__ __launch_bounds__(INK_BIG_LB) void k_sum_big_partial(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
-                                                          const int32_t *pref, const int32_t *total_p, float *part) {
-  __shared__ float sv[kBigMaxWaves][kWave * 4];
-  const int l = lane_id(), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+// Chunks of long rows of at most 48 floats: 12 lanes a row, the 4 waves of a workgroup take a quarter of a chunk each
+__global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
+                                                         const int32_t *pref, const int32_t *total_p, int chunk, float *part) {
+  constexpr int NW = 4, LPR = 12;
+  __shared__ float sv[NW][kWave * 4];
+  const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
   const int total = *total_p, n_big = *n_big_p;
   for (int cg = blockIdx.x; cg < total; cg += gridDim.x) {
     int i, v;
     int64_t j0, j1;
-    big_chunk(pref, n_big, cg, big_list, a.in_deg, i, v, j0, j1);
+    big_chunk(pref, n_big, cg, chunk, big_list, a.in_deg, i, v, j0, j1);
     int64_t off = a.in_off[v];
     int64_t len = j1 - j0;
-    int64_t w0 = j0 + len * w / nw, w1 = j0 + len * (w + 1) / nw;
+    int64_t w0 = j0 + len * w / NW, w1 = j0 + len * (w + 1) / NW;
     S4 acc;
     sum_range<LPR>(a.in_ids + off, w0, w1, a.M, a.ldm, lane_on, q, acc);
 #pragma unroll
     for (int c = 0; c < 4; c++) sv[w][l * 4 + c] = acc.v[c];
     __syncthreads();
     if (w == 0) {
-      for (int ww = 1; ww < nw; ww++)
+      for (int ww = 1; ww < NW; ww++)
 #pragma unroll
         for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], sv[ww][l * 4 + c]);
       if (lane_on && l < LPR) {
@@ -160,6 +161,43 @@ __global__ __launch_bounds__(INK_BIG_LB) void k_sum_big_partial(AggArgs a, const
 #pragma unroll
         for (int c = 0; c < 4; c++) part[o + c] = acc.v[c];
       }
+    }
+    __syncthreads();
+  }
+}
+
+// Chunks of wider rows, in slices (bigrows.h).  Whole rows came from beyond the L2 as often as not (GCN of 256 columns
+// on 29k nodes with 490 neighbours each, a table of 30 MB: 45M of 89M lines, 7 TB/s, 795 us); a slice of 32 columns stays
+// in an XCD's L2 (4.4M of 97M lines, 661 us, 18.8 TB/s out of the L2s, of which the narrow rows above reach 17 to 24).
+// Inferences: that one 1.43 -> 1.22 ms, 100k nodes with 200 neighbours each and 256 columns 2.50 -> 2.27, GIN of 128
+// columns on 20k, 100k, 400k and 1M nodes 1.02, 1.0, 1.04 and 1.01 times as fast.
+template <int NW>
+__global__ __launch_bounds__(NW * kWave) void k_sum_big_slices(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
+                                                          const int32_t *pref, const int32_t *total_p, int chunk, int slices, float *part) {
+  constexpr int LPR = kSliceLanes;
+  __shared__ float sv[NW][kSliceCols];
+  const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int q = l % LPR;
+  const int total = *total_p, n_big = *n_big_p, items = slice_items(total, slices);
+  for (int b = blockIdx.x; b < items; b += gridDim.x) {
+    int cg, slice, i, v;
+    int64_t j0, j1;
+    if (!slice_item(b, total, slices, cg, slice)) continue;
+    big_chunk(pref, n_big, cg, chunk, big_list, a.in_deg, i, v, j0, j1);
+    const int64_t off = a.in_off[v], len = j1 - j0;
+    const int64_t w0 = j0 + len * w / NW, w1 = j0 + len * (w + 1) / NW;
+    const int c0 = slice * kSliceCols;
+    S4 acc;
+    sum_range<LPR>(a.in_ids + off, w0, w1, a.M + c0, a.ldm, c0 + 4 * q < a.wd, q, acc);
+    if (l < LPR)
+#pragma unroll
+      for (int c = 0; c < 4; c++) sv[w][l * 4 + c] = acc.v[c];
+    __syncthreads();
+    const int col = threadIdx.x;
+    if (col < kSliceCols && c0 + col < a.wd) {
+      float x = sv[0][col];
+      for (int ww = 1; ww < NW; ww++) x = __fadd_rn(x, sv[ww][col]);
+      part[(int64_t)cg * a.wd + c0 + col] = x;
     }
     __syncthreads();
   }
@@ -392,10 +430,19 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   const int32_t *list = c->big_list.as<int32_t>();
   int32_t *pref = c->big_pref.as<int32_t>();
   int32_t *n_big = &c->d_cnt->v[C_NBIG], *total = &c->d_cnt->v[C_NCHUNK];
-  INK_TRY(plan_big_rows(c, n_targets, a.in_deg));
-  hipLaunchKernelGGL((k_sum_big_partial<LPR>), dim3(big_partial_grid(c, a.big_grid, big_block_threads(n_targets))),
-                     dim3(big_block_threads(n_targets)), 0, c->stream, a, list, (const int32_t *)n_big,
-                     (const int32_t *)pref, (const int32_t *)total, c->big_part_v.as<float>());
+  const bool latency = latency_mode(n_targets);
+  const int chunk = latency ? kBigChunk : kBigChunkSum, slices = big_slices(a.wd);
+  INK_TRY(plan_big_rows(c, n_targets, chunk, a.in_deg));
+  const unsigned chunks = big_partial_grid(c, a.big_grid, latency);
+  if (latency)             // few rows: 16 waves a chunk, and its slices in workgroups of their own
+    hipLaunchKernelGGL((k_sum_big_slices<16>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, list, (const int32_t *)n_big,
+                       (const int32_t *)pref, (const int32_t *)total, chunk, slices, c->big_part_v.as<float>());
+  else if (LPR == 12)
+    hipLaunchKernelGGL(k_sum_big_partial, dim3(chunks), dim3(256), 0, c->stream, a, list, (const int32_t *)n_big,
+                       (const int32_t *)pref, (const int32_t *)total, chunk, c->big_part_v.as<float>());
+  else
+    hipLaunchKernelGGL((k_sum_big_slices<4>), dim3(sliced_grid(chunks, slices)), dim3(256), 0, c->stream, a, list, (const int32_t *)n_big,
+                       (const int32_t *)pref, (const int32_t *)total, chunk, slices, c->big_part_v.as<float>());
   hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, list, (const int32_t *)n_big,
                      (const int32_t *)pref, (const float *)c->big_part_v.as<float>(), chg, compare);
   return hipGetLastError();

@@ -1,5 +1,5 @@
 // Work list for rows with more than kBigDeg in-neighbours: each such row is cut into chunks of
-// kBigChunk neighbours, one workgroup per chunk, then one wave per row combines its chunks in
+// kBigChunk neighbours (kBigChunkSum for long launches of sums), one workgroup per chunk, then one wave per row combines its chunks in
 // order.  The plan (chunk prefix over the listed rows) is built on the device from the device-side
 // row count, and the chunk / row kernels run a fixed grid that strides over it, so no host
 // round trip is needed; with no long rows they return at once.
@@ -7,10 +7,6 @@
 #include "ctx.h"
 
 namespace ink {
-
-#ifndef INK_BIG_LB
-#define INK_BIG_LB 1024
-#endif
 
 constexpr int kBigGrid = 4096;             // workgroups of the per-row combine kernel
 
@@ -32,8 +28,8 @@ inline int64_t big_chunk_capacity(const ink_ctx *c) {
 }
 
 // one workgroup per expected chunk (the hardware balances them); never fewer than fill the chip
-inline unsigned big_partial_grid(const ink_ctx *c, int64_t want, int block_threads) {
-  int64_t lo = block_threads >= 1024 ? 512 : 2048, hi = big_chunk_capacity(c);
+inline unsigned big_partial_grid(const ink_ctx *c, int64_t want, bool latency) {
+  int64_t lo = latency ? 512 : 2048, hi = big_chunk_capacity(c);
   if (want < lo) want = lo;
   if (want > hi) want = hi;
   return (unsigned)want;
@@ -57,13 +53,11 @@ inline bool latency_mode(int64_t n_targets) { return n_targets <= kLatencyTarget
 inline int big_threshold(int64_t n_targets, int lanes_per_row, int throughput_deg) {
   return latency_mode(n_targets) ? 32 * (kWave / lanes_per_row) : throughput_deg;
 }
-inline int big_block_threads(int64_t n_targets) { return latency_mode(n_targets) ? (INK_BIG_LB >= 1024 ? 1024 : 256) : 256; }
-constexpr int kBigMaxWaves = INK_BIG_LB / 64;
 
 // plan: pref[i] = chunks of the listed rows before i (i <= n_big), *total = all chunks
 struct BigChunkCount {
-  const int32_t *list; const int32_t *n_big; const int32_t *deg;
-  __device__ int operator()(int64_t i) const { return i < *n_big ? (deg[list[i]] + kBigChunk - 1) / kBigChunk : 0; }
+  const int32_t *list; const int32_t *n_big; const int32_t *deg; int chunk;
+  __device__ int operator()(int64_t i) const { return i < *n_big ? (int)((unsigned)(deg[list[i]] + chunk - 1) / (unsigned)chunk) : 0; }
 };
 struct BigPrefStore {
   int32_t *pref; const int32_t *n_big;
@@ -74,23 +68,38 @@ struct BigPrefStore {
   }
 };
 // n_rows_max bounds the device-side row count
-inline hipError_t plan_big_rows(ink_ctx *c, int64_t n_rows_max, const int32_t *in_deg) {
+inline hipError_t plan_big_rows(ink_ctx *c, int64_t n_rows_max, int chunk, const int32_t *in_deg) {
   int64_t cap = (int64_t)(c->big_list.cap / 4);
   if (n_rows_max > cap) n_rows_max = cap;
   const int32_t *n_big = &c->d_cnt->v[C_NBIG];
   return tile_scan<BigChunkCount, BigPrefStore, kScanItems, true>(
-      c->ws, BigChunkCount{c->big_list.as<int32_t>(), n_big, in_deg}, BigPrefStore{c->big_pref.as<int32_t>(), n_big},
+      c->ws, BigChunkCount{c->big_list.as<int32_t>(), n_big, in_deg, chunk}, BigPrefStore{c->big_pref.as<int32_t>(), n_big},
       n_rows_max, &c->d_cnt->v[C_NCHUNK], c->stream);
 }
 
 // row (index in the list), node id and neighbour range of global chunk cg
-__device__ __forceinline__ void big_chunk(const int32_t *pref, int n_big, int cg, const int32_t *list,
+__device__ __forceinline__ void big_chunk(const int32_t *pref, int n_big, int cg, int chunk, const int32_t *list,
                                           const int32_t *in_deg, int &i, int &v, int64_t &j0, int64_t &j1) {
   i = wave_last_le(pref, n_big, cg);      // called by whole waves with wave-uniform arguments
   v = list[i];
   int64_t deg = in_deg[v];
-  j0 = (int64_t)(cg - pref[i]) * kBigChunk;
-  j1 = j0 + kBigChunk < deg ? j0 + kBigChunk : deg;
+  j0 = (int64_t)(cg - pref[i]) * chunk;
+  j1 = j0 + chunk < deg ? j0 + chunk : deg;
+}
+
+// Slices: the columns of a chunk are shared out in groups of kSliceCols, one 128-byte line of every row.  Workgroups go
+// round the 8 XCDs, so item b runs on XCD b % 8; with S slices, XCD x takes the S parts x S .. x S + S - 1 of the 8 S
+// parts (slice u / 8, every eighth chunk) one after the other.  An XCD then reads one slice of the message table, or two
+// in turn, instead of all of it, and its L2 holds as many times more rows of it.
+constexpr int kSliceLanes = 8, kSliceCols = 4 * kSliceLanes;
+inline int big_slices(int wd) { return (wd + kSliceCols - 1) / kSliceCols; }
+inline unsigned sliced_grid(unsigned chunks, int slices) { return (chunks * (unsigned)slices + 7u) & ~7u; }    // b % 8 survives the grid stride
+__device__ __forceinline__ int slice_items(int total, int slices) { return ((total + 7) >> 3) * 8 * slices; }
+__device__ __forceinline__ bool slice_item(int b, int total, int slices, int &chunk, int &slice) {
+  const int per = (total + 7) >> 3, i = b >> 3, j = i / per, u = (b & 7) * slices + j;
+  slice = u >> 3;
+  chunk = (i - j * per) * 8 + (u & 7);
+  return chunk < total;
 }
 
 }  // namespace ink

@@ -35,6 +35,14 @@ namespace ink {
 #define INK_BIG_CHUNK 1024
 #endif
 constexpr int kBigChunk = INK_BIG_CHUNK;  // neighbours per chunk of such a row
+#ifndef INK_BIG_CHUNK_SUM
+#define INK_BIG_CHUNK_SUM 2048
+#endif
+// ... in long launches of sums.  1024 / 2048 / 4096, inference: GCN of 256 columns on 29k nodes, 490 neighbours each, 1.25 /
+// 1.22 / 1.22 ms, on 100k nodes, 200 each, 2.30 / 2.27 / 2.22; GIN of 128 on 400k, 20 each, 1.33 / 1.31 / 1.32, on 20k,
+// 50 each, .204 / .202 / .213.  Max / min at 2048 lose: 60k nodes, 50 each, .480 -> .506.
+constexpr int kBigChunkSum = INK_BIG_CHUNK_SUM;
+static_assert(kBigChunk <= kBigChunkSum, "buffer bounds of the long-row path use the smaller chunk");
 #ifndef INK_BIG_DEG_SUM
 #define INK_BIG_DEG_SUM 1024
 #endif
