@@ -11,6 +11,7 @@
 // recompute that the value-only rule of Sec. 2.5.1 would need.
 #include <algorithm>
 
+#include "rowblock.h"
 #include "select.h"
 
 #ifndef INK_EV_INLINE_WIDE
@@ -27,11 +28,10 @@ namespace ink {
 // ------------------------------------------------------------------ full re-aggregation
 // what a recompute launch does besides storing the rows
 enum { FULL_COMPARE = 1,        // compare with the cached row: store and mark only what changed
-       FULL_COUNT_GATHER = 2,   // tally the neighbour rows fetched
-       FULL_COUNT_CHANGED = 4,  // tally the rows whose value changed
-       FULL_COUNT_LONG = 8 };   // tally the neighbour rows that go to the long-row path
+       FULL_TALLY = 2,          // count the rows and the neighbour rows fetched
+       FULL_COUNT_CHANGED = 4 };   // count the rows whose value changed
 
-// One wave per row, the grid strides over the rows; n_targets_dev (optional) is the device-side
+// A wave takes blocks of rows (rowblock.h), the grid strides over them; n_targets_dev (optional) is the device-side
 // row count, n_targets then only bounds it.
 template <bool IS_MIN, int LPR>
 __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targets, int64_t n_targets,
@@ -41,48 +41,46 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
   if (n_targets_dev) { int64_t nd = *n_targets_dev; n_targets = nd < n_targets ? nd : n_targets; }
-  const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kWave);
-  // wave-uniform, so that the row's place and length are scalar loads that are under way together (inference of 625k
-  // nodes, 3 layers of 128: 4.80 -> 4.69 ms).  79 registers, 6 waves per SIMD: held to 64 the kernel keeps addresses in
-  // scratch and takes a third longer
+  const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x / kWave);
+  const int per = row_block(n_targets, n_waves);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  for (int64_t wid = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave; wid < n_targets; wid += stride) {
-    const int v = targets ? targets[wid] : (int)wid;
-    const int deg = a.in_deg[v];
-    const int64_t off = a.in_off[v];
-    const bool asc = a.in_asc[v] != 0;
-    if ((flags & FULL_COUNT_GATHER) && l == 0)
-      atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER], (unsigned long long)deg);
-    if ((flags & FULL_COUNT_LONG) && deg > a.big_deg && l == 0)     // few rows: also tallied when every row is recomputed
-      atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER_LONG], (unsigned long long)deg);
-    if (deg > a.big_deg) {
-      if (l == 0) big_list[atomicAdd(n_big, 1)] = v;
-      continue;
-    }
-    F4 bv; I4 bi; F4 sv; I4 si;
-    gather_range<IS_MIN, LPR>(a.in_ids + off, 0, deg, a.M, a.ldm, lane_on, q, a.nonneg, asc, bv, bi, sv, si);
-    finish_empty<IS_MIN>(bv, bi, sv, si);
-    RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
-    F4 dum; I4 dumi;
-    bool ch;
-    if (flags & FULL_COMPARE) ch = store_row<LPR>(o, v, lane_on, q, bv, bi, sv, si, false, dum, dumi);
-    else {
-      const int64_t o4 = (int64_t)v * a.ld + 4 * q;       // every lane group has the row: the first two store half of the tables each
-      if (lane_on && l < LPR) {
-        store_past(a.A + o4, bv.v);
-        store_past(a.ARG + o4, bi.v);
+  int64_t nb = 0, nb_long = 0;
+  for (int64_t r0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * per; r0 < n_targets; r0 += n_waves * per) {
+    RowBlock B;
+    B.load(a, targets, r0, n_targets - r0 < per ? (int)(n_targets - r0) : per, chg, big_list, n_big, nb, nb_long);
+    int win = 0;
+    if (B.todo) win = B.first_ids(a.in_ids, __builtin_ctzll(B.todo));
+    while (B.todo) {
+      const int j = __builtin_ctzll(B.todo), v = B.row(j);
+      B.todo &= B.todo - 1;
+      const int next = B.todo ? B.first_ids(a.in_ids, __builtin_ctzll(B.todo)) : 0;
+      F4 bv; I4 bi; F4 sv; I4 si;
+      gather_row<IS_MIN, LPR>(a.in_ids + B.place(j), B.length(j), win, a.M, a.ldm, lane_on, q, a.nonneg, B.ascending(j), bv, bi, sv, si);
+      win = next;
+      finish_empty<IS_MIN>(bv, bi, sv, si);
+      RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
+      F4 dum; I4 dumi;
+      bool ch;
+      if (flags & FULL_COMPARE) ch = store_row<LPR>(o, v, lane_on, q, bv, bi, sv, si, false, dum, dumi);
+      else {
+        const int64_t o4 = (int64_t)v * a.ld + 4 * q;       // every lane group has the row: the first two store half of the tables each
+        if (lane_on && l < LPR) {
+          store_past(a.A + o4, bv.v);
+          store_past(a.ARG + o4, bi.v);
+        }
+        if (lane_on && (LPR == kWave || l / LPR == 1)) {
+          store_past(a.UB + o4, sv.v);
+          store_past(a.ARG2 + o4, si.v);
+        }
+        ch = false;
       }
-      if (lane_on && (LPR == kWave || l / LPR == 1)) {
-        store_past(a.UB + o4, sv.v);
-        store_past(a.ARG2 + o4, si.v);
+      if (ch && chg && l == 0) {
+        mark_bit(chg, v);
+        if ((flags & FULL_COUNT_CHANGED) && a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull);
       }
-      ch = false;
-    }
-    if (ch && chg && l == 0) {
-      mark_bit(chg, v);
-      if ((flags & FULL_COUNT_CHANGED) && a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull);
     }
   }
+  if (flags & FULL_TALLY) tally_rows(cnt, nb, nb_long);
 }
 
 // cooperative path for rows with more than kBigDeg in-neighbours: a workgroup per chunk of
@@ -407,7 +405,7 @@ static hipError_t full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targets
     KernelTimer kt(c, a.layer, INK_K_AGG_FULL);
     hipLaunchKernelGGL((k_agg_full<IS_MIN, LPR>), dim3((unsigned)blocks), dim3(256), 0, c->stream, a, targets, n_targets,
                        (const int32_t *)nullptr, chg, c->big_list.as<int32_t>(), &c->d_cnt->v[C_NBIG],
-                       (compare ? FULL_COMPARE : 0) | (targets ? FULL_COUNT_GATHER : 0) | FULL_COUNT_LONG, c->d_cnt);
+                       (compare ? FULL_COMPARE | FULL_TALLY : 0), c->d_cnt);
     INK_TRY(hipGetLastError());
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);

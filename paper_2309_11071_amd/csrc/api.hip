@@ -598,6 +598,7 @@ static AggArgs agg_args(ink_ctx *c, int l) {       // layer l in 1..k
   a.big_deg = kBigDeg;
   a.big_grid = 2 * c->big_hint[l] + 1024;
   a.count_cond = 1;
+  a.keep_empty = false;
   a.layer = l;
   return a;
 }
@@ -1094,6 +1095,10 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
   if (dense) {
     // so many events that re-aggregating every node costs less than grouping them (Sec. 5.1)
     Prof p(c, INK_T_AGG);
+    if (c->is_select) {      // rows without neighbours are empty already, but for those that lost theirs: their bits are set beforehand
+      if (n_del > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n_del), dim3(256), 0, s, (const int32_t *)c->del_dst, (int)n_del, bm);
+      a.keep_empty = true;
+    }
     API_TRY(agg_full_any(c, a, bm));
     return INK_OK;
   }

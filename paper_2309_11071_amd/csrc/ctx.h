@@ -272,6 +272,7 @@ struct AggArgs {
   float *UB;                        // max/min: bound on the best value among the non-holders (same layout)
   const uint8_t *in_asc;            // per node: in-list ascending by id (lets ties go to the first seen)
   int32_t *ARG2;                    // max/min: the non-holder that has exactly that value (lowest id), or -1 if not known
+  bool keep_empty;                  // recompute of every row: those without neighbours keep what they have unless their bit is set
   int d;                            // columns handled by this launch (<= 256; wider rows go block by block)
   int wd;                           // d rounded up to 4
   bool is_min;

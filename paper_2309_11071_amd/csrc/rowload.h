@@ -13,6 +13,12 @@
 
 namespace ink {
 
+// ids [at, at + 64) of a list of n, one per lane; those past the end repeat the last
+__device__ __forceinline__ int ids_ahead(const int32_t *ids, int at, int n) {
+  const int k = at + lane_id();
+  return at < n ? ids[k < n ? k : n - 1] : 0;
+}
+
 template <int LPR> struct RowTable {
   const char *base;         // LPR < 64: of this lane's four floats
   uint32_t row_bytes, lane_bytes;

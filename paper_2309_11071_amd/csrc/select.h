@@ -184,19 +184,15 @@ __device__ __forceinline__ void take_batch(const RowTable<LPR> &tab, int win, in
   }
 }
 
-// Best and runner-up of the rows ids[j0 .. j1) by the whole wave, per lane group
+// Best and runner-up of the n rows ids[..] by the whole wave, per lane group; win: the first ids, one per lane
 template <bool IS_MIN, int LPR, bool NONNEG>
-__device__ __forceinline__ void gather_top2(const int32_t *ids, int64_t j0, int64_t j1, const RowTable<LPR> &tab, Top2<IS_MIN> &t) {
+__device__ __forceinline__ void gather_top2(const int32_t *ids, int n, int win, const RowTable<LPR> &tab, Top2<IS_MIN> &t) {
   constexpr int G = kWave / LPR;
   constexpr int U = LPR == 8 ? INK_U_SEL8 : LPR == 16 ? INK_U_SEL16 : (LPR == 32 ? INK_U_SEL32 : INK_U_SEL64);
-  const int l = lane_id();
   t.init();
-  const int32_t *p = ids + j0;
-  const int n = __builtin_amdgcn_readfirstlane((int)(j1 - j0));
-  int win = n > 0 ? p[l < n ? l : n - 1] : 0;
   for (int jb = 0; jb < n; jb += kWave) {
-    const int cnt = n - jb < kWave ? n - jb : kWave, ahead = jb + kWave + l;
-    const int next = jb + kWave < n ? p[ahead < n ? ahead : n - 1] : 0;
+    const int cnt = n - jb < kWave ? n - jb : kWave;
+    const int next = ids_ahead(ids, jb + kWave, n);
     for (int it = 0; it < cnt;) {
       const int left = cnt - it;
       if (left >= G * U) { take_batch<IS_MIN, LPR, NONNEG, U, true>(tab, win, it, cnt, t); it += G * U; }
@@ -210,12 +206,12 @@ __device__ __forceinline__ void gather_top2(const int32_t *ids, int64_t j0, int6
 // The same entry by entry, for rows in whose result an infinity or a NaN stands that the doubles do not order as values
 // are: a NaN takes no place, the worst infinity takes one only in lists not known to be ascending (asc).
 template <bool IS_MIN, int LPR>
-__device__ __forceinline__ void gather_slow(const int32_t *ids, int64_t j0, int64_t j1, const RowTable<LPR> &tab, bool asc,
+__device__ __forceinline__ void gather_slow(const int32_t *ids, int n, const RowTable<LPR> &tab, bool asc,
                                             F4 &bv, I4 &bi, F4 &sv, I4 &si) {
 #pragma unroll
   for (int c = 0; c < 4; c++) { bv.v[c] = worst<IS_MIN>(); bi.v[c] = 0x7fffffff; sv.v[c] = worst<IS_MIN>(); si.v[c] = 0x7fffffff; }
 #pragma unroll 1
-  for (int64_t j = j0 + tab.g; j < j1; j += kWave / LPR) {
+  for (int j = tab.g; j < n; j += kWave / LPR) {
     const int id = ids[j];
     const float4 r = tab.load(id);
     const float x[4] = {r.x, r.y, r.z, r.w};
@@ -225,16 +221,16 @@ __device__ __forceinline__ void gather_slow(const int32_t *ids, int64_t j0, int6
   reduce_groups_i<IS_MIN, LPR>(bv, bi, sv, si);
 }
 
-// Selection over neighbours ids[j0 .. j1) of one row, by the whole wave.  On return every lane holds the best and the
-// runner-up (value, id) of its 4 dimensions over the range; (worst, INT_MAX) where there is none.  nonneg, asc (both
-// wave-uniform): the table has no value with its sign bit set; the ids are ascending.
+// Selection over the n neighbours ids[..] of one row, by the whole wave; win: ids_ahead(ids, 0, n).  On return every lane
+// holds the best and the runner-up (value, id) of its 4 dimensions; (worst, INT_MAX) where there is none.  n, nonneg and
+// asc are wave-uniform: the table has no value with its sign bit set; the ids are ascending.
 template <bool IS_MIN, int LPR>
-__device__ __forceinline__ void gather_range(const int32_t *ids, int64_t j0, int64_t j1, const float *M, int ldm, bool lane_on,
-                                             int q, bool nonneg, bool asc, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
+__device__ __forceinline__ void gather_row(const int32_t *ids, int n, int win, const float *M, int ldm, bool lane_on, int q,
+                                           bool nonneg, bool asc, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
   const RowTable<LPR> tab(M, ldm, lane_on, q);
   Top2<IS_MIN> t;
-  if (nonneg) gather_top2<IS_MIN, LPR, true>(ids, j0, j1, tab, t);
-  else gather_top2<IS_MIN, LPR, false>(ids, j0, j1, tab, t);
+  if (nonneg) gather_top2<IS_MIN, LPR, true>(ids, n, win, tab, t);
+  else gather_top2<IS_MIN, LPR, false>(ids, n, win, tab, t);
   merge_groups<IS_MIN, LPR>(t);
   bool odd = false, zero = false;
 #pragma unroll
@@ -263,7 +259,14 @@ __device__ __forceinline__ void gather_range(const int32_t *ids, int64_t j0, int
         }
     }
   }
-  if (__ballot(odd && lane_on) != 0ull) gather_slow<IS_MIN, LPR>(ids, j0, j1, tab, asc, bv, bi, sv, si);
+  if (__ballot(odd && lane_on) != 0ull) gather_slow<IS_MIN, LPR>(ids, n, tab, asc, bv, bi, sv, si);
+}
+// ... over ids[j0 .. j1)
+template <bool IS_MIN, int LPR>
+__device__ __forceinline__ void gather_range(const int32_t *ids, int64_t j0, int64_t j1, const float *M, int ldm, bool lane_on,
+                                             int q, bool nonneg, bool asc, F4 &bv, I4 &bi, F4 &sv, I4 &si) {
+  const int n = __builtin_amdgcn_readfirstlane((int)(j1 - j0));
+  gather_row<IS_MIN, LPR>(ids + j0, n, ids_ahead(ids + j0, 0, n), M, ldm, lane_on, q, nonneg, asc, bv, bi, sv, si);
 }
 
 // 16 bytes of a table row that nothing reads again before it has left the caches: past them, so that they keep the
