@@ -35,8 +35,7 @@ enum { FULL_COMPARE = 1,        // compare with the cached row: store and mark o
 // row count, n_targets then only bounds it.
 template <bool IS_MIN, int LPR>
 __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targets, int64_t n_targets,
-                                                  const int32_t *n_targets_dev, uint64_t *chg, int32_t *big_list,
-                                                  int32_t *n_big, int flags, Counters *cnt) {
+                                                  const int32_t *n_targets_dev, uint64_t *chg, int flags, Counters *cnt) {
   const int l = lane_id();
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
@@ -47,7 +46,7 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
   int64_t nb = 0, nb_long = 0;
   for (int64_t r0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * per; r0 < n_targets; r0 += n_waves * per) {
     RowBlock B;
-    B.load(a, targets, r0, n_targets - r0 < per ? (int)(n_targets - r0) : per, chg, big_list, n_big, nb, nb_long);
+    B.load(a, targets, r0, n_targets - r0 < per ? (int)(n_targets - r0) : per, chg, cnt, nb, nb_long);
     int win = 0;
     if (B.todo) win = B.first_ids(a.in_ids, __builtin_ctzll(B.todo));
     while (B.todo) {
@@ -86,9 +85,8 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
 // cooperative path for rows with more than kBigDeg in-neighbours: a workgroup per chunk of
 // kBigChunk neighbours (its 4 waves take a quarter each), partial rows to scratch
 template <bool IS_MIN, int LPR>
-__global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
-                                                     const int32_t *pref, const int32_t *total_p, float *part_v,
-                                                     int32_t *part_i, float *part_s, int32_t *part_j) {
+__global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const Counters *cnt, float *part_v, int32_t *part_i,
+                                                     float *part_s, int32_t *part_j) {
   constexpr int NW = 4;
   __shared__ float sv[NW][kWave * 4];
   __shared__ int si[NW][kWave * 4];
@@ -97,11 +95,11 @@ __global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const int32_t *b
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
-  const int total = *total_p, n_big = *n_big_p;
+  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG];
   for (int cg = blockIdx.x; cg < total; cg += gridDim.x) {
     int i, v;
     int64_t j0, j1;
-    big_chunk(pref, n_big, cg, kBigChunk, big_list, a.in_deg, i, v, j0, j1);
+    big_chunk(a.big, n_big, cg, a.in_deg, i, v, j0, j1);
     int64_t off = a.in_off[v];
     int64_t len = j1 - j0;
     int64_t w0 = j0 + len * w / NW, w1 = j0 + len * (w + 1) / NW;
@@ -137,20 +135,19 @@ __global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const int32_t *b
 // bytes, 625k nodes and rows of 128 floats), but the chunks' fixed costs four times over take as much (10 to 600k nodes,
 // rows of 128 and 256 floats: 0.94 to 1.0 of the speed).
 template <bool IS_MIN>
-__global__ __launch_bounds__(1024) void k_big_slices(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
-                                                     const int32_t *pref, const int32_t *total_p, int slices, float *part_v,
-                                                     int32_t *part_i, float *part_s, int32_t *part_j) {
+__global__ __launch_bounds__(1024) void k_big_slices(AggArgs a, const Counters *cnt, int slices, float *part_v, int32_t *part_i,
+                                                     float *part_s, int32_t *part_j) {
   constexpr int LPR = kSliceLanes, NW = 16;
   __shared__ float sv[NW][kSliceCols], ss[NW][kSliceCols];
   __shared__ int si[NW][kSliceCols], sj[NW][kSliceCols];
   const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = l % LPR;
-  const int total = *total_p, n_big = *n_big_p, items = slice_items(total, slices);
+  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG], items = slice_items(total, slices);
   for (int b = blockIdx.x; b < items; b += gridDim.x) {
     int cg, slice, i, v;
     int64_t j0, j1;
     if (!slice_item(b, total, slices, cg, slice)) continue;
-    big_chunk(pref, n_big, cg, kBigChunk, big_list, a.in_deg, i, v, j0, j1);
+    big_chunk(a.big, n_big, cg, a.in_deg, i, v, j0, j1);
     const int64_t off = a.in_off[v], len = j1 - j0;
     const int64_t w0 = j0 + len * w / NW, w1 = j0 + len * (w + 1) / NW;
     const int c0 = slice * kSliceCols;
@@ -177,24 +174,22 @@ __global__ __launch_bounds__(1024) void k_big_slices(AggArgs a, const int32_t *b
 // One wave per big row: its lane groups take the partial rows in turn, U of them in flight, then the row is stored.  (One
 // row after the other made a hub's chain the launch's time: 45 us on 12.5M edges and rows of 128 floats, now 21.)
 template <bool IS_MIN, int LPR>
-__global__ __launch_bounds__(64) void k_big_final(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
-                                                  const int32_t *pref, const float *part_v, const int32_t *part_i,
-                                                  const float *part_s, const int32_t *part_j, uint64_t *chg,
-                                                  int compare, Counters *cnt) {
+__global__ __launch_bounds__(64) void k_big_final(AggArgs a, const float *part_v, const int32_t *part_i, const float *part_s,
+                                                  const int32_t *part_j, uint64_t *chg, int compare, Counters *cnt) {
   const int l = lane_id();
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
   constexpr int G = kWave / LPR, U = 4;
   const int g = l / LPR, qo = lane_on ? 4 * q : 0;
-  const int n_big = *n_big_p;
+  const int n_big = cnt->v[C_NBIG];
   for (int i = blockIdx.x; i < n_big; i += gridDim.x) {
-    int v = big_list[i];
+    int v = a.big.list[i];
     F4 bv; I4 bi; F4 s2; I4 j2;
 #pragma unroll
     for (int c = 0; c < 4; c++) {
       bv.v[c] = worst<IS_MIN>(); bi.v[c] = 0x7fffffff; s2.v[c] = worst<IS_MIN>(); j2.v[c] = 0x7fffffff;
     }
-    const int p0 = pref[i], p1 = pref[i + 1];
+    const int p0 = a.big.base[i], p1 = p0 + big_row_chunks(a.in_deg[v], a.big.chunk);
     for (int pb = p0; pb < p1; pb += G * U) {
       float4 xv[U], xs[U];
       int4 xi[U], xj[U];
@@ -244,7 +239,7 @@ constexpr int kEvBlock = INK_EV_BLOCK;
 template <bool IS_MIN, int LPR, bool INLINE>
 __global__ __launch_bounds__(256) void k_agg_events(AggArgs a, const int32_t *targets, const int32_t *seg,
                                                     const int32_t *n_targets_p, const uint32_t *ev, uint64_t *chg,
-                                                    int32_t *big_list, int32_t *exp_list, Counters *cnt, int ev_block,
+                                                    int32_t *exp_list, Counters *cnt, int ev_block,
                                                     LongEvents lng) {
   static_assert(kEvBlock + 2 <= kWave, "a lane per target and bound of the block");
   RowSink exp;
@@ -267,7 +262,7 @@ __global__ __launch_bounds__(256) void k_agg_events(AggArgs a, const int32_t *ta
       Cached<IS_MIN> c;
       EvAcc<IS_MIN> s;
       reduce_events<IS_MIN, LPR>(a, v, ev, e0, e1, lane_on, q, c, s);
-      finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, big_list, exp_list, exp, cnt);
+      finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, exp_list, exp, cnt);
     }
   }
   if constexpr (!INLINE) exp.flush(exp_list, &cnt->v[C_NEXP]);
@@ -323,7 +318,7 @@ __global__ __launch_bounds__(256) void k_ev_partial(AggArgs a, const int32_t *ta
 // One wave per long segment: its lane groups take the chunks in turn, then the target is decided.
 template <bool IS_MIN, int LPR, bool INLINE>
 __global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targets, const int32_t *seg, LongEvents lng,
-                                                 EvPart part, uint64_t *chg, int32_t *big_list, int32_t *exp_list,
+                                                 EvPart part, uint64_t *chg, int32_t *exp_list,
                                                  Counters *cnt) {
   constexpr int G = kWave / LPR;
   RowSink exp;
@@ -355,7 +350,7 @@ __global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targe
         }
       }
     s.any_del = __ballot((fl & 4) != 0) != 0ull;
-    finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, big_list, exp_list, exp, cnt);
+    finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, exp_list, exp, cnt);
   }
   if constexpr (!INLINE) exp.flush(exp_list, &cnt->v[C_NEXP]);
 }
@@ -365,22 +360,15 @@ static int lanes_per_row(int ld) { return ld <= 64 ? 16 : (ld <= 128 ? 32 : 64);
 
 template <bool IS_MIN, int LPR>
 static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compare, int64_t n_rows_max) {
-  const int32_t *list = c->big_list.as<int32_t>();
-  int32_t *pref = c->big_pref.as<int32_t>();
-  int32_t *n_big = &c->d_cnt->v[C_NBIG], *total = &c->d_cnt->v[C_NCHUNK];
-  INK_TRY(plan_big_rows(c, n_rows_max, kBigChunk, a.in_deg));
   const unsigned chunks = big_partial_grid(c, a.big_grid, latency_mode(n_rows_max));
   if (latency_mode(n_rows_max)) {
     const int slices = big_slices(a.wd);
-    hipLaunchKernelGGL((k_big_slices<IS_MIN>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, list,
-                       (const int32_t *)n_big, (const int32_t *)pref, (const int32_t *)total, slices, c->big_part_v.as<float>(),
-                       c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
+    hipLaunchKernelGGL((k_big_slices<IS_MIN>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, (const Counters *)c->d_cnt, slices,
+                       c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
   } else
-    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(chunks), dim3(256), 0, c->stream, a, list, (const int32_t *)n_big,
-                       (const int32_t *)pref, (const int32_t *)total, c->big_part_v.as<float>(),
+    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(chunks), dim3(256), 0, c->stream, a, (const Counters *)c->d_cnt, c->big_part_v.as<float>(),
                        c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
-  hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, list,
-                     (const int32_t *)n_big, (const int32_t *)pref, (const float *)c->big_part_v.as<float>(),
+  hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)c->big_part_v.as<float>(),
                      (const int32_t *)c->big_part_i.as<int32_t>(), (const float *)c->big_part_s.as<float>(),
                      (const int32_t *)c->big_part_j.as<int32_t>(), chg, compare, c->d_cnt);
   return hipGetLastError();
@@ -399,13 +387,13 @@ static hipError_t full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targets
   a.big_deg = big_threshold(n_targets, LPR, kBigDeg);
   int compare = chg != nullptr;
   INK_TRY(ensure_big_buffers(c, a.wd, true));
-  INK_TRY(hipMemsetAsync(&c->d_cnt->v[C_NBIG], 0, sizeof(int32_t), c->stream));
+  a.big = big_rows_of(c, kBigChunk);
+  INK_TRY(clear_big_rows(c));
   int64_t blocks = std::min<int64_t>((n_targets + 3) / 4, kFullGrid);
   {
     KernelTimer kt(c, a.layer, INK_K_AGG_FULL);
     hipLaunchKernelGGL((k_agg_full<IS_MIN, LPR>), dim3((unsigned)blocks), dim3(256), 0, c->stream, a, targets, n_targets,
-                       (const int32_t *)nullptr, chg, c->big_list.as<int32_t>(), &c->d_cnt->v[C_NBIG],
-                       (compare ? FULL_COMPARE | FULL_TALLY : 0), c->d_cnt);
+                       (const int32_t *)nullptr, chg, (compare ? FULL_COMPARE | FULL_TALLY : 0), c->d_cnt);
     INK_TRY(hipGetLastError());
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
@@ -422,15 +410,15 @@ static hipError_t launch_events(ink_ctx *c, const AggArgs &a, const int32_t *tar
   int64_t blocks = std::min<int64_t>(((n_targets + ev_block - 1) / ev_block + 3) / 4, INK_EVENT_GRID);
   LongEvents lng{nullptr, nullptr, latency ? kEvLongLatency : kEvLong};
   INK_TRY(ensure_long_events(c, eb, a.wd, true, &lng));
-  int32_t *big_list = c->big_list.as<int32_t>(), *exp_list = c->exp_list.as<int32_t>();
+  int32_t *exp_list = c->exp_list.as<int32_t>();
   hipLaunchKernelGGL((k_agg_events<IS_MIN, LPR, INLINE>), dim3((unsigned)blocks), dim3(256), 0, c->stream, a, targets, seg,
-                     n_targets_dev, ev, chg, big_list, exp_list, c->d_cnt, ev_block, lng);
+                     n_targets_dev, ev, chg, exp_list, c->d_cnt, ev_block, lng);
   if (eb.max_seg > lng.limit) {      // otherwise no segment can be long
     EvPart part{c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>()};
     hipLaunchKernelGGL((k_ev_partial<IS_MIN, LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(eb.n_events, lng.limit), 8192)),
                        dim3(256), 0, c->stream, a, targets, seg, ev, lng, part, (const Counters *)c->d_cnt);
     hipLaunchKernelGGL((k_ev_final<IS_MIN, LPR, INLINE>), dim3((unsigned)std::min<int64_t>(long_ev_rows(eb.n_events, lng.limit), 8192)),
-                       dim3(64), 0, c->stream, a, targets, seg, lng, part, chg, big_list, exp_list, c->d_cnt);
+                       dim3(64), 0, c->stream, a, targets, seg, lng, part, chg, exp_list, c->d_cnt);
   }
   return hipGetLastError();
 }
@@ -445,6 +433,7 @@ static hipError_t events_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targe
   AggArgs a = a_in;
   a.big_deg = big_threshold(n_targets, LPR, kBigDeg);
   INK_TRY(ensure_big_buffers(c, a.wd, true));
+  a.big = big_rows_of(c, kBigChunk);
   INK_TRY(c->exp_list.reserve((size_t)n_targets * 4));
   const bool inline_exposed = INK_EV_INLINE_WIDE == 0 ? false : (LPR >= (INK_EV_INLINE_WIDE == 1 ? 64 : (INK_EV_INLINE_WIDE == 2 ? 32 : 16)) || latency_mode(n_targets));
   if (inline_exposed) INK_TRY((launch_events<IS_MIN, LPR, true>(c, a, targets, seg, n_targets, n_targets_dev, ev, eb, chg)));
@@ -454,7 +443,7 @@ static hipError_t events_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targe
     int64_t rb = std::min<int64_t>((n_targets + 3) / 4, latency_mode(n_targets) ? 2048 : 16384);
     hipLaunchKernelGGL((k_agg_full<IS_MIN, LPR>), dim3((unsigned)rb), dim3(256), 0, c->stream, a,
                        (const int32_t *)c->exp_list.as<int32_t>(), n_targets, (const int32_t *)&c->d_cnt->v[C_NEXP], chg,
-                       c->big_list.as<int32_t>(), &c->d_cnt->v[C_NBIG], FULL_COMPARE | FULL_COUNT_CHANGED, c->d_cnt);
+                       FULL_COMPARE | FULL_COUNT_CHANGED, c->d_cnt);
     INK_TRY(hipGetLastError());
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
@@ -480,7 +469,9 @@ hipError_t agg_select_full(ink_ctx *c, const AggArgs &a, const int32_t *targets,
 }
 
 template <bool IS_MIN, int LPR>
-static hipError_t long_rows_t(ink_ctx *c, const AggArgs &a, int64_t n_targets, uint64_t *chg) {
+static hipError_t long_rows_t(ink_ctx *c, const AggArgs &a_in, int64_t n_targets, uint64_t *chg) {
+  AggArgs a = a_in;
+  a.big = big_rows_of(c, kBigChunk);
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
   return run_big<IS_MIN, LPR>(c, a, chg, 1, n_targets);
 }
@@ -489,7 +480,11 @@ hipError_t agg_select_long_rows(ink_ctx *c, const AggArgs &a, int64_t n_targets,
   DISPATCH(long_rows_t, c, a, n_targets, chg);
 }
 
-hipError_t agg_select_reserve(ink_ctx *c, const AggArgs &a) { return ensure_big_buffers(c, a.wd, true); }
+hipError_t agg_select_reserve(ink_ctx *c, AggArgs &a) {
+  INK_TRY(ensure_big_buffers(c, a.wd, true));
+  a.big = big_rows_of(c, kBigChunk);
+  return hipSuccess;
+}
 int agg_select_long_degree(const AggArgs &a, int64_t n_targets) { return big_threshold(n_targets, lanes_per_row(a.wd), kBigDeg); }
 
 hipError_t agg_select_events(ink_ctx *c, const AggArgs &a, const int32_t *targets, const int32_t *seg,

@@ -108,7 +108,7 @@ __device__ __forceinline__ bool store_sum(float *A, int ld, int d, int v, bool l
 
 template <int LPR>
 __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targets, int64_t n_targets, uint64_t *chg,
-                                                  int32_t *big_list, int32_t *n_big, int compare, Counters *cnt) {
+                                                  int compare, Counters *cnt) {
   const int l = lane_id();
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
   if (deg > a.big_deg && l == 0)      // few rows: also tallied when every row is recomputed
     atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER_LONG], (unsigned long long)deg);
   if (deg > a.big_deg) {
-    if (l == 0) big_list[atomicAdd(n_big, 1)] = v;
+    if (l == 0) list_big_row(a.big, cnt, v, deg);
     return;
   }
   S4 acc;
@@ -132,18 +132,17 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
 }
 
 // Chunks of long rows of at most 48 floats: 12 lanes a row, the 4 waves of a workgroup take a quarter of a chunk each
-__global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
-                                                         const int32_t *pref, const int32_t *total_p, int chunk, float *part) {
+__global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const Counters *cnt, float *part) {
   constexpr int NW = 4, LPR = 12;
   __shared__ float sv[NW][kWave * 4];
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
-  const int total = *total_p, n_big = *n_big_p;
+  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG];
   for (int cg = blockIdx.x; cg < total; cg += gridDim.x) {
     int i, v;
     int64_t j0, j1;
-    big_chunk(pref, n_big, cg, chunk, big_list, a.in_deg, i, v, j0, j1);
+    big_chunk(a.big, n_big, cg, a.in_deg, i, v, j0, j1);
     int64_t off = a.in_off[v];
     int64_t len = j1 - j0;
     int64_t w0 = j0 + len * w / NW, w1 = j0 + len * (w + 1) / NW;
@@ -172,18 +171,17 @@ __global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const int32_
 // Inferences: that one 1.43 -> 1.22 ms, 100k nodes with 200 neighbours each and 256 columns 2.50 -> 2.27, GIN of 128
 // columns on 20k, 100k, 400k and 1M nodes 1.02, 1.0, 1.04 and 1.01 times as fast.
 template <int NW>
-__global__ __launch_bounds__(NW * kWave) void k_sum_big_slices(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
-                                                          const int32_t *pref, const int32_t *total_p, int chunk, int slices, float *part) {
+__global__ __launch_bounds__(NW * kWave) void k_sum_big_slices(AggArgs a, const Counters *cnt, int slices, float *part) {
   constexpr int LPR = kSliceLanes;
   __shared__ float sv[NW][kSliceCols];
   const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = l % LPR;
-  const int total = *total_p, n_big = *n_big_p, items = slice_items(total, slices);
+  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG], items = slice_items(total, slices);
   for (int b = blockIdx.x; b < items; b += gridDim.x) {
     int cg, slice, i, v;
     int64_t j0, j1;
     if (!slice_item(b, total, slices, cg, slice)) continue;
-    big_chunk(pref, n_big, cg, chunk, big_list, a.in_deg, i, v, j0, j1);
+    big_chunk(a.big, n_big, cg, a.in_deg, i, v, j0, j1);
     const int64_t off = a.in_off[v], len = j1 - j0;
     const int64_t w0 = j0 + len * w / NW, w1 = j0 + len * (w + 1) / NW;
     const int c0 = slice * kSliceCols;
@@ -204,21 +202,20 @@ __global__ __launch_bounds__(NW * kWave) void k_sum_big_slices(AggArgs a, const 
 }
 
 template <int LPR>
-__global__ __launch_bounds__(64) void k_sum_big_final(AggArgs a, const int32_t *big_list, const int32_t *n_big_p,
-                                                      const int32_t *pref, const float *part, uint64_t *chg,
-                                                      int compare) {
+__global__ __launch_bounds__(64) void k_sum_big_final(AggArgs a, const float *part, uint64_t *chg, int compare,
+                                                      const Counters *cnt) {
   const int l = lane_id();
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
   constexpr int G = kWave / LPR, U = 8;
   const int g = l / LPR < G ? l / LPR : G - 1, qo = lane_on ? 4 * q : 0;
-  const int n_big = *n_big_p;
+  const int n_big = cnt->v[C_NBIG];
   for (int i = blockIdx.x; i < n_big; i += gridDim.x) {
-    int v = big_list[i];
+    int v = a.big.list[i];
     S4 acc;
 #pragma unroll
     for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
-    const int p0 = pref[i], p1 = pref[i + 1];
+    const int p0 = a.big.base[i], p1 = p0 + big_row_chunks(a.in_deg[v], a.big.chunk);
     for (int pb = p0; pb < p1; pb += G * U) {       // lane groups take the chunks in turn, U of them in flight
       float4 x[U];
 #pragma unroll
@@ -419,32 +416,27 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   a.big_deg = big_threshold(n_targets, LPR, kBigDegSum);
   int compare = chg != nullptr;
   INK_TRY(ensure_big_buffers(c, a.wd, false));
-  INK_TRY(hipMemsetAsync(&c->d_cnt->v[C_NBIG], 0, sizeof(int32_t), c->stream));
+  const bool latency = latency_mode(n_targets);
+  a.big = big_rows_of(c, latency ? kBigChunk : kBigChunkSum);
+  INK_TRY(clear_big_rows(c));
   {
     KernelTimer kt(c, a.layer, INK_K_AGG_FULL);
     hipLaunchKernelGGL((k_sum_full<LPR>), dim3((unsigned)((n_targets + 3) / 4)), dim3(256), 0, c->stream, a, targets,
-                       n_targets, chg, c->big_list.as<int32_t>(), &c->d_cnt->v[C_NBIG], compare, c->d_cnt);
+                       n_targets, chg, compare, c->d_cnt);
     INK_TRY(hipGetLastError());
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
-  const int32_t *list = c->big_list.as<int32_t>();
-  int32_t *pref = c->big_pref.as<int32_t>();
-  int32_t *n_big = &c->d_cnt->v[C_NBIG], *total = &c->d_cnt->v[C_NCHUNK];
-  const bool latency = latency_mode(n_targets);
-  const int chunk = latency ? kBigChunk : kBigChunkSum, slices = big_slices(a.wd);
-  INK_TRY(plan_big_rows(c, n_targets, chunk, a.in_deg));
+  const int slices = big_slices(a.wd);
   const unsigned chunks = big_partial_grid(c, a.big_grid, latency);
+  const Counters *cnt = c->d_cnt;
+  float *part = c->big_part_v.as<float>();
   if (latency)             // few rows: 16 waves a chunk, and its slices in workgroups of their own
-    hipLaunchKernelGGL((k_sum_big_slices<16>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, list, (const int32_t *)n_big,
-                       (const int32_t *)pref, (const int32_t *)total, chunk, slices, c->big_part_v.as<float>());
+    hipLaunchKernelGGL((k_sum_big_slices<16>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, cnt, slices, part);
   else if (LPR == 12)
-    hipLaunchKernelGGL(k_sum_big_partial, dim3(chunks), dim3(256), 0, c->stream, a, list, (const int32_t *)n_big,
-                       (const int32_t *)pref, (const int32_t *)total, chunk, c->big_part_v.as<float>());
+    hipLaunchKernelGGL(k_sum_big_partial, dim3(chunks), dim3(256), 0, c->stream, a, cnt, part);
   else
-    hipLaunchKernelGGL((k_sum_big_slices<4>), dim3(sliced_grid(chunks, slices)), dim3(256), 0, c->stream, a, list, (const int32_t *)n_big,
-                       (const int32_t *)pref, (const int32_t *)total, chunk, slices, c->big_part_v.as<float>());
-  hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, list, (const int32_t *)n_big,
-                     (const int32_t *)pref, (const float *)c->big_part_v.as<float>(), chg, compare);
+    hipLaunchKernelGGL((k_sum_big_slices<4>), dim3(sliced_grid(chunks, slices)), dim3(256), 0, c->stream, a, cnt, slices, part);
+  hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)part, chg, compare, cnt);
   return hipGetLastError();
 }
 

@@ -43,8 +43,10 @@ struct EventInputs {
 // round); a lane then looks for the source of each of its events only between those two, usually a
 // few candidates, instead of searching the whole prefix array once per event.
 template <int D, int ITEMS>
-__global__ __launch_bounds__(kSortThreads) void k_make_events(EventInputs in, uint32_t *key, uint32_t *val, int32_t *hist, int nb) {
+__global__ __launch_bounds__(kSortThreads) void k_make_events(EventInputs in, uint32_t *key, uint32_t *val, int32_t *hist, int nb, Counters *cnt) {
   __shared__ int h[1 << D];
+  if (blockIdx.x == 0)                 // the layer's counters start here
+    for (int i = threadIdx.x; i < (int)(sizeof(Counters) / sizeof(int32_t)); i += kSortThreads) ((int32_t *)cnt)[i] = 0;
   tile_hist_clear<D>(h);
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int64_t n = (int64_t)in.n_del + in.n_chg + in.n_ins;
@@ -82,16 +84,24 @@ __global__ __launch_bounds__(kSortThreads) void k_make_events(EventInputs in, ui
   tile_hist_store<D>(h, hist, nb);
 }
 
-static void make_events(const SortPlan &p, const EventInputs &in, uint32_t *key, uint32_t *val, int32_t *hist, hipStream_t s) {
-#define INK_MAKE(D, I) hipLaunchKernelGGL((k_make_events<D, I>), dim3(p.tiles), dim3(kSortThreads), 0, s, in, key, val, hist, p.tiles)
+static void make_events(const SortPlan &p, const EventInputs &in, uint32_t *key, uint32_t *val, int32_t *hist, Counters *cnt, hipStream_t s) {
+#define INK_MAKE(D, I) hipLaunchKernelGGL((k_make_events<D, I>), dim3(p.tiles), dim3(kSortThreads), 0, s, in, key, val, hist, p.tiles, cnt)
   if (p.digit_bits == 8) { if (p.items == 4) INK_MAKE(8, 4); else INK_MAKE(8, 12); }
   else if (p.digit_bits == 9) { if (p.items == 4) INK_MAKE(9, 4); else INK_MAKE(9, 12); }
   else { if (p.items == 4) INK_MAKE(11, 4); else INK_MAKE(11, 12); }
 #undef INK_MAKE
 }
 
-__global__ __launch_bounds__(64) void k_publish(const Counters *d, HostCounters *h, uint32_t *h_seq, uint32_t seq) {
-  publish_wave(d, h, h_seq, seq);
+// The record; on the way the marks of a batch that ends with it are cleared: zero_at[0 .. n_zero) of `zero`.
+constexpr int kPublishThreads = 512;
+__global__ __launch_bounds__(kPublishThreads) void k_publish(const Counters *d, HostCounters *h, uint32_t *h_seq, uint32_t seq,
+                                                             const int32_t *zero_at, int n_zero, int32_t *zero) {
+  if (n_zero > 0) {                     // nothing is written after the record
+    for (int i = threadIdx.x; i < n_zero; i += kPublishThreads) zero[zero_at[i]] = 0;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+  if (threadIdx.x < kWave) publish_wave(d, h, h_seq, seq);
 }
 
 // A layer with few events (at most THREADS * ITEMS): clearing the counters, creating the events,
@@ -196,13 +206,14 @@ __global__ __launch_bounds__(THREADS) void k_small_collect(const int32_t *t_list
 // rows whose flag is set -> their positions (idx) and ids (f_list), the count, and, with
 // want_events, the exclusive prefix of their kept out-degrees and its total.
 template <int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_small_emit(const uint8_t *flag, const int32_t *rows, int nC, int32_t *idx,
+__global__ __launch_bounds__(THREADS) void k_small_emit(const uint8_t *flag, const int32_t *rows, int nC, const int32_t *nC_dev, int32_t *idx,
                                                         int32_t *f_list, int want_events, const int32_t *deg,
                                                         const int32_t *new_out, int32_t *f_pref, Counters *cnt,
                                                         HostCounters *h, uint32_t *h_seq, uint32_t seq) {
   __shared__ int s_f[THREADS * ITEMS];
   __shared__ int sm[THREADS / kWave + 1];
   const int t0 = threadIdx.x * ITEMS;
+  if (nC_dev) nC = min(nC, *nC_dev);
   int f[ITEMS], c = 0;
 #pragma unroll
   for (int k = 0; k < ITEMS; k++) {
@@ -244,9 +255,9 @@ __global__ __launch_bounds__(THREADS) void k_small_emit(const uint8_t *flag, con
   if (threadIdx.x < kWave) publish_wave(cnt, h, h_seq, seq);
 }
 
-__global__ void k_mark_nodes(const int32_t *list, int n, uint64_t *bm) {
+__global__ void k_mark_nodes(const int32_t *list, int n, const int32_t *list2, int n2, uint64_t *bm) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) { int v = list[i]; atomicOr((unsigned long long *)&bm[v >> 6], 1ull << (v & 63)); }
+  if (i < n + n2) { int v = i < n ? list[i] : list2[i - n]; atomicOr((unsigned long long *)&bm[v >> 6], 1ull << (v & 63)); }
 }
 
 // The changed rows of a long layer: their positions, their ids and the prefix of the events they propagate, in one scan
@@ -256,8 +267,9 @@ __global__ void k_mark_nodes(const int32_t *list, int n, uint64_t *bm) {
 struct EmitRows {
   const uint8_t *flag; const int32_t *rows;      // flags are read 8 at a time: room for 7 past n
   const int32_t *deg, *new_out;                  // deg null: no events wanted
-  int64_t n;
+  int64_t bound; const int32_t *n_dev;           // rows: bound, or fewer as *n_dev says
   __device__ __forceinline__ unsigned long long flags8(int64_t base) const {
+    const int64_t n = n_dev && *n_dev < bound ? *n_dev : bound;
     if (base >= n) return 0;
     const unsigned long long f = *reinterpret_cast<const unsigned long long *>(flag + base);
     return n - base >= 8 ? f : f & ((1ull << (8 * (n - base))) - 1);
@@ -305,7 +317,7 @@ __global__ __launch_bounds__(kEmitThreads) void k_emit_count(EmitRows e, unsigne
 }
 
 __global__ __launch_bounds__(kEmitThreads) void k_emit_write(EmitRows e, const unsigned long long *tile, int32_t *idx, int32_t *ids,
-                                                             int32_t *pref, int32_t *n_rows, int32_t *n_events) {
+                                                             int32_t *pref, Counters *cnt, HostCounters *h, uint32_t *h_seq, uint32_t seq) {
   __shared__ unsigned long long sm[kEmitThreads / kWave];
   unsigned long long part = 0, before, tot;
   for (int i = threadIdx.x; i < (int)blockIdx.x; i += kEmitThreads) part += tile[i];
@@ -322,10 +334,14 @@ __global__ __launch_bounds__(kEmitThreads) void k_emit_write(EmitRows e, const u
     if (e.deg) pref[p] = (int32_t)(uint32_t)at;
     at += v[k];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    *n_rows = (int32_t)((before + tot) >> 32);
-    if (e.deg) *n_events = (int32_t)(uint32_t)(before + tot);
+  if (blockIdx.x != gridDim.x - 1) return;
+  if (threadIdx.x == 0) {
+    cnt->v[C_NEXT] = (int32_t)((before + tot) >> 32);
+    if (e.deg) cnt->v[C_NEV] = (int32_t)(uint32_t)(before + tot);
+    __threadfence();
   }
+  __syncthreads();
+  if (threadIdx.x < kWave) publish_wave(cnt, h, h_seq, seq);      // the counts are all the host waits for; the lists are for kernels behind this one
 }
 
 __global__ void k_gather_i32(const int32_t *table, const int32_t *idx, int n, const int32_t *n_dev, int32_t *out) {
@@ -556,9 +572,12 @@ static void prof_collect(ink_ctx *c) {
   c->ev_pending.clear();
 }
 
-hipError_t ink::read_counters(ink_ctx *c) {
+hipError_t ink::read_counters(ink_ctx *c, bool end_batch) {
   const uint32_t seq = ++c->pub_seq;
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, c->stream, (const Counters *)c->d_cnt, c->h_cnt, c->h_seq, seq);
+  const int n_zero = end_batch ? (int)c->n_touched_src : 0;
+  if (end_batch) c->n_touched_src = 0;
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(n_zero > 0 ? kPublishThreads : kWave), 0, c->stream, (const Counters *)c->d_cnt, c->h_cnt, c->h_seq, seq,
+                     (const int32_t *)c->b_uniq.as<int32_t>(), n_zero, c->new_out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return wait_published(c, c->h_seq, seq);
@@ -1091,12 +1110,12 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
   bool dense = nE > 0 && (double)nE > dense_line(c, nE, a.d, c->n_edges_now, n_seed > 0);
   S.dense = dense;
   const bool small = !dense && nE > 0 && nE <= kSmallLayer;
-  if (!small) API_TRY(hipMemsetAsync(dc, 0, sizeof(Counters), s));
+  if (dense || nE == 0) API_TRY(hipMemsetAsync(dc, 0, sizeof(Counters), s));      // otherwise the kernel that makes the events does
   if (dense) {
     // so many events that re-aggregating every node costs less than grouping them (Sec. 5.1)
     Prof p(c, INK_T_AGG);
     if (c->is_select) {      // rows without neighbours are empty already, but for those that lost theirs: their bits are set beforehand
-      if (n_del > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n_del), dim3(256), 0, s, (const int32_t *)c->del_dst, (int)n_del, bm);
+      if (n_del > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n_del), dim3(256), 0, s, (const int32_t *)c->del_dst, (int)n_del, (const int32_t *)nullptr, 0, bm);
       a.keep_empty = true;
     }
     API_TRY(agg_full_any(c, a, bm));
@@ -1133,7 +1152,7 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
       Prof p(c, INK_T_EVENTS);
       make_events(sp, EventInputs{c->del_src, c->del_dst, c->ins_src, c->ins_dst, (int)n_del, (int)n_ins, F, (int)nF,
                                   c->f_pref.as<int32_t>(), (int)n_chg, c->gout.off, c->gout.ids, c->is_select ? 0 : 1},
-                  key, val, c->ws.hist.as<int32_t>(), s);
+                  key, val, c->ws.hist.as<int32_t>(), dc, s);
       API_TRY(hipGetLastError());
     }
     Prof p(c, INK_T_GROUP);
@@ -1157,7 +1176,7 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
       nT = c->h_cnt->v[C_NT];
     }
     API_TRY(agg_full_any(c, a, bm, c->t_list.as<int32_t>(), nT));
-    if (nT > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(nT), dim3(256), 0, s, (const int32_t *)c->t_list.as<int32_t>(), (int)nT, bm);
+    if (nT > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(nT), dim3(256), 0, s, (const int32_t *)c->t_list.as<int32_t>(), (int)nT, (const int32_t *)nullptr, 0, bm);
     API_TRY(hipGetLastError());
     return INK_OK;
   }
@@ -1171,7 +1190,7 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
     for (int b = 0; b < agg_blocks(a); b++) {
       AggArgs ab = agg_block(a, b);
       int c0 = b * kAggBlock;
-      if (b > 0) API_TRY(hipMemsetAsync(&dc->v[C_NBIG], 0, 4 * sizeof(int32_t), s));   // lists of long rows, exposed rows and long segments
+      if (b > 0) API_TRY(hipMemsetAsync(&dc->v[C_NEXP], 0, 5 * sizeof(int32_t), s));   // lists of long rows, exposed rows and long segments
       if (c->is_select)
         API_TRY(agg_select_events(c, ab, c->t_list.as<int32_t>(), c->t_seg.as<int32_t>(), nT, &dc->v[C_NT],
                                   c->ev_val.as<uint32_t>(), eb, bm));
@@ -1235,8 +1254,7 @@ static ink_status collect_rows(ink_ctx *c, const int32_t *extra0, int64_t n0, co
     API_TRY(hipGetLastError());
     if (flags_cleared) *flags_cleared = true;
   } else {
-    if (n0 > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n0), dim3(256), 0, s, extra0, (int)n0, c->bm_a);
-    if (n1 > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n1), dim3(256), 0, s, extra1, (int)n1, c->bm_a);
+    if (n0 + n1 > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n0 + n1), dim3(256), 0, s, extra0, (int)n0, extra1, (int)n1, c->bm_a);
     API_TRY(bitmap_to_list(c->ws, c->bm_a, c->n, c->c_list.as<int32_t>(), &c->d_cnt->v[C_NC], 1, s));
   }
   if (bound >= 0) { *nC = bound; return INK_OK; }
@@ -1252,7 +1270,7 @@ static ink_status collect_rows(ink_ctx *c, const int32_t *extra0, int64_t n0, co
 // are gathered into res_emb and the batch's marks are cleared before that round trip, so nothing
 // is left to launch after it; *result_done says whether that happened.
 constexpr size_t kEagerResultBytes = (size_t)64 << 20;
-static ink_status emit_changed(ink_ctx *c, int64_t nC, int nxt, bool keep_old, int ld, bool want_events,
+static ink_status emit_changed(ink_ctx *c, int64_t nC, const int32_t *nC_dev, int nxt, bool keep_old, int ld, bool want_events,
                                int64_t *nF2, int64_t *n_chg, const Table *result = nullptr,
                                bool *result_done = nullptr) {
   hipStream_t s = c->stream;
@@ -1261,16 +1279,14 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, int nxt, bool keep_old, i
   *nF2 = 0; *n_chg = 0;
   API_TRY(c->f_list[nxt].reserve((size_t)nC * 4));
   const bool small = nC <= kSmallLayer;
-  uint32_t published = 0;
+  const uint32_t seq = ++c->pub_seq;         // the kernel that finds the counts publishes them itself
   if (small) {
     if (want_events) API_TRY(c->f_pref.reserve((size_t)(nC + 1) * 4));
 #define INK_SMALL_EMIT(T, I)                                                                                       \
   hipLaunchKernelGGL((k_small_emit<T, I>), dim3(1), dim3(T), 0, s, (const uint8_t *)c->c_flag.as<uint8_t>(),        \
-                     (const int32_t *)c->c_list.as<int32_t>(), (int)nC, c->c_idx.as<int32_t>(),                    \
+                     (const int32_t *)c->c_list.as<int32_t>(), (int)nC, nC_dev, c->c_idx.as<int32_t>(),            \
                      c->f_list[nxt].as<int32_t>(), want_events ? 1 : 0, (const int32_t *)c->gout.deg,              \
                      (const int32_t *)c->new_out, c->f_pref.as<int32_t>(), dc, c->h_cnt, c->h_seq, seq)
-    const uint32_t seq = ++c->pub_seq;       // the kernel publishes the counters itself
-    published = seq;
     if (nC <= 256) INK_SMALL_EMIT(256, 1);
     else if (nC <= 1024) INK_SMALL_EMIT(256, 4);
     else INK_SMALL_EMIT(1024, 4);
@@ -1280,10 +1296,10 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, int nxt, bool keep_old, i
     const int tiles = nblocks(nC, kEmitTile);
     API_TRY(c->ws.blk.reserve((size_t)tiles * sizeof(unsigned long long)));
     unsigned long long *tile = c->ws.blk.as<unsigned long long>();
-    const EmitRows e{c->c_flag.as<uint8_t>(), c->c_list.as<int32_t>(), want_events ? c->gout.deg : nullptr, c->new_out, nC};
+    const EmitRows e{c->c_flag.as<uint8_t>(), c->c_list.as<int32_t>(), want_events ? c->gout.deg : nullptr, c->new_out, nC, nC_dev};
     hipLaunchKernelGGL(k_emit_count, dim3(tiles), dim3(kEmitThreads), 0, s, e, tile);
     hipLaunchKernelGGL(k_emit_write, dim3(tiles), dim3(kEmitThreads), 0, s, e, (const unsigned long long *)tile,
-                       c->c_idx.as<int32_t>(), c->f_list[nxt].as<int32_t>(), c->f_pref.as<int32_t>(), &dc->v[C_NEXT], &dc->v[C_NEV]);
+                       c->c_idx.as<int32_t>(), c->f_list[nxt].as<int32_t>(), c->f_pref.as<int32_t>(), dc, c->h_cnt, c->h_seq, seq);
   }
   if (keep_old) {
     API_TRY(c->f_old[nxt].reserve((size_t)nC * ld * 4));
@@ -1295,14 +1311,13 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, int nxt, bool keep_old, i
     API_TRY(c->res_emb.reserve((size_t)nC * result->d * 4));
     gather_rows(s, (const float *)result->f(), result->ld, result->d, (const int32_t *)c->f_list[nxt].as<int32_t>(), nC,
                 c->res_emb.as<float>(), &dc->v[C_NEXT]);
-    API_TRY(graph_end_batch(c));
     *result_done = true;
   }
   API_TRY(hipGetLastError());
   // with the result gathered, one record after it ends the call: no synchronisation of the stream on top
   c->drained = result_done && *result_done;
-  if (small && !c->drained) API_TRY(wait_published(c, c->h_seq, published));
-  else API_TRY(read_counters(c));
+  if (c->drained) API_TRY(read_counters(c, true));
+  else API_TRY(wait_published(c, c->h_seq, seq));
   *nF2 = c->h_cnt->v[C_NEXT];
   if (want_events) *n_chg = (uint32_t)c->h_cnt->v[C_NEV];
   return INK_OK;
@@ -1374,7 +1389,6 @@ static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cu
         const int32_t *rows = c->c_list.as<int32_t>();
         float *old_rows = want_old ? c->c_old.as<float>() : nullptr;
         if (!gcn) {
-          if (lazy && !flags_cleared) API_TRY(hipMemsetAsync(c->c_flag.p, 0, (size_t)nC, s));   // flags past the count stay 0
           API_TRY(run_transform(c, l, rows, nC, c->c_flag.as<uint8_t>(), old_rows, nC_dev));
         } else {
           if (!flags_cleared) API_TRY(hipMemsetAsync(c->c_flag.p, 0, (size_t)nC, s));
@@ -1384,7 +1398,7 @@ static ink_status propagate_layers(ink_ctx *c, int64_t nF, int64_t n_chg, int cu
         // the baseline propagates from every node of the affected area, changed or not
         if (c->affected_mode && !last) API_TRY(hipMemsetAsync(c->c_flag.p, 1, (size_t)nC, s));
       }
-      st = emit_changed(c, nC, nxt, want_old, ld_next, !last, &nF2, &n_chg2, last ? &c->H[l] : nullptr, &result_done);
+      st = emit_changed(c, nC, nC_dev, nxt, want_old, ld_next, !last, &nF2, &n_chg2, last ? &c->H[l] : nullptr, &result_done);
       if (st != INK_OK) return st;
     } else if (lazy) {
       API_TRY(read_counters(c));
@@ -1436,7 +1450,7 @@ static hipError_t layer_one_launch(ink_ctx *c, int l) {
   p.F = c->f_list[(l - 1) & 1].as<int32_t>(); p.F_next = c->f_list[l & 1].as<int32_t>(); p.pref = c->f_pref.as<int32_t>();
   p.out_off = c->gout.off; p.out_ids = c->gout.ids; p.out_deg = c->gout.deg; p.new_out = c->new_out;
   p.touched_src = c->b_uniq.as<int32_t>();
-  p.t_list = c->t_list.as<int32_t>(); p.big_list = c->big_list.as<int32_t>(); p.bm = c->bm_a;
+  p.t_list = c->t_list.as<int32_t>(); p.bm = c->bm_a;
   p.Hp = c->H[l - 1].f(); p.ldh = c->H[l - 1].ld; p.d_in = L.in_dim;
   p.W = L.W1; p.Kp = L.K1p; p.Np = L.N1p; p.bias = L.b1; p.n_out = L.out_dim; p.relu = L.act == INK_ACT_RELU;
   p.user = c->USER[l].f(); p.ld_user = c->USER[l].ld;
@@ -1571,7 +1585,7 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
                        (const float *)c->XW[1].f(), c->Msc[1].f(), ld, c->Msc[1].d, c->c_old.as<float>(),
                        c->c_flag.as<uint8_t>());
     API_TRY(hipGetLastError());
-    ink_status st = emit_changed(c, nD, cur, true, ld, true, &nF, &n_chg);
+    ink_status st = emit_changed(c, nD, nullptr, cur, true, ld, true, &nF, &n_chg);
     if (st != INK_OK) return st;
   }
   int first = 1;
@@ -1678,7 +1692,7 @@ static ink_status update_features_impl(ink_ctx *c, const int32_t *node_ids, cons
                        c->Msc[1].d, c->c_old.as<float>(), c->c_flag.as<uint8_t>());
     API_TRY(hipGetLastError());
   }
-  ink_status st = emit_changed(c, n, cur, keep_old, ld_msg, true, &nF, &n_chg);
+  ink_status st = emit_changed(c, n, nullptr, cur, keep_old, ld_msg, true, &nF, &n_chg);
   if (st != INK_OK) return st;
   st = propagate_layers(c, nF, n_chg, cur, 0, 0, nullptr, 0, out);
   if (st != INK_OK) return st;

@@ -1,8 +1,8 @@
 // Work list for rows with more than kBigDeg in-neighbours: each such row is cut into chunks of
 // kBigChunk neighbours (kBigChunkSum for long launches of sums), one workgroup per chunk, then one wave per row combines its chunks in
-// order.  The plan (chunk prefix over the listed rows) is built on the device from the device-side
-// row count, and the chunk / row kernels run a fixed grid that strides over it, so no host
-// round trip is needed; with no long rows they return at once.
+// order.  A row takes its chunks when it is listed, so the plan stands when the list does (a scan of the list for it was one or
+// two launches more), and the chunk / row kernels run a fixed grid that strides over it, so no host round trip is
+// needed; with no long rows they return at once.
 #pragma once
 #include "ctx.h"
 
@@ -54,37 +54,31 @@ inline int big_threshold(int64_t n_targets, int lanes_per_row, int throughput_de
   return latency_mode(n_targets) ? 32 * (kWave / lanes_per_row) : throughput_deg;
 }
 
-// plan: pref[i] = chunks of the listed rows before i (i <= n_big), *total = all chunks
-struct BigChunkCount {
-  const int32_t *list; const int32_t *n_big; const int32_t *deg; int chunk;
-  __device__ int operator()(int64_t i) const { return i < *n_big ? (int)((unsigned)(deg[list[i]] + chunk - 1) / (unsigned)chunk) : 0; }
-};
-struct BigPrefStore {
-  int32_t *pref; const int32_t *n_big;
-  __device__ void operator()(int64_t i, int v, int ex) const {
-    int n = *n_big;
-    if (i < n) pref[i] = ex;
-    if (i == n - 1) pref[n] = ex + v;
-  }
-};
-// n_rows_max bounds the device-side row count
-inline hipError_t plan_big_rows(ink_ctx *c, int64_t n_rows_max, int chunk, const int32_t *in_deg) {
-  int64_t cap = (int64_t)(c->big_list.cap / 4);
-  if (n_rows_max > cap) n_rows_max = cap;
-  const int32_t *n_big = &c->d_cnt->v[C_NBIG];
-  return tile_scan<BigChunkCount, BigPrefStore, kScanItems, true>(
-      c->ws, BigChunkCount{c->big_list.as<int32_t>(), n_big, in_deg, chunk}, BigPrefStore{c->big_pref.as<int32_t>(), n_big},
-      n_rows_max, &c->d_cnt->v[C_NCHUNK], c->stream);
+inline BigRows big_rows_of(ink_ctx *c, int chunk) { return BigRows{c->big_list.as<int32_t>(), c->big_pref.as<int32_t>(), chunk}; }
+inline hipError_t clear_big_rows(ink_ctx *c) { return hipMemsetAsync(&c->d_cnt->v[C_NCHUNK], 0, 2 * sizeof(int32_t), c->stream); }
+
+__device__ __forceinline__ int big_row_chunks(int deg, int chunk) { return (int)((unsigned)(deg + chunk - 1) / (unsigned)chunk); }
+// places for `rows` rows of `chunks` chunks together: the first of each
+__device__ __forceinline__ void reserve_big(Counters *cnt, int rows, int chunks, int &i, int &base) {
+  const unsigned long long t = atomicAdd((unsigned long long *)&cnt->v[C_NCHUNK], ((unsigned long long)rows << 32) + (unsigned)chunks);
+  i = (int)(t >> 32);
+  base = (int)(uint32_t)t;
+}
+// lists row v (one lane)
+__device__ __forceinline__ void list_big_row(const BigRows &b, Counters *cnt, int v, int deg) {
+  int i, base;
+  reserve_big(cnt, 1, big_row_chunks(deg, b.chunk), i, base);
+  b.list[i] = v;
+  b.base[i] = base;
 }
 
 // row (index in the list), node id and neighbour range of global chunk cg
-__device__ __forceinline__ void big_chunk(const int32_t *pref, int n_big, int cg, int chunk, const int32_t *list,
-                                          const int32_t *in_deg, int &i, int &v, int64_t &j0, int64_t &j1) {
-  i = wave_last_le(pref, n_big, cg);      // called by whole waves with wave-uniform arguments
-  v = list[i];
+__device__ __forceinline__ void big_chunk(const BigRows &b, int n_big, int cg, const int32_t *in_deg, int &i, int &v, int64_t &j0, int64_t &j1) {
+  i = wave_last_le(b.base, n_big, cg);      // called by whole waves with wave-uniform arguments
+  v = b.list[i];
   int64_t deg = in_deg[v];
-  j0 = (int64_t)(cg - pref[i]) * chunk;
-  j1 = j0 + chunk < deg ? j0 + chunk : deg;
+  j0 = (int64_t)(cg - b.base[i]) * b.chunk;
+  j1 = j0 + b.chunk < deg ? j0 + b.chunk : deg;
 }
 
 // Slices: the columns of a chunk are shared out in groups of kSliceCols, one 128-byte line of every row.  Workgroups go

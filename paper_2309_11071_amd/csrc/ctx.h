@@ -115,7 +115,7 @@ struct HostCounters {
 // The graph stage of short batches has a block of its own (ink_ctx::d_gcnt): next to the slots above it holds
 // the pool space each side needs (stripe 0, words 0 and 1), the effective ops as the out side sees them, the effective ops
 // of the in side whether or not the apply kernel may run (C_GINS, C_GDEL) and whether it may (C_OK).
-enum { C_ERR = 0, C_NEV = 1, C_NT, C_NBIG, C_NEXP, C_NEVL, C_NEVCH, C_NC, C_NEXT, C_NCHUNK, C_NOPS, C_TMP0, C_TMP1,
+enum { C_ERR = 0, C_NEV = 1, C_NT, C_NEXP, C_NCHUNK, C_NBIG, C_NEVL, C_NEVCH, C_NC, C_NEXT, C_NOPS, C_TMP0, C_TMP1,
        C_TMP2, C_TMP3, C_OT, C_OCH, C_TOP64 = 18, C_TOP64B = 20,
        C_OINS = 22, C_ODEL, C_GINS, C_GDEL, C_OK, C_ONE = 31 };
 
@@ -258,12 +258,16 @@ ink_status graph_apply_batch(ink_ctx *c, const void *raw, int64_t n, int64_t *n_
                              hipError_t (*queued)(ink_ctx *) = nullptr);
 hipError_t graph_reserve(ink_ctx *c, int64_t max_batch);   // batch buffers for that many entries
 ink_status graph_add_nodes(ink_ctx *c, int64_t n_new);   // empty edge blocks for nodes n .. n + n_new - 1 (before n grows)
-hipError_t read_counters(ink_ctx *c);        // device counters -> c->h_cnt, waits for them
+hipError_t read_counters(ink_ctx *c, bool end_batch = false);   // device counters -> c->h_cnt, waits for them; with end_batch as graph_end_batch on the way
 hipError_t wait_published(ink_ctx *c, const uint32_t *h_seq, uint32_t seq);   // until that record has arrived
 hipError_t graph_end_batch(ink_ctx *c);     // clears per-batch marks (new_out)
 hipError_t graph_export(ink_ctx *c, int64_t *rowptr_h, int32_t *col_h);
 
 // ---- aggregation (agg.hip)
+// Rows that are re-gathered in chunks (bigrows.h): node and first chunk of each, in ascending order of both; the counters
+// C_NCHUNK and C_NBIG are one 64-bit word, so that one atomic takes a row's place and its chunks'.
+struct BigRows { int32_t *list, *base; int chunk; };
+static_assert(C_NCHUNK % 2 == 0 && C_NBIG == C_NCHUNK + 1, "chunks in the lower half, rows in the upper");
 struct AggArgs {
   int n;
   const int64_t *in_off; const int32_t *in_deg; const int32_t *in_ids;
@@ -278,6 +282,7 @@ struct AggArgs {
   bool is_min;
   bool nonneg;                      // no message has its sign bit set (the layer before ends in ReLU, which gives +0 for every other value)
   int big_deg;                      // rows with more in-neighbours go to the chunked cooperative path
+  BigRows big;                      // its list
   int64_t big_grid;                 // workgroups to launch for the chunk kernel (it strides if there are more chunks)
   int layer;                        // 1-based layer the launch belongs to (per-kernel timing)
   int count_cond;                   // tally the per-target condition counters (only the first 256-column block of a wide row does)
@@ -293,7 +298,7 @@ hipError_t agg_select_events(ink_ctx *c, const AggArgs &a, const int32_t *target
                              uint64_t *chg);
 // the long exposed rows that the event stage of a layer listed (at most n_targets), as agg_select_events ends
 hipError_t agg_select_long_rows(ink_ctx *c, const AggArgs &a, int64_t n_targets, uint64_t *chg);
-hipError_t agg_select_reserve(ink_ctx *c, const AggArgs &a);      // its buffers, before the list is filled
+hipError_t agg_select_reserve(ink_ctx *c, AggArgs &a);      // its buffers, before the list is filled (and the list's place in a)
 int agg_select_long_degree(const AggArgs &a, int64_t n_targets);   // rows with more neighbours are listed
 // sum-type aggregators (agg_sum.hip): A holds the plain sum of message rows.  F (ascending ids)
 // and f_old (their previous message rows, row stride ld_old) describe the changed sources.
@@ -340,7 +345,7 @@ struct OneLayer {
   const int32_t *del_s, *del_d, *ins_s, *ins_d;    // applied edge changes
   const int32_t *F; int32_t *F_next, *pref;        // changed sources of this layer and of the next; prefix of their kept out-edges
   const int64_t *out_off; const int32_t *out_ids, *out_deg; int32_t *new_out; const int32_t *touched_src;
-  int32_t *t_list, *big_list; uint64_t *bm;
+  int32_t *t_list; uint64_t *bm;
   const float *Hp; int ldh; int d_in;              // SAGE transform
   const float *W; int Kp, Np; const float *bias; int n_out, relu;
   const float *user; int ld_user;

@@ -286,7 +286,7 @@ __global__ __launch_bounds__(kOneThreads) void k_layer_one(OneLayer p) {
         Cached<IS_MIN> c;
         EvAcc<IS_MIN> s;
         reduce_events<IS_MIN, LPR>(p.a, v, S.sv, e0, e1, lane_on, q, c, s);
-        finish_target<IS_MIN, LPR, true>(p.a, v, c, s, lane_on, q, p.bm, p.big_list, nullptr, exp, cnt);
+        finish_target<IS_MIN, LPR, true>(p.a, v, c, s, lane_on, q, p.bm, nullptr, exp, cnt);
       }
     }
     __threadfence_block();
@@ -294,10 +294,10 @@ __global__ __launch_bounds__(kOneThreads) void k_layer_one(OneLayer p) {
     // long exposed rows
     const int n_big = __hip_atomic_load(&cnt->v[C_NBIG], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int64_t nb = 0;
-    for (int i = 0; i < n_big; i++) nb += p.a.in_deg[p.big_list[i]];
+    for (int i = 0; i < n_big; i++) nb += p.a.in_deg[p.a.big.list[i]];
     status = nb * p.a.wd <= kOneGather ? kOneDone : kOneEventsDone;
     if (status == kOneDone) {
-      for (int i = 0; i < n_big; i++) recompute_long_row<IS_MIN, LPR>(S, p.a, p.big_list[i], p.bm, cnt);
+      for (int i = 0; i < n_big; i++) recompute_long_row<IS_MIN, LPR>(S, p.a, p.a.big.list[i], p.bm, cnt);
       __threadfence_block();
       __syncthreads();
       // rows to transform: targets whose aggregate changed, sources (their own message changed)

@@ -6,6 +6,7 @@
 // rows without an event takes a byte per target from every event, 60 us per 10M, and saves another 0.3 % of the edges.  Where
 // every row is gathered the blocks change nothing (inference of 625k nodes 4.23 against 4.22 ms).
 #pragma once
+#include "bigrows.h"
 #include "rowload.h"
 
 namespace ink {
@@ -16,8 +17,8 @@ struct RowBlock {
   int v, deg, asc, off_lo, off_hi;         // lane j: row j of the block
   uint64_t todo;                           // wave-uniform: rows of the block that are gathered by this wave
   // rows [r0, r0 + k) of the launch; those with more than big_deg neighbours go to the list (one place per block)
-  __device__ __forceinline__ void load(const AggArgs &a, const int32_t *targets, int64_t r0, int k, const uint64_t *set, int32_t *big_list,
-                                       int32_t *n_big, int64_t &nb, int64_t &nb_long) {
+  __device__ __forceinline__ void load(const AggArgs &a, const int32_t *targets, int64_t r0, int k, const uint64_t *set, Counters *cnt,
+                                       int64_t &nb, int64_t &nb_long) {
     const int l = lane_id();
     const int j = l < k ? l : k - 1;
     v = targets ? targets[r0 + j] : (int)(r0 + j);
@@ -31,10 +32,15 @@ struct RowBlock {
     const uint64_t bigs = __ballot(big);
     todo = __ballot(on) & ~bigs;
     if (bigs) {
-      int base = 0;
-      if (l == 0) base = atomicAdd(n_big, __popcll(bigs));
-      base = __builtin_amdgcn_readfirstlane(base);
-      if (big) big_list[base + __popcll(bigs & ((1ull << l) - 1))] = v;
+      const int mine = big ? big_row_chunks(deg, a.big.chunk) : 0;
+      int upto = mine;                     // chunks of the block's rows up to this one
+#pragma unroll
+      for (int o = 1; o < kRowBlock; o <<= 1) { const int y = __shfl_up(upto, o, kWave); if (l >= o) upto += y; }
+      int i = 0, base = 0;
+      if (l == kRowBlock - 1) reserve_big(cnt, __popcll(bigs), upto, i, base);
+      i = __builtin_amdgcn_readlane(i, kRowBlock - 1) + __popcll(bigs & ((1ull << l) - 1));
+      base = __builtin_amdgcn_readlane(base, kRowBlock - 1) + upto - mine;
+      if (big) { a.big.list[i] = v; a.big.base[i] = base; }
     }
   }
   __device__ __forceinline__ int row(int j) const { return __builtin_amdgcn_readlane(v, j); }

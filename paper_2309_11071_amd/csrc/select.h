@@ -478,7 +478,7 @@ struct RowSink {
 // results), the recompute of an exposed row of moderate length, and the store.
 template <bool IS_MIN, int LPR, bool INLINE>
 __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cached<IS_MIN> &k, EvAcc<IS_MIN> &s,
-                                              bool lane_on, int q, uint64_t *chg, int32_t *big_list, int32_t *exp_list,
+                                              bool lane_on, int q, uint64_t *chg, int32_t *exp_list,
                                               RowSink &exp, Counters *cnt) {
   const int l = lane_id();
   const F4 &ov = k.ov; const I4 &oi = k.oi; const F4 &ou = k.ou; const I4 &o2 = k.o2;
@@ -572,7 +572,7 @@ __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cac
     // recomputed by the kernels that follow: long rows chunk by chunk, the others one wave per row
     if (l == 0) {
       if (deg > a.big_deg) {
-        big_list[atomicAdd(&cnt->v[C_NBIG], 1)] = v;
+        list_big_row(a.big, cnt, v, deg);
         atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_REGATHER_LONG], (unsigned long long)deg);
       }
     }
