@@ -114,6 +114,8 @@ def load_library():
     lib.ink_apply_user_events.restype = C.c_int
     lib.ink_add_nodes.argtypes = [vp, vp, C.c_int64, C.POINTER(_Result)]
     lib.ink_add_nodes.restype = C.c_int
+    lib.ink_copy_result.argtypes = [vp, vp, vp, C.c_int64]
+    lib.ink_copy_result.restype = C.c_int
     lib.ink_get_layer.argtypes = [vp, C.c_int32, C.c_int32, C.c_int64, C.c_int64, vp, C.c_int32,
                                   C.POINTER(C.c_int32)]
     lib.ink_get_layer.restype = C.c_int
@@ -190,6 +192,12 @@ class Ink:
         if st != 0:
             raise InkError(st, self._lib.ink_last_error(self._h).decode())
 
+    def _fetch(self, n):
+        """The last result on the host: ids and embeddings."""
+        ids, emb = np.empty(n, np.int32), np.empty((n, self.out_dim), np.float32)
+        self._check(self._lib.ink_copy_result(self._h, ids.ctypes.data, emb.ctypes.data, n))
+        return ids, emb
+
     def full_infer(self):
         self._check(self._lib.ink_full_infer(self._h))
 
@@ -207,12 +215,7 @@ class Ink:
         out = dict(n_changed=r.n_changed, n_applied_ins=r.n_applied_ins, n_applied_del=r.n_applied_del,
                    n_noop=r.n_noop, changed_ids_ptr=r.changed_ids, embeddings_ptr=r.embeddings)
         if fetch:
-            ids = np.empty(r.n_changed, np.int32)
-            emb = np.empty((r.n_changed, self.out_dim), np.float32)
-            if r.n_changed:
-                _dtoh(ids, r.changed_ids)
-                _dtoh(emb, r.embeddings)
-            out["changed_ids"], out["embeddings"] = ids, emb
+            out["changed_ids"], out["embeddings"] = self._fetch(r.n_changed)
         return out
 
     def apply_updates_device(self, dev_ptr, n, affected=False):
@@ -240,12 +243,7 @@ class Ink:
         out = dict(n_changed=r.n_changed, n_applied_ins=r.n_applied_ins, n_applied_del=r.n_applied_del,
                    n_noop=r.n_noop, changed_ids_ptr=r.changed_ids, embeddings_ptr=r.embeddings)
         if fetch:
-            ids = np.empty(r.n_changed, np.int32)
-            emb = np.empty((r.n_changed, self.out_dim), np.float32)
-            if r.n_changed:
-                _dtoh(ids, r.changed_ids)
-                _dtoh(emb, r.embeddings)
-            out["changed_ids"], out["embeddings"] = ids, emb
+            out["changed_ids"], out["embeddings"] = self._fetch(r.n_changed)
         return out
 
     def apply_user_events(self, events, rows, fetch=True):
@@ -265,12 +263,7 @@ class Ink:
         out = dict(n_changed=r.n_changed, n_applied_ins=r.n_applied_ins, n_applied_del=r.n_applied_del,
                    n_noop=r.n_noop, changed_ids_ptr=r.changed_ids, embeddings_ptr=r.embeddings)
         if fetch:
-            ids = np.empty(r.n_changed, np.int32)
-            emb = np.empty((r.n_changed, self.out_dim), np.float32)
-            if r.n_changed:
-                _dtoh(ids, r.changed_ids)
-                _dtoh(emb, r.embeddings)
-            out["changed_ids"], out["embeddings"] = ids, emb
+            out["changed_ids"], out["embeddings"] = self._fetch(r.n_changed)
         return out
 
     def add_nodes(self, features, fetch=True):
@@ -283,12 +276,7 @@ class Ink:
         self.n += features.shape[0]
         out = dict(n_changed=r.n_changed, changed_ids_ptr=r.changed_ids, embeddings_ptr=r.embeddings)
         if fetch:
-            ids = np.empty(r.n_changed, np.int32)
-            emb = np.empty((r.n_changed, self.out_dim), np.float32)
-            if r.n_changed:
-                _dtoh(ids, r.changed_ids)
-                _dtoh(emb, r.embeddings)
-            out["changed_ids"], out["embeddings"] = ids, emb
+            out["changed_ids"], out["embeddings"] = self._fetch(r.n_changed)
         return out
 
     def update_features_device(self, ids_ptr, rows_ptr, n):

@@ -350,33 +350,54 @@ __global__ void k_gather_i32(const int32_t *table, const int32_t *idx, int n, co
   if (i < n) out[i] = table[idx[i]];
 }
 
+// Where a result goes besides the library's own buffer: pinned host memory, ids and rows, if it has at most `rows` rows.
+// The stores have left the chip when a wave ends, before the record that the host waits for is written.
+struct HostMirror { int32_t *ids; float *emb; int64_t rows; };
+
 __global__ void k_gather_rows(const float *table, int ld, int d, const int32_t *rows, int64_t n, const int32_t *n_dev,
-                              float *out) {
+                              float *out, HostMirror m) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n_dev) n = *n_dev;
   int64_t r = t / d;
   int k = (int)(t % d);
-  if (r < n) out[r * d + k] = table[(int64_t)rows[r] * ld + k];
+  if (r < n) {
+    const int v = rows[r];
+    const float x = table[(int64_t)v * ld + k];
+    out[r * d + k] = x;
+    if (n <= m.rows) {
+      m.emb[r * d + k] = x;
+      if (k == 0) m.ids[r] = v;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+  }
 }
 
 // the same, 16 bytes per thread, for d a multiple of 4
 __global__ void k_gather_rows4(const float *table, int ld, int d4, const int32_t *rows, int64_t n, const int32_t *n_dev,
-                               float *out) {
+                               float *out, HostMirror m) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n_dev) n = *n_dev;
   int64_t r = t / d4;
   int k = (int)(t - r * d4);
-  if (r < n)
-    reinterpret_cast<float4 *>(out)[r * d4 + k] = *reinterpret_cast<const float4 *>(table + (int64_t)rows[r] * ld + 4 * k);
+  if (r < n) {
+    const int v = rows[r];
+    const float4 x = *reinterpret_cast<const float4 *>(table + (int64_t)v * ld + 4 * k);
+    reinterpret_cast<float4 *>(out)[r * d4 + k] = x;
+    if (n <= m.rows) {
+      reinterpret_cast<float4 *>(m.emb)[r * d4 + k] = x;
+      if (k == 0) m.ids[r] = v;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+  }
 }
 
 // n bounds the row count (and sizes the launch); with n_dev the exact count is read on the device
 static void gather_rows(hipStream_t s, const float *table, int ld, int d, const int32_t *rows, int64_t n, float *out,
-                        const int32_t *n_dev = nullptr) {
+                        const int32_t *n_dev = nullptr, HostMirror m = HostMirror{nullptr, nullptr, -1}) {
   if (n <= 0) return;
   if (d % 4 == 0)
-    hipLaunchKernelGGL(k_gather_rows4, grid1(n * (d / 4)), dim3(256), 0, s, table, ld, d / 4, rows, n, n_dev, out);
-  else hipLaunchKernelGGL(k_gather_rows, grid1(n * d), dim3(256), 0, s, table, ld, d, rows, n, n_dev, out);
+    hipLaunchKernelGGL(k_gather_rows4, grid1(n * (d / 4)), dim3(256), 0, s, table, ld, d / 4, rows, n, n_dev, out, m);
+  else hipLaunchKernelGGL(k_gather_rows, grid1(n * d), dim3(256), 0, s, table, ld, d, rows, n, n_dev, out, m);
 }
 
 __global__ void k_pack_rows(const void *table, int ld, int d, int64_t row0, int64_t nrows, void *out) {
@@ -521,6 +542,16 @@ static ink_status seal(ink_ctx *c, ink_status st) {
   if (st != INK_E_OOM && st != INK_E_DEVICE) return st;
   c->broken = true;
   return drain(c, st);
+}
+// Around a call with a result: the last one is gone when it starts, and results stop going to the host once one was not fetched.
+static void begin_result(ink_ctx *c) {
+  if (c->mirrored && !c->fetched && c->last.n > 0) c->mirror = false;
+  c->last.n = -1;
+  c->mirrored = c->fetched = false;
+}
+static ink_status end_result(ink_ctx *c, ink_status st, const ink_update_result *out) {
+  if (st == INK_OK) { c->last.ids = out->changed_ids; c->last.rows = out->embeddings; c->last.n = out->n_changed; }
+  return seal(c, st);
 }
 static const char *kBrokenMsg = "the context is unusable after a failed update (INK_E_OOM / INK_E_DEVICE): destroy it";
 
@@ -889,6 +920,7 @@ extern "C" void ink_destroy(ink_ctx *c) {
   if (c->d_gcnt) (void)hipFree(c->d_gcnt);
   if (c->d_chain) (void)hipFree(c->d_chain);
   if (c->h_cnt) (void)hipHostFree(c->h_cnt);
+  if (c->h_res) (void)hipHostFree(c->h_res);
   if (c->bm_a) (void)hipFree(c->bm_a);
   for (DevBuf *b : {&c->ws.blk, &c->ws.hist, &c->ws.tmpk, &c->ws.tmpv, &c->b_raw, &c->b_misc, &c->b_uniq, &c->b_del_s,
                     &c->b_del_d, &c->b_ins_s, &c->b_ins_d, &c->f_list[0], &c->f_list[1], &c->f_old[0], &c->f_old[1],
@@ -1008,6 +1040,7 @@ static ink_status full_infer_impl(ink_ctx *c) {
 extern "C" ink_status ink_full_infer(ink_ctx *c) {
   if (!c) return INK_E_ARG;
   if (c->broken) return fail(c, INK_E_STATE, kBrokenMsg);
+  begin_result(c);
   return seal(c, full_infer_impl(c));
 }
 
@@ -1051,6 +1084,7 @@ extern "C" ink_status ink_full_infer_noalloc(ink_ctx *c) {
     bufs[i]->fixed = true;
     used += sizes[i];
   }
+  begin_result(c);
   const int profile = c->profile;
   c->profile = 0;                    // HIP events are created on demand: not in this call
   ink_status st = full_infer_impl(c);
@@ -1263,6 +1297,12 @@ static ink_status collect_rows(ink_ctx *c, const int32_t *extra0, int64_t n0, co
   return INK_OK;
 }
 
+// for a gather whose record the call waits for
+static HostMirror host_mirror(ink_ctx *c) {
+  c->mirrored = c->mirror;
+  return c->mirror ? HostMirror{c->mirror_ids(), c->mirror_emb(), c->mirror_rows()} : HostMirror{nullptr, nullptr, -1};
+}
+
 // rows of c_list whose flag is set -> f_list[nxt] (ids) and, for sum-type, f_old[nxt] (old rows
 // taken from c_old with row stride ld).  With want_events the events those rows will propagate in
 // the next layer are counted in the same round trip (prefix of kept out-degrees in f_pref).
@@ -1310,7 +1350,7 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, const int32_t *nC_dev, in
   if (result && (size_t)nC * result->d * 4 <= kEagerResultBytes) {
     API_TRY(c->res_emb.reserve((size_t)nC * result->d * 4));
     gather_rows(s, (const float *)result->f(), result->ld, result->d, (const int32_t *)c->f_list[nxt].as<int32_t>(), nC,
-                c->res_emb.as<float>(), &dc->v[C_NEXT]);
+                c->res_emb.as<float>(), &dc->v[C_NEXT], host_mirror(c));
     *result_done = true;
   }
   API_TRY(hipGetLastError());
@@ -1457,6 +1497,8 @@ static hipError_t layer_one_launch(ink_ctx *c, int l) {
   p.out = c->H[l].f(); p.ld_out = c->H[l].ld;
   p.layer = l; p.last = l == c->n_layers;
   p.res = c->res_emb.as<float>();
+  static_assert(2 * kOneEvents * (4 + 4 * INK_MAX_OUT_DIM) <= INK_RESULT_HOST_BYTES, "its result fits there");
+  if (p.last && c->mirror) { p.h_ids = c->mirror_ids(); p.h_emb = c->mirror_emb(); }
   p.h = c->h_one[l]; p.h_seq = c->h_oseq[l]; p.seq = c->one_seq[l] = ++c->pub_seq;
   return layer_one(c, p);
 }
@@ -1498,6 +1540,7 @@ static ink_status layer_one_finish(ink_ctx *c, int64_t n_seed, int *l_next, bool
   if (l > c->n_layers) {
     c->n_touched_src = 0;                                 // the last layer has cleared the marks
     out->n_changed = *nF;
+    c->mirrored = c->mirror;
     if (*nF > 0) { out->changed_ids = c->f_list[c->n_layers & 1].as<int32_t>(); out->embeddings = c->res_emb.as<float>(); }
   }
   return INK_OK;
@@ -1509,7 +1552,8 @@ extern "C" ink_status ink_apply_updates(ink_ctx *c, const ink_edge_update *upd, 
   if (!c) return INK_E_ARG;
   if (c->broken) return fail(c, INK_E_STATE, kBrokenMsg);
   c->affected_mode = false;
-  return seal(c, apply_updates_impl(c, upd, n, out));
+  begin_result(c);
+  return end_result(c, apply_updates_impl(c, upd, n, out), out);
 }
 
 extern "C" ink_status ink_apply_updates_affected(ink_ctx *c, const ink_edge_update *upd, int64_t n,
@@ -1517,9 +1561,10 @@ extern "C" ink_status ink_apply_updates_affected(ink_ctx *c, const ink_edge_upda
   if (!c) return INK_E_ARG;
   if (c->broken) return fail(c, INK_E_STATE, kBrokenMsg);
   c->affected_mode = true;
+  begin_result(c);
   ink_status st = apply_updates_impl(c, upd, n, out);
   c->affected_mode = false;
-  return seal(c, st);
+  return end_result(c, st, out);
 }
 
 static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int64_t n, ink_update_result *out) {
@@ -1613,7 +1658,8 @@ extern "C" ink_status ink_update_features(ink_ctx *c, const int32_t *node_ids, c
                                           ink_update_result *out) {
   if (!c) return INK_E_ARG;
   if (c->broken) return fail(c, INK_E_STATE, kBrokenMsg);
-  return seal(c, update_features_impl(c, node_ids, rows, n, out));
+  begin_result(c);
+  return end_result(c, update_features_impl(c, node_ids, rows, n, out), out);
 }
 
 static ink_status update_features_impl(ink_ctx *c, const int32_t *node_ids, const float *rows, int64_t n,
@@ -1825,7 +1871,8 @@ extern "C" ink_status ink_apply_user_events(ink_ctx *c, const ink_user_event *ev
                                             int32_t row_stride, int64_t n, ink_update_result *out) {
   if (!c) return INK_E_ARG;
   if (c->broken) return fail(c, INK_E_STATE, kBrokenMsg);
-  return seal(c, apply_user_events_impl(c, events, rows, row_stride, n, out));
+  begin_result(c);
+  return end_result(c, apply_user_events_impl(c, events, rows, row_stride, n, out), out);
 }
 
 // ------------------------------------------------------------------------------------ node arrival
@@ -1846,7 +1893,8 @@ static ink_status add_nodes_impl(ink_ctx *c, const float *features, int64_t n_ne
 extern "C" ink_status ink_add_nodes(ink_ctx *c, const float *features, int64_t n_new, ink_update_result *out) {
   if (!c) return INK_E_ARG;
   if (c->broken) return fail(c, INK_E_STATE, kBrokenMsg);
-  return seal(c, add_nodes_impl(c, features, n_new, out));
+  begin_result(c);
+  return end_result(c, add_nodes_impl(c, features, n_new, out), out);
 }
 
 static ink_status add_nodes_impl(ink_ctx *c, const float *features, int64_t n_new, ink_update_result *out) {
@@ -1951,6 +1999,27 @@ extern "C" ink_status ink_get_layer(ink_ctx *c, int32_t layer, int32_t which, in
                        dev_dst);
   API_TRY(hipGetLastError());
   if (dst_mem != INK_MEM_DEVICE) API_TRY(hipMemcpyAsync(dst, dev_dst, bytes, hipMemcpyDeviceToHost, c->stream));
+  API_TRY(hipStreamSynchronize(c->stream));
+  return INK_OK;
+}
+
+extern "C" ink_status ink_copy_result(ink_ctx *c, int32_t *ids, float *embeddings, int64_t n) {
+  if (!c) return INK_E_ARG;
+  if (c->broken) return fail(c, INK_E_STATE, kBrokenMsg);
+  if (c->last.n < 0) return fail(c, INK_E_STATE, "ink_copy_result: the last call left no result");
+  if (n != c->last.n || (n > 0 && (!ids || !embeddings))) return fail(c, INK_E_ARG, "ink_copy_result: NULL argument or not the result's size");
+  c->fetched = true;
+  if (!c->h_res && hipHostMalloc((void **)&c->h_res, INK_RESULT_HOST_BYTES, hipHostMallocCoherent) != hipSuccess) { c->h_res = nullptr; (void)hipGetLastError(); }
+  c->mirror = c->h_res != nullptr;
+  if (n == 0) return INK_OK;
+  const size_t row = (size_t)c->H[c->n_layers].d * 4;
+  if (c->mirrored && n <= c->mirror_rows()) {
+    memcpy(ids, c->mirror_ids(), (size_t)n * 4);
+    memcpy(embeddings, c->mirror_emb(), (size_t)n * row);
+    return INK_OK;
+  }
+  API_TRY(hipMemcpyAsync(ids, c->last.ids, (size_t)n * 4, hipMemcpyDeviceToHost, c->stream));
+  API_TRY(hipMemcpyAsync(embeddings, c->last.rows, (size_t)n * row, hipMemcpyDeviceToHost, c->stream));
   API_TRY(hipStreamSynchronize(c->stream));
   return INK_OK;
 }

@@ -219,6 +219,16 @@ struct ink_ctx {
   ink::DevBuf stage0, stage1;        // transform staging
   ink::DevBuf res_ids, res_emb;      // result of the last batch
 
+  // the last result (n < 0: none), and its copy in pinned memory: where the kernel that gathers a result writes it, too
+  struct Result { const int32_t *ids = nullptr; const float *rows = nullptr; int64_t n = -1; } last;
+  char *h_res = nullptr;             // INK_RESULT_HOST_BYTES, allocated by the first ink_copy_result
+  bool mirror = false;               // results are asked for on the host
+  bool mirrored = false;             // the last one was written there if it fits
+  bool fetched = true;               // ... and has been asked for
+  int64_t mirror_rows() const { return INK_RESULT_HOST_BYTES / (4 + 4 * (int64_t)H[n_layers].d) / 4 * 4; }
+  int32_t *mirror_ids() const { return reinterpret_cast<int32_t *>(h_res); }
+  float *mirror_emb() const { return reinterpret_cast<float *>(h_res) + mirror_rows(); }
+
   ink_stats stats;
   struct Pending { int cls, layer, kern; hipEvent_t a, b; };
   std::vector<hipEvent_t> ev_free;
@@ -352,6 +362,7 @@ struct OneLayer {
   float *out; int ld_out;
   int layer, last;
   float *res;                                      // last layer: the changed rows, packed
+  int32_t *h_ids; float *h_emb;                    // ... and ids and rows in pinned memory (null: not wanted there)
   HostCounters *h; uint32_t *h_seq; uint32_t seq;
 };
 hipError_t layer_one(ink_ctx *c, const OneLayer &p);

@@ -335,7 +335,12 @@ __global__ __launch_bounds__(kOneThreads) void k_layer_one(OneLayer p) {
         __threadfence_block();
         __syncthreads();
         const int d = p.n_out;
-        for (int i = t; i < nF2 * d; i += kOneThreads) p.res[i] = p.out[(int64_t)S.cand[i / d] * p.ld_out + i % d];
+        for (int i = t; i < nF2 * d; i += kOneThreads) {
+          const float x = p.out[(int64_t)S.cand[i / d] * p.ld_out + i % d];
+          p.res[i] = x;
+          if (p.h_emb) p.h_emb[i] = x;
+        }
+        if (p.h_ids && t < nF2) p.h_ids[t] = S.cand[t];
         const int n_src = n_ins + n_del > 0 ? p.g->v[C_OT] : 0;
         for (int i = t; i < n_src; i += kOneThreads) p.new_out[p.touched_src[i]] = 0;
       }
