@@ -51,7 +51,7 @@ template <int MODE> __device__ __forceinline__ float row_scalar(const XformArgs 
 }
 // GCN also writes the combined row as h_l
 template <int MODE>
-__device__ __forceinline__ void finish_x4(const XformArgs &x, int64_t row, int k, float sc, const RawX<MODE> &r, float v[4]) {
+__device__ __forceinline__ void finish_x4(const XformArgs &x, int64_t row, int k, float sc, bool store_h, const RawX<MODE> &r, float v[4]) {
   v[0] = r.a.x; v[1] = r.a.y; v[2] = r.a.z; v[3] = r.a.w;
   if constexpr (MODE == 0) {
     const int d4 = xform_self_row(x.d_in);
@@ -84,7 +84,7 @@ __device__ __forceinline__ void finish_x4(const XformArgs &x, int64_t row, int k
       if (x.in_relu) t = t > 0.f ? t : 0.f;
       v[i] = k + i < x.d_in ? t : 0.f;
     }
-    if (x.h_store && k < x.ld_hs) *reinterpret_cast<float4 *>(x.h_store + row * x.ld_hs + k) = make_float4(v[0], v[1], v[2], v[3]);
+    if (store_h && x.h_store && k < x.ld_hs) *reinterpret_cast<float4 *>(x.h_store + row * x.ld_hs + k) = make_float4(v[0], v[1], v[2], v[3]);
   }
 }
 
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(NW * 64) void k_xform(XformArgs x) {
     for (int kk = 0; kk < KPT; kk++) xv[kk] = 0.f;
     if (xrow >= 0) {
 #pragma unroll
-      for (int kk = 0; kk < KPT; kk += 4) finish_x4<MODE>(x, xrow, k0 + xks + kk, sc, raw[kk / 4], xv + kk);
+      for (int kk = 0; kk < KPT; kk += 4) finish_x4<MODE>(x, xrow, k0 + xks + kk, sc, true, raw[kk / 4], xv + kk);
     }
     if (xstage) {   // even k first, then odd k
       float *xp = Xs + xr * XS + (xks >> 1);
@@ -263,6 +263,150 @@ __global__ __launch_bounds__(NW * 64) void k_xform(XformArgs x) {
     __syncthreads();
   }
   xform_epilogue<TPW, CS, NT, BM>(x, acc, srow, sout, schg, rt, ct0, l, t, r0);
+}
+
+// ---- few rows
+// Few rows are a chain of latencies: the kernel above takes 17 us for any number up to some thousands (256 inputs, 128
+// outputs), two barriers and a gather for each of its eight chunks.  Here a wave owns 16 rows and TPW tiles of 16 columns, has the inputs and weights of four chunks under
+// way, and meets the others only to join the flags of its rows.  v_mfma_f32_16x16x4_f32 takes half the cycles of
+// 32x32x2 for twice the k and adds its four products in ascending order like the two of the other (test_gpu_xform_few).
+__device__ __forceinline__ void swap32(float &x, float &y) {     // upper lanes of x <-> lower lanes of y
+  const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(t[0]); y = __uint_as_float(t[1]);
+}
+__device__ __forceinline__ void swap16(float &x, float &y) {     // odd rows of 16 lanes of x <-> even rows of y
+  const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(t[0]); y = __uint_as_float(t[1]);
+}
+
+typedef float f4acc __attribute__((ext_vector_type(4)));
+constexpr int kFewWaves = 8;
+
+template <int MODE, int TPW>
+__global__ __launch_bounds__(kFewWaves * kWave) void k_xform_few(XformArgs x) {
+  constexpr int D = TPW == 2 || MODE == 3 ? 2 : 4;       // chunks of KT under way, as many as the registers hold
+  __shared__ uint32_t part[kFewWaves];
+  const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int kq = l >> 4;                          // which of a step's four k
+  int64_t n_rows = x.n_rows;
+  if (x.n_rows_dev) {          // the launch covers an upper bound; workgroups past the count leave
+    int64_t nd = *x.n_rows_dev;
+    n_rows = nd < n_rows ? nd : n_rows;
+  }
+  const int64_t r0 = (int64_t)blockIdx.x * 16;
+  if (r0 >= n_rows) return;
+  const int n_ch = x.Kp / KT;
+  // the weights of tile ct: lane (k % 2) * 32 + col % 32 of the layout (xform_weight_index)
+  float4 b[D][TPW][4];
+  const float4 *wp[TPW];
+#pragma unroll
+  for (int i = 0; i < TPW; i++) {
+    const int ct = w * TPW + i;
+    wp[i] = reinterpret_cast<const float4 *>(x.W) + (ct >> 1) * 256 + (kq & 1) * 32 + (ct & 1) * 16 + (l & 15);
+  }
+  auto issue_w = [&](int d, int ch) {
+    const int64_t o = (int64_t)(ch < n_ch ? ch : n_ch - 1) * 8 * x.Np;
+#pragma unroll
+    for (int i = 0; i < TPW; i++)
+#pragma unroll
+      for (int u = 0; u < 4; u++) b[d][i][u] = wp[i][o + u * 64];
+  };
+#pragma unroll
+  for (int d = 0; d < D; d++) issue_w(d, d);
+  // lanes past the last row repeat it: no load stands under a condition, and nothing of it is stored
+  const int left = n_rows - r0 < 16 ? (int)(n_rows - r0) : 16;
+  const int64_t j = r0 + ((l & 15) < left ? (l & 15) : left - 1);
+  const int64_t row = (MODE == 2 || !x.rows) ? j : (int64_t)x.rows[j];
+  const int orow = (int)(!x.to_table ? j : MODE == 2 && x.out_rows ? (int64_t)x.out_rows[j] : row);
+  const bool store_h = w == 0 && (l & 15) < left;
+  RawX<MODE> raw[D][2];
+  auto issue = [&](int d, int ch) {
+    const int k0 = (ch < n_ch ? ch : n_ch - 1) * KT + 4 * kq;
+#pragma unroll
+    for (int i = 0; i < 2; i++) issue_x4<MODE>(x, row, k0 + 16 * i, raw[d][i]);
+  };
+#pragma unroll
+  for (int d = 0; d < D; d++) issue(d, d);
+  const float sc = row_scalar<MODE>(x, row);
+  // the rows that are replaced: a lane holds rows 4 kq + r, column l % 16 of each of its tiles
+  const bool compare = x.to_table && (x.row_changed || x.old_rows);     // a whole inference only stores
+  int o[4];
+  float old[TPW][4];
+#pragma unroll
+  for (int r = 0; r < 4; r++) o[r] = __shfl(orow, 4 * kq + r, kWave);
+#pragma unroll
+  for (int i = 0; i < TPW; i++) {
+    const int col = (w * TPW + i) * 16 + (l & 15);
+#pragma unroll
+    for (int r = 0; r < 4; r++) old[i][r] = compare && col < x.n_out ? x.out[(int64_t)o[r] * x.ld_out + col] : 0.f;
+  }
+  f4acc acc[TPW];
+#pragma unroll
+  for (int i = 0; i < TPW; i++)
+#pragma unroll
+    for (int r = 0; r < 4; r++) acc[i][r] = 0.f;
+  auto chunk = [&](const int d, const int ch) __attribute__((always_inline)) {     // d: constant
+    float a[8];                                    // step s: k 4 s + kq
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      float *v = a + 4 * i;                        // lanes kq hold k 16 i + 4 kq ..: transposed over the four lane groups
+      finish_x4<MODE>(x, row, ch * KT + 16 * i + 4 * kq, sc, store_h, raw[d][i], v);
+      swap32(v[0], v[2]); swap32(v[1], v[3]);
+      swap16(v[0], v[1]); swap16(v[2], v[3]);
+    }
+    issue(d, ch + D);
+#pragma unroll
+    for (int i = 0; i < TPW; i++)
+#pragma unroll
+      for (int s = 0; s < 8; s++) {
+        const float4 q = b[d][i][s >> 1];
+        const float bw = s & 1 ? (kq >> 1 ? q.w : q.z) : (kq >> 1 ? q.y : q.x);
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], bw, acc[i], 0, 0, 0);
+      }
+    issue_w(d, ch + D);
+  };
+  int ch = 0;
+  for (; ch + D <= n_ch; ch += D)
+#pragma unroll
+    for (int d = 0; d < D; d++) chunk(d, ch + d);
+#pragma unroll
+  for (int d = 0; d < D - 1; d++)
+    if (ch + d < n_ch) chunk(d, ch + d);
+  unsigned changed = 0;                            // bit r: some value of this lane's row r
+#pragma unroll
+  for (int i = 0; i < TPW; i++) {
+    const int col = (w * TPW + i) * 16 + (l & 15);
+    if (col >= x.n_out) continue;
+    const float bias = x.bias ? x.bias[col] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int rl = 4 * kq + r;
+      if (rl >= left) continue;
+      float v = acc[i][r];
+      if (x.bias) v = __fadd_rn(v, bias);
+      if (x.user) v = __fadd_rn(v, x.user[(int64_t)o[r] * x.ld_user + col]);
+      if (x.out_scale) v = __fmul_rn(v, x.out_scale[o[r]]);
+      if (x.relu) v = v > 0.f ? v : 0.f;
+      float *p = x.out + (int64_t)o[r] * x.ld_out + col;
+      if (compare) {
+        if (x.old_rows) x.old_rows[(r0 + rl) * x.ld_old + col] = old[i][r];
+        if (__float_as_uint(old[i][r]) != __float_as_uint(v)) { *p = v; changed |= 1u << r; }
+      } else *p = v;
+    }
+  }
+  if (!(x.to_table && x.row_changed)) return;
+  uint32_t rows = 0;                               // bit of every row of the tile
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const uint64_t m = __ballot((changed >> r) & 1u);
+#pragma unroll
+    for (int q = 0; q < 4; q++) rows |= ((m >> (16 * q)) & 0xffffu ? 1u : 0u) << (4 * q + r);
+  }
+  if (l == 0) part[w] = rows;
+  __syncthreads();
+  if (w != 0) return;
+  for (int i = 1; i < (int)(blockDim.x / kWave); i++) rows |= part[i];
+  if (l < left) x.row_changed[r0 + l] = (uint8_t)((rows >> l) & 1u);
 }
 
 #ifndef INK_XF_WIDE_FROM
@@ -302,6 +446,25 @@ static hipError_t launch(ink_ctx *c, const XformArgs &x) {
 hipError_t xform_run(ink_ctx *c, const XformArgs &x) {
   if (x.n_rows <= 0) return hipSuccess;
   if (x.Np % 32 || x.Kp % KT || x.Np > 256) return hipErrorInvalidValue;
+  // Rows up to which the time is the chain of one workgroup.  500 / 2000 / 6000 rows of 256 inputs and 128 outputs take 12 / 13 /
+  // 22 us, in the other form 17 / 17 / 18; a bound that is found before its count is usually twice it.  Updates, the few-row form against
+  // none: 50 edges on 100k nodes, widths 100, 256, 47, .43 -> .38 ms, 100 on 10k nodes .39 -> .375, 333 on 87k nodes .75 -> .73.
+  if (x.n_rows <= (x.n_rows_dev ? 4096 : 2048)) {
+    const dim3 grid((unsigned)((x.n_rows + 15) / 16));
+    const int tiles = x.Np / 16;
+#define INK_FEW(M)                                                                                             \
+  if (tiles <= kFewWaves) hipLaunchKernelGGL((k_xform_few<M, 1>), grid, dim3(tiles * kWave), 0, c->stream, x);   \
+  else hipLaunchKernelGGL((k_xform_few<M, 2>), grid, dim3(tiles / 2 * kWave), 0, c->stream, x)
+    switch (x.mode) {
+      case 0: INK_FEW(0); break;
+      case 1: INK_FEW(1); break;
+      case 2: INK_FEW(2); break;
+      case 3: INK_FEW(3); break;
+      default: return hipErrorInvalidValue;
+    }
+#undef INK_FEW
+    return hipGetLastError();
+  }
   switch (x.mode) {
     case 0: return launch<0>(c, x);
     case 1: return launch<1>(c, x);
