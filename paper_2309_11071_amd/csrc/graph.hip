@@ -549,7 +549,9 @@ static ink_status apply_side(ink_ctx *c, GraphSide &g, SideBufs &b, int64_t n_op
 // An entry that a later one on the same edge overrides, or a self loop, stays in the lists as a dead op.
 // Bound by the latency of its few launches and of one round trip; measured per update call with 10 000
 // entries on 612 k nodes / 15.5 M edges: 0.15 ms less than two sequential sides with two round trips, with 1 to 500
-// entries 0.03 - 0.06 ms less.
+// entries 0.03 - 0.06 ms less.  Of its six launches for 10 000 entries (205 us) the two of one workgroup a side took half: now
+// they take all entries at once instead of 1024 a turn, the blocks' places are read by the workgroups of the merge, which
+// has the sorted chunks in LDS, and the walk has a wave per chunk (142 us; 612k nodes with hubs 2.53 -> 2.40 ms a pass of two updates).
 constexpr int kOneChunk = 1024;        // entries that one workgroup sorts
 constexpr int kMaxChunks = (int)(kShortBatch / kOneChunk);
 constexpr uint64_t kNoKey = ~0ull;     // sorts behind every (node, other) pair
@@ -559,7 +561,9 @@ struct ShortSide {           // op lists of one direction (device pointers), in 
   int32_t *uniq, *seg, *chunk_pref;
   int32_t *nd_ins, *nd_del, *fill, *pfx;
   const int64_t *off; const int32_t *deg, *cap, *ids;
+  int64_t *uoff; int32_t *udeg, *ucap; // the touched nodes' blocks, one behind the other
   uint64_t *skey; int32_t *sidx;       // sorted chunks (batches of more than one)
+  int64_t *eoff; int32_t *edeg, *ecap; // the blocks of the ops' nodes (batches of more than one chunk)
   int slot_n, slot_ch;                 // touched nodes, chunks of their blocks (slots of the graph counters)
 };
 
@@ -606,33 +610,28 @@ __device__ __forceinline__ void clear_graph_slots(Counters *g, int err) {
   if (i < 32 && i != C_TMP0 && i != C_TMP1 && i != C_OT && i != C_OCH) g->v[i] = i == C_ERR ? err : 0;
 }
 
-// Distinct nodes of the sorted op list (node of op i: node(i), n ops), the start of each node's ops plus the
+// Distinct nodes of the sorted op list (node of op i: node(i), n <= THREADS ops), the start of each node's ops plus the
 // closing offset, the prefix of the chunk counts of their blocks, and both totals.  sm: LDS of the scans.
 template <int THREADS, class NodeAt>
 __device__ __forceinline__ void heads_and_chunks(NodeAt node, int n, const ShortSide &o, int *sm, Counters *g) {
-  int n_uniq = 0;
-  for (int i0 = 0; i0 < n; i0 += THREADS) {
-    const int i = i0 + threadIdx.x;
-    const int v = i < n ? node(i) : -1;
-    const int h = i < n && (i == 0 || v != node(i - 1));
-    int tot;
-    const int ex = n_uniq + block_excl_scan<THREADS>(h, sm, &tot);
-    if (h) { o.uniq[ex] = v; o.seg[ex] = i; }
-    n_uniq += tot;
-  }
-  if (threadIdx.x == 0) o.seg[n_uniq] = n;
+  const int i = threadIdx.x;
+  const int v = i < n ? node(i) : -1;
+  const int h = i < n && (i == 0 || v != node(i - 1));
+  int n_uniq, n_ch;
+  const int ex = block_excl_scan<THREADS>(h, sm, &n_uniq);
+  if (h) { o.uniq[ex] = v; o.seg[ex] = i; }
+  if (i == 0) o.seg[n_uniq] = n;
   __threadfence_block();
   __syncthreads();
-  int n_ch = 0;
-  for (int i0 = 0; i0 < n_uniq; i0 += THREADS) {
-    const int i = i0 + threadIdx.x;
-    const int ch = i < n_uniq ? (o.deg[o.uniq[i]] + kChunk - 1) / kChunk : 0;
-    int tot;
-    const int ex = n_ch + block_excl_scan<THREADS>(ch, sm, &tot);
-    if (i < n_uniq) o.chunk_pref[i] = ex;
-    n_ch += tot;
+  int ch = 0;
+  if (i < n_uniq) {
+    const int u = o.uniq[i], d = o.deg[u];
+    o.udeg[i] = d; o.ucap[i] = o.cap[u]; o.uoff[i] = o.off[u];
+    ch = (d + kChunk - 1) / kChunk;
   }
-  if (threadIdx.x == 0) { g->v[o.slot_n] = n_uniq; g->v[o.slot_ch] = n_ch; }
+  const int ec = block_excl_scan<THREADS>(ch, sm, &n_ch);
+  if (i < n_uniq) o.chunk_pref[i] = ec;
+  if (i == 0) { g->v[o.slot_n] = n_uniq; g->v[o.slot_ch] = n_ch; }
 }
 
 // Up to THREADS entries: one workgroup per side does everything up to the op lists.
@@ -678,10 +677,10 @@ __global__ __launch_bounds__(kOneChunk) void k_short_sort(const RawUpdate *raw, 
   o.skey[i] = S.k[cur][t];
   o.sidx[i] = S.i[cur][t];
 }
-__device__ __forceinline__ int batch_bad(const int32_t *chunk_err, int n_chunks) {
-  int e = 0;
-  for (int c = 0; c < n_chunks; c++) e |= chunk_err[c];
-  return e;
+__device__ __forceinline__ int batch_bad(const int32_t *chunk_err, int n_chunks) {      // whole wave
+  static_assert(kMaxChunks <= kWave, "a lane per chunk");
+  const int e = lane_id() < n_chunks ? chunk_err[lane_id()] : 0;
+  return (__ballot(e & 1) ? 1 : 0) | (__ballot(e & 2) ? 2 : 0);
 }
 // ... and merged by rank: an element's place is the sum of its ranks in all chunks (the searches of one thread
 // advance in step, so their loads are in flight together).
@@ -689,8 +688,17 @@ __global__ __launch_bounds__(kOneChunk) void k_short_merge(int n, int n_chunks, 
   const int side = (int)blockIdx.x >= n_chunks, ch = (int)blockIdx.x - (side ? n_chunks : 0), t = threadIdx.x;
   const ShortSide &o = side ? out : in;
   if (batch_bad(chunk_err, n_chunks)) return;
+  // all keys of the side in LDS: ten steps of dependent reads took 31 us out of the L2, 10 chunks
+  __shared__ uint64_t S[kMaxChunks * kOneChunk];
+  uint64_t in_flight[kMaxChunks];
+#pragma unroll
+  for (int c = 0; c < kMaxChunks; c++) in_flight[c] = c < n_chunks ? o.skey[c * kOneChunk + t] : kNoKey;
+#pragma unroll
+  for (int c = 0; c < kMaxChunks; c++)
+    if (c < n_chunks) S[c * kOneChunk + t] = in_flight[c];
+  __syncthreads();
   const int me = ch * kOneChunk + t;
-  const uint64_t k = o.skey[me];
+  const uint64_t k = S[me];
   if (k == kNoKey) return;
   int lo[kMaxChunks];
 #pragma unroll
@@ -699,61 +707,127 @@ __global__ __launch_bounds__(kOneChunk) void k_short_merge(int n, int n_chunks, 
 #pragma unroll
     for (int c = 0; c < kMaxChunks; c++) {
       if (c >= n_chunks || c == ch) continue;
-      const uint64_t x = o.skey[c * kOneChunk + lo[c] + step - 1];
+      const uint64_t x = S[c * kOneChunk + lo[c] + step - 1];
       if (c < ch ? x <= k : x < k) lo[c] += step;      // equal keys of earlier chunks stand before, of later ones behind
     }
   }
   int rank = t;
-  bool dead = t + 1 < kOneChunk && o.skey[me + 1] == k;
+  bool dead = t + 1 < kOneChunk && S[me + 1] == k;
 #pragma unroll
   for (int c = 0; c < kMaxChunks; c++) {
     if (c >= n_chunks || c == ch) continue;
     // the search above covers 1023 elements; the last step settles the chunk's last one
-    const uint64_t x = o.skey[c * kOneChunk + lo[c]];
+    const uint64_t x = S[c * kOneChunk + lo[c]];
     const bool before = c < ch ? x <= k : x < k;
     rank += lo[c] + (before ? 1 : 0);
-    dead |= c > ch && (before ? (lo[c] + 1 < kOneChunk && o.skey[c * kOneChunk + lo[c] + 1] == k) : x == k);
+    dead |= c > ch && (before ? (lo[c] + 1 < kOneChunk && S[c * kOneChunk + lo[c] + 1] == k) : x == k);
   }
   const int node = (int)(k >> 32), other = (int)(uint32_t)k;
   dead |= node == other;
   o.node[rank] = node; o.other[rank] = other; o.op[rank] = (uint8_t)(dead ? 2 : o.sidx[me] >> 16); o.pos[rank] = -1;
+  o.edeg[rank] = o.deg[node]; o.ecap[rank] = o.cap[node]; o.eoff[rank] = o.off[node];       // here many workgroups share the random reads
 }
-__global__ __launch_bounds__(kOneChunk) void k_short_heads(int n, int n_chunks, ShortSide in, ShortSide out, const int32_t *chunk_err,
-                                                           Counters *g) {
-  __shared__ int sm[kOneChunk / kWave + 1];
-  const int side = blockIdx.x;
-  const ShortSide &o = side ? out : in;
-  const int err = batch_bad(chunk_err, n_chunks);
-  if (side == 0) clear_graph_slots(g, err);
-  const int32_t *node = o.node;
-  heads_and_chunks<kOneChunk>([=](int i) { return node[i]; }, err ? 0 : n, o, sm, g);
+// Up to ITEMS * 1024 entries by one workgroup in one pass: wave w has entries w * 64 ITEMS .., lane l of its k-th group of 64
+// the k-th of them, so that loads are coalesced, all under way together, and ranks are counts of ballot bits.
+struct Items {
+  int base;                                       // first entry of the wave
+  template <int ITEMS> __device__ __forceinline__ static Items of() { return Items{(int)(threadIdx.x / kWave) * (ITEMS * kWave)}; }
+  __device__ __forceinline__ int at(int k) const { return base + k * kWave + lane_id(); }
+};
+// exclusive prefix of one value per wave over the workgroup, and the total (sm: a slot per wave)
+__device__ __forceinline__ int wave_prefix(int x, int *sm, int *total) {
+  const int w = threadIdx.x / kWave;
+  __syncthreads();
+  if (lane_id() == 0) sm[w] = x;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int i = 0; i < kOneChunk / kWave; i++) { before += i < w ? sm[i] : 0; all += sm[i]; }
+  *total = all;
+  return before;
 }
 
-// Walk the blocks of the touched nodes of both sides, one chunk of slots per workgroup visit; an id found in
+template <int ITEMS>
+__global__ __launch_bounds__(kOneChunk) void k_short_heads(int n, int n_chunks, ShortSide in, ShortSide out, const int32_t *chunk_err,
+                                                           Counters *g) {
+  __shared__ int sm[kOneChunk / kWave];
+  const ShortSide &o = blockIdx.x ? out : in;
+  const int err = batch_bad(chunk_err, n_chunks);
+  if (blockIdx.x == 0) clear_graph_slots(g, err);
+  if (err) n = 0;
+  const Items it = Items::of<ITEMS>();
+  const uint64_t below = (1ull << lane_id()) - 1;
+  int v[ITEMS], pv[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const int i = it.at(k);
+    v[k] = i < n ? o.node[i] : -1;
+    pv[k] = i > 0 && i < n ? o.node[i - 1] : -1;
+  }
+  uint64_t head[ITEMS];
+  int cnt = 0, n_uniq, n_ch;
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) { head[k] = __ballot(v[k] != pv[k]); cnt += __popcll(head[k]); }       // node ids are not negative
+  int at = wave_prefix(cnt, sm, &n_uniq);
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    if (v[k] != pv[k]) {
+      const int u = at + __popcll(head[k] & below), i = it.at(k), d = o.edeg[i];
+      o.uniq[u] = v[k]; o.seg[u] = i;
+      o.udeg[u] = d; o.ucap[u] = o.ecap[i]; o.uoff[u] = o.eoff[i];
+    }
+    at += __popcll(head[k]);
+  }
+  if (threadIdx.x == 0) o.seg[n_uniq] = n;
+  __threadfence_block();
+  __syncthreads();
+  int ch[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) ch[k] = it.at(k) < n_uniq ? o.udeg[it.at(k)] : 0;
+  cnt = 0;
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const int c = (ch[k] + kChunk - 1) / kChunk, inc = wave_incl_scan(c);
+    ch[k] = cnt + inc - c;
+    cnt += __builtin_amdgcn_readlane(inc, kWave - 1);
+  }
+  const int before = wave_prefix(cnt, sm, &n_ch);
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++)
+    if (it.at(k) < n_uniq) o.chunk_pref[it.at(k)] = before + ch[k];
+  if (threadIdx.x == 0) { g->v[o.slot_n] = n_uniq; g->v[o.slot_ch] = n_ch; }
+}
+
+// Walk the blocks of the touched nodes of both sides, one chunk of slots per wave visit (most blocks are short: a
+// workgroup per visit left three of its waves without work in their chains of loads); an id found in
 // the node's op list records its slot (of several ops on one edge the last one, which is the live one, may
 // not be missed).  Reads only: the blocks are walked with 16-byte loads, a node's few ops sit in registers.
 __global__ __launch_bounds__(256) void k_short_classify(ShortSide in, ShortSide out, const Counters *g) {
   const int nch_in = g->v[in.slot_ch], total = nch_in + g->v[out.slot_ch];
-  const int l = lane_id();
-  for (int c = blockIdx.x; c < total; c += gridDim.x) {
+  const int l = lane_id(), wave = (int)(blockIdx.x * (256 / kWave)) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  for (int c = wave; c < total; c += gridDim.x * (256 / kWave)) {
     const bool second = c >= nch_in;
     const ShortSide &o = second ? out : in;
     const int ch = second ? c - nch_in : c;
     const int i = wave_last_le(o.chunk_pref, g->v[o.slot_n], ch);      // node owning this chunk
-    const int v = o.uniq[i];
     const int s0 = o.seg[i], cnt = o.seg[i + 1] - s0;
-    const int d = o.deg[v];
-    const int32_t *ids = o.ids + o.off[v];       // blocks start on 16-byte boundaries and hold a multiple of 4 slots
+    const int d = o.udeg[i];
+    const int32_t *ids = o.ids + o.uoff[i];      // blocks start on 16-byte boundaries and hold a multiple of 4 slots
     const int mine = o.other[s0 + (l < cnt ? l : 0)];
-    const int p_end = (ch - o.chunk_pref[i] + 1) * kChunk < d ? (ch - o.chunk_pref[i] + 1) * kChunk : d;
-    // workgroup-uniform trip count: the ops are read from all lanes of the wave
-    for (int p0 = (ch - o.chunk_pref[i]) * kChunk; p0 < p_end; p0 += 4 * 256) {
-      const int p = p0 + 4 * (int)threadIdx.x;
-      int e[4] = {-1, -1, -1, -1};
-      if (p < p_end) {
-        const int4 e4 = *reinterpret_cast<const int4 *>(ids + p);
-        e[0] = e4.x; e[1] = e4.y; e[2] = e4.z; e[3] = e4.w;
-      }
+    const int p_begin = (ch - o.chunk_pref[i]) * kChunk, p_end = p_begin + kChunk < d ? p_begin + kChunk : d;
+    constexpr int U = 4;                         // loads under way
+    for (int p0 = p_begin; p0 < p_end; p0 += 4 * kWave * U) {
+     int4 q[U];
+#pragma unroll
+     for (int u = 0; u < U; u++) {
+       const int p = p0 + 4 * (u * kWave + l);
+       q[u] = p0 + 4 * u * kWave < p_end ? *reinterpret_cast<const int4 *>(ids + (p < p_end ? p : p0)) : make_int4(-1, -1, -1, -1);
+     }
+#pragma unroll
+     for (int u = 0; u < U; u++) {
+      const int p = p0 + 4 * (u * kWave + l);
+      if (p0 + 4 * u * kWave >= p_end) break;
+      const int e[4] = {p < p_end ? q[u].x : -1, p < p_end ? q[u].y : -1, p < p_end ? q[u].z : -1, p < p_end ? q[u].w : -1};
       if (cnt <= 8) {
         for (int m = 0; m < cnt; m++) {
           const int x = __builtin_amdgcn_readlane(mine, m);
@@ -772,18 +846,20 @@ __global__ __launch_bounds__(256) void k_short_classify(ShortSide in, ShortSide 
           if (a > s0 && o.other[a - 1] == e[j] && p + j < d) o.pos[a - 1] = p + j;
         }
       }
+     }
     }
   }
 }
 
 // Effective ops, one workgroup per side: Delta E in (dst, src) order (in side), insertions and deletions per
 // touched node, the pool space that relocations need.  The workgroup that ends second decides whether
-// the batch may be applied and publishes the record.
+// the batch may be applied and publishes the record.  n <= ITEMS * 1024.
+template <int ITEMS>
 __global__ __launch_bounds__(kOneChunk) void k_short_finish(int n, ShortSide in, ShortSide out, int32_t *ins_s, int32_t *ins_d,
                                                             int32_t *del_s, int32_t *del_d, float slack, long long room_in,
                                                             long long room_out, Counters *g, HostCounters *h, uint32_t *h_seq,
                                                             uint32_t seq) {
-  __shared__ int sm[kOneChunk / kWave + 1];
+  __shared__ int sm[kOneChunk / kWave];
   __shared__ unsigned long long s_need;
   __shared__ int s_last;
   const int side = blockIdx.x, t = threadIdx.x;
@@ -791,28 +867,53 @@ __global__ __launch_bounds__(kOneChunk) void k_short_finish(int n, ShortSide in,
   const int n_uniq = g->v[o.slot_n];
   const int n_ops = n_uniq ? n : 0;              // none after a malformed entry
   if (t == 0) s_need = 0;
-  int carry = 0;                                 // insertions in the low half, deletions in the high half
-  for (int k0 = 0; k0 < n_ops; k0 += kOneChunk) {
-    const int k = k0 + t;
-    const int e = k < n_ops ? effect_of(o.op[k], o.pos[k]) : 0;
-    const int x = (e == 1) + ((e == 2) << 16);
-    int tot;
-    const int ex = carry + block_excl_scan<kOneChunk>(x, sm, &tot);
-    if (k < n_ops) o.pfx[k] = ex + x;
-    if (side == 0 && e == 1) { ins_s[ex & 0xFFFF] = o.other[k]; ins_d[ex & 0xFFFF] = o.node[k]; }
-    if (side == 0 && e == 2) { del_s[ex >> 16] = o.other[k]; del_d[ex >> 16] = o.node[k]; }
-    carry += tot;
+  const Items it = Items::of<ITEMS>();
+  const uint64_t below = (1ull << lane_id()) - 1;
+  int e[ITEMS], pos[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const int i = it.at(k);
+    e[k] = i < n_ops ? o.op[i] : 2;              // 2: a dead op
+    pos[k] = i < n_ops ? o.pos[i] : -1;
+  }
+  int cnt = 0, carry;                            // insertions in the low half, deletions in the high half
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    e[k] = effect_of((uint8_t)e[k], pos[k]);
+    cnt += __popcll(__ballot(e[k] == 1)) + (__popcll(__ballot(e[k] == 2)) << 16);
+  }
+  int at = wave_prefix(cnt, sm, &carry);
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const uint64_t mi = __ballot(e[k] == 1), md = __ballot(e[k] == 2);
+    const int i = it.at(k), ei = (at & 0xFFFF) + __popcll(mi & below), ed = (at >> 16) + __popcll(md & below);
+    if (i < n_ops) o.pfx[i] = (ei + (e[k] == 1)) + ((ed + (e[k] == 2)) << 16);
+    if (side == 0 && e[k] == 1) { ins_s[ei] = o.other[i]; ins_d[ei] = o.node[i]; }
+    if (side == 0 && e[k] == 2) { del_s[ed] = o.other[i]; del_d[ed] = o.node[i]; }
+    at += __popcll(mi) + (__popcll(md) << 16);
   }
   __threadfence_block();
   __syncthreads();
   unsigned long long need = 0;
-  for (int i = t; i < n_uniq; i += kOneChunk) {
-    const int s0 = o.seg[i], s1 = o.seg[i + 1], v = o.uniq[i];
-    const int x = o.pfx[s1 - 1] - (s0 ? o.pfx[s0 - 1] : 0);
-    const int ni = x & 0xFFFF, nd = x >> 16;
+  int s0[ITEMS], s1[ITEMS], dg[ITEMS], cp[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const int i = it.at(k) < n_uniq ? it.at(k) : 0;
+    s0[k] = n_uniq ? o.seg[i] : 0; s1[k] = n_uniq ? o.seg[i + 1] : 0;
+    dg[k] = n_uniq ? o.udeg[i] : 0; cp[k] = n_uniq ? o.ucap[i] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    s1[k] = s1[k] > 0 ? o.pfx[s1[k] - 1] : 0; s0[k] = s0[k] > 0 ? o.pfx[s0[k] - 1] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    const int i = it.at(k);
+    if (i >= n_uniq) continue;
+    const int x = s1[k] - s0[k], ni = x & 0xFFFF, nd = x >> 16;
     o.nd_ins[i] = ni; o.nd_del[i] = nd;
-    const int d2 = o.deg[v] - nd + ni, cp = o.cap[v];
-    if (d2 > cp) need += (unsigned long long)relocated_cap(d2, cp, slack);
+    const int d2 = dg[k] - nd + ni;
+    if (d2 > cp[k]) need += (unsigned long long)relocated_cap(d2, cp[k], slack);
   }
   if (need) atomicAdd(&s_need, need);
   __syncthreads();
@@ -1018,7 +1119,7 @@ __global__ __launch_bounds__(1024) void k_graph_one(const RawUpdate *raw, int n,
 
 static size_t short_bytes(int64_t n) {
   const size_t pad = (size_t)(n + kOneChunk - 1) / kOneChunk * kOneChunk;
-  return 2 * (pad * 12 + 13 * ((size_t)(n + 64) * 4 + 256)) + 4096;
+  return 2 * (pad * 12 + 22 * ((size_t)(n + 64) * 4 + 256)) + 4096;
 }
 
 hipError_t graph_reserve(ink_ctx *c, int64_t max_batch) {
@@ -1099,6 +1200,8 @@ static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n6
     b.node = ar.get<int32_t>(n); b.other = ar.get<int32_t>(n); b.op = ar.get<uint8_t>(n); b.pos = ar.get<int32_t>(n);
     b.seg = ar.get<int32_t>(n + 2); b.chunk_pref = ar.get<int32_t>(n + 1);
     b.nd_ins = ar.get<int32_t>(n + 1); b.nd_del = ar.get<int32_t>(n + 1); b.fill = ar.get<int32_t>(n + 1); b.pfx = ar.get<int32_t>(n + 1);
+    b.uoff = ar.get<int64_t>(n); b.udeg = ar.get<int32_t>(n); b.ucap = ar.get<int32_t>(n);
+    b.eoff = ar.get<int64_t>(n); b.edeg = ar.get<int32_t>(n); b.ecap = ar.get<int32_t>(n);
     b.off = gs[k]->off; b.deg = gs[k]->deg; b.cap = gs[k]->cap; b.ids = gs[k]->ids;
     b.slot_n = k ? C_OT : C_TMP0; b.slot_ch = k ? C_OCH : C_TMP1;
   }
@@ -1113,13 +1216,19 @@ static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n6
   else {
     hipLaunchKernelGGL(k_short_sort, dim3(2 * n_chunks), dim3(kOneChunk), 0, s, raw, n, c->n, n_chunks, sd[0], sd[1], chunk_err);
     hipLaunchKernelGGL(k_short_merge, dim3(2 * n_chunks), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err);
-    hipLaunchKernelGGL(k_short_heads, dim3(2), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err, g);
+    if (n <= 4 * kOneChunk) hipLaunchKernelGGL(k_short_heads<4>, dim3(2), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err, g);
+    else hipLaunchKernelGGL(k_short_heads<kMaxChunks>, dim3(2), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err, g);
   }
   hipLaunchKernelGGL(k_short_classify, dim3(n <= kOneChunk ? 256 : 2048), dim3(256), 0, s, sd[0], sd[1], (const Counters *)g);
   const uint32_t seq = ++c->pub_seq;
-  hipLaunchKernelGGL(k_short_finish, dim3(2), dim3(kOneChunk), 0, s, n, sd[0], sd[1], c->ins_src, c->ins_dst, c->del_src, c->del_dst,
-                     c->slack, (long long)(c->gin.pool_cap - c->gin.pool_top), (long long)(c->gout.pool_cap - c->gout.pool_top), g,
-                     c->h_gcnt, c->h_gseq, seq);
+#define INK_FINISH(I)                                                                                                              \
+  hipLaunchKernelGGL(k_short_finish<I>, dim3(2), dim3(kOneChunk), 0, s, n, sd[0], sd[1], c->ins_src, c->ins_dst, c->del_src, c->del_dst, \
+                     c->slack, (long long)(c->gin.pool_cap - c->gin.pool_top), (long long)(c->gout.pool_cap - c->gout.pool_top), g, \
+                     c->h_gcnt, c->h_gseq, seq)
+  if (n <= kOneChunk) INK_FINISH(1);
+  else if (n <= 4 * kOneChunk) INK_FINISH(4);
+  else INK_FINISH(kMaxChunks);
+#undef INK_FINISH
   auto apply = [&](const int32_t *ok) {
     hipLaunchKernelGGL(k_apply, dim3(2 * n), dim3(256), 0, s, apply_side_of(sd[0], c->gin, g, C_TOP64, nullptr),
                        apply_side_of(sd[1], c->gout, g, C_TOP64B, c->new_out), n, c->slack, ok);
