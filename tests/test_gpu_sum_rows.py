@@ -1,0 +1,33 @@
+"""Sums of few rows: long rows are taken from 33 neighbours on, in chunks of 1024 that many waves share, and in slices of
+32 columns.  Lengths around both limits and widths around whole slices, over all nodes of a graph that is small enough."""
+import numpy as np
+import pytest
+
+import synth
+from util import Harness
+from test_gpu_edge_cases import tiny_model, INS, DEL
+
+pytestmark = pytest.mark.gpu
+LENGTHS = np.r_[np.arange(0, 300, 7), 31, 32, 33, 63, 64, 65, 127, 128, 129, 1023, 1024, 1025, 2047, 2048, 2049, 3073, 7700]
+
+
+@pytest.mark.parametrize("kind,agg,d", [("sage", "sum", 3), ("sage", "mean", 32), ("gin", "sum", 33), ("sage", "mean", 48), ("gin", "sum", 52),
+                                        ("sage", "mean", 64), ("gcn", "gcn_sym", 97), ("gin", "sum", 128), ("sage", "sum", 250), ("sage", "mean", 301)])
+def test_long_rows_in_short_launches(kind, agg, d):
+    n = 8192
+    rng = np.random.default_rng(d)
+    src = np.concatenate([rng.choice(n - 100, size=k, replace=False) + 100 for k in LENGTHS])
+    dst = np.repeat(np.arange(LENGTHS.size), LENGTHS)
+    src, dst = synth.keys_to_edges(np.unique(synth.edge_keys(src.astype(np.int32), dst.astype(np.int32))))
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    dims = (9, d, 6) if kind == "gcn" else (d, 6)
+    h = Harness(graph=(n, src, dst), X=X[:, :dims[0]].copy(), model=tiny_model(kind, agg, dims, seed=d, hidden=16), precision="f64",
+                dense_threshold=1e-6)
+    h.check_state(exact=False)
+    gone = rng.choice(src.size, size=40, replace=False)               # and with every row summed again after a batch
+    op = np.r_[np.full(40, DEL), np.full(2, INS)].astype(np.uint8)
+    bs = np.r_[src[gone], [5, 6]].astype(np.int32)
+    bd = np.r_[dst[gone], [n - 1, n - 2]].astype(np.int32)
+    h.step(op, bs, bd, exact=False)
+    h.check_state(exact=False)
+    h.ink.close()
