@@ -131,9 +131,11 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
   if (ch && chg && l == 0) mark_bit_s(chg, v);
 }
 
-// Chunks of long rows of at most 48 floats: 12 lanes a row, the 4 waves of a workgroup take a quarter of a chunk each
+// Chunks of long rows of at most 48 floats, or of a table too large for slices to pay (kSlicedTableBytes), as they are: the 4
+// waves of a workgroup take a quarter of a chunk each
+template <int LPR>
 __global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const Counters *cnt, float *part) {
-  constexpr int NW = 4, LPR = 12;
+  constexpr int NW = 4;
   __shared__ float sv[NW][kWave * 4];
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const Counte
   }
 }
 
-// Chunks of wider rows, in slices (bigrows.h).  Whole rows came from beyond the L2 as often as not (GCN of 256 columns
+// Chunks of the other rows, in slices (bigrows.h).  Whole rows came from beyond the L2 as often as not (GCN of 256 columns
 // on 29k nodes with 490 neighbours each, a table of 30 MB: 45M of 89M lines, 7 TB/s, 795 us); a slice of 32 columns stays
 // in an XCD's L2 (4.4M of 97M lines, 661 us, 18.8 TB/s out of the L2s, of which the narrow rows above reach 17 to 24).
 // Inferences: that one 1.43 -> 1.22 ms, 100k nodes with 200 neighbours each and 256 columns 2.50 -> 2.27, GIN of 128
@@ -469,8 +471,8 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   float *part = c->big_part_v.as<float>();
   if (latency)             // few rows: 16 waves a chunk, and its slices in workgroups of their own
     hipLaunchKernelGGL((k_sum_big_slices<16>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, cnt, slices, part);
-  else if (LPR == 12)
-    hipLaunchKernelGGL(k_sum_big_partial, dim3(chunks), dim3(256), 0, c->stream, a, cnt, part);
+  else if (LPR == 12 || (int64_t)a.n * a.ldm * 4 > kSlicedTableBytes)
+    hipLaunchKernelGGL((k_sum_big_partial<LPR>), dim3(chunks), dim3(256), 0, c->stream, a, cnt, part);
   else
     hipLaunchKernelGGL((k_sum_big_slices<4>), dim3(sliced_grid(chunks, slices)), dim3(256), 0, c->stream, a, cnt, slices, part);
   hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)part, chg, compare, cnt);

@@ -86,6 +86,11 @@ __device__ __forceinline__ void big_chunk(const BigRows &b, int n_big, int cg, c
 // parts (slice u / 8, every eighth chunk) one after the other.  An XCD then reads one slice of the message table, or two
 // in turn, instead of all of it, and its L2 holds as many times more rows of it.
 constexpr int kSliceLanes = 8, kSliceCols = 4 * kSliceLanes;
+// Tables up to which long launches of sums go by slices.  Beyond, hardly a row is read twice while it is in an L2, and a
+// row in four or eight parts is as many address translations.  Inferences, slices against whole rows: GIN of 128 columns,
+// 20 edges a node, 1M / 2.5M nodes (1.3 GB) 4.03 / 10.5 ms against 4.11 / 10.6, 5M (2.6 GB) / 10M 22.5 / 46.5 against
+// 22.2 / 45.2; GCN of 256 on 1M (1 GB) 9.45 against 9.55, on 4M (4.1 GB) 21.95 against 21.3.
+constexpr int64_t kSlicedTableBytes = 2ll << 30;
 inline int big_slices(int wd) { return (wd + kSliceCols - 1) / kSliceCols; }
 inline unsigned sliced_grid(unsigned chunks, int slices) { return (chunks * (unsigned)slices + 7u) & ~7u; }    // b % 8 survives the grid stride
 __device__ __forceinline__ int slice_items(int total, int slices) { return ((total + 7) >> 3) * 8 * slices; }

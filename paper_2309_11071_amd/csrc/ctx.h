@@ -288,7 +288,7 @@ struct AggArgs {
   const float *M; int ldm;          // message table
   float *A; int32_t *ARG; int ld;   // aggregated table and argument table (row stride ld)
   float *UB;                        // max/min: bound on the best value among the non-holders (same layout)
-  const uint8_t *in_asc;            // per node: in-list ascending by id (lets ties go to the first seen)
+  const uint8_t *in_asc;            // per node: in-list ascending by id (asked only for rows with infinities or NaN: equal values leave the first its place)
   int32_t *ARG2;                    // max/min: the non-holder that has exactly that value (lowest id), or -1 if not known
   bool keep_empty;                  // recompute of every row: those without neighbours keep what they have unless their bit is set
   int d;                            // columns handled by this launch (<= 256; wider rows go block by block)

@@ -31,3 +31,26 @@ def test_long_rows_in_short_launches(kind, agg, d):
     h.step(op, bs, bd, exact=False)
     h.check_state(exact=False)
     h.ink.close()
+
+
+@pytest.mark.parametrize("d,n", [(64, 2 ** 23 + 9), (128, 2 ** 22 + 9), (256, 2 ** 21 + 9)])
+def test_long_rows_of_a_table_beyond_2_gib(d, n):
+    """Whole rows instead of slices.  Terms are positive and no sum is more than 1024 additions deep in a lane group plus 3
+    waves, 17 chunks and 2 groups: 1100 roundings of 2 ** -24 at most."""
+    from paper_2309_11071_amd import Ink
+    lengths = [1024, 1025, 2047, 2048, 2049, 4097, 33001]
+    rng = np.random.default_rng(d)
+    rowptr = np.zeros(n + 1, np.int64)
+    rowptr[1:len(lengths) + 1] = np.cumsum(lengths)
+    rowptr[len(lengths) + 1:] = rowptr[len(lengths)]
+    col = np.concatenate([np.sort(rng.choice(n - 100, size=k, replace=False) + 100) for k in lengths]).astype(np.int32)
+    base = rng.random((2 ** 14, d), dtype=np.float32)
+    X = np.resize(base, (n, d))
+    ink = Ink(rowptr, col, X, tiny_model("sage", "sum", (d, 3), seed=d))
+    ink.full_infer()
+    got = ink.get_layer(1, 1, 0, len(lengths) + 1)
+    ink.close()
+    for i, k in enumerate(lengths):
+        want = X[col[rowptr[i]:rowptr[i + 1]]].astype(np.float64).sum(0)
+        assert (np.abs(got[i] - want) <= 1100 * 2.0 ** -24 * want).all(), k
+    assert (got[len(lengths)] == 0).all()
