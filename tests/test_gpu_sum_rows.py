@@ -33,6 +33,28 @@ def test_long_rows_in_short_launches(kind, agg, d):
     h.ink.close()
 
 
+@pytest.mark.parametrize("kind,agg,d", [("sage", "sum", 129), ("gin", "sum", 200), ("sage", "mean", 256), ("gcn", "gcn_sym", 250)])
+def test_events_of_wide_rows(kind, agg, d):
+    """Every number of events a target that its last batches can leave over, around the window of 64, of changed, removed
+    and inserted edges."""
+    n, k = 3000, np.r_[np.arange(1, 27), 63, 64, 65, 66, 100, 127]
+    rng = np.random.default_rng(d)
+    src = np.concatenate([rng.choice(200, size=c, replace=False) for c in k])
+    dst = np.repeat(1000 + np.arange(k.size), k)
+    src, dst = synth.keys_to_edges(np.unique(synth.edge_keys(src.astype(np.int32), dst.astype(np.int32))))
+    dims = (9, d, 6) if kind == "gcn" else (d, 12, 6)
+    X = rng.standard_normal((n, dims[0])).astype(np.float32)
+    h = Harness(graph=(n, src, dst), X=X, model=tiny_model(kind, agg, dims, seed=d, hidden=16), precision="f64", dense_threshold=-1)
+    h.feature_step(np.arange(200, dtype=np.int32), rng.standard_normal((200, dims[0])).astype(np.float32), exact=False)
+    h.check_state(exact=False)
+    gone = np.unique(dst, return_index=True)[1]                        # one edge of every target goes and another comes
+    op = np.r_[np.full(k.size, DEL), np.full(k.size, INS)].astype(np.uint8)
+    bs = np.r_[src[gone], 300 + np.arange(k.size)].astype(np.int32)
+    h.step(op, bs, np.r_[dst[gone], dst[gone]].astype(np.int32), exact=False)
+    h.check_state(exact=False)
+    h.ink.close()
+
+
 @pytest.mark.parametrize("d,n", [(64, 2 ** 23 + 9), (128, 2 ** 22 + 9), (256, 2 ** 21 + 9)])
 def test_long_rows_of_a_table_beyond_2_gib(d, n):
     """Whole rows instead of slices.  Terms are positive and no sum is more than 1024 additions deep in a lane group plus 3
