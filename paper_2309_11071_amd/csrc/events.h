@@ -22,15 +22,21 @@ __device__ __forceinline__ void seed_event(int i, const int32_t *del_s, const in
 // out-edges of a changed source that exist in both snapshots: the block minus the ids appended by this batch
 __device__ __forceinline__ int kept_out_degree(const int32_t *deg, const int32_t *new_out, int u) { return deg[u] - new_out[u]; }
 
-// propagated event e: source = the changed node owning it, target = its e-th kept out-neighbour.
-// payload_index: store the position in F instead of the node id.
-__device__ __forceinline__ void expand_event(int e, const int32_t *F, int nF, const int32_t *pref, const int64_t *off,
-                                             const int32_t *ids, int payload_index, uint32_t *key, uint32_t *val) {
+// the changed source that owns propagated event e: the last of those whose prefix is not above it (pref[0] <= e)
+__device__ __forceinline__ int source_of_event(const int32_t *pref, int nF, int e) {
   int lo = 0, hi = nF - 1;
   while (lo < hi) {
     int mid = (lo + hi + 1) >> 1;
     if (pref[mid] <= e) lo = mid; else hi = mid - 1;
   }
+  return lo;
+}
+
+// propagated event e: source = the changed node owning it, target = its e-th kept out-neighbour.
+// payload_index: store the position in F instead of the node id.
+__device__ __forceinline__ void expand_event(int e, const int32_t *F, int nF, const int32_t *pref, const int64_t *off,
+                                             const int32_t *ids, int payload_index, uint32_t *key, uint32_t *val) {
+  const int lo = source_of_event(pref, nF, e);
   int u = F[lo];
   int p = e - pref[lo];
   *key = (uint32_t)ids[off[u] + p];
