@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
   const bool lane_on = 4 * q < a.wd;
   if (n_targets_dev) { int64_t nd = *n_targets_dev; n_targets = nd < n_targets ? nd : n_targets; }
   const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-  const int per = row_block(n_targets, n_waves);
+  const int per = ieee_mode_off(row_block(n_targets, n_waves));
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   int64_t nb = 0, nb_long = 0;
   for (int64_t r0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * per; r0 < n_targets; r0 += n_waves * per) {
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const Counters *
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
-  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG];
+  const int total = ieee_mode_off(cnt->v[C_NCHUNK]), n_big = cnt->v[C_NBIG];
   for (int cg = blockIdx.x; cg < total; cg += gridDim.x) {
     int i, v;
     int64_t j0, j1;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(1024) void k_big_slices(AggArgs a, const Counters *
   __shared__ int si[NW][kSliceCols], sj[NW][kSliceCols];
   const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = l % LPR;
-  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG], items = slice_items(total, slices);
+  const int total = ieee_mode_off(cnt->v[C_NCHUNK]), n_big = cnt->v[C_NBIG], items = slice_items(total, slices);
   for (int b = blockIdx.x; b < items; b += gridDim.x) {
     int cg, slice, i, v;
     int64_t j0, j1;
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void k_agg_events(AggArgs a, const int32_t *ta
   const int l = lane_id();
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
-  const int n = *n_targets_p;
+  const int n = INLINE ? ieee_mode_off(*n_targets_p) : *n_targets_p;      // exposed rows are gathered here
   const int n_blk = (n + ev_block - 1) / ev_block;      // ev_block <= kEvBlock: 1 for short launches, whose targets should not queue behind each other in one wave
   const int n_waves = (int)gridDim.x * (int)(blockDim.x / kWave);
   const int wave0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave));
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targe
   RowSink exp;
   const int l = lane_id(), q = l % LPR, g = l / LPR;
   const bool lane_on = 4 * q < a.wd;
-  const int n = cnt->v[C_NEVL];
+  const int n = INLINE ? ieee_mode_off(cnt->v[C_NEVL]) : cnt->v[C_NEVL];
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const LongSeg L = lng.list[i];
     const int v = targets[L.target];

@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kOneThreads) void k_layer_one(OneLayer p) {
   bool go = p.g->v[C_OK] != 0;
   int nF = 0, n_chg = 0;
   if (p.layer > 1) { go = go && p.chain->done == p.layer - 1; nF = p.chain->n_f; n_chg = p.chain->n_ev; }
-  const int nE = n_ins + n_del + n_chg;
+  const int nE = ieee_mode_off(n_ins + n_del + n_chg);
   go = go && n_chg <= kOneEvents && nE <= kOneEvents && nF <= kOneEvents;
   __syncthreads();                              // all have read the chain record before it is rewritten
   if (go) {                                     // otherwise the counters may be those of a layer that the host continues

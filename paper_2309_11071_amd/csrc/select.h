@@ -110,6 +110,18 @@ template <bool IS_MIN> __device__ __forceinline__ double last_of(double x, doubl
 // no entry: worse than any (a finite double beyond those of the infinities)
 template <bool IS_MIN> __device__ __forceinline__ constexpr int no_entry() { return IS_MIN ? 0x7fe00000 : (int)0xffe00000; }
 
+// A float NaN from 0x7ff00000 (or 0xfff00000) on is a NaN as a double, too.  It is never best: a kernel that gathers turns
+// its IEEE mode off, in which v_max_f64 / v_min_f64 answer a signalling NaN with a quiet one (and the next entry would
+// replace that, the best so far gone) instead of the other operand.  But the worse of it and the best is the best, which
+// stands as its own runner-up from then on, unless a better entry makes that true: gather_row looks for it in the end.
+// The statement passes on a value that the kernel's loop over rows needs and touches nothing else: as a builtin it was a
+// write to memory, after which no load was a scalar one (k_agg_events 151 -> 344 us), as a volatile statement it cost k_big_partial
+// five registers and a wave per SIMD.
+__device__ __forceinline__ int ieee_mode_off(int x) {
+  asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0" : "+s"(x));
+  return x;
+}
+
 template <bool IS_MIN> struct Top2 {
   double b[4], s[4];
   __device__ __forceinline__ void init() {
@@ -243,7 +255,7 @@ __device__ __forceinline__ void gather_row(const int32_t *ids, int n, int win, c
       const bool has = is_entry<IS_MIN>(e[k]);
       v[k] = has ? __int_as_float(hi) : worst<IS_MIN>();
       id[k] = has ? entry_id<IS_MIN>(e[k]) : 0x7fffffff;
-      odd |= has && !better<IS_MIN>(v[k], worst<IS_MIN>());
+      odd |= has && (!better<IS_MIN>(v[k], worst<IS_MIN>()) || (k == 1 && __double2loint(e[0]) == __double2loint(e[1])));
       zero |= hi == 0;
     }
     bv.v[c] = v[0]; bi.v[c] = id[0]; sv.v[c] = v[1]; si.v[c] = id[1];

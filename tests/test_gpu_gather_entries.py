@@ -53,3 +53,41 @@ def test_special_values(agg, d, inf):
             got = ink.get_layer(1, which)
             assert np.array_equal(got.view(np.uint32), want[which - 1].view(np.uint32)), (n, which)
         ink.close()
+
+
+NANS = np.array([0x7f800001, 0x7fc00000, 0x7fe00000, 0x7fefffff, 0x7ff00000, 0x7ff00001, 0x7ff7ffff, 0x7ff80000, 0x7fffffff,
+                 0xff800001, 0xffc00000, 0xffe00000, 0xffefffff, 0xfff00000, 0xfff00001, 0xfff7ffff, 0xfff80000, 0xffffffff], np.uint32).view(F)
+
+
+@pytest.mark.parametrize("agg,d", [("max", 12), ("min", 64), ("max", 128), ("min", 100), ("max", 250), ("min", 300)])
+def test_a_nan_takes_no_place(agg, d):
+    """NaNs of every kind that the bits of a double can be made of (none, quiet, signalling), few, many, and nothing else"""
+    from paper_2309_11071_amd import Ink
+    from paper_2309_11071_amd.binding import make_updates
+    rng = np.random.default_rng(d)
+    lengths = np.r_[np.arange(70), 127, 128, 129, 300, 1030, 3000]
+    for n in (9000, 5000):
+        dst = np.repeat(np.arange(lengths.size), lengths)
+        src = np.concatenate([rng.choice(n - 200, size=k, replace=False) + 200 for k in lengths])
+        rp, col = oracle.csr_from_keys(n, np.unique(synth.edge_keys(src.astype(np.int32), dst.astype(np.int32))))
+        for share in (0.02, 0.5, 1.0):
+            X = rng.standard_normal((n, d)).astype(F)
+            nan = rng.random((n, d)) < share
+            X[nan] = rng.choice(NANS, size=int(nan.sum()))
+            ink = Ink(rp, col, X, tiny_model("sage", agg, (d, 4), seed=3))
+            ink.full_infer()
+            want = reference(rp, col, np.where(np.isnan(X), F(np.inf if agg == "min" else -np.inf), X), agg == "min")
+            for which in (1, 2, 3, 4):
+                got = ink.get_layer(1, which)
+                assert np.array_equal(got.view(np.uint32), want[which - 1].view(np.uint32)), (n, share, which)
+            keys = synth.edge_keys(col, np.repeat(np.arange(n, dtype=np.int32), np.diff(rp)))
+            for size in (20, 400):             # edges that go: rows gathered by the kernels that reduce a target's events
+                gone = rng.choice(keys.size, size=size, replace=False)
+                s, t = synth.keys_to_edges(keys[gone])
+                ink.apply_updates(make_updates(np.full(size, 1, np.uint8), s.astype(np.int32), t.astype(np.int32)))
+                keys = np.delete(keys, gone)
+                want = reference(*oracle.csr_from_keys(n, keys), np.where(np.isnan(X), F(np.inf if agg == "min" else -np.inf), X), agg == "min")
+                for which in (1, 2):
+                    got = ink.get_layer(1, which)
+                    assert np.array_equal(got.view(np.uint32), want[which - 1].view(np.uint32)), (n, share, size, which)
+            ink.close()
