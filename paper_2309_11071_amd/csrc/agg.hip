@@ -360,13 +360,12 @@ static int lanes_per_row(int ld) { return ld <= 64 ? 16 : (ld <= 128 ? 32 : 64);
 
 template <bool IS_MIN, int LPR>
 static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compare, int64_t n_rows_max) {
-  const unsigned chunks = big_partial_grid(c, a.big_grid, latency_mode(n_rows_max));
   if (latency_mode(n_rows_max)) {
     const int slices = big_slices(a.wd);
-    hipLaunchKernelGGL((k_big_slices<IS_MIN>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, (const Counters *)c->d_cnt, slices,
+    hipLaunchKernelGGL((k_big_slices<IS_MIN>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, (const Counters *)c->d_cnt, slices,
                        c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
   } else
-    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(chunks), dim3(256), 0, c->stream, a, (const Counters *)c->d_cnt, c->big_part_v.as<float>(),
+    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, (const Counters *)c->d_cnt, c->big_part_v.as<float>(),
                        c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
   hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)c->big_part_v.as<float>(),
                      (const int32_t *)c->big_part_i.as<int32_t>(), (const float *)c->big_part_s.as<float>(),

@@ -466,15 +466,14 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
   const int slices = big_slices(a.wd);
-  const unsigned chunks = big_partial_grid(c, a.big_grid, latency);
   const Counters *cnt = c->d_cnt;
   float *part = c->big_part_v.as<float>();
   if (latency)             // few rows: 16 waves a chunk, and its slices in workgroups of their own
-    hipLaunchKernelGGL((k_sum_big_slices<16>), dim3(sliced_grid(chunks, slices)), dim3(1024), 0, c->stream, a, cnt, slices, part);
+    hipLaunchKernelGGL((k_sum_big_slices<16>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part);
   else if (LPR == 12 || (int64_t)a.n * a.ldm * 4 > kSlicedTableBytes)
-    hipLaunchKernelGGL((k_sum_big_partial<LPR>), dim3(chunks), dim3(256), 0, c->stream, a, cnt, part);
+    hipLaunchKernelGGL((k_sum_big_partial<LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, cnt, part);
   else
-    hipLaunchKernelGGL((k_sum_big_slices<4>), dim3(sliced_grid(chunks, slices)), dim3(256), 0, c->stream, a, cnt, slices, part);
+    hipLaunchKernelGGL((k_sum_big_slices<4>), dim3(big_grid(c, a.big_chunks, slices, false)), dim3(256), 0, c->stream, a, cnt, slices, part);
   hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)part, chg, compare, cnt);
   return hipGetLastError();
 }

@@ -704,7 +704,7 @@ static AggArgs agg_args(ink_ctx *c, int l) {       // layer l in 1..k
   a.is_min = c->is_min;
   a.nonneg = l > 1 && c->kind != INK_MODEL_GCN && c->layers[l - 2].act == INK_ACT_RELU;
   a.big_deg = kBigDeg;
-  a.big_grid = 2 * c->big_hint[l] + 1024;
+  a.big_chunks = 2 * c->big_hint[l] + 1024;
   a.count_cond = 1;
   a.keep_empty = false;
   a.layer = l;
@@ -1016,7 +1016,7 @@ static hipError_t agg_full_any(ink_ctx *c, const AggArgs &a_in, uint64_t *chg, c
   AggArgs a = a_in;
   if (!targets) {        // every node: the chunk count is bounded by the edge count
     n_targets = c->n;
-    a.big_grid = c->n_edges_now / kBigChunk + std::min<int64_t>(c->n, c->n_edges_now / kBigDeg) + 1;
+    a.big_chunks = c->n_edges_now / kBigChunk + std::min<int64_t>(c->n, c->n_edges_now / kBigDeg) + 1;
   }
   for (int b = 0; b < agg_blocks(a); b++) {
     AggArgs ab = agg_block(a, b);

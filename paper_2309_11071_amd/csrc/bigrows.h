@@ -27,12 +27,19 @@ inline int64_t big_chunk_capacity(const ink_ctx *c) {
   return e / kBigChunk + big_rows_capacity(c);
 }
 
-// one workgroup per expected chunk (the hardware balances them); never fewer than fill the chip
-inline unsigned big_partial_grid(const ink_ctx *c, int64_t want, bool latency) {
-  int64_t lo = latency ? 512 : 2048, hi = big_chunk_capacity(c);
-  if (want < lo) want = lo;
-  if (want > hi) want = hi;
-  return (unsigned)want;
+// Workgroups of a chunk kernel: one per expected chunk and slice (the hardware balances them), no more than there can be,
+// and otherwise at least what fills the chip (1024 threads each in a short launch, 256 in a long one).  A kernel strides over the
+// chunks that are there, so kBigGridMax only keeps the launch below the 2^32 threads that HIP takes: a graph of 2M nodes and 440M
+// edges has 2.1M chunks at most, 17M workgroups of 256 threads in slices of 256 columns.  Multiples of 8, so that b % 8
+// survives the stride.
+constexpr int64_t kBigGridMax = 1 << 20;
+static_assert(kBigGridMax % 8 == 0 && kBigGridMax * 1024 < 1ll << 32, "threads of a launch");
+inline unsigned big_grid(const ink_ctx *c, int64_t chunks, int slices, bool latency) {
+  int64_t n = chunks * slices, least = latency ? 1024 : 2048, most = big_chunk_capacity(c) * slices;
+  if (n < least) n = least;
+  if (n > most) n = most;
+  if (n > kBigGridMax) n = kBigGridMax;
+  return (unsigned)((n + 7) & ~7ll);
 }
 
 // buffers of the long-row path; call before the kernel that fills the list (growing drops contents)
@@ -92,7 +99,6 @@ constexpr int kSliceLanes = 8, kSliceCols = 4 * kSliceLanes;
 // 22.2 / 45.2; GCN of 256 on 1M (1 GB) 9.45 against 9.55, on 4M (4.1 GB) 21.95 against 21.3.
 constexpr int64_t kSlicedTableBytes = 2ll << 30;
 inline int big_slices(int wd) { return (wd + kSliceCols - 1) / kSliceCols; }
-inline unsigned sliced_grid(unsigned chunks, int slices) { return (chunks * (unsigned)slices + 7u) & ~7u; }    // b % 8 survives the grid stride
 __device__ __forceinline__ int slice_items(int total, int slices) { return ((total + 7) >> 3) * 8 * slices; }
 __device__ __forceinline__ bool slice_item(int b, int total, int slices, int &chunk, int &slice) {
   const int per = (total + 7) >> 3, i = b >> 3, j = i / per, u = (b & 7) * slices + j;

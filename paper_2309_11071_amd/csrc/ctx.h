@@ -297,7 +297,7 @@ struct AggArgs {
   bool nonneg;                      // no message has its sign bit set (the layer before ends in ReLU, which gives +0 for every other value)
   int big_deg;                      // rows with more in-neighbours go to the chunked cooperative path
   BigRows big;                      // its list
-  int64_t big_grid;                 // workgroups to launch for the chunk kernel (it strides if there are more chunks)
+  int64_t big_chunks;               // its chunks, about: what the chunk kernel is launched for (it strides if there are more)
   int layer;                        // 1-based layer the launch belongs to (per-kernel timing)
   int count_cond;                   // tally the per-target condition counters (only the first 256-column block of a wide row does)
 };

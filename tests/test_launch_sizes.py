@@ -1,0 +1,37 @@
+"""Host-side check, without a GPU, of the launches of the long-row kernels: HIP takes fewer than 2^32 threads, graphs may have
+some 10^9 edges, and a workgroup of a sliced launch must keep its XCD over the stride of the grid."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r'''
+#include <cstdio>
+#include "bigrows.h"
+int main() {
+  ink_ctx c;
+  const int64_t nodes[] = {1, 100, 8192, 8193, 2000000, 4000000, (1ll << 30) - 1}, per_node[] = {0, 1, 20, 220, 536};
+  for (int64_t n : nodes)
+    for (int64_t p : per_node) {
+      const int64_t edges = n * p < (1ll << 30) - 1 ? n * p : (1ll << 30) - 1;
+      c.n = (int)n; c.n_cap = n; c.n_edges = c.n_edges_now = edges;
+      const int64_t every = edges / ink::kBigChunk + (n < edges / ink::kBigDeg ? n : edges / ink::kBigDeg) + 1;
+      for (int64_t chunks : {int64_t(0), int64_t(1), every, 2 * every})
+        for (int slices = 1; slices <= ink::big_slices(256); slices++)
+          for (int latency = 0; latency < 2; latency++)
+            printf("%lld %d\n", (long long)ink::big_grid(&c, chunks, slices, latency != 0), latency ? 1024 : 256);
+    }
+}
+'''
+
+
+def test_grids_of_the_long_row_kernels(tmp_path):
+    src = tmp_path / "grids.cpp"
+    src.write_text(PROGRAM)
+    exe = tmp_path / "grids"
+    subprocess.check_call(["hipcc", "-std=c++17", "-O0", "--offload-arch=gfx950", "-x", "hip", "-I", os.path.join(ROOT, "paper_2309_11071_amd", "csrc"),
+                           str(src), "-o", str(exe)], stderr=subprocess.DEVNULL)
+    rows = [tuple(map(int, line.split())) for line in subprocess.check_output([str(exe)], text=True).splitlines()]
+    assert len(rows) > 1000
+    for groups, threads in rows:
+        assert 0 < groups and groups % 8 == 0 and groups * threads < 2 ** 32
+    assert max(g for g, _ in rows) > 2 ** 19               # the bound does not touch what graphs of usual sizes launch
