@@ -704,7 +704,7 @@ static AggArgs agg_args(ink_ctx *c, int l) {       // layer l in 1..k
   a.is_min = c->is_min;
   a.nonneg = l > 1 && c->kind != INK_MODEL_GCN && c->layers[l - 2].act == INK_ACT_RELU;
   a.big_deg = kBigDeg;
-  a.big_chunks = 2 * c->big_hint[l] + 1024;
+  a.big_chunks = 2 * c->big_hint[l];
   a.count_cond = 1;
   a.keep_empty = false;
   a.layer = l;

@@ -18,7 +18,7 @@ int main() {
       for (int64_t chunks : {int64_t(0), int64_t(1), every, 2 * every})
         for (int slices = 1; slices <= ink::big_slices(256); slices++)
           for (int latency = 0; latency < 2; latency++)
-            printf("%lld %d\n", (long long)ink::big_grid(&c, chunks, slices, latency != 0), latency ? 1024 : 256);
+            printf("%lld %lld %d\n", (long long)chunks, (long long)ink::big_grid(&c, chunks, slices, latency != 0), latency ? 1024 : 256);
     }
 }
 '''
@@ -32,6 +32,8 @@ def test_grids_of_the_long_row_kernels(tmp_path):
                            str(src), "-o", str(exe)], stderr=subprocess.DEVNULL)
     rows = [tuple(map(int, line.split())) for line in subprocess.check_output([str(exe)], text=True).splitlines()]
     assert len(rows) > 1000
-    for groups, threads in rows:
+    for chunks, groups, threads in rows:
         assert 0 < groups and groups % 8 == 0 and groups * threads < 2 ** 32
-    assert max(g for g, _ in rows) > 2 ** 19               # the bound does not touch what graphs of usual sizes launch
+        if chunks == 0:                                    # usually there are none: nothing but an empty launch
+            assert groups * threads <= 2 ** 20
+    assert max(g for _, g, _ in rows) > 2 ** 19               # the bound does not touch what graphs of usual sizes launch
