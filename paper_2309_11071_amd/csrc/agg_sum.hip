@@ -455,8 +455,8 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   a.big_deg = big_threshold(n_targets, LPR, kBigDegSum);
   int compare = chg != nullptr;
   INK_TRY(ensure_big_buffers(c, a.wd, false));
-  const bool latency = latency_mode(n_targets);
-  a.big = big_rows_of(c, latency ? kBigChunk : kBigChunkSum);
+  const bool latency = latency_mode(n_targets), whole = LPR == 12 || (int64_t)a.n * a.ldm * 4 > kSlicedTableBytes;
+  a.big = big_rows_of(c, latency || whole ? kBigChunk : kBigChunkSum);
   INK_TRY(clear_big_rows(c));
   {
     KernelTimer kt(c, a.layer, INK_K_AGG_FULL);
@@ -470,7 +470,7 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   float *part = c->big_part_v.as<float>();
   if (latency)             // few rows: 16 waves a chunk, and its slices in workgroups of their own
     hipLaunchKernelGGL((k_sum_big_slices<16>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part);
-  else if (LPR == 12 || (int64_t)a.n * a.ldm * 4 > kSlicedTableBytes)
+  else if (whole)
     hipLaunchKernelGGL((k_sum_big_partial<LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, cnt, part);
   else
     hipLaunchKernelGGL((k_sum_big_slices<4>), dim3(big_grid(c, a.big_chunks, slices, false)), dim3(256), 0, c->stream, a, cnt, slices, part);

@@ -38,9 +38,11 @@ constexpr int kBigChunk = INK_BIG_CHUNK;  // neighbours per chunk of such a row
 #ifndef INK_BIG_CHUNK_SUM
 #define INK_BIG_CHUNK_SUM 2048
 #endif
-// ... in long launches of sums.  1024 / 2048 / 4096, inference: GCN of 256 columns on 29k nodes, 490 neighbours each, 1.25 /
-// 1.22 / 1.22 ms, on 100k nodes, 200 each, 2.30 / 2.27 / 2.22; GIN of 128 on 400k, 20 each, 1.33 / 1.31 / 1.32, on 20k,
-// 50 each, .204 / .202 / .213.  Max / min at 2048 lose: 60k nodes, 50 each, .480 -> .506.
+// ... in long launches of sums that go by slices, whose lane groups add 64 rows in a chain.  1024 / 2048 / 4096, inference: GCN of
+// 256 columns on 29k nodes, 490 neighbours each, 1.25 / 1.22 / 1.22 ms, on 100k nodes, 200 each, 2.30 / 2.27 / 2.22; GIN of 128 on
+// 400k, 20 each, 1.33 / 1.31 / 1.32, on 20k, 50 each, .204 / .202 / .213.  Whole rows keep 1024: with 2048 their chains are twice as
+// long, and the error of a long row against 64 bits grew by a fifth to two fifths (41 columns 1.34e-7 -> 1.61e-7, 256 columns of a table
+// beyond 2 GB 2.9e-7 -> 4.0e-7; slices 1.6e-7).  Max / min at 2048 lose: 60k nodes, 50 each, .480 -> .506.
 constexpr int kBigChunkSum = INK_BIG_CHUNK_SUM;
 static_assert(kBigChunk <= kBigChunkSum, "buffer bounds of the long-row path use the smaller chunk");
 #ifndef INK_BIG_DEG_SUM
