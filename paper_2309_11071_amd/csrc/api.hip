@@ -121,8 +121,11 @@ static void make_events(const SortPlan &p, const EventInputs &in, uint32_t *key,
 #undef INK_MAKE
 }
 
-// The record; on the way the marks of a batch that ends with it are cleared: zero_at[0 .. n_zero) of `zero`.
+// The record; on the way the marks of a batch that ends with it are cleared: zero_at[0 .. n_zero) of `zero`.  That is one
+// workgroup's chain, .7 us per 1000 marks, and a launch of k_zero_at in front of the record instead takes 2.3 us and a gap: from
+// some 5000 marks on it is the shorter (10000 / 50000 / 1M marks 10 / 26 / 295 us in the record).
 constexpr int kPublishThreads = 512;
+constexpr int64_t kPublishMarks = 4096;
 __global__ __launch_bounds__(kPublishThreads) void k_publish(const Counters *d, HostCounters *h, uint32_t *h_seq, uint32_t seq,
                                                              const int32_t *zero_at, int n_zero, int32_t *zero) {
   if (n_zero > 0) {                     // nothing is written after the record
@@ -662,6 +665,10 @@ static void prof_collect(ink_ctx *c) {
 }
 
 hipError_t ink::read_counters(ink_ctx *c, bool end_batch) {
+  if (end_batch && c->n_touched_src > kPublishMarks) {
+    const hipError_t e = graph_end_batch(c);
+    if (e != hipSuccess) return e;
+  }
   const uint32_t seq = ++c->pub_seq;
   const int n_zero = end_batch ? (int)c->n_touched_src : 0;
   if (end_batch) c->n_touched_src = 0;
