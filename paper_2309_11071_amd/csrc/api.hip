@@ -1113,6 +1113,7 @@ extern "C" ink_status ink_full_infer(ink_ctx *c) {
 extern "C" ink_status ink_full_infer_noalloc(ink_ctx *c) {
   if (!c) return INK_E_ARG;
   if (c->broken) return fail(c, INK_E_STATE, kBrokenMsg);
+  begin_result(c);
   void *base = c->scratch;
   if (!base) return fail(c, INK_E_DEVICE, "ink_full_infer_noalloc: the scratch array's address was not found at ink_create");
   // what the full inference reserves, from the same bounds its kernels' launchers use
@@ -1149,7 +1150,6 @@ extern "C" ink_status ink_full_infer_noalloc(ink_ctx *c) {
     bufs[i]->fixed = true;
     used += sizes[i];
   }
-  begin_result(c);
   const int profile = c->profile;
   c->profile = 0;                    // HIP events are created on demand: not in this call
   ink_status st = full_infer_impl(c);

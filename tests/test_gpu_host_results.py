@@ -50,3 +50,44 @@ def test_results_on_the_host(agg, dout):
     with pytest.raises(InkError):
         h.ink._fetch(0)
     h.ink.close()
+
+
+@pytest.mark.parametrize("refused", ["op", "id", "feature id", "infer"])
+def test_nothing_is_left_behind_a_refused_call(refused):
+    """A call that tried to change the context and was refused takes the last result with it, as the header says."""
+    n = 300
+    rng = np.random.default_rng(4)
+    dst = np.arange(1, n, dtype=np.int32)
+    h = Harness(graph=(n, dst - 1, dst), X=rng.standard_normal((n, 4)).astype(np.float32), model=tiny_model("sage", "max", (4, 3), seed=1))
+    r = h.ink.apply_updates(make_updates([INS], [5], [3]))
+    assert r["n_changed"] > 0
+    h.ink._fetch(r["n_changed"])                             # as often as one likes
+    if refused == "infer":
+        h.ink.full_infer_noalloc()
+    else:
+        with pytest.raises(InkError):
+            if refused == "feature id":
+                h.ink.update_features(np.array([n], np.int32), np.ones((1, 4), np.float32))
+            else:
+                h.ink.apply_updates(make_updates([2 if refused == "op" else INS], [5], [n if refused == "id" else 4]))
+    with pytest.raises(InkError) as e:
+        h.ink._fetch(r["n_changed"])
+    assert e.value.status == 2
+    h.ink.close()
+
+
+def test_nothing_is_left_behind_a_refused_inference():
+    from paper_2309_11071_amd import Ink
+    n, rng = 200_000, np.random.default_rng(5)               # staging rows of 128 floats for every node: more than the static array holds
+    dst = np.arange(1, n, dtype=np.int32)
+    ink = Ink(*synth.in_csr_from_edges(n, dst - 1, dst), rng.standard_normal((n, 4)).astype(np.float32), tiny_model("gin", "sum", (4, 3), seed=1, hidden=128))
+    ink.full_infer()
+    r = ink.update_features(np.arange(4, dtype=np.int32), np.ones((4, 4), np.float32))
+    assert r["n_changed"] > 0
+    with pytest.raises(InkError) as e:
+        ink.full_infer_noalloc()
+    assert e.value.status == 5
+    with pytest.raises(InkError) as e:
+        ink._fetch(r["n_changed"])
+    assert e.value.status == 2
+    ink.close()
