@@ -758,8 +758,8 @@ static hipError_t run_transform(ink_ctx *c, int l, const int32_t *rows, int64_t 
 }
 
 // ------------------------------------------------------------------------------------ static work memory
-// Work memory of ink_full_infer_noalloc: the list of long rows, its chunk prefix, the partial rows
-// of the chunks, the block sums of the scan that plans them and GIN's staging rows.  One array per
+// Work memory of ink_full_infer_noalloc: the list of long rows, the first chunk of each, the partial
+// rows of the chunks and GIN's staging rows.  One array per
 // GPU for the life of the process, shared by every call on that GPU.  Nothing in it has to start
 // from zero: every part is written by the launch that reads it afterwards.
 static __device__ __align__(256) unsigned char scratch[INK_NOALLOC_SCRATCH_BYTES];
@@ -1126,9 +1126,8 @@ extern "C" ink_status ink_full_infer_noalloc(ink_ctx *c) {
   const size_t pref_b = align256((list_b / 4 + 1) * 4);
   const size_t part_b = align256((size_t)big_chunk_capacity(c) * wd_max * 4);
   const int n_part = c->is_select ? 4 : 1;
-  const size_t blk_b = align256((size_t)nblocks((int64_t)(list_b / 4), kScanTile) * 4);
   const size_t stage_b = align256((size_t)c->n * n1p_max * 4);
-  const size_t need = list_b + pref_b + (size_t)n_part * part_b + blk_b + stage_b;
+  const size_t need = list_b + pref_b + (size_t)n_part * part_b + stage_b;
   if (need > (size_t)INK_NOALLOC_SCRATCH_BYTES) {
     char msg[256];
     snprintf(msg, sizeof(msg), "ink_full_infer_noalloc: this graph and model need %zu bytes of work memory, the static "
@@ -1137,9 +1136,9 @@ extern "C" ink_status ink_full_infer_noalloc(ink_ctx *c) {
   }
   // lend the carve-outs to the buffers the kernels' launchers use, run, and put the owners back
   DevBuf *bufs[] = {&c->big_list, &c->big_pref, &c->big_part_v, &c->big_part_i, &c->big_part_s, &c->big_part_j,
-                    &c->ws.blk, &c->stage0};
+                    &c->stage0};
   const size_t sizes[] = {list_b, pref_b, part_b, c->is_select ? part_b : 0, c->is_select ? part_b : 0,
-                          c->is_select ? part_b : 0, blk_b, stage_b};
+                          c->is_select ? part_b : 0, stage_b};
   constexpr int NB = sizeof(bufs) / sizeof(bufs[0]);
   DevBuf saved[NB];
   size_t used = 0;

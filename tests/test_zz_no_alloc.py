@@ -75,3 +75,22 @@ def test_no_alloc_rejects_what_does_not_fit():
     assert np.array_equal(before, ink.get_layer(2, 0))      # refused before anything ran
     ink.full_infer()                                         # the context stays usable
     ink.close()
+
+
+@pytest.mark.parametrize("kind,agg,d,hidden", [("gin", "sum", 16, 128), ("gin", "mean", 20, 100)])
+def test_no_alloc_needs_what_the_header_says(kind, agg, d, hidden):
+    """The need that a refusal names."""
+    import re
+    from paper_2309_11071_amd import Ink, InkError
+    n, rng = 200_000, np.random.default_rng(d)
+    dst = np.sort(rng.integers(0, n, 50_000)).astype(np.int32)
+    rp, col = synth.in_csr_from_edges(n, ((dst + 1 + rng.integers(0, 9, dst.size)) % n).astype(np.int32), dst)
+    cfg = synth.WorkloadConfig(4, "t", kind, agg, n, 1, False, (d, 16, 16), hidden, 2, False)
+    ink = Ink(rp, col, rng.standard_normal((n, d)).astype(np.float32), synth.make_model(cfg))
+    with pytest.raises(InkError) as e:
+        ink.full_infer_noalloc()
+    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    R, hid = min(n, max(col.size // 256, 8192)) + 1, (hidden + 31) // 32 * 32
+    need = up(4 * R) + up(up(4 * R) + 4) + up(((d + 3) // 4 * 4) * (col.size // 1024 + R) * 4) + up(4 * n * hid)
+    assert int(re.search(r"need (\d+) bytes", str(e.value)).group(1)) == need
+    ink.close()
