@@ -234,8 +234,9 @@ ink_status ink_apply_updates(ink_ctx *ctx, const ink_edge_update *updates, int64
 
 /* The result of the last call that returned one (ink_apply_updates, ink_apply_updates_affected, ink_update_features,
  * ink_apply_user_events, ink_add_nodes), copied to host memory: n ids and n rows of the last layer's width, n being that
- * result's n_changed.  For callers who want every result on the host: from the first such call on, modest results
- * (INK_RESULT_HOST_BYTES) are written to pinned memory by the kernel that gathers them, until one of them is not asked for.
+ * result's n_changed.  For callers who want every result on the host: from the first such call on, and in a context
+ * whose batches are in host memory from the start, modest results (INK_RESULT_HOST_BYTES) are written to pinned memory by the
+ * kernel that gathers them, until one of them is not asked for.
  * Errors: INK_E_STATE if there is none or another call that changes the context (or tried to) has come since,
  * INK_E_ARG if n is another number. */
 #define INK_RESULT_HOST_BYTES (1u << 20)

@@ -227,7 +227,7 @@ struct ink_ctx {
 
   // the last result (n < 0: none), and its copy in pinned memory: where the kernel that gathers a result writes it, too
   struct Result { const int32_t *ids = nullptr; const float *rows = nullptr; int64_t n = -1; } last;
-  char *h_res = nullptr;             // INK_RESULT_HOST_BYTES, allocated by the first ink_copy_result
+  char *h_res = nullptr;             // INK_RESULT_HOST_BYTES, allocated with a context for batches in host memory, otherwise by the first ink_copy_result
   bool mirror = false;               // results are asked for on the host
   bool mirrored = false;             // the last one was written there if it fits
   bool fetched = true;               // ... and has been asked for
