@@ -610,8 +610,9 @@ static void begin_result(ink_ctx *c) {
   c->last.n = -1;
   c->mirrored = c->fetched = false;
 }
-static hipError_t reserve_host_results(ink_ctx *c) {
-  return c->h_res ? hipSuccess : hipHostMalloc((void **)&c->h_res, INK_RESULT_HOST_BYTES, hipHostMallocCoherent);
+static void want_host_results(ink_ctx *c) {      // without the pinned memory results are copied
+  if (!c->h_res && hipHostMalloc((void **)&c->h_res, INK_RESULT_HOST_BYTES, hipHostMallocCoherent) != hipSuccess) { c->h_res = nullptr; (void)hipGetLastError(); }
+  c->mirror = c->h_res != nullptr;
 }
 static ink_status end_result(ink_ctx *c, ink_status st, const ink_update_result *out) {
   if (st == INK_OK) { c->last.ids = out->changed_ids; c->last.rows = out->embeddings; c->last.n = out->n_changed; }
@@ -902,11 +903,9 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
     c->h_batch = reinterpret_cast<ink_edge_update *>(h + kRecords);
     CREATE_TRY(hipMalloc(&c->d_chain, sizeof(Chain)));
   }
-  if (!c->batch_dev) {      // who hands batches over in host memory wants results there, and the first one, too: first pass of
-                            // 100 updates and their inverse, 10k nodes 1.15 -> .93 ms, 333 on 87k nodes 1.86 -> 1.45
-    CREATE_TRY(reserve_host_results(c));
-    c->mirror = true;
-  }
+  // Who hands batches over in host memory wants results there, and the first one, too: first pass of 100 updates and
+  // their inverse, 10k nodes, 1.15 -> .93 ms, 333 on 87k nodes 1.86 -> 1.45.
+  if (!c->batch_dev) want_host_results(c);
   size_t bmw = ((size_t)nc + 63) / 64;
   CREATE_TRY(hipMalloc(&c->bm_a, bmw * 8));
   CREATE_TRY(hipMemset(c->bm_a, 0, bmw * 8));
@@ -2085,8 +2084,7 @@ extern "C" ink_status ink_copy_result(ink_ctx *c, int32_t *ids, float *embedding
   if (c->last.n < 0) return fail(c, INK_E_STATE, "ink_copy_result: the last call left no result");
   if (n != c->last.n || (n > 0 && (!ids || !embeddings))) return fail(c, INK_E_ARG, "ink_copy_result: NULL argument or not the result's size");
   c->fetched = true;
-  if (reserve_host_results(c) != hipSuccess) { c->h_res = nullptr; (void)hipGetLastError(); }
-  c->mirror = c->h_res != nullptr;
+  want_host_results(c);
   if (n == 0) return INK_OK;
   const size_t row = (size_t)c->H[c->n_layers].d * 4;
   if (c->mirrored && n <= c->mirror_rows()) {
