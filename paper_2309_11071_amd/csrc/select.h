@@ -15,18 +15,9 @@ template <bool IS_MIN> __device__ __forceinline__ bool better(float x, float y) 
 template <bool IS_MIN> __device__ __forceinline__ float worst() {
   return IS_MIN ? __builtin_huge_valf() : -__builtin_huge_valf();
 }
-// lexicographic: better value first, lower id on equal value
-template <bool IS_MIN> __device__ __forceinline__ void take(float x, int id, float &bv, int &bi) {
-  if (better<IS_MIN>(x, bv) || (x == bv && id < bi)) { bv = x; bi = id; }
-}
-
 template <bool IS_MIN> __device__ __forceinline__ float best_of(float x, float y) { return better<IS_MIN>(x, y) ? x : y; }
-// the same with the runner-up value sv (best value among the entries that are not the holder)
-template <bool IS_MIN> __device__ __forceinline__ void take2(float x, int id, float &bv, int &bi, float &sv) {
-  if (better<IS_MIN>(x, bv) || (x == bv && id < bi)) { sv = bv; bv = x; bi = id; }
-  else if (better<IS_MIN>(x, sv)) sv = x;
-}
-// merge of the triples of two disjoint sets
+// merge of two disjoint sets, each with its best value, that one's id and its runner-up value sv (best among the others);
+// better value first, lower id on equal value
 template <bool IS_MIN> __device__ __forceinline__ void merge2(float ov, int oi, float os, float &bv, int &bi, float &sv) {
   float loser;
   if (better<IS_MIN>(ov, bv) || (ov == bv && oi < bi)) { loser = bv; bv = ov; bi = oi; }
@@ -261,7 +252,9 @@ __device__ __forceinline__ void gather_row(const int32_t *ids, int n, int win, c
     bv.v[c] = v[0]; bi.v[c] = id[0]; sv.v[c] = v[1]; si.v[c] = id[1];
   }
   if (!nonneg) {
-    if (__ballot(zero && lane_on) != 0ull) {        // the sign of a zero
+    // The sign of a zero, from the row it came from, which is in the L2 still.  Features with many zeros pay for it, inference
+    // against features without: 625k nodes and rows of 128 floats 1.24 ms against 1.22, 200k and 64 floats .298 against .285.
+    if (__ballot(zero && lane_on) != 0ull) {
       const float *m = M + 4 * q;
 #pragma unroll
       for (int c = 0; c < 4; c++)
