@@ -373,10 +373,11 @@ static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compa
   return hipGetLastError();
 }
 
-// Workgroups of a recompute launch, whose waves stride over the rows.  With a wave per row half of the chip's places
-// for waves stood empty (3.8 of 8 per SIMD: a workgroup waits until all its places are free, and its rows differ in
-// length), with as many waves as the chip holds the last long rows are a tail: inference of 625k nodes, 3 layers of
-// 128 floats, 2048 / 4096 / 16384 / 65536 workgroups / a wave per row 4.89 / 4.60 / 4.53 / 4.59 / 4.71 ms.
+// Workgroups of a recompute launch, whose waves stride over the rows in blocks of up to 16.  The kernel has 94 to 103
+// registers, 4 or 5 waves per SIMD: 2048 workgroups at most are on the chip together.  As many as that leave the last long rows as a
+// tail, and many more have a row or three a wave and nothing from the blocks.  2048 / 4096 / 8192 / 16384 / 65536 workgroups / a
+// wave per row, inference: 625k nodes, 3 layers of 128 floats, 4.16 / 4.07 / 4.00 / 4.00 / 4.11 / 4.54 ms, 200k nodes of 64
+// floats .562 / .563 / .543 / .549 / .638 / .641, 100k of 256 .963 / .939 / .931 / .929 / .967 / .963.
 constexpr int64_t kFullGrid = 16384;
 
 template <bool IS_MIN, int LPR>

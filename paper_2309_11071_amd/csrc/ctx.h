@@ -14,8 +14,10 @@ namespace ink {
 #ifndef INK_BIG_DEG
 #define INK_BIG_DEG 256
 #endif
-// neighbour rows in flight per lane group while gathering, by aggregator family and, for max / min, lanes per row.  8 where the
-// registers allow: for max / min over rows of 128 floats 8 take 84 and cost 3 % (625k nodes, inference: 5.15 against 4.99 ms).
+// Neighbour rows in flight per lane group while gathering, by aggregator family and, for max / min, lanes per row.  8 where they
+// gain anything: for max / min over rows of 64 floats they cost 3 % (200k nodes, inference: .549 -> .566 ms; 109 instead of 94
+// registers), over 128 floats nothing is gained (625k nodes 4.00 and 4.01 ms), over 256 floats 4 instead of 8 cost 1 % (100k
+// nodes .929 -> .940).
 #ifndef INK_U_SEL8
 #define INK_U_SEL8 4
 #endif

@@ -6,8 +6,8 @@
 // everything before the first use.  So a slot past the end repeats the last row (it is in the L1) and its value is
 // dropped where it is used, and lanes past the row's end read its start.  Measured against conditional loads, whole
 // passes: 116k-node GCN with 57M edges 3.53 -> 3.34 ms, 3-layer max on 1.25M nodes 9.81 -> 9.53, its inference on 625k
-// nodes 5.18 -> 4.99.  There the short rows (6.9M of 12.5M edges, four tables written) move 5.8 TB/s a layer and the long ones
-// 8.5 TB/s out of the caches, so what is left is the memory's.
+// nodes 5.18 -> 4.99.  There the short rows (6.7M of 12.5M edges, four tables written) now move 7.8 TB/s a layer and the long ones
+// 9.4 TB/s, out of the caches in part, so what is left is the memory's.
 #pragma once
 #include "ctx.h"
 
