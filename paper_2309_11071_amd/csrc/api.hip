@@ -281,9 +281,12 @@ __global__ __launch_bounds__(THREADS) void k_small_emit(const uint8_t *flag, con
   if (threadIdx.x < kWave) publish_wave(cnt, h, h_seq, seq);
 }
 
-__global__ void k_mark_nodes(const int32_t *list, int n, const int32_t *list2, int n2, uint64_t *bm) {
+// Sets the bits of the listed nodes; with deg only of those that have no edge left.
+__global__ void k_mark_nodes(const int32_t *list, int n, const int32_t *list2, int n2, uint64_t *bm, const int32_t *deg) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n + n2) { int v = i < n ? list[i] : list2[i - n]; atomicOr((unsigned long long *)&bm[v >> 6], 1ull << (v & 63)); }
+  if (i >= n + n2) return;
+  const int v = i < n ? list[i] : list2[i - n];
+  if (!deg || deg[v] == 0) atomicOr((unsigned long long *)&bm[v >> 6], 1ull << (v & 63));
 }
 
 // The changed rows of a long layer: their positions, their ids and the prefix of the events they propagate, in one scan
@@ -1219,8 +1222,12 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
   if (dense) {
     // so many events that re-aggregating every node costs less than grouping them (Sec. 5.1)
     Prof p(c, INK_T_AGG);
-    if (c->is_select) {      // rows without neighbours are empty already, but for those that lost theirs: their bits are set beforehand
-      if (n_del > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n_del), dim3(256), 0, s, (const int32_t *)c->del_dst, (int)n_del, (const int32_t *)nullptr, 0, bm);
+    // Rows without neighbours are empty already, but for those that lost theirs: their bits are set beforehand
+    // (and their rows transformed, even if they had aggregated to 0).  Of others only what changed may be marked, and in the baseline,
+    // where a marked node propagates whether or not it changed, of these, too.
+    if (c->is_select && !c->affected_mode) {
+      if (n_del > 0)
+        hipLaunchKernelGGL(k_mark_nodes, grid1(n_del), dim3(256), 0, s, (const int32_t *)c->del_dst, (int)n_del, (const int32_t *)nullptr, 0, bm, (const int32_t *)c->gin.deg);
       a.keep_empty = true;
     }
     API_TRY(agg_full_any(c, a, bm));
@@ -1281,7 +1288,7 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
       nT = c->h_cnt->v[C_NT];
     }
     API_TRY(agg_full_any(c, a, bm, c->t_list.as<int32_t>(), nT));
-    if (nT > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(nT), dim3(256), 0, s, (const int32_t *)c->t_list.as<int32_t>(), (int)nT, (const int32_t *)nullptr, 0, bm);
+    if (nT > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(nT), dim3(256), 0, s, (const int32_t *)c->t_list.as<int32_t>(), (int)nT, (const int32_t *)nullptr, 0, bm, (const int32_t *)nullptr);
     API_TRY(hipGetLastError());
     return INK_OK;
   }
@@ -1359,7 +1366,7 @@ static ink_status collect_rows(ink_ctx *c, const int32_t *extra0, int64_t n0, co
     API_TRY(hipGetLastError());
     if (flags_cleared) *flags_cleared = true;
   } else {
-    if (n0 + n1 > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n0 + n1), dim3(256), 0, s, extra0, (int)n0, extra1, (int)n1, c->bm_a);
+    if (n0 + n1 > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n0 + n1), dim3(256), 0, s, extra0, (int)n0, extra1, (int)n1, c->bm_a, (const int32_t *)nullptr);
     API_TRY(bitmap_to_list(c->ws, c->bm_a, c->n, c->c_list.as<int32_t>(), &c->d_cnt->v[C_NC], 1, s));
   }
   if (bound >= 0) { *nC = bound; return INK_OK; }

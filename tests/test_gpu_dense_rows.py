@@ -32,3 +32,25 @@ def test_rows_without_neighbours(agg, d, n):
         h.step((1 - op)[::-1].copy(), bs[::-1].copy(), bd[::-1].copy())
         h.check_state(); h.check_bound(max_nodes=n)
     h.ink.close()
+
+
+@pytest.mark.parametrize("affected", [False, True])
+def test_a_dense_layer_passes_on_what_changed(affected):
+    """Targets that lose edges without effect are not counted among the nodes whose aggregate changed: an update transforms the
+    rows that changed and no others, the baseline propagates from these and the changed edges' sources alone."""
+    n, hubs, rng = 4000, 50, np.random.default_rng(1)
+    src = np.concatenate([np.r_[3000 + i, rng.choice(np.arange(100, 2900), size=20, replace=False)] for i in range(hubs)])
+    dst = np.repeat(np.arange(hubs), 21)
+    src, dst = synth.keys_to_edges(np.unique(synth.edge_keys(src.astype(np.int32), dst.astype(np.int32))))
+    X = rng.random((n, 8)).astype(np.float32)
+    X[3000:3000 + hubs] = 9.0                                # one neighbour of every hub holds all of its dimensions
+    h = Harness(graph=(n, src, dst), X=X, model=tiny_model("sage", "max", (8, 6, 3), seed=1), dense_threshold=1e-6)
+    low = np.flatnonzero(src < 2900)
+    low = low[np.unique(dst[low], return_index=True)[1]]     # one edge of every hub that holds nothing
+    top = np.flatnonzero((src >= 3000) & (dst < 7))          # and what holds everything of seven of them
+    gone = np.r_[low, top]
+    h.step(np.full(gone.size, DEL, np.uint8), src[gone].astype(np.int32), dst[gone].astype(np.int32), affected=affected)
+    L = h.ink.stats()["layers"]
+    assert L[0]["dense"] and L[0]["n_transformed"] == 7 and L[0]["n_changed"] == 7 and L[1]["n_sources"] == 7
+    h.check_state()
+    h.ink.close()
