@@ -91,3 +91,24 @@ def test_a_nan_takes_no_place(agg, d):
                     got = ink.get_layer(1, which)
                     assert np.array_equal(got.view(np.uint32), want[which - 1].view(np.uint32)), (n, share, size, which)
             ink.close()
+
+
+def test_no_nan_behind_a_relu():
+    """What lets the gathers of later layers look for none: rows of a layer that ends in ReLU have no NaN and no sign bit, in an inference
+    and in updates of few and of many rows."""
+    from paper_2309_11071_amd import Ink
+    n, d, rng = 5000, 12, np.random.default_rng(2)
+    dst = rng.integers(0, n, 4 * n).astype(np.int32)
+    src = ((dst + 1 + rng.integers(0, n - 1, dst.size)) % n).astype(np.int32)
+    X = rng.standard_normal((n, d)).astype(F)
+    X[rng.random((n, d)) < 0.05] = NANS[0]
+    ink = Ink(*oracle.csr_from_keys(n, np.unique(synth.edge_keys(src, dst))), X, tiny_model("sage", "max", (d, 8, 4), seed=3))
+    ink.full_infer()
+    for rows in (0, 3, 2000):
+        if rows:
+            Y = rng.standard_normal((rows, d)).astype(F)
+            Y[rng.random((rows, d)) < 0.2] = rng.choice(NANS)
+            ink.update_features(rng.choice(n, size=rows, replace=False).astype(np.int32), Y)
+        got = ink.get_layer(1, 0)
+        assert not np.isnan(got).any() and not np.signbit(got).any() and (got > 0).any()
+    ink.close()
