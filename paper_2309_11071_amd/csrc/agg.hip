@@ -373,7 +373,7 @@ static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compa
   return hipGetLastError();
 }
 
-// Workgroups of a recompute launch, whose waves stride over the rows in blocks of up to 16.  The kernel has 94 to 103
+// Workgroups of a recompute launch, whose waves stride over the rows in blocks of up to 16.  The kernel has 94 to 105
 // registers, 4 or 5 waves per SIMD: 2048 workgroups at most are on the chip together.  As many as that leave the last long rows as a
 // tail, and many more have a row or three a wave and nothing from the blocks.  2048 / 4096 / 8192 / 16384 / 65536 workgroups / a
 // wave per row, inference: 625k nodes, 3 layers of 128 floats, 4.16 / 4.07 / 4.00 / 4.00 / 4.11 / 4.54 ms, 200k nodes of 64
