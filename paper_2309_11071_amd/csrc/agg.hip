@@ -84,18 +84,15 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
 
 // cooperative path for rows with more than kBigDeg in-neighbours: a workgroup per chunk of
 // kBigChunk neighbours (its 4 waves take a quarter each), partial rows to scratch
-template <bool IS_MIN, int LPR>
-__global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const Counters *cnt, float *part_v, int32_t *part_i,
-                                                     float *part_s, int32_t *part_j) {
-  constexpr int NW = 4;
-  __shared__ float sv[NW][kWave * 4];
-  __shared__ int si[NW][kWave * 4];
-  __shared__ float ss[NW][kWave * 4];
-  __shared__ int sj[NW][kWave * 4];
+struct BigParts { float *v; int32_t *i; float *s; int32_t *j; };     // best, its id, runner-up, its id: a row per chunk
+
+// whole rows: the NW waves of a workgroup take a part of a chunk each
+template <bool IS_MIN, int LPR, int NW>
+__device__ __forceinline__ void whole_chunks(const AggArgs &a, int total, int n_big, float (*sv)[kWave * 4], int (*si)[kWave * 4], float (*ss)[kWave * 4],
+                                             int (*sj)[kWave * 4], const BigParts &part) {
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
-  const int total = ieee_mode_off(cnt->v[C_NCHUNK]), n_big = cnt->v[C_NBIG];
   for (int cg = blockIdx.x; cg < total; cg += gridDim.x) {
     int i, v;
     int64_t j0, j1;
@@ -120,7 +117,7 @@ __global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const Counters *
         int64_t o = (int64_t)cg * a.wd + 4 * q;
 #pragma unroll
         for (int c = 0; c < 4; c++) {
-          part_v[o + c] = bv.v[c]; part_i[o + c] = bi.v[c]; part_s[o + c] = s2.v[c]; part_j[o + c] = j2.v[c];
+          part.v[o + c] = bv.v[c]; part.i[o + c] = bi.v[c]; part.s[o + c] = s2.v[c]; part.j[o + c] = j2.v[c];
         }
       }
     }
@@ -128,21 +125,31 @@ __global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const Counters *
   }
 }
 
+template <bool IS_MIN, int LPR>
+__global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const Counters *cnt, BigParts part) {
+  constexpr int NW = 4;
+  __shared__ float sv[NW][kWave * 4], ss[NW][kWave * 4];
+  __shared__ int si[NW][kWave * 4], sj[NW][kWave * 4];
+  const int total = ieee_mode_off(cnt->v[C_NCHUNK]);
+  whole_chunks<IS_MIN, LPR, NW>(a, total, cnt->v[C_NBIG], sv, si, ss, sj, part);
+}
+
 // The same for launches of few targets, where one chunk's time is the launch's: 16 waves take a slice of kSliceCols
-// columns of a chunk, so that a row of 128 floats is spread over four workgroups, and a load brings eight rows.
+// columns of a chunk, so that a row of 128 floats is spread over four workgroups, and a load brings eight rows; many
+// chunks (kSlicedItems) are whole rows again, 16 waves each.
 // Updates of 100 edges: 10k nodes, rows of 64 floats, 1.13 -> 1.06 ms for four, 1.25M nodes, rows of 128, 1.58 -> 1.53 ms a pass.
 // Long launches stay with whole rows: the slices leave a third of the reads beyond the L2 out (16.6M -> 10.8M of 128
 // bytes, 625k nodes and rows of 128 floats), but the chunks' fixed costs four times over take as much (10 to 600k nodes,
 // rows of 128 and 256 floats: 0.94 to 1.0 of the speed).
-template <bool IS_MIN>
-__global__ __launch_bounds__(1024) void k_big_slices(AggArgs a, const Counters *cnt, int slices, float *part_v, int32_t *part_i,
-                                                     float *part_s, int32_t *part_j) {
+template <bool IS_MIN, int ROW>
+__global__ __launch_bounds__(1024) void k_big_short(AggArgs a, const Counters *cnt, int slices, BigParts part) {
   constexpr int LPR = kSliceLanes, NW = 16;
-  __shared__ float sv[NW][kSliceCols], ss[NW][kSliceCols];
-  __shared__ int si[NW][kSliceCols], sj[NW][kSliceCols];
+  __shared__ float sv[NW][kWave * 4], ss[NW][kWave * 4];
+  __shared__ int si[NW][kWave * 4], sj[NW][kWave * 4];
+  const int total = ieee_mode_off(cnt->v[C_NCHUNK]), n_big = cnt->v[C_NBIG];
+  if (slices > 2 && total > kSlicedItems / slices) { whole_chunks<IS_MIN, ROW, NW>(a, total, n_big, sv, si, ss, sj, part); return; }
   const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int q = l % LPR;
-  const int total = ieee_mode_off(cnt->v[C_NCHUNK]), n_big = cnt->v[C_NBIG], items = slice_items(total, slices);
+  const int q = l % LPR, items = slice_items(total, slices);
   for (int b = blockIdx.x; b < items; b += gridDim.x) {
     int cg, slice, i, v;
     int64_t j0, j1;
@@ -165,7 +172,7 @@ __global__ __launch_bounds__(1024) void k_big_slices(AggArgs a, const Counters *
       int xi = si[0][col], xj = sj[0][col];
       for (int ww = 1; ww < NW; ww++) merge2i<IS_MIN>(sv[ww][col], si[ww][col], ss[ww][col], sj[ww][col], xv, xi, xs, xj);
       const int64_t o = (int64_t)cg * a.wd + c0 + col;
-      part_v[o] = xv; part_i[o] = xi; part_s[o] = xs; part_j[o] = xj;
+      part.v[o] = xv; part.i[o] = xi; part.s[o] = xs; part.j[o] = xj;
     }
     __syncthreads();
   }
@@ -360,13 +367,13 @@ static int lanes_per_row(int ld) { return ld <= 64 ? 16 : (ld <= 128 ? 32 : 64);
 
 template <bool IS_MIN, int LPR>
 static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compare, int64_t n_rows_max) {
+  const Counters *cnt = c->d_cnt;
+  const BigParts part{c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>()};
   if (latency_mode(n_rows_max)) {
     const int slices = big_slices(a.wd);
-    hipLaunchKernelGGL((k_big_slices<IS_MIN>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, (const Counters *)c->d_cnt, slices,
-                       c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
+    hipLaunchKernelGGL((k_big_short<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part);
   } else
-    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, (const Counters *)c->d_cnt, c->big_part_v.as<float>(),
-                       c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>());
+    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, cnt, part);
   hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)c->big_part_v.as<float>(),
                      (const int32_t *)c->big_part_i.as<int32_t>(), (const float *)c->big_part_s.as<float>(),
                      (const int32_t *)c->big_part_j.as<int32_t>(), chg, compare, c->d_cnt);

@@ -133,14 +133,11 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
 
 // Chunks of long rows of at most 48 floats, or of a table too large for slices to pay (kSlicedTableBytes), as they are: the 4
 // waves of a workgroup take a quarter of a chunk each
-template <int LPR>
-__global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const Counters *cnt, float *part) {
-  constexpr int NW = 4;
-  __shared__ float sv[NW][kWave * 4];
+template <int LPR, int NW>
+__device__ __forceinline__ void whole_sum_chunks(const AggArgs &a, int total, int n_big, float (*sv)[kWave * 4], float *part) {
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
-  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG];
   for (int cg = blockIdx.x; cg < total; cg += gridDim.x) {
     int i, v;
     int64_t j0, j1;
@@ -167,18 +164,23 @@ __global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const Counte
   }
 }
 
+template <int LPR>
+__global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const Counters *cnt, float *part) {
+  constexpr int NW = 4;
+  __shared__ float sv[NW][kWave * 4];
+  whole_sum_chunks<LPR, NW>(a, cnt->v[C_NCHUNK], cnt->v[C_NBIG], sv, part);
+}
+
 // Chunks of the other rows, in slices (bigrows.h).  Whole rows came from beyond the L2 as often as not (GCN of 256 columns
 // on 29k nodes with 490 neighbours each, a table of 30 MB: 45M of 89M lines, 7 TB/s, 795 us); a slice of 32 columns stays
 // in an XCD's L2 (4.4M of 97M lines, 661 us, 18.8 TB/s out of the L2s, of which the narrow rows above reach 17 to 24).
 // Inferences: that one 1.43 -> 1.22 ms, 100k nodes with 200 neighbours each and 256 columns 2.50 -> 2.27, GIN of 128
 // columns on 20k, 100k, 400k and 1M nodes 1.02, 1.0, 1.04 and 1.01 times as fast.
 template <int NW>
-__global__ __launch_bounds__(NW * kWave) void k_sum_big_slices(AggArgs a, const Counters *cnt, int slices, float *part) {
+__device__ __forceinline__ void sum_slices(const AggArgs &a, int total, int n_big, int slices, float (*sv)[kSliceCols], float *part) {
   constexpr int LPR = kSliceLanes;
-  __shared__ float sv[NW][kSliceCols];
   const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int q = l % LPR;
-  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG], items = slice_items(total, slices);
+  const int q = l % LPR, items = slice_items(total, slices);
   for (int b = blockIdx.x; b < items; b += gridDim.x) {
     int cg, slice, i, v;
     int64_t j0, j1;
@@ -201,6 +203,22 @@ __global__ __launch_bounds__(NW * kWave) void k_sum_big_slices(AggArgs a, const 
     }
     __syncthreads();
   }
+}
+
+__global__ __launch_bounds__(256) void k_sum_big_slices(AggArgs a, const Counters *cnt, int slices, float *part) {
+  __shared__ float sv[4][kSliceCols];
+  sum_slices<4>(a, cnt->v[C_NCHUNK], cnt->v[C_NBIG], slices, sv, part);
+}
+
+// Launches of few targets: 16 waves a chunk, and its slices in workgroups of their own unless they are many (kSlicedItems).  64
+// registers, so that a CU holds two.
+template <int LPR>
+__global__ __launch_bounds__(1024, 8) void k_sum_big_short(AggArgs a, const Counters *cnt, int slices, float *part) {
+  constexpr int NW = 16;
+  __shared__ float whole[NW][kWave * 4], sliced[NW][kSliceCols];
+  const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG];
+  if (total > kSlicedItems / slices) whole_sum_chunks<LPR, NW>(a, total, n_big, whole, part);
+  else sum_slices<NW>(a, total, n_big, slices, sliced, part);
 }
 
 template <int LPR>
@@ -468,12 +486,12 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   const int slices = big_slices(a.wd);
   const Counters *cnt = c->d_cnt;
   float *part = c->big_part_v.as<float>();
-  if (latency)             // few rows: 16 waves a chunk, and its slices in workgroups of their own
-    hipLaunchKernelGGL((k_sum_big_slices<16>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part);
+  if (latency)
+    hipLaunchKernelGGL((k_sum_big_short<LPR>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part);
   else if (whole)
     hipLaunchKernelGGL((k_sum_big_partial<LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, cnt, part);
   else
-    hipLaunchKernelGGL((k_sum_big_slices<4>), dim3(big_grid(c, a.big_chunks, slices, false)), dim3(256), 0, c->stream, a, cnt, slices, part);
+    hipLaunchKernelGGL(k_sum_big_slices, dim3(big_grid(c, a.big_chunks, slices, false)), dim3(256), 0, c->stream, a, cnt, slices, part);
   hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)part, chg, compare, cnt);
   return hipGetLastError();
 }

@@ -27,7 +27,8 @@ inline int64_t big_chunk_capacity(const ink_ctx *c) {
   return e / kBigChunk + big_rows_capacity(c);
 }
 
-// Workgroups of a chunk kernel: one per expected chunk and slice (the hardware balances them), no more than there can be,
+// Workgroups of a chunk kernel: one per expected chunk and slice (the hardware balances them; in a short launch one per chunk, whose
+// slices are kSlicedItems at most or strided over), no more than there can be,
 // and otherwise at least what fills the chip (1024 threads each in a short launch, 256 in a long one).  Most updates have no long
 // row, and empty workgroups cost their start: 8192 of 1024 threads, rows of 256 floats, 8.6 us, 1024 of them 2.7 (200 updates on
 // 100k nodes with 10 neighbours each 204 -> 192 us).  A kernel strides over the chunks that are there, so kBigGridMax only keeps the launch below the 2^32 threads that HIP takes: a graph of 2M nodes and 440M
@@ -36,7 +37,7 @@ inline int64_t big_chunk_capacity(const ink_ctx *c) {
 constexpr int64_t kBigGridMax = 1 << 20;
 static_assert(kBigGridMax % 8 == 0 && kBigGridMax * 1024 < 1ll << 32, "threads of a launch");
 inline unsigned big_grid(const ink_ctx *c, int64_t chunks, int slices, bool latency) {
-  int64_t n = chunks * slices, least = latency ? 1024 : 2048, most = big_chunk_capacity(c) * slices;
+  int64_t n = latency ? chunks : chunks * slices, least = latency ? 1024 : 2048, most = big_chunk_capacity(c) * slices;
   if (n < least) n = least;
   if (n > most) n = most;
   if (n > kBigGridMax) n = kBigGridMax;
@@ -99,6 +100,13 @@ constexpr int kSliceLanes = 8, kSliceCols = 4 * kSliceLanes;
 // 20 edges a node, 1M / 2.5M nodes (1.3 GB) 4.03 / 10.5 ms against 4.11 / 10.6, 5M (2.6 GB) / 10M 22.5 / 46.5 against
 // 22.2 / 45.2; GCN of 256 on 1M (1 GB) 9.45 against 9.55, on 4M (4.1 GB) 21.95 against 21.3.
 constexpr int64_t kSlicedTableBytes = 2ll << 30;
+// Items (chunks times slices) up to which short launches go by slices: what the chip holds of their workgroups of 1024 threads, where
+// the launch's time is one chunk's.  Beyond, an item's fixed costs are paid once for every slice, and whole rows are faster.  Inferences
+// of 8000 nodes with 8 to 4000 rows of 150 to 1000 neighbours, whole / in slices, us, at 512 items, 1024 items and 4000 rows: GCN of 250
+// columns 89 / 85, 87 / 89, 315 / 432; mean of 128 47 / 45.5, 49.5 / 51, 148 / 208; max of 128 67.5 / 65, 70 / 82, 398 / 602; min of 250 86.5 / 84,
+// 88 / 102, 469 / 1131.  (Max / min of at most two slices, 64 floats, stay with them: 60 / 59, 122 / 117, 368 / 345; sums of 64 39 / 38.5, 58 / 60,
+// 132.5 / 141.5.)
+constexpr int kSlicedItems = 512;
 inline int big_slices(int wd) { return (wd + kSliceCols - 1) / kSliceCols; }
 __device__ __forceinline__ int slice_items(int total, int slices) { return ((total + 7) >> 3) * 8 * slices; }
 __device__ __forceinline__ bool slice_item(int b, int total, int slices, int &chunk, int &slice) {

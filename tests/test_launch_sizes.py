@@ -34,6 +34,8 @@ def test_grids_of_the_long_row_kernels(tmp_path):
     assert len(rows) > 1000
     for chunks, groups, threads in rows:
         assert 0 < groups and groups % 8 == 0 and groups * threads < 2 ** 32
+        if threads == 1024:                                # a short launch has no workgroup without a chunk for each slice of each chunk
+            assert groups <= max(chunks, 1024) + 8
         if chunks == 0:                                    # usually there are none: nothing but an empty launch
             assert groups * threads <= 2 ** 20
     assert max(g for _, g, _ in rows) > 2 ** 19               # the bound does not touch what graphs of usual sizes launch
