@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
 }
 
 // cooperative path for rows with more than kBigDeg in-neighbours: a workgroup per chunk of
-// kBigChunk neighbours (its 4 waves take a quarter each), partial rows to scratch
+// kBigChunk neighbours, partial rows to scratch
 struct BigParts { float *v; int32_t *i; float *s; int32_t *j; };     // best, its id, runner-up, its id: a row per chunk
 
 // whole rows: the NW waves of a workgroup take a part of a chunk each

@@ -131,8 +131,8 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
   if (ch && chg && l == 0) mark_bit_s(chg, v);
 }
 
-// Chunks of long rows of at most 48 floats, or of a table too large for slices to pay (kSlicedTableBytes), as they are: the 4
-// waves of a workgroup take a quarter of a chunk each
+// Chunks of long rows of at most 48 floats, of a table too large for slices to pay (kSlicedTableBytes), or of a short launch with many
+// (kSlicedItems), as they are: the NW waves of a workgroup take a part of a chunk each
 template <int LPR, int NW>
 __device__ __forceinline__ void whole_sum_chunks(const AggArgs &a, int total, int n_big, float (*sv)[kWave * 4], float *part) {
   const int l = lane_id(), w = threadIdx.x / kWave;
