@@ -335,7 +335,7 @@ __global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targe
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const LongSeg L = lng.list[i];
     const int v = targets[L.target];
-    const int nch = (seg[L.target + 1] - seg[L.target] + kEvChunk - 1) / kEvChunk;
+    const int nch = (seg[L.target + 1] - seg[L.target] + lng.chunk - 1) / lng.chunk;
     Cached<IS_MIN> c;
     load_cached<IS_MIN>(a, v, lane_on, q, c);
     EvAcc<IS_MIN> s;
@@ -415,16 +415,16 @@ static hipError_t launch_events(ink_ctx *c, const AggArgs &a, const int32_t *tar
   // few targets per wave visit while the launch has fewer blocks than the chip has waves to spread them over
   const int ev_block = (int)std::max<int64_t>(1, std::min<int64_t>(kEvBlock, n_targets / 32768));
   int64_t blocks = std::min<int64_t>(((n_targets + ev_block - 1) / ev_block + 3) / 4, INK_EVENT_GRID);
-  LongEvents lng{nullptr, nullptr, latency ? kEvLongLatency : kEvLong};
+  LongEvents lng = long_events(eb.n_events, latency);
   INK_TRY(ensure_long_events(c, eb, a.wd, true, &lng));
   int32_t *exp_list = c->exp_list.as<int32_t>();
   hipLaunchKernelGGL((k_agg_events<IS_MIN, LPR, INLINE>), dim3((unsigned)blocks), dim3(256), 0, c->stream, a, targets, seg,
                      n_targets_dev, ev, chg, exp_list, c->d_cnt, ev_block, lng);
   if (eb.max_seg > lng.limit) {      // otherwise no segment can be long
     EvPart part{c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>()};
-    hipLaunchKernelGGL((k_ev_partial<IS_MIN, LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(eb.n_events, lng.limit), 8192)),
+    hipLaunchKernelGGL((k_ev_partial<IS_MIN, LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(lng, eb.n_events), 8192)),
                        dim3(256), 0, c->stream, a, targets, seg, ev, lng, part, (const Counters *)c->d_cnt);
-    hipLaunchKernelGGL((k_ev_final<IS_MIN, LPR, INLINE>), dim3((unsigned)std::min<int64_t>(long_ev_rows(eb.n_events, lng.limit), 8192)),
+    hipLaunchKernelGGL((k_ev_final<IS_MIN, LPR, INLINE>), dim3((unsigned)std::min<int64_t>(long_ev_rows(lng, eb.n_events), 8192)),
                        dim3(64), 0, c->stream, a, targets, seg, lng, part, chg, exp_list, c->d_cnt);
   }
   return hipGetLastError();

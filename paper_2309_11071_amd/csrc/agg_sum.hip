@@ -446,7 +446,7 @@ __global__ __launch_bounds__(64) void k_sum_ev_final(AggArgs a, const int32_t *t
   const int n = cnt->v[C_NEVL];
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const LongSeg L = lng.list[i];
-    const int nch = (seg[L.target + 1] - seg[L.target] + kEvChunk - 1) / kEvChunk;
+    const int nch = (seg[L.target + 1] - seg[L.target] + lng.chunk - 1) / lng.chunk;
     S4 acc;
 #pragma unroll
     for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
@@ -502,15 +502,15 @@ static hipError_t sum_events_t(ink_ctx *c, const AggArgs &a, const int32_t *targ
                                const SumSources &src, uint64_t *chg) {
   if (n_targets <= 0) return hipSuccess;
   KernelTimer kt(c, a.layer, INK_K_AGG_EVENTS);
-  LongEvents lng{nullptr, nullptr, latency_mode(n_targets) ? kEvLongLatency : kEvLong};
+  LongEvents lng = long_events(eb.n_events, latency_mode(n_targets));
   INK_TRY(ensure_long_events(c, eb, a.wd, false, &lng));
   hipLaunchKernelGGL((k_sum_events<LPR>), dim3((unsigned)((n_targets + 3) / 4)), dim3(256), 0, c->stream, a, targets,
                      seg, n_targets_dev, ev, src, chg, c->d_cnt, lng);
   if (eb.max_seg > lng.limit) {      // otherwise no segment can be long
     float *part = c->big_part_v.as<float>();
-    hipLaunchKernelGGL((k_sum_ev_partial<LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(eb.n_events, lng.limit), 8192)),
+    hipLaunchKernelGGL((k_sum_ev_partial<LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(lng, eb.n_events), 8192)),
                        dim3(256), 0, c->stream, a, seg, ev, src, lng, part, (const Counters *)c->d_cnt);
-    hipLaunchKernelGGL((k_sum_ev_final<LPR>), dim3((unsigned)std::min<int64_t>(long_ev_rows(eb.n_events, lng.limit), 8192)),
+    hipLaunchKernelGGL((k_sum_ev_final<LPR>), dim3((unsigned)std::min<int64_t>(long_ev_rows(lng, eb.n_events), 8192)),
                        dim3(64), 0, c->stream, a, targets, seg, lng, (const float *)part, chg, c->d_cnt);
   }
   return hipGetLastError();

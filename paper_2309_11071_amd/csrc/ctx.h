@@ -145,14 +145,6 @@ __device__ __forceinline__ void publish_wave(const Counters *d, HostCounters *h,
   if (l == 0) __hip_atomic_store(h_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// A target with more than this many events is reduced by many waves (longev.h) instead of one.
-// 128 makes the lists and partial rows of a large launch cost more than the chains they cut (17 M
-// events: 2.0 against 1.75 ms), 512 leaves visible chains in mid-size ones (470 k events: 0.25
-// against 0.21 ms).
-constexpr int kEvLong = 256;          // large launches
-constexpr int kEvLongLatency = 128;   // launches of few targets, where one wave's chain is the launch's time
-constexpr int kEvChunk = 256;         // events of such a segment per workgroup
-
 }  // namespace ink
 
 struct ink_ctx {

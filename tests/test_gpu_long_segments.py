@@ -44,3 +44,24 @@ def test_hub_segments(kind, agg, d, n_src, fan):
     h.step(op, bs, bd, exact=exact)
     h.check_state(exact=exact)
     h.ink.close()
+
+
+@pytest.mark.parametrize("kind,agg,d", [("sage", "max", 100), ("sage", "min", 20), ("gin", "sum", 40)])
+@pytest.mark.parametrize("n_src,fan", [(1500, 190), (6000, 190)])     # 285 000 and 1 140 000 events in one layer
+def test_limits_of_mid_size_launches(kind, agg, d, n_src, fan):
+    """Targets with 63 to 300 events, around every limit and chunk that a launch of that many events may take."""
+    n, lengths = n_src + 12000, (63, 64, 65, 127, 128, 129, 192, 193, 255, 256, 257, 300)
+    rng = np.random.default_rng(n_src + d)
+    s = np.arange(n_src)
+    src = [np.repeat(s, fan)] + [rng.choice(s, size=k, replace=False) for k in lengths]
+    dst = [rng.integers(n_src + 20, n, size=n_src * fan)] + [np.full(k, n_src + i) for i, k in enumerate(lengths)]
+    keys = np.unique(synth.edge_keys(np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32)))
+    src, dst = synth.keys_to_edges(keys)
+    exact = agg in ("max", "min")
+    X = rng.integers(-3, 4, size=(n, d)).astype(np.float32)
+    h = Harness(graph=(n, src, dst), X=X, model=tiny_model(kind, agg, (d, 24, 6), seed=d, hidden=16), dense_threshold=-1,
+                precision="f32" if exact else "f64")
+    h.feature_step(s.astype(np.int32), rng.integers(-3, 4, size=(n_src, d)), exact=exact)
+    assert h.ink.stats()["layers"][0]["n_events"] == len(src)
+    h.check_state(exact=exact)
+    h.ink.close()
