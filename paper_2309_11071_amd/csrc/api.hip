@@ -297,15 +297,21 @@ struct EmitRows {
   const uint8_t *flag; const int32_t *rows;      // flags are read 8 at a time: room for 7 past n
   const int32_t *deg, *new_out;                  // deg null: no events wanted
   int64_t bound; const int32_t *n_dev;           // rows: bound, or fewer as *n_dev says
+  __device__ __forceinline__ int64_t count() const { return n_dev && *n_dev < bound ? *n_dev : bound; }
   __device__ __forceinline__ unsigned long long flags8(int64_t base) const {
-    const int64_t n = n_dev && *n_dev < bound ? *n_dev : bound;
+    const int64_t n = count();
     if (base >= n) return 0;
     const unsigned long long f = *reinterpret_cast<const unsigned long long *>(flag + base);
     return n - base >= 8 ? f : f & ((1ull << (8 * (n - base))) - 1);
   }
   __device__ __forceinline__ int events(int u) const { return deg ? kept_out_degree(deg, new_out, u) : 0; }
 };
-constexpr int kEmitThreads = 256, kEmitTile = kEmitThreads * 8;
+// Rows per thread.  Every load of a row's degrees is a miss, and 8 rows a thread left the layers in the middle to a handful of
+// workgroups: count and write, 8 rows a thread against 1, 6k rows 21 / 9 us, 150k 23 / 10.  Beyond the line the sums of the tiles
+// before its own, which every workgroup adds up, count more; the last layer of 700k rows, which asks for no degree, takes 15 us with 8.
+constexpr int kEmitThreads = 256;
+constexpr int64_t kEmitFew = 1 << 18;
+inline int emit_per_thread(int64_t n) { return n <= kEmitFew ? 1 : 8; }
 
 __device__ __forceinline__ unsigned long long block_excl_scan64(unsigned long long x, unsigned long long *sm, unsigned long long *total) {
   const int l = lane_id(), w = threadIdx.x / kWave;
@@ -325,37 +331,54 @@ __device__ __forceinline__ unsigned long long block_excl_scan64(unsigned long lo
   return before + inc - x;
 }
 
-// u[k]: id of row base + k, v[k]: its packed count (0 if its flag is not set)
-__device__ __forceinline__ unsigned long long emit_items(const EmitRows &e, int64_t base, int u[8], unsigned long long v[8]) {
-  const unsigned long long f = e.flags8(base);
+// u[k]: id of row base + k, v[k]: its packed count (0 if its flag is not set).  The count, the flags and the ids are asked for
+// together and the degrees of all rows behind them, whether or not they are wanted (past the count the list may hold anything:
+// node 0 stands in).
+template <int I>
+__device__ __forceinline__ unsigned long long emit_items(const EmitRows &e, int64_t base, int u[I], unsigned long long v[I]) {
   unsigned long long s = 0;
 #pragma unroll
-  for (int k = 0; k < 8; k++) {
-    u[k] = 0; v[k] = 0;
-    if ((f >> (8 * k)) & 0xFF) { u[k] = e.rows[base + k]; v[k] = (1ull << 32) + (unsigned)e.events(u[k]); }
+  for (int k = 0; k < I; k++) { u[k] = 0; v[k] = 0; }
+  if (base >= e.bound) return 0;
+  static_assert(I == 1 || I == 8, "one load of flags");
+  const unsigned long long f = I == 8 ? *reinterpret_cast<const unsigned long long *>(e.flag + base) : e.flag[base];
+#pragma unroll
+  for (int k = 0; k < I; k++) u[k] = e.rows[base + k < e.bound ? base + k : e.bound - 1];
+  const int64_t n = e.count();
+  int ev[I];
+#pragma unroll
+  for (int k = 0; k < I; k++) u[k] = base + k < n ? u[k] : 0;
+#pragma unroll
+  for (int k = 0; k < I; k++) ev[k] = e.events(u[k]);
+#pragma unroll
+  for (int k = 0; k < I; k++) {
+    if (base + k < n && ((f >> (8 * k)) & 0xFF)) v[k] = (1ull << 32) + (unsigned)ev[k];
     s += v[k];
   }
   return s;
 }
 
+template <int I>
 __global__ __launch_bounds__(kEmitThreads) void k_emit_count(EmitRows e, unsigned long long *tile) {
   __shared__ unsigned long long sm[kEmitThreads / kWave];
-  int u[8]; unsigned long long v[8], tot;
-  (void)block_excl_scan64(emit_items(e, (int64_t)blockIdx.x * kEmitTile + threadIdx.x * 8, u, v), sm, &tot);
+  int u[I]; unsigned long long v[I], tot;
+  (void)block_excl_scan64(emit_items<I>(e, ((int64_t)blockIdx.x * kEmitThreads + threadIdx.x) * I, u, v), sm, &tot);
   if (threadIdx.x == 0) tile[blockIdx.x] = tot;
 }
 
+template <int I>
 __global__ __launch_bounds__(kEmitThreads) void k_emit_write(EmitRows e, const unsigned long long *tile, int32_t *idx, int32_t *ids,
                                                              int32_t *pref, Counters *cnt, HostCounters *h, uint32_t *h_seq, uint32_t seq) {
   __shared__ unsigned long long sm[kEmitThreads / kWave];
   unsigned long long part = 0, before, tot;
   for (int i = threadIdx.x; i < (int)blockIdx.x; i += kEmitThreads) part += tile[i];
+  const int64_t base = ((int64_t)blockIdx.x * kEmitThreads + threadIdx.x) * I;
+  int u[I]; unsigned long long v[I];
+  const unsigned long long mine = emit_items<I>(e, base, u, v);
   (void)block_excl_scan64(part, sm, &before);
-  const int64_t base = (int64_t)blockIdx.x * kEmitTile + threadIdx.x * 8;
-  int u[8]; unsigned long long v[8];
-  unsigned long long at = before + block_excl_scan64(emit_items(e, base, u, v), sm, &tot);
+  unsigned long long at = before + block_excl_scan64(mine, sm, &tot);
 #pragma unroll
-  for (int k = 0; k < 8; k++) {
+  for (int k = 0; k < I; k++) {
     if (!v[k]) continue;
     const int p = (int)(at >> 32);
     idx[p] = (int32_t)(base + k);
@@ -405,7 +428,7 @@ __global__ void k_gather_rows4(const float *table, int ld, int d4, const int32_t
 // of the transformed rows; what stands before them it counts itself, in the tile sums of k_emit_count and the flags of its
 // own tile, or, without tile sums (at most kSmallLayer rows), in all flags.  Emission of a short layer in one workgroup and a
 // gather behind it took 12 and 7 us; 100 updates on 10k nodes .357 -> .342 ms a pass of two.
-__global__ __launch_bounds__(256) void k_emit_result(EmitRows e, const unsigned long long *tile, int per, const float *table, int ld, int d,
+__global__ __launch_bounds__(256) void k_emit_result(EmitRows e, const unsigned long long *tile, int tile_rows, int per, const float *table, int ld, int d,
                                                      int32_t *ids, float *out, HostMirror m, Counters *cnt) {
   __shared__ int sm[256 / kWave];
   __shared__ int row[256], n_here;
@@ -413,10 +436,10 @@ __global__ __launch_bounds__(256) void k_emit_result(EmitRows e, const unsigned 
   const int64_t n = e.n_dev && *e.n_dev < e.bound ? *e.n_dev : e.bound;
   const int64_t r0 = (int64_t)blockIdx.x * per;
   if (r0 >= n && !(n == 0 && blockIdx.x == 0)) return;
-  const int64_t t0 = tile ? r0 / kEmitTile : 0;
+  const int64_t t0 = tile ? r0 / tile_rows : 0;
   int before = 0;
   for (int64_t i = t; i < t0; i += 256) before += (int)(tile[i] >> 32);
-  for (int64_t p = t0 * kEmitTile + 8 * t; p < r0; p += 8 * 256) before += __popcll(e.flags8(p) & 0x0101010101010101ull);
+  for (int64_t p = t0 * tile_rows + 8 * t; p < r0; p += 8 * 256) before += __popcll(e.flags8(p) & 0x0101010101010101ull);
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) before += __shfl_xor(before, o, kWave);
   if (l == 0) sm[w] = before;
@@ -1397,19 +1420,20 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, const int32_t *nC_dev, in
   *nF2 = 0; *n_chg = 0;
   API_TRY(c->f_list[nxt].reserve((size_t)nC * 4));
   const bool small = nC <= kSmallLayer;
-  const int tiles = nblocks(nC, kEmitTile);
+  const int per_thread = emit_per_thread(nC), tile_rows = per_thread * kEmitThreads, tiles = nblocks(nC, tile_rows);
   const EmitRows e{c->c_flag.as<uint8_t>(), c->c_list.as<int32_t>(), want_events ? c->gout.deg : nullptr, c->new_out, nC, nC_dev};
   unsigned long long *tile = nullptr;
   if (!small) {
     API_TRY(c->ws.blk.reserve((size_t)tiles * sizeof(unsigned long long)));
     tile = c->ws.blk.as<unsigned long long>();
-    hipLaunchKernelGGL(k_emit_count, dim3(tiles), dim3(kEmitThreads), 0, s, e, tile);
+    if (per_thread == 1) hipLaunchKernelGGL(k_emit_count<1>, dim3(tiles), dim3(kEmitThreads), 0, s, e, tile);
+    else hipLaunchKernelGGL(k_emit_count<8>, dim3(tiles), dim3(kEmitThreads), 0, s, e, tile);
   }
   const uint32_t seq = ++c->pub_seq;         // the kernel that finds the counts publishes them itself
   if (result && (size_t)nC * result->d * 4 <= kEagerResultBytes) {
     API_TRY(c->res_emb.reserve((size_t)nC * result->d * 4));
     const int per = nC <= 65536 ? 64 : 256;          // wide rows want workgroups, long tables few sums
-    hipLaunchKernelGGL(k_emit_result, dim3((unsigned)((nC + per - 1) / per)), dim3(256), 0, s, e, (const unsigned long long *)tile, per,
+    hipLaunchKernelGGL(k_emit_result, dim3((unsigned)((nC + per - 1) / per)), dim3(256), 0, s, e, (const unsigned long long *)tile, tile_rows, per,
                        (const float *)result->f(), result->ld, result->d, c->f_list[nxt].as<int32_t>(), c->res_emb.as<float>(),
                        host_mirror(c), dc);
     *result_done = true;
@@ -1426,8 +1450,12 @@ static ink_status emit_changed(ink_ctx *c, int64_t nC, const int32_t *nC_dev, in
 #undef INK_SMALL_EMIT
   } else {
     if (want_events) API_TRY(c->f_pref.reserve((size_t)(nC + 1) * 4));
-    hipLaunchKernelGGL(k_emit_write, dim3(tiles), dim3(kEmitThreads), 0, s, e, (const unsigned long long *)tile,
-                       c->c_idx.as<int32_t>(), c->f_list[nxt].as<int32_t>(), c->f_pref.as<int32_t>(), dc, c->h_cnt, c->h_seq, seq);
+#define INK_EMIT(I)                                                                                                              \
+  hipLaunchKernelGGL(k_emit_write<I>, dim3(tiles), dim3(kEmitThreads), 0, s, e, (const unsigned long long *)tile, c->c_idx.as<int32_t>(), \
+                     c->f_list[nxt].as<int32_t>(), c->f_pref.as<int32_t>(), dc, c->h_cnt, c->h_seq, seq)
+    if (per_thread == 1) INK_EMIT(1);
+    else INK_EMIT(8);
+#undef INK_EMIT
   }
   if (keep_old) {
     API_TRY(c->f_old[nxt].reserve((size_t)nC * ld * 4));
