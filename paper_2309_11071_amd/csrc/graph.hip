@@ -549,9 +549,8 @@ static ink_status apply_side(ink_ctx *c, GraphSide &g, SideBufs &b, int64_t n_op
 // An entry that a later one on the same edge overrides, or a self loop, stays in the lists as a dead op.
 // Bound by the latency of its few launches and of one round trip; measured per update call with 10 000
 // entries on 612 k nodes / 15.5 M edges: 0.15 ms less than two sequential sides with two round trips, with 1 to 500
-// entries 0.03 - 0.06 ms less.  Of its six launches for 10 000 entries (205 us) the two of one workgroup a side took half: now
-// they take all entries at once instead of 1024 a turn, the blocks' places are read by the workgroups of the merge, which
-// has the sorted chunks in LDS, and the walk has a wave per chunk (142 us; 612k nodes with hubs 2.53 -> 2.40 ms a pass of two updates).
+// entries 0.03 - 0.06 ms less.  Its six launches for 10 000 entries take 84 us: sort 13, merge 12, heads 8, walk 24, finish 10, apply
+// 18 (205 with a workgroup a side for heads and finish that took 1024 entries a turn, 149 when it took all at once).
 constexpr int kOneChunk = 1024;        // entries that one workgroup sorts
 constexpr int kMaxChunks = (int)(kShortBatch / kOneChunk);
 constexpr uint64_t kNoKey = ~0ull;     // sorts behind every (node, other) pair
@@ -559,7 +558,8 @@ constexpr uint64_t kNoKey = ~0ull;     // sorts behind every (node, other) pair
 struct ShortSide {           // op lists of one direction (device pointers), in (node, other) order
   int32_t *node, *other; uint8_t *op; int32_t *pos;
   int32_t *uniq, *seg, *chunk_pref;
-  int32_t *nd_ins, *nd_del, *fill, *pfx;
+  int32_t *nd_ins, *nd_del, *fill;
+  int32_t *head;                       // per op: its node's place in uniq if it is the node's first, else -1
   const int64_t *off; const int32_t *deg, *cap, *ids;
   int64_t *uoff; int32_t *udeg, *ucap; // the touched nodes' blocks, one behind the other
   uint64_t *skey; int32_t *sidx;       // sorted chunks (batches of more than one)
@@ -608,6 +608,7 @@ __device__ __forceinline__ uint64_t update_key(const RawUpdate &a, int side) {
 __device__ __forceinline__ void clear_graph_slots(Counters *g, int err) {
   const int i = threadIdx.x;
   if (i < 32 && i != C_TMP0 && i != C_TMP1 && i != C_OT && i != C_OCH) g->v[i] = i == C_ERR ? err : 0;
+  if (i < 2) g->stripe[0][i] = 0;      // what the sides need of the pools
 }
 
 // Distinct nodes of the sorted op list (node of op i: node(i), n <= THREADS ops), the start of each node's ops plus the
@@ -620,6 +621,7 @@ __device__ __forceinline__ void heads_and_chunks(NodeAt node, int n, const Short
   int n_uniq, n_ch;
   const int ex = block_excl_scan<THREADS>(h, sm, &n_uniq);
   if (h) { o.uniq[ex] = v; o.seg[ex] = i; }
+  if (i < n) o.head[i] = h ? ex : -1;
   if (i == 0) o.seg[n_uniq] = n;
   __threadfence_block();
   __syncthreads();
@@ -683,128 +685,128 @@ __device__ __forceinline__ int batch_bad(const int32_t *chunk_err, int n_chunks)
   return (__ballot(e & 1) ? 1 : 0) | (__ballot(e & 2) ? 2 : 0);
 }
 // ... and merged by rank: an element's place is the sum of its ranks in all chunks (the searches of one thread
-// advance in step, so their loads are in flight together).
-__global__ __launch_bounds__(kOneChunk) void k_short_merge(int n, int n_chunks, ShortSide in, ShortSide out, const int32_t *chunk_err) {
-  const int side = (int)blockIdx.x >= n_chunks, ch = (int)blockIdx.x - (side ? n_chunks : 0), t = threadIdx.x;
+// advance in step, so their loads are in flight together).  A workgroup has all keys of its side in LDS (ten steps of dependent
+// reads took 31 us out of the L2, 10 chunks) and finds the places of 256 of them: the searches are what takes the time, and with
+// 1024 a workgroup four times as many of them share a CU's LDS (10000 entries 26 -> 12 us, with the reads of a step asked for together).
+constexpr int kMergeThreads = 256, kMergeParts = kOneChunk / kMergeThreads;
+template <int C>               // at least n_chunks: chunks past them repeat the first, and what is found there is not used
+__global__ __launch_bounds__(kMergeThreads) void k_short_merge(int n, int n_chunks, ShortSide in, ShortSide out, const int32_t *chunk_err) {
+  const int part = (int)blockIdx.x % kMergeParts, b = (int)blockIdx.x / kMergeParts;
+  const int side = b >= n_chunks, ch = b - (side ? n_chunks : 0), t = part * kMergeThreads + threadIdx.x;
   const ShortSide &o = side ? out : in;
   if (batch_bad(chunk_err, n_chunks)) return;
-  // all keys of the side in LDS: ten steps of dependent reads took 31 us out of the L2, 10 chunks
-  __shared__ uint64_t S[kMaxChunks * kOneChunk];
-  uint64_t in_flight[kMaxChunks];
+  __shared__ __align__(16) uint64_t S[C * kOneChunk];
+  {
+    constexpr int U = kOneChunk / 2 / kMergeThreads;      // 16 bytes a load, all under way together
+    const ulonglong2 *src = reinterpret_cast<const ulonglong2 *>(o.skey) + threadIdx.x;
+    ulonglong2 x[C][U];
 #pragma unroll
-  for (int c = 0; c < kMaxChunks; c++) in_flight[c] = c < n_chunks ? o.skey[c * kOneChunk + t] : kNoKey;
+    for (int c = 0; c < C; c++)
 #pragma unroll
-  for (int c = 0; c < kMaxChunks; c++)
-    if (c < n_chunks) S[c * kOneChunk + t] = in_flight[c];
+      for (int u = 0; u < U; u++) x[c][u] = src[(c < n_chunks ? c : 0) * (kOneChunk / 2) + u * kMergeThreads];
+#pragma unroll
+    for (int c = 0; c < C; c++)
+#pragma unroll
+      for (int u = 0; u < U; u++) reinterpret_cast<ulonglong2 *>(S)[c * (kOneChunk / 2) + u * kMergeThreads + threadIdx.x] = x[c][u];
+  }
   __syncthreads();
   const int me = ch * kOneChunk + t;
   const uint64_t k = S[me];
   if (k == kNoKey) return;
-  int lo[kMaxChunks];
+  int lo[C];
 #pragma unroll
-  for (int c = 0; c < kMaxChunks; c++) lo[c] = 0;
+  for (int c = 0; c < C; c++) lo[c] = 0;
   for (int step = kOneChunk / 2; step > 0; step >>= 1) {
+    uint64_t x[C];
 #pragma unroll
-    for (int c = 0; c < kMaxChunks; c++) {
-      if (c >= n_chunks || c == ch) continue;
-      const uint64_t x = S[c * kOneChunk + lo[c] + step - 1];
-      if (c < ch ? x <= k : x < k) lo[c] += step;      // equal keys of earlier chunks stand before, of later ones behind
-    }
+    for (int c = 0; c < C; c++) x[c] = S[c * kOneChunk + lo[c] + step - 1];
+#pragma unroll
+    for (int c = 0; c < C; c++) lo[c] += (x[c] < k) | ((x[c] == k) & (c < ch)) ? step : 0;      // equal keys of earlier chunks stand before, of later ones behind
   }
   int rank = t;
   bool dead = t + 1 < kOneChunk && S[me + 1] == k;
 #pragma unroll
-  for (int c = 0; c < kMaxChunks; c++) {
-    if (c >= n_chunks || c == ch) continue;
+  for (int c = 0; c < C; c++) {
     // the search above covers 1023 elements; the last step settles the chunk's last one
-    const uint64_t x = S[c * kOneChunk + lo[c]];
-    const bool before = c < ch ? x <= k : x < k;
-    rank += lo[c] + (before ? 1 : 0);
-    dead |= c > ch && (before ? (lo[c] + 1 < kOneChunk && S[c * kOneChunk + lo[c] + 1] == k) : x == k);
+    const uint64_t x = S[c * kOneChunk + lo[c]], y = S[c * kOneChunk + (lo[c] + 1 < kOneChunk ? lo[c] + 1 : lo[c])];
+    const bool before = (x < k) | ((x == k) & (c < ch)), other = c < n_chunks && c != ch;
+    rank += other ? lo[c] + (before ? 1 : 0) : 0;
+    dead |= other && c > ch && (before ? (lo[c] + 1 < kOneChunk && y == k) : x == k);
   }
-  const int node = (int)(k >> 32), other = (int)(uint32_t)k;
-  dead |= node == other;
-  o.node[rank] = node; o.other[rank] = other; o.op[rank] = (uint8_t)(dead ? 2 : o.sidx[me] >> 16); o.pos[rank] = -1;
+  const int node = (int)(k >> 32), end = (int)(uint32_t)k;
+  dead |= node == end;
+  o.node[rank] = node; o.other[rank] = end; o.op[rank] = (uint8_t)(dead ? 2 : o.sidx[me] >> 16); o.pos[rank] = -1;
   o.edeg[rank] = o.deg[node]; o.ecap[rank] = o.cap[node]; o.eoff[rank] = o.off[node];       // here many workgroups share the random reads
 }
-// Up to ITEMS * 1024 entries by one workgroup in one pass: wave w has entries w * 64 ITEMS .., lane l of its k-th group of 64
-// the k-th of them, so that loads are coalesced, all under way together, and ranks are counts of ballot bits.
-struct Items {
-  int base;                                       // first entry of the wave
-  template <int ITEMS> __device__ __forceinline__ static Items of() { return Items{(int)(threadIdx.x / kWave) * (ITEMS * kWave)}; }
-  __device__ __forceinline__ int at(int k) const { return base + k * kWave + lane_id(); }
-};
-// exclusive prefix of one value per wave over the workgroup, and the total (sm: a slot per wave)
-__device__ __forceinline__ int wave_prefix(int x, int *sm, int *total) {
-  const int w = threadIdx.x / kWave;
+
+// Exclusive prefix of x over a workgroup of 1024, and the total, of two counts packed into 64 bits (sm: a slot per wave).
+__device__ __forceinline__ uint64_t chunk_prefix(uint64_t x, uint64_t *sm, uint64_t *total) {
+  const int l = lane_id(), w = threadIdx.x / kWave;
+  uint64_t inc = x;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint64_t y = __shfl_up((unsigned long long)inc, o, kWave);
+    if (l >= o) inc += y;
+  }
+  __syncthreads();                 // sm may still be read by the scan before
+  if (l == kWave - 1) sm[w] = inc;
   __syncthreads();
-  if (lane_id() == 0) sm[w] = x;
-  __syncthreads();
-  int before = 0, all = 0;
+  uint64_t before = 0, all = 0;
 #pragma unroll
   for (int i = 0; i < kOneChunk / kWave; i++) { before += i < w ? sm[i] : 0; all += sm[i]; }
   *total = all;
-  return before;
+  return before + inc - x;
 }
 
-template <int ITEMS>
+// The touched nodes of the merged entries: a workgroup has 1024 of them and counts what stands before them itself, so that
+// nothing waits for another workgroup.  (One workgroup a side for all entries took 26 us for 10000, this takes 8.)
 __global__ __launch_bounds__(kOneChunk) void k_short_heads(int n, int n_chunks, ShortSide in, ShortSide out, const int32_t *chunk_err,
                                                            Counters *g) {
-  __shared__ int sm[kOneChunk / kWave];
-  const ShortSide &o = blockIdx.x ? out : in;
+  __shared__ uint64_t sm[kOneChunk / kWave];
+  const int side = (int)blockIdx.x >= n_chunks, b = (int)blockIdx.x - (side ? n_chunks : 0), t = threadIdx.x;
+  const ShortSide &o = side ? out : in;
   const int err = batch_bad(chunk_err, n_chunks);
   if (blockIdx.x == 0) clear_graph_slots(g, err);
   if (err) n = 0;
-  const Items it = Items::of<ITEMS>();
-  const uint64_t below = (1ull << lane_id()) - 1;
-  int v[ITEMS], pv[ITEMS];
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    const int i = it.at(k);
-    v[k] = i < n ? o.node[i] : -1;
-    pv[k] = i > 0 && i < n ? o.node[i - 1] : -1;
-  }
-  uint64_t head[ITEMS];
-  int cnt = 0, n_uniq, n_ch;
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) { head[k] = __ballot(v[k] != pv[k]); cnt += __popcll(head[k]); }       // node ids are not negative
-  int at = wave_prefix(cnt, sm, &n_uniq);
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    if (v[k] != pv[k]) {
-      const int u = at + __popcll(head[k] & below), i = it.at(k), d = o.edeg[i];
-      o.uniq[u] = v[k]; o.seg[u] = i;
-      o.udeg[u] = d; o.ucap[u] = o.ecap[i]; o.uoff[u] = o.eoff[i];
+  // heads in the upper half, chunks of their blocks in the lower
+  auto count = [](int pv, int v, int d) __attribute__((always_inline)) {
+    return v != pv ? (1ull << 32) + (unsigned)((d + kChunk - 1) / kChunk) : 0ull;      // node ids are not negative
+  };
+  uint64_t part = 0, before, tot;
+  const int i = b * kOneChunk + t;
+  const uint64_t mine = i < n ? count(i > 0 ? o.node[i - 1] : -1, o.node[i], o.edeg[i]) : 0;
+  if (!err)
+    for (int k = t; k < b * (kOneChunk / 4); k += kOneChunk) {       // four entries a load
+      const int pv = k > 0 ? o.node[4 * k - 1] : -1;
+      const int4 v = reinterpret_cast<const int4 *>(o.node)[k], d = reinterpret_cast<const int4 *>(o.edeg)[k];
+      part += count(pv, v.x, d.x) + count(v.x, v.y, d.y) + count(v.y, v.z, d.z) + count(v.z, v.w, d.w);
     }
-    at += __popcll(head[k]);
+  (void)chunk_prefix(part, sm, &before);
+  const uint64_t at = before + chunk_prefix(mine, sm, &tot);
+  const int u = (int)(at >> 32);
+  if (mine) {
+    o.uniq[u] = o.node[i]; o.seg[u] = i;
+    o.udeg[u] = o.edeg[i]; o.ucap[u] = o.ecap[i]; o.uoff[u] = o.eoff[i];
+    o.chunk_pref[u] = (int)(uint32_t)at;
   }
-  if (threadIdx.x == 0) o.seg[n_uniq] = n;
-  __threadfence_block();
-  __syncthreads();
-  int ch[ITEMS];
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) ch[k] = it.at(k) < n_uniq ? o.udeg[it.at(k)] : 0;
-  cnt = 0;
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    const int c = (ch[k] + kChunk - 1) / kChunk, inc = wave_incl_scan(c);
-    ch[k] = cnt + inc - c;
-    cnt += __builtin_amdgcn_readlane(inc, kWave - 1);
+  if (i < n) o.head[i] = mine ? u : -1;
+  if (b == n_chunks - 1 && t == 0) {
+    const int n_uniq = (int)((before + tot) >> 32);
+    o.seg[n_uniq] = n;
+    g->v[o.slot_n] = n_uniq; g->v[o.slot_ch] = (int)(uint32_t)(before + tot);
   }
-  const int before = wave_prefix(cnt, sm, &n_ch);
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++)
-    if (it.at(k) < n_uniq) o.chunk_pref[it.at(k)] = before + ch[k];
-  if (threadIdx.x == 0) { g->v[o.slot_n] = n_uniq; g->v[o.slot_ch] = n_ch; }
 }
 
 // Walk the blocks of the touched nodes of both sides, one chunk of slots per wave visit (most blocks are short: a
 // workgroup per visit left three of its waves without work in their chains of loads); an id found in
 // the node's op list records its slot (of several ops on one edge the last one, which is the live one, may
-// not be missed).  Reads only: the blocks are walked with 16-byte loads, a node's few ops sit in registers.
+// not be missed).  Reads only: the blocks are walked with 16-byte loads, a node's few ops sit in registers, those of a hub in
+// LDS, where every id looks for itself: out of the L2 the searches of one hub's chunk were the launch's end (10000 entries 37 -> 24 us).
+constexpr int kClassifyOps = 1024;
 __global__ __launch_bounds__(256) void k_short_classify(ShortSide in, ShortSide out, const Counters *g) {
   const int nch_in = g->v[in.slot_ch], total = nch_in + g->v[out.slot_ch];
-  const int l = lane_id(), wave = (int)(blockIdx.x * (256 / kWave)) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  __shared__ int s_ops[256 / kWave][kClassifyOps];
+  const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), wave = (int)(blockIdx.x * (256 / kWave)) + w;
   for (int c = wave; c < total; c += gridDim.x * (256 / kWave)) {
     const bool second = c >= nch_in;
     const ShortSide &o = second ? out : in;
@@ -814,6 +816,12 @@ __global__ __launch_bounds__(256) void k_short_classify(ShortSide in, ShortSide 
     const int d = o.udeg[i];
     const int32_t *ids = o.ids + o.uoff[i];      // blocks start on 16-byte boundaries and hold a multiple of 4 slots
     const int mine = o.other[s0 + (l < cnt ? l : 0)];
+    const bool staged = cnt > 8 && cnt <= kClassifyOps;
+    if (staged) {                                // read by this wave alone
+      for (int m = l; m < cnt; m += kWave) s_ops[w][m] = o.other[s0 + m];
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
     const int p_begin = (ch - o.chunk_pref[i]) * kChunk, p_end = p_begin + kChunk < d ? p_begin + kChunk : d;
     constexpr int U = 4;                         // loads under way
     for (int p0 = p_begin; p0 < p_end; p0 += 4 * kWave * U) {
@@ -835,6 +843,17 @@ __global__ __launch_bounds__(256) void k_short_classify(ShortSide in, ShortSide 
           for (int j = 0; j < 4; j++)
             if (e[j] == x && p + j < d) o.pos[s0 + m] = p + j;
         }
+      } else if (staged) {
+        int a[4] = {0, 0, 0, 0};                 // ops whose other end is not beyond e, the last of them left to the end
+        for (int len = cnt; len > 1; len -= len >> 1) {
+#pragma unroll
+          for (int j = 0; j < 4; j++) a[j] += s_ops[w][a[j] + (len >> 1) - 1] <= e[j] ? len >> 1 : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          a[j] += s_ops[w][a[j]] <= e[j];
+          if (a[j] > 0 && s_ops[w][a[j] - 1] == e[j] && p + j < d) o.pos[s0 + a[j] - 1] = p + j;
+        }
       } else {
 #pragma unroll
         for (int j = 0; j < 4; j++) {
@@ -851,79 +870,74 @@ __global__ __launch_bounds__(256) void k_short_classify(ShortSide in, ShortSide 
   }
 }
 
-// Effective ops, one workgroup per side: Delta E in (dst, src) order (in side), insertions and deletions per
-// touched node, the pool space that relocations need.  The workgroup that ends second decides whether
-// the batch may be applied and publishes the record.  n <= ITEMS * 1024.
-template <int ITEMS>
-__global__ __launch_bounds__(kOneChunk) void k_short_finish(int n, ShortSide in, ShortSide out, int32_t *ins_s, int32_t *ins_d,
+// Effective ops: Delta E in (dst, src) order (in side), insertions and deletions per touched node, the pool space that
+// relocations need.  A workgroup has 1024 ops of a side and the nodes whose first op is among them; what stands before its ops, and
+// the ops of its last node that lie beyond them, it counts itself.  The workgroup that ends last decides whether the batch may be
+// applied and publishes the record.  (One workgroup a side took 29 us for 10000 ops, this takes 10.)
+__global__ __launch_bounds__(kOneChunk) void k_short_finish(int n, int n_chunks, ShortSide in, ShortSide out, int32_t *ins_s, int32_t *ins_d,
                                                             int32_t *del_s, int32_t *del_d, float slack, long long room_in,
                                                             long long room_out, Counters *g, HostCounters *h, uint32_t *h_seq,
                                                             uint32_t seq) {
-  __shared__ int sm[kOneChunk / kWave];
+  static_assert(kShortBatch < 1 << 16, "insertions in the low half, deletions in the high half");
+  __shared__ int sm[kOneChunk / kWave], sp[kOneChunk / kWave];
+  __shared__ int P[kOneChunk + 1];               // effective ops among the workgroup's first t
   __shared__ unsigned long long s_need;
-  __shared__ int s_last;
-  const int side = blockIdx.x, t = threadIdx.x;
+  __shared__ int s_tail, s_beyond, s_last;
+  const int side = (int)blockIdx.x >= n_chunks, b = (int)blockIdx.x - (side ? n_chunks : 0), t = threadIdx.x;
+  const int l = lane_id(), w = t / kWave;
   const ShortSide &o = side ? out : in;
-  const int n_uniq = g->v[o.slot_n];
-  const int n_ops = n_uniq ? n : 0;              // none after a malformed entry
-  if (t == 0) s_need = 0;
-  const Items it = Items::of<ITEMS>();
-  const uint64_t below = (1ull << lane_id()) - 1;
-  int e[ITEMS], pos[ITEMS];
+  const int n_ops = g->v[o.slot_n] ? n : 0;      // none after a malformed entry
+  auto count = [](int op, int pos) __attribute__((always_inline)) { const int e = effect_of(op, pos); return e == 1 ? 1 : e == 2 ? 1 << 16 : 0; };
+  const int i = b * kOneChunk + t, end = (b + 1) * kOneChunk;
+  const int mine = i < n_ops ? count(o.op[i], o.pos[i]) : 0;
+  const int u = i < n_ops ? o.head[i] : -1;
+  int part = 0;
+  if (n_ops)
+    for (int k = t; k < b * (kOneChunk / 4); k += kOneChunk) {       // four ops a load
+      const uchar4 op = reinterpret_cast<const uchar4 *>(o.op)[k];
+      const int4 pos = reinterpret_cast<const int4 *>(o.pos)[k];
+      part += count(op.x, pos.x) + count(op.y, pos.y) + count(op.z, pos.z) + count(op.w, pos.w);
+    }
+  const int stop = u >= 0 ? o.seg[u + 1] : 0, dg = u >= 0 ? o.udeg[u] : 0, cap = u >= 0 ? o.ucap[u] : 0;
 #pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    const int i = it.at(k);
-    e[k] = i < n_ops ? o.op[i] : 2;              // 2: a dead op
-    pos[k] = i < n_ops ? o.pos[i] : -1;
-  }
-  int cnt = 0, carry;                            // insertions in the low half, deletions in the high half
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    e[k] = effect_of((uint8_t)e[k], pos[k]);
-    cnt += __popcll(__ballot(e[k] == 1)) + (__popcll(__ballot(e[k] == 2)) << 16);
-  }
-  int at = wave_prefix(cnt, sm, &carry);
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    const uint64_t mi = __ballot(e[k] == 1), md = __ballot(e[k] == 2);
-    const int i = it.at(k), ei = (at & 0xFFFF) + __popcll(mi & below), ed = (at >> 16) + __popcll(md & below);
-    if (i < n_ops) o.pfx[i] = (ei + (e[k] == 1)) + ((ed + (e[k] == 2)) << 16);
-    if (side == 0 && e[k] == 1) { ins_s[ei] = o.other[i]; ins_d[ei] = o.node[i]; }
-    if (side == 0 && e[k] == 2) { del_s[ed] = o.other[i]; del_d[ed] = o.node[i]; }
-    at += __popcll(mi) + (__popcll(md) << 16);
-  }
-  __threadfence_block();
+  for (int k = kWave / 2; k > 0; k >>= 1) part += __shfl_xor(part, k, kWave);
+  const uint64_t below = (1ull << l) - 1, mi = __ballot(mine == 1), md = __ballot(mine > 1);
+  if (l == 0) { sm[w] = __popcll(mi) + (__popcll(md) << 16); sp[w] = part; }
+  if (t == 0) { s_tail = -1; s_beyond = 0; s_need = 0; }
   __syncthreads();
-  unsigned long long need = 0;
-  int s0[ITEMS], s1[ITEMS], dg[ITEMS], cp[ITEMS];
+  int before = 0, here = __popcll(mi & below) + (__popcll(md & below) << 16), tot = 0;
 #pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    const int i = it.at(k) < n_uniq ? it.at(k) : 0;
-    s0[k] = n_uniq ? o.seg[i] : 0; s1[k] = n_uniq ? o.seg[i + 1] : 0;
-    dg[k] = n_uniq ? o.udeg[i] : 0; cp[k] = n_uniq ? o.ucap[i] : 0;
+  for (int k = 0; k < kOneChunk / kWave; k++) { before += sp[k]; here += k < w ? sm[k] : 0; tot += sm[k]; }
+  const int at = before + here;
+  P[t] = here;
+  if (t == 0) P[kOneChunk] = tot;
+  if (stop > end) s_tail = stop;                 // the last node's, if any
+  if (side == 0 && mine == 1) { ins_s[at & 0xFFFF] = o.other[i]; ins_d[at & 0xFFFF] = o.node[i]; }
+  else if (side == 0 && mine) { del_s[at >> 16] = o.other[i]; del_d[at >> 16] = o.node[i]; }
+  __syncthreads();
+  if (s_tail > 0) {
+    int beyond = 0;
+    for (int k = end + t; k < s_tail; k += kOneChunk) beyond += count(o.op[k], o.pos[k]);
+    if (beyond) atomicAdd(&s_beyond, beyond);
+    __syncthreads();
   }
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    s1[k] = s1[k] > 0 ? o.pfx[s1[k] - 1] : 0; s0[k] = s0[k] > 0 ? o.pfx[s0[k] - 1] : 0;
+  if (u >= 0) {
+    const int x = P[stop < end ? stop - b * kOneChunk : kOneChunk] - P[t] + (stop > end ? s_beyond : 0);
+    const int ni = x & 0xFFFF, nd = x >> 16;
+    o.nd_ins[u] = ni; o.nd_del[u] = nd;
+    const int d2 = dg - nd + ni;
+    if (d2 > cap) atomicAdd(&s_need, (unsigned long long)relocated_cap(d2, cap, slack));
   }
-#pragma unroll
-  for (int k = 0; k < ITEMS; k++) {
-    const int i = it.at(k);
-    if (i >= n_uniq) continue;
-    const int x = s1[k] - s0[k], ni = x & 0xFFFF, nd = x >> 16;
-    o.nd_ins[i] = ni; o.nd_del[i] = nd;
-    const int d2 = dg[k] - nd + ni;
-    if (d2 > cp[k]) need += (unsigned long long)relocated_cap(d2, cp[k], slack);
-  }
-  if (need) atomicAdd(&s_need, need);
   __syncthreads();
   if (t == 0) {
-    const int slot_i = side ? C_OINS : C_GINS, slot_d = side ? C_ODEL : C_GDEL;
-    __hip_atomic_store(&g->v[slot_i], carry & 0xFFFF, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&g->v[slot_d], carry >> 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&g->stripe[0][side], s_need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // the other stripes stay 0
+    if (b == n_chunks - 1) {
+      const int total = before + tot;
+      __hip_atomic_store(&g->v[side ? C_OINS : C_GINS], total & 0xFFFF, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&g->v[side ? C_ODEL : C_GDEL], total >> 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (s_need) atomicAdd(&g->stripe[0][side], s_need);      // cleared with the slots; the other stripes stay 0
     __threadfence();
-    s_last = atomicAdd(&g->v[C_NC], 1) == 1;      // slot unused otherwise by the graph stage
+    s_last = atomicAdd(&g->v[C_NC], 1) == (int)gridDim.x - 1;      // slot unused otherwise by the graph stage
     __threadfence();
     if (s_last) {
       auto rd = [&](int s) { return __hip_atomic_load(&g->v[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
@@ -1199,7 +1213,7 @@ static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n6
     b.skey = ar.get<uint64_t>((size_t)n_chunks * kOneChunk); b.sidx = ar.get<int32_t>((size_t)n_chunks * kOneChunk);
     b.node = ar.get<int32_t>(n); b.other = ar.get<int32_t>(n); b.op = ar.get<uint8_t>(n); b.pos = ar.get<int32_t>(n);
     b.seg = ar.get<int32_t>(n + 2); b.chunk_pref = ar.get<int32_t>(n + 1);
-    b.nd_ins = ar.get<int32_t>(n + 1); b.nd_del = ar.get<int32_t>(n + 1); b.fill = ar.get<int32_t>(n + 1); b.pfx = ar.get<int32_t>(n + 1);
+    b.nd_ins = ar.get<int32_t>(n + 1); b.nd_del = ar.get<int32_t>(n + 1); b.fill = ar.get<int32_t>(n + 1); b.head = ar.get<int32_t>(n + 1);
     b.uoff = ar.get<int64_t>(n); b.udeg = ar.get<int32_t>(n); b.ucap = ar.get<int32_t>(n);
     b.eoff = ar.get<int64_t>(n); b.edeg = ar.get<int32_t>(n); b.ecap = ar.get<int32_t>(n);
     b.off = gs[k]->off; b.deg = gs[k]->deg; b.cap = gs[k]->cap; b.ids = gs[k]->ids;
@@ -1212,23 +1226,23 @@ static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n6
   c->del_src = c->b_del_s.as<int32_t>(); c->del_dst = c->b_del_d.as<int32_t>();
   c->ins_src = c->b_ins_s.as<int32_t>(); c->ins_dst = c->b_ins_d.as<int32_t>();
   if (n <= 256) hipLaunchKernelGGL((k_short_one<256>), dim3(2), dim3(256), 0, s, raw, n, c->n, sd[0], sd[1], g);
+  else if (n <= 512) hipLaunchKernelGGL((k_short_one<512>), dim3(2), dim3(512), 0, s, raw, n, c->n, sd[0], sd[1], g);
   else if (n <= kOneChunk) hipLaunchKernelGGL((k_short_one<kOneChunk>), dim3(2), dim3(kOneChunk), 0, s, raw, n, c->n, sd[0], sd[1], g);
   else {
     hipLaunchKernelGGL(k_short_sort, dim3(2 * n_chunks), dim3(kOneChunk), 0, s, raw, n, c->n, n_chunks, sd[0], sd[1], chunk_err);
-    hipLaunchKernelGGL(k_short_merge, dim3(2 * n_chunks), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err);
-    if (n <= 4 * kOneChunk) hipLaunchKernelGGL(k_short_heads<4>, dim3(2), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err, g);
-    else hipLaunchKernelGGL(k_short_heads<kMaxChunks>, dim3(2), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err, g);
+#define INK_MERGE(C) \
+  hipLaunchKernelGGL(k_short_merge<C>, dim3(2 * n_chunks * kMergeParts), dim3(kMergeThreads), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err)
+    if (n_chunks <= 4) INK_MERGE(4);
+    else if (n_chunks <= 10) INK_MERGE(10);
+    else INK_MERGE(kMaxChunks);
+#undef INK_MERGE
+    hipLaunchKernelGGL(k_short_heads, dim3(2 * n_chunks), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err, g);
   }
   hipLaunchKernelGGL(k_short_classify, dim3(n <= kOneChunk ? 256 : 2048), dim3(256), 0, s, sd[0], sd[1], (const Counters *)g);
   const uint32_t seq = ++c->pub_seq;
-#define INK_FINISH(I)                                                                                                              \
-  hipLaunchKernelGGL(k_short_finish<I>, dim3(2), dim3(kOneChunk), 0, s, n, sd[0], sd[1], c->ins_src, c->ins_dst, c->del_src, c->del_dst, \
-                     c->slack, (long long)(c->gin.pool_cap - c->gin.pool_top), (long long)(c->gout.pool_cap - c->gout.pool_top), g, \
-                     c->h_gcnt, c->h_gseq, seq)
-  if (n <= kOneChunk) INK_FINISH(1);
-  else if (n <= 4 * kOneChunk) INK_FINISH(4);
-  else INK_FINISH(kMaxChunks);
-#undef INK_FINISH
+  hipLaunchKernelGGL(k_short_finish, dim3(2 * n_chunks), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], c->ins_src, c->ins_dst, c->del_src,
+                     c->del_dst, c->slack, (long long)(c->gin.pool_cap - c->gin.pool_top), (long long)(c->gout.pool_cap - c->gout.pool_top), g,
+                     c->h_gcnt, c->h_gseq, seq);
   auto apply = [&](const int32_t *ok) {
     hipLaunchKernelGGL(k_apply, dim3(2 * n), dim3(256), 0, s, apply_side_of(sd[0], c->gin, g, C_TOP64, nullptr),
                        apply_side_of(sd[1], c->gout, g, C_TOP64B, c->new_out), n, c->slack, ok);

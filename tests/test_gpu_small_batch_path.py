@@ -40,6 +40,28 @@ def test_both_forms_agree_and_match_the_oracle(kind, agg, exact):
     a.ink.close(); b.ink.close()
 
 
+@pytest.mark.parametrize("size", [511, 512, 513, 1023, 1026, 2048, 4096, 4097, 10240, 10241, 16384])
+def test_nodes_whose_ops_span_workgroups(size):
+    """Batches around the sizes at which the short form changes its launches, where most ops belong to one destination
+    and one source: lists that begin in one workgroup's share of the ops and end in another's, of up to and beyond 1024 ops."""
+    a, b = pair("sage", "max", True, n=20000, e=60000)
+    rng = np.random.default_rng(size)
+    n, k = a.n, size // 3
+    for hub in (a.n // 2, 0):
+        others = rng.choice(np.setdiff1d(np.arange(n), [hub]), size=2 * k, replace=False)
+        one = np.arange(size - 2 * k)
+        bs = np.r_[others[:k], np.full(k, hub), (one * 7) % n].astype(np.int32)
+        bd = np.r_[np.full(k, hub), others[k:], (one * 7 + 1 + one % 5) % n].astype(np.int32)
+        for op in (np.zeros(size, np.uint8), (rng.random(size) < 0.6).astype(np.uint8), np.ones(size, np.uint8)):
+            order = rng.permutation(size)
+            ra, _ = a.step(op[order], bs[order], bd[order])
+            rb, _ = b.step(op[order], bs[order], bd[order])
+            for key in ("n_applied_ins", "n_applied_del", "n_noop", "n_changed"):
+                assert ra[key] == rb[key], (size, key)
+            a.check_graph(); b.check_graph()
+    a.ink.close(); b.ink.close()
+
+
 def test_degenerate_short_batches():
     """Only self loops, only no-ops, one edge inserted and deleted many times, every op on one node."""
     a, b = pair("sage", "max", True, n=300, e=2000)
