@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256) void k_agg_events(AggArgs a, const int32_t *ta
       Cached<IS_MIN> c;
       EvAcc<IS_MIN> s;
       reduce_events<IS_MIN, LPR>(a, v, ev, e0, e1, lane_on, q, c, s);
-      finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, exp_list, exp, cnt);
+      finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, BitMark{chg}, exp_list, exp, cnt);
     }
   }
   if constexpr (!INLINE) exp.flush(exp_list, &cnt->v[C_NEXP]);
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targe
         }
       }
     s.any_del = __ballot((fl & 4) != 0) != 0ull;
-    finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, chg, exp_list, exp, cnt);
+    finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, BitMark{chg}, exp_list, exp, cnt);
   }
   if constexpr (!INLINE) exp.flush(exp_list, &cnt->v[C_NEXP]);
 }

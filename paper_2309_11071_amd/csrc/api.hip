@@ -915,7 +915,7 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
   {   // one pinned allocation: layer record + sequence number, graph record + sequence number, one more per layer, batch staging
     static_assert(sizeof(HostCounters) == 192, "records and sequence numbers on their own cache lines");
     char *h = nullptr;
-    constexpr size_t kRecords = 256 * (INK_MAX_LAYERS + 2);
+    constexpr size_t kRecords = kRecordBytes * (INK_MAX_LAYERS + 2);
     CREATE_TRY(hipHostMalloc((void **)&h, kRecords + kPinnedBatch * sizeof(ink_edge_update), hipHostMallocCoherent));
     memset(h, 0, kRecords);
     c->h_cnt = reinterpret_cast<HostCounters *>(h);
@@ -923,11 +923,10 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
     c->h_gcnt = reinterpret_cast<HostCounters *>(h + 256);
     c->h_gseq = reinterpret_cast<uint32_t *>(h + 448);
     for (int l = 1; l <= INK_MAX_LAYERS; l++) {
-      c->h_one[l] = reinterpret_cast<HostCounters *>(h + 256 * (l + 1));
-      c->h_oseq[l] = reinterpret_cast<uint32_t *>(h + 256 * (l + 1) + 192);
+      c->h_one[l] = reinterpret_cast<HostCounters *>(h + kRecordBytes * (l + 1));
+      c->h_oseq[l] = reinterpret_cast<uint32_t *>(h + kRecordBytes * (l + 1) + sizeof(HostCounters));
     }
     c->h_batch = reinterpret_cast<ink_edge_update *>(h + kRecords);
-    CREATE_TRY(hipMalloc(&c->d_chain, sizeof(Chain)));
   }
   // Who hands batches over in host memory wants results there, and the first one, too: first pass of 100 updates and
   // their inverse, 10k nodes, 1.15 -> .93 ms, 333 on 87k nodes 1.86 -> 1.45.
@@ -1016,7 +1015,6 @@ extern "C" void ink_destroy(ink_ctx *c) {
   if (c->cnorm) (void)hipFree(c->cnorm);
   if (c->d_cnt) (void)hipFree(c->d_cnt);
   if (c->d_gcnt) (void)hipFree(c->d_gcnt);
-  if (c->d_chain) (void)hipFree(c->d_chain);
   if (c->h_cnt) (void)hipHostFree(c->h_cnt);
   if (c->h_res) (void)hipHostFree(c->h_res);
   if (c->bm_a) (void)hipFree(c->bm_a);
@@ -1588,53 +1586,49 @@ static bool layer_one_possible(const ink_ctx *c, int64_t n_batch) {
   return true;
 }
 
-static hipError_t layer_one_launch(ink_ctx *c, int l) {
-  const DevLayer &L = c->layers[l - 1];
-  OneLayer p;
-  memset(&p, 0, sizeof(p));
-  p.a = agg_args(c, l);
-  p.a.big_deg = agg_select_long_degree(p.a, kOneEvents);
-  INK_TRY(agg_select_reserve(c, p.a));
-  p.g = c->d_gcnt; p.chain = c->d_chain; p.cnt = c->d_cnt;
-  p.del_s = c->del_src; p.del_d = c->del_dst; p.ins_s = c->ins_src; p.ins_d = c->ins_dst;
-  p.F = c->f_list[(l - 1) & 1].as<int32_t>(); p.F_next = c->f_list[l & 1].as<int32_t>(); p.pref = c->f_pref.as<int32_t>();
-  p.out_off = c->gout.off; p.out_ids = c->gout.ids; p.out_deg = c->gout.deg; p.new_out = c->new_out;
-  p.touched_src = c->b_uniq.as<int32_t>();
-  p.t_list = c->t_list.as<int32_t>(); p.bm = c->bm_a;
-  p.Hp = c->H[l - 1].f(); p.ldh = c->H[l - 1].ld; p.d_in = L.in_dim;
-  p.W = L.W1; p.Kp = L.K1p; p.Np = L.N1p; p.bias = L.b1; p.n_out = L.out_dim; p.relu = L.act == INK_ACT_RELU;
-  p.user = c->USER[l].f(); p.ld_user = c->USER[l].ld;
-  p.out = c->H[l].f(); p.ld_out = c->H[l].ld;
-  p.layer = l; p.last = l == c->n_layers;
-  p.res = c->res_emb.as<float>();
-  static_assert(2 * kOneEvents * (4 + 4 * INK_MAX_OUT_DIM) <= INK_RESULT_HOST_BYTES, "its result fits there");
-  if (p.last && c->mirror) { p.h_ids = c->mirror_ids(); p.h_emb = c->mirror_emb(); }
-  p.h = c->h_one[l]; p.h_seq = c->h_oseq[l]; p.seq = c->one_seq[l] = ++c->pub_seq;
-  return layer_one(c, p);
-}
-
-// Behind the graph stage, before its record is awaited: as many layers as ran in one workgroup last time.
-static hipError_t layer_one_begin(ink_ctx *c) {
+// Behind the graph stage, before its record is awaited.
+static hipError_t layers_one_begin(ink_ctx *c) {
   const size_t rows = 2 * kOneEvents;
   for (DevBuf *b : {&c->f_list[0], &c->f_list[1], &c->t_list, &c->f_pref}) INK_TRY(b->reserve((rows + 2) * 4));
   INK_TRY(c->res_emb.reserve(rows * c->H[c->n_layers].d * 4));
-  const int depth = std::max(1, std::min(c->one_hint, c->n_layers));
-  for (int l = 1; l <= depth; l++) INK_TRY(layer_one_launch(c, l));
-  return hipSuccess;
+  OneUpdate p;
+  memset(&p, 0, sizeof(p));
+  AggArgs a[INK_MAX_LAYERS];
+  for (int l = 1; l <= c->n_layers; l++) {       // all layers before the first pointer is taken: they share the buffers
+    a[l - 1] = agg_args(c, l);
+    INK_TRY(agg_select_reserve(c, a[l - 1]));
+  }
+  for (int l = 1; l <= c->n_layers; l++) {
+    const DevLayer &L = c->layers[l - 1];
+    OneLayer &q = p.layer[l - 1];
+    q.a = a[l - 1];
+    q.a.big = a[c->n_layers - 1].big;
+    q.a.big_deg = agg_select_long_degree(q.a, kOneEvents);
+    q.Hp = c->H[l - 1].f(); q.ldh = c->H[l - 1].ld; q.d_in = L.in_dim;
+    q.W = L.W1; q.Kp = L.K1p; q.Np = L.N1p; q.bias = L.b1; q.n_out = L.out_dim; q.relu = L.act == INK_ACT_RELU;
+    q.user = c->USER[l].f(); q.ld_user = c->USER[l].ld;
+    q.out = c->H[l].f(); q.ld_out = c->H[l].ld;
+    c->one_seq[l] = ++c->pub_seq;
+  }
+  p.g = c->d_gcnt; p.cnt = c->d_cnt;
+  p.del_s = c->del_src; p.del_d = c->del_dst; p.ins_s = c->ins_src; p.ins_d = c->ins_dst;
+  p.f_list[0] = c->f_list[0].as<int32_t>(); p.f_list[1] = c->f_list[1].as<int32_t>(); p.pref = c->f_pref.as<int32_t>();
+  p.out_off = c->gout.off; p.out_ids = c->gout.ids; p.out_deg = c->gout.deg; p.new_out = c->new_out;
+  p.touched_src = c->b_uniq.as<int32_t>();
+  p.t_list = c->t_list.as<int32_t>(); p.bm = c->bm_a;
+  p.res = c->res_emb.as<float>();
+  static_assert(2 * kOneEvents * (4 + 4 * INK_MAX_OUT_DIM) <= INK_RESULT_HOST_BYTES, "its result fits there");
+  if (c->mirror) { p.h_ids = c->mirror_ids(); p.h_emb = c->mirror_emb(); }
+  p.h = reinterpret_cast<char *>(c->h_one[1]); p.seq = c->one_seq[1];
+  p.n_layers = c->n_layers;
+  return layers_one(c, p);
 }
 
-// The records of those layers; further layers the same way while they are small.  *l_next: first layer not done, with
-// its sources in f_list[(*l_next - 1) & 1]; *events_done: its events are.
-static ink_status layer_one_finish(ink_ctx *c, int64_t n_seed, int *l_next, bool *events_done, int64_t *nF, int64_t *n_chg,
-                                   ink_update_result *out) {
-  int launched = std::max(1, std::min(c->one_hint, c->n_layers)), l = 1;
-  for (; l <= c->n_layers; l++) {
-    if (n_seed == 0 && *nF == 0) break;                   // nothing left to propagate
-    if (l > launched) {
-      if (*n_chg > kOneEvents || n_seed + *n_chg > kOneEvents || *nF > kOneEvents) break;
-      API_TRY(layer_one_launch(c, l));
-      launched = l;
-    }
+// Their records.  *l_next: first layer not done, with its sources in f_list[(*l_next - 1) & 1]; *events_done: its events are.
+static ink_status layers_one_finish(ink_ctx *c, int64_t n_seed, int *l_next, bool *events_done, int64_t *nF, int64_t *n_chg,
+                                    ink_update_result *out) {
+  int l = 1;
+  for (; l <= c->n_layers && n_seed > 0; l++) {
     API_TRY(wait_published(c, c->h_oseq[l], c->one_seq[l]));
     const HostCounters *h = c->h_one[l];
     if (h->v[C_ONE] != kOneDone) { *events_done = h->v[C_ONE] == kOneEventsDone; break; }
@@ -1645,7 +1639,6 @@ static ink_status layer_one_finish(ink_ctx *c, int64_t n_seed, int *l_next, bool
     S.n_changed = *nF = h->v[C_NEXT];
     *n_chg = (uint32_t)h->v[C_NEV];
   }
-  if (n_seed > 0) c->one_hint = l - 1;
   *l_next = l;
   if (l > c->n_layers) {
     c->n_touched_src = 0;                                 // the last layer has cleared the marks
@@ -1712,7 +1705,7 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
       }
     }
     one = n <= kOneEvents && n <= c->small_batch && layer_one_possible(c, n);
-    ink_status st = graph_apply_batch(c, raw, n, &n_ins, &n_del, one ? layer_one_begin : nullptr);
+    ink_status st = graph_apply_batch(c, raw, n, &n_ins, &n_del, one ? layers_one_begin : nullptr);
     if (st != INK_OK) return drain(c, st);       // behind the record that tells of a bad entry stand launches that do nothing for it
   }
   out->n_applied_ins = n_ins; out->n_applied_del = n_del; out->n_noop = n - n_ins - n_del;
@@ -1746,7 +1739,7 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
   int first = 1;
   bool events_done = false;
   if (one) {
-    ink_status st = layer_one_finish(c, n_seed, &first, &events_done, &nF, &n_chg, out);
+    ink_status st = layers_one_finish(c, n_seed, &first, &events_done, &nF, &n_chg, out);
     if (st != INK_OK) return st;
     cur = (first - 1) & 1;
   }

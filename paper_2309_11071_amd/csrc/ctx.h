@@ -90,7 +90,6 @@ constexpr int64_t kPinnedBatch = 1024;     // host batches up to this size are r
 // A layer of at most this many events can run in one workgroup (layer_one.hip), which leaves in slot C_ONE how far it came.
 constexpr int kOneEvents = 32;
 enum { kOneNothing = 0, kOneEventsDone, kOneDone };
-struct Chain { int32_t done, n_f, n_ev, pad; };   // device: last layer done that way, its changed rows and the events they propagate
 
 constexpr int kStripes = 64;
 enum { ST_EXPOSED = 0, ST_REGATHER, ST_ACHG, ST_NODEL, ST_NOEFFECT, ST_COVERED, ST_REGATHER_LONG, ST_PAD7, ST_N };
@@ -186,11 +185,9 @@ struct ink_ctx {
   ink::Counters *d_gcnt = nullptr;   // the graph stage's own block, its pinned mirror and sequence number
   ink::HostCounters *h_gcnt = nullptr;
   uint32_t *h_gseq = nullptr;
-  ink::Chain *d_chain = nullptr;
   ink::HostCounters *h_one[INK_MAX_LAYERS + 1] = {nullptr};   // records of the layers that ran in one workgroup, and
   uint32_t *h_oseq[INK_MAX_LAYERS + 1] = {nullptr};           // their sequence numbers (pinned)
   uint32_t one_seq[INK_MAX_LAYERS + 1] = {0};                 // what to wait for
-  int one_hint = INK_MAX_LAYERS;     // layers that ran that way in the last update that could
   ink_edge_update *h_batch = nullptr;   // pinned staging of short host batches
   int64_t small_batch = 16384;       // batches up to this size take the short form of the graph stage
   uint64_t *bm_a = nullptr;          // node bitmaps (n bits each)
@@ -348,24 +345,30 @@ struct XformArgs {
 hipError_t xform_run(ink_ctx *c, const XformArgs &x);
 // SAGE: row of the padded weight matrix where W_self starts (both halves of the input at multiples of 4)
 __host__ __device__ inline int xform_self_row(int in_dim) { return (in_dim + 3) & ~3; }
-// ---- a small layer in one workgroup (layer_one.hip)
+// ---- the layers of a small update in one workgroup (layer_one.hip)
+constexpr int kRecordBytes = 256;                  // a layer's record: HostCounters and its sequence number behind them
 struct OneLayer {
   AggArgs a;                                       // with big_deg of a short launch
-  const Counters *g; Chain *chain; Counters *cnt;  // graph stage's counters; the chain; this layer's counters
-  const int32_t *del_s, *del_d, *ins_s, *ins_d;    // applied edge changes
-  const int32_t *F; int32_t *F_next, *pref;        // changed sources of this layer and of the next; prefix of their kept out-edges
-  const int64_t *out_off; const int32_t *out_ids, *out_deg; int32_t *new_out; const int32_t *touched_src;
-  int32_t *t_list; uint64_t *bm;
+  int lanes;                                       // lanes per row
   const float *Hp; int ldh; int d_in;              // SAGE transform
   const float *W; int Kp, Np; const float *bias; int n_out, relu;
   const float *user; int ld_user;
   float *out; int ld_out;
-  int layer, last;
-  float *res;                                      // last layer: the changed rows, packed
-  int32_t *h_ids; float *h_emb;                    // ... and ids and rows in pinned memory (null: not wanted there)
-  HostCounters *h; uint32_t *h_seq; uint32_t seq;
 };
-hipError_t layer_one(ink_ctx *c, const OneLayer &p);
+struct OneUpdate {
+  const Counters *g; Counters *cnt;                // graph stage's counters; where a layer that is not finished leaves its own
+  const int32_t *del_s, *del_d, *ins_s, *ins_d;    // applied edge changes
+  int32_t *f_list[2], *pref;                       // changed sources that layer l leaves: [l & 1]; prefix of their kept out-edges
+  const int64_t *out_off; const int32_t *out_ids, *out_deg; int32_t *new_out; const int32_t *touched_src;
+  int32_t *t_list; uint64_t *bm;
+  float *res;                                      // the changed rows of the last layer, packed
+  int32_t *h_ids; float *h_emb;                    // ... and ids and rows in pinned memory (null: not wanted there)
+  char *h; uint32_t seq;                           // record of layer 1, the others behind it; its sequence number, those of the others follow
+  int n_layers;
+  OneLayer layer[INK_MAX_LAYERS];
+};
+static_assert(sizeof(OneUpdate) <= 4096, "fits a launch's arguments");
+hipError_t layers_one(ink_ctx *c, OneUpdate &p);
 // position of W[k][col] in the padded device copy: k-chunks of 32, in a chunk one tile per 32 columns, in the order
 // in which a wave loads its operands of the tile's 16 two-k steps: lane (k % 2) * 32 + col % 32 needs k % 32 / 2 = 0 .. 15,
 // four of them per 16-byte load, and the 64 lanes of a load are contiguous

@@ -337,6 +337,10 @@ __device__ __forceinline__ void finish_empty(F4 &bv, I4 &bi, F4 &sv, I4 &si) {
 __device__ __forceinline__ void mark_bit(uint64_t *bm, int v) {
   atomicOr((unsigned long long *)&bm[v >> 6], 1ull << (v & 63));
 }
+struct BitMark {
+  uint64_t *bm;
+  __device__ __forceinline__ void operator()(int v) const { mark_bit(bm, v); }
+};
 
 // ------------------------------------------------------------------ event-driven incremental update
 // Events of a target arrive as one contiguous segment of ev_val (kind << 30 | source id).
@@ -484,10 +488,10 @@ struct RowSink {
 };
 
 // The decision for target v once its events are reduced (the lane groups still hold partial
-// results), the recompute of an exposed row of moderate length, and the store.
-template <bool IS_MIN, int LPR, bool INLINE>
+// results), the recompute of an exposed row of moderate length, and the store.  `mark` notes a change of its value.
+template <bool IS_MIN, int LPR, bool INLINE, class Mark>
 __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cached<IS_MIN> &k, EvAcc<IS_MIN> &s,
-                                              bool lane_on, int q, uint64_t *chg, int32_t *exp_list,
+                                              bool lane_on, int q, const Mark &mark, int32_t *exp_list,
                                               RowSink &exp, Counters *cnt) {
   const int l = lane_id();
   const F4 &ov = k.ov; const I4 &oi = k.oi; const F4 &ou = k.ou; const I4 &o2 = k.o2;
@@ -574,7 +578,7 @@ __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cac
         finish_empty<IS_MIN>(bv, bi, sv, si);
         RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
         const bool ch = store_row<LPR>(o, v, lane_on, q, bv, bi, sv, si, true, ov, oi);
-        if (ch && l == 0) { mark_bit(chg, v); if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull); }
+        if (ch && l == 0) { mark(v); if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull); }
         return;
       }
     }
@@ -603,7 +607,7 @@ __device__ __forceinline__ void finish_target(const AggArgs &a, int v, const Cac
     }
   }
   const bool ch = __ballot(vchg) != 0ull;
-  if (ch && l == 0) { mark_bit(chg, v); if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull); }
+  if (ch && l == 0) { mark(v); if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull); }
 }
 
 // The events [e0, e1) of target v into s and the target's cached row into c; every lane group keeps

@@ -120,3 +120,20 @@ def test_bad_entries_leave_everything_untouched():
     for l in (1, 2):
         assert np.array_equal(dev.get_layer(l, 0).view(np.uint32), h.ink.get_layer(l, 0).view(np.uint32))
     dev.close(); h.ink.close()
+
+
+@pytest.mark.parametrize("agg,dims", [("max", (256, 128, 90)), ("min", (250, 96, 256, 20)), ("max", (130, 20, 64, 64, 64, 64, 64, 33, 9))])
+def test_products_handed_from_wave_to_wave(agg, dims):
+    """Two to eight waves a tile, one to four blocks of k, waves that take a second block; the most layers there can be.
+    One edge, the most rows of one tile (16 targets and sources) and one more."""
+    n = 4000
+    src, dst = ring_with_hub(n, 300, dims[1])
+    rng = np.random.default_rng(dims[0])
+    X = rng.integers(-3, 4, size=(n, dims[0])).astype(np.float32)
+    h = Harness(graph=(n, src, dst), X=X, model=tiny_model("sage", agg, dims, seed=dims[1]), precision="f32")
+    for size in (1, 3, 16, 17, 1):
+        s, d = rng.integers(0, n, size=size).astype(np.int32), rng.choice(n, size=size, replace=False).astype(np.int32)
+        h.step(np.full(size, INS, np.uint8), s, d)
+        h.step(np.full(size, DEL, np.uint8), s[::-1].copy(), d[::-1].copy())
+    h.check_state(); h.check_graph()
+    h.ink.close()
