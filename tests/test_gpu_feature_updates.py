@@ -173,3 +173,40 @@ def test_device_resident_arguments_match_host_arguments():
         assert np.array_equal(dev.get_layer(l, 0).view(np.uint32), h.ink.get_layer(l, 0).view(np.uint32))
     dev.close()
     h.ink.close()
+
+
+@pytest.mark.parametrize("kind,agg,exact", [("sage", "max", True), ("gin", "sum", False), ("gcn", "gcn_sym", False)])
+def test_sizes_at_the_edges_of_the_one_workgroup_form(kind, agg, exact):
+    """Ids ordered and checked in one workgroup of three sizes, from pinned memory or a copy, and beyond it; bad ids in
+    device memory, which only the device sees, are refused at each and change nothing."""
+    import torch
+    from paper_2309_11071_amd import Ink
+    from paper_2309_11071_amd.binding import InkError
+    dims = (6, 5, 4)
+    h, rng = harness(kind, agg, dims, n=5000, e=20000, exact=exact)
+    rp, col = h.ink.get_graph()
+    dev = Ink(rp, col, h.X, h.model, batch_device=True)
+    dev.full_infer()
+    for size in (1, 256, 257, 1024, 1025, 3072, 3073, 4096, 4097):
+        ids = rng.choice(h.n, size=size, replace=False).astype(np.int32)
+        rows = rng.standard_normal((size, dims[0])).astype(np.float32)
+        t_rows = torch.from_numpy(rows).cuda()
+        for bad, at in ((h.n, 0), (-1, size - 1), (1 << 30, size // 2), (int(ids[0]), size - 1)):
+            wrong = ids.copy()
+            wrong[at] = bad
+            if size == 1 and bad == ids[0]:
+                continue
+            t_ids = torch.from_numpy(wrong).cuda()
+            torch.cuda.synchronize()
+            with pytest.raises(InkError, match="more than once" if bad == ids[0] else "out of range"):
+                dev.update_features_device(t_ids.data_ptr(), t_rows.data_ptr(), size)
+        assert np.array_equal(dev.get_layer(0, 0), h.X)
+        res, _ = h.feature_step(ids, rows, exact=exact, tol=1e-5)
+        t_ids = torch.from_numpy(ids).cuda()
+        torch.cuda.synchronize()
+        r = dev.update_features_device(t_ids.data_ptr(), t_rows.data_ptr(), size)
+        assert r["n_changed"] == res["n_changed"]
+        for l in (0, 1, 2):
+            assert np.array_equal(dev.get_layer(l, 0).view(np.uint32), h.ink.get_layer(l, 0).view(np.uint32))
+    h.check_state(exact=exact, tol=1e-5)
+    dev.close(); h.ink.close()
