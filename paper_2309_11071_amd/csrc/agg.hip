@@ -86,10 +86,10 @@ __global__ __launch_bounds__(256) void k_agg_full(AggArgs a, const int32_t *targ
 // kBigChunk neighbours, partial rows to scratch
 struct BigParts { float *v; int32_t *i; float *s; int32_t *j; };     // best, its id, runner-up, its id: a row per chunk
 
-// whole rows: the NW waves of a workgroup take a part of a chunk each
-template <bool IS_MIN, int LPR, int NW>
+// whole rows: the NW waves of a workgroup take a part of a chunk each; the wave that has stored a part calls stored(place of its row in the list, node)
+template <bool IS_MIN, int LPR, int NW, bool COHERENT, class Stored>
 __device__ __forceinline__ void whole_chunks(const AggArgs &a, int total, int n_big, float (*sv)[kWave * 4], int (*si)[kWave * 4], float (*ss)[kWave * 4],
-                                             int (*sj)[kWave * 4], const BigParts &part) {
+                                             int (*sj)[kWave * 4], const BigParts &part, const Stored &stored) {
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
@@ -117,9 +117,11 @@ __device__ __forceinline__ void whole_chunks(const AggArgs &a, int total, int n_
         int64_t o = (int64_t)cg * a.wd + 4 * q;
 #pragma unroll
         for (int c = 0; c < 4; c++) {
-          part.v[o + c] = bv.v[c]; part.i[o + c] = bi.v[c]; part.s[o + c] = s2.v[c]; part.j[o + c] = j2.v[c];
+          put_part<COHERENT>(part.v + o + c, bv.v[c]); put_part<COHERENT>(part.i + o + c, bi.v[c]);
+          put_part<COHERENT>(part.s + o + c, s2.v[c]); put_part<COHERENT>(part.j + o + c, j2.v[c]);
         }
       }
+      stored(i, v);
     }
     __syncthreads();
   }
@@ -131,7 +133,53 @@ __global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const Counters *
   __shared__ float sv[NW][kWave * 4], ss[NW][kWave * 4];
   __shared__ int si[NW][kWave * 4], sj[NW][kWave * 4];
   const int total = ieee_mode_off(cnt->v[C_NCHUNK]);
-  whole_chunks<IS_MIN, LPR, NW>(a, total, cnt->v[C_NBIG], sv, si, ss, sj, part);
+  whole_chunks<IS_MIN, LPR, NW, false>(a, total, cnt->v[C_NBIG], sv, si, ss, sj, part, [](int, int) {});
+}
+
+// One wave combines the parts [p0, p1) of row v: its lane groups take them in turn, U of them in flight, then the row is stored.  (One
+// row after the other made a hub's chain the launch's time: 45 us on 12.5M edges and rows of 128 floats, now 21.)
+template <bool IS_MIN, int LPR, int U, bool COHERENT>
+__device__ __forceinline__ void combine_row(const AggArgs &a, int v, int p0, int p1, const BigParts &part, uint64_t *chg, int compare, Counters *cnt) {
+  const int l = lane_id();
+  const int q = l % LPR;
+  const bool lane_on = 4 * q < a.wd;
+  constexpr int G = kWave / LPR;
+  const int g = l / LPR, qo = lane_on ? 4 * q : 0;
+  F4 bv; I4 bi; F4 s2; I4 j2;
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    bv.v[c] = worst<IS_MIN>(); bi.v[c] = 0x7fffffff; s2.v[c] = worst<IS_MIN>(); j2.v[c] = 0x7fffffff;
+  }
+  for (int pb = p0; pb < p1; pb += G * U) {
+    float4 xv[U], xs[U];
+    int4 xi[U], xj[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int p = pb + u * G + g;
+      const int64_t o = (int64_t)(p < p1 ? p : p1 - 1) * a.wd + qo;
+      xv[u] = get_part<COHERENT, float4>(part.v + o); xi[u] = get_part<COHERENT, int4>(part.i + o);
+      xs[u] = get_part<COHERENT, float4>(part.s + o); xj[u] = get_part<COHERENT, int4>(part.j + o);
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const bool on = pb + u * G + g < p1;        // a partial row past the end is empty: it takes no place
+      const float yv[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w}, ys[4] = {xs[u].x, xs[u].y, xs[u].z, xs[u].w};
+      const int yi[4] = {xi[u].x, xi[u].y, xi[u].z, xi[u].w}, yj[4] = {xj[u].x, xj[u].y, xj[u].z, xj[u].w};
+#pragma unroll
+      for (int c = 0; c < 4; c++)
+        merge2i<IS_MIN>(on ? yv[c] : worst<IS_MIN>(), on ? yi[c] : 0x7fffffff, on ? ys[c] : worst<IS_MIN>(),
+                        on ? yj[c] : 0x7fffffff, bv.v[c], bi.v[c], s2.v[c], j2.v[c]);
+    }
+  }
+  reduce_groups_i<IS_MIN, LPR>(bv, bi, s2, j2);
+  finish_empty<IS_MIN>(bv, bi, s2, j2);
+  RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
+  F4 dum; I4 dumi;
+  bool ch = store_row<LPR>(o, v, lane_on, q, bv, bi, s2, j2, false, dum, dumi);
+  if (compare && ch && chg && l == 0) {
+    mark_bit(chg, v);
+    if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull);
+  }
 }
 
 // The same for launches of few targets, where one chunk's time is the launch's: 16 waves take a slice of kSliceCols
@@ -142,12 +190,17 @@ __global__ __launch_bounds__(256) void k_big_partial(AggArgs a, const Counters *
 // bytes, 625k nodes and rows of 128 floats), but the chunks' fixed costs four times over take as much (10 to 600k nodes,
 // rows of 128 and 256 floats: 0.94 to 1.0 of the speed).
 template <bool IS_MIN, int ROW>
-__global__ __launch_bounds__(1024) void k_big_short(AggArgs a, const Counters *cnt, int slices, BigParts part) {
+__global__ __launch_bounds__(1024) void k_big_short(AggArgs a, Counters *cnt, int slices, BigParts part, uint64_t *chg, int compare, int32_t *arrived) {
   constexpr int LPR = kSliceLanes, NW = 16;
   __shared__ float sv[NW][kWave * 4], ss[NW][kWave * 4];
   __shared__ int si[NW][kWave * 4], sj[NW][kWave * 4];
   const int total = ieee_mode_off(cnt->v[C_NCHUNK]), n_big = cnt->v[C_NBIG];
-  if (slices > 2 && total > kSlicedItems / slices) { whole_chunks<IS_MIN, ROW, NW>(a, total, n_big, sv, si, ss, sj, part); return; }
+  const bool whole = slices > 2 && total > kSlicedItems / slices;
+  auto stored = [&](int i, int v) {          // a row's last part combines it: a launch of its own took 6 to 7 us, this 4 to 5 (100 updates on 10k nodes 338 -> 324 us a pass)
+    const int chunks = big_row_chunks(a.in_deg[v], a.big.chunk), p0 = a.big.base[i];
+    if (last_to_arrive(arrived + i, whole ? chunks : chunks * slices)) combine_row<IS_MIN, ROW, 2, true>(a, v, p0, p0 + chunks, part, chg, compare, cnt);
+  };
+  if (whole) { whole_chunks<IS_MIN, ROW, NW, true>(a, total, n_big, sv, si, ss, sj, part, stored); return; }
   const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = l % LPR, items = slice_items(total, slices);
   for (int b = blockIdx.x; b < items; b += gridDim.x) {
@@ -172,61 +225,20 @@ __global__ __launch_bounds__(1024) void k_big_short(AggArgs a, const Counters *c
       int xi = si[0][col], xj = sj[0][col];
       for (int ww = 1; ww < NW; ww++) merge2i<IS_MIN>(sv[ww][col], si[ww][col], ss[ww][col], sj[ww][col], xv, xi, xs, xj);
       const int64_t o = (int64_t)cg * a.wd + c0 + col;
-      part.v[o] = xv; part.i[o] = xi; part.s[o] = xs; part.j[o] = xj;
+      put_part<true>(part.v + o, xv); put_part<true>(part.i + o, xi); put_part<true>(part.s + o, xs); put_part<true>(part.j + o, xj);
     }
+    if (w == 0) stored(i, v);
     __syncthreads();
   }
 }
 
-// One wave per big row: its lane groups take the partial rows in turn, U of them in flight, then the row is stored.  (One
-// row after the other made a hub's chain the launch's time: 45 us on 12.5M edges and rows of 128 floats, now 21.)
+// A kernel for long launches, whose rows are many.  (In theirs the chunk kernel's registers would suffer from the combination: 80 -> 126.)
 template <bool IS_MIN, int LPR>
-__global__ __launch_bounds__(64) void k_big_final(AggArgs a, const float *part_v, const int32_t *part_i, const float *part_s,
-                                                  const int32_t *part_j, uint64_t *chg, int compare, Counters *cnt) {
-  const int l = lane_id();
-  const int q = l % LPR;
-  const bool lane_on = 4 * q < a.wd;
-  constexpr int G = kWave / LPR, U = 4;
-  const int g = l / LPR, qo = lane_on ? 4 * q : 0;
+__global__ __launch_bounds__(64) void k_big_final(AggArgs a, BigParts part, uint64_t *chg, int compare, Counters *cnt) {
   const int n_big = cnt->v[C_NBIG];
   for (int i = blockIdx.x; i < n_big; i += gridDim.x) {
-    int v = a.big.list[i];
-    F4 bv; I4 bi; F4 s2; I4 j2;
-#pragma unroll
-    for (int c = 0; c < 4; c++) {
-      bv.v[c] = worst<IS_MIN>(); bi.v[c] = 0x7fffffff; s2.v[c] = worst<IS_MIN>(); j2.v[c] = 0x7fffffff;
-    }
-    const int p0 = a.big.base[i], p1 = p0 + big_row_chunks(a.in_deg[v], a.big.chunk);
-    for (int pb = p0; pb < p1; pb += G * U) {
-      float4 xv[U], xs[U];
-      int4 xi[U], xj[U];
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        const int p = pb + u * G + g;
-        const int64_t o = (int64_t)(p < p1 ? p : p1 - 1) * a.wd + qo;
-        xv[u] = ld4(part_v + o); xi[u] = *reinterpret_cast<const int4 *>(part_i + o);
-        xs[u] = ld4(part_s + o); xj[u] = *reinterpret_cast<const int4 *>(part_j + o);
-      }
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        const bool on = pb + u * G + g < p1;        // a partial row past the end is empty: it takes no place
-        const float yv[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w}, ys[4] = {xs[u].x, xs[u].y, xs[u].z, xs[u].w};
-        const int yi[4] = {xi[u].x, xi[u].y, xi[u].z, xi[u].w}, yj[4] = {xj[u].x, xj[u].y, xj[u].z, xj[u].w};
-#pragma unroll
-        for (int c = 0; c < 4; c++)
-          merge2i<IS_MIN>(on ? yv[c] : worst<IS_MIN>(), on ? yi[c] : 0x7fffffff, on ? ys[c] : worst<IS_MIN>(),
-                          on ? yj[c] : 0x7fffffff, bv.v[c], bi.v[c], s2.v[c], j2.v[c]);
-      }
-    }
-    reduce_groups_i<IS_MIN, LPR>(bv, bi, s2, j2);
-    finish_empty<IS_MIN>(bv, bi, s2, j2);
-    RowOut o{a.A, a.ARG, a.UB, a.ARG2, a.ld, a.d};
-    F4 dum; I4 dumi;
-    bool ch = store_row<LPR>(o, v, lane_on, q, bv, bi, s2, j2, false, dum, dumi);
-    if (compare && ch && chg && l == 0) {
-      mark_bit(chg, v);
-      if (a.count_cond) atomicAdd(&cnt->stripe[blockIdx.x % kStripes][ST_ACHG], 1ull);
-    }
+    const int v = a.big.list[i], p0 = a.big.base[i];
+    combine_row<IS_MIN, LPR, 4, false>(a, v, p0, p0 + big_row_chunks(a.in_deg[v], a.big.chunk), part, chg, compare, cnt);
   }
 }
 
@@ -279,17 +291,51 @@ __global__ __launch_bounds__(256) void k_agg_events(AggArgs a, const int32_t *ta
 // runner-up candidate value, and the flags (bit 0 reset, bit 1 runner-up invalid, bit 2 any_del).
 struct EvPart { float *v; int32_t *i; float *s; int32_t *f; };
 
-// One workgroup per chunk of a long segment: its waves take a quarter of the events each.
-template <bool IS_MIN, int LPR>
+// One wave per long segment: its lane groups take the chunks in turn, then the target is decided.
+template <bool IS_MIN, int LPR, bool INLINE, bool COHERENT>
+__device__ __forceinline__ void combine_segment(const AggArgs &a, const int32_t *targets, const LongEvents &lng, const LongSeg &L, int n_ev,
+                                                const EvPart &part, uint64_t *chg, int32_t *exp_list, RowSink &exp, Counters *cnt) {
+  constexpr int G = kWave / LPR;
+  const int l = lane_id(), q = l % LPR, g = l / LPR;
+  const bool lane_on = 4 * q < a.wd;
+  const int v = targets[L.target];
+  const int nch = long_seg_chunks(lng, n_ev);
+  Cached<IS_MIN> c;
+  load_cached<IS_MIN>(a, v, lane_on, q, c);
+  EvAcc<IS_MIN> s;
+  s.init();
+  int fl = 0;
+  if (lane_on)
+    for (int p = g; p < nch; p += G) {
+      const int64_t o = (int64_t)(L.base + p) * a.wd + 4 * q;
+      const float4 pv = get_part<COHERENT, float4>(part.v + o), ps = get_part<COHERENT, float4>(part.s + o);
+      const int4 pi = get_part<COHERENT, int4>(part.i + o), pf = get_part<COHERENT, int4>(part.f + o);
+      const float xv[4] = {pv.x, pv.y, pv.z, pv.w}, xs[4] = {ps.x, ps.y, ps.z, ps.w};
+      const int xi[4] = {pi.x, pi.y, pi.z, pi.w}, xf[4] = {pf.x, pf.y, pf.z, pf.w};
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        merge2<IS_MIN>(xv[k], xi[k], xs[k], s.cv.v[k], s.ci.v[k], s.cs.v[k]);
+        s.reset[k] |= (xf[k] & 1) != 0;
+        s.inv2[k] |= (xf[k] & 2) != 0;
+        fl |= xf[k];
+      }
+    }
+  s.any_del = __ballot((fl & 4) != 0) != 0ull;
+  finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, BitMark{chg}, exp_list, exp, cnt);
+}
+
+// One workgroup per chunk of a long segment: its waves take a quarter of the events each.  ARRIVE (short launches): the segment's last chunk
+// combines it; a launch of its own took 4 to 5 us, most often for nothing.
+template <bool IS_MIN, int LPR, bool ARRIVE>
 __global__ __launch_bounds__(256) void k_ev_partial(AggArgs a, const int32_t *targets, const int32_t *seg, const uint32_t *ev,
-                                                    LongEvents lng, EvPart part, const Counters *cnt) {
+                                                    LongEvents lng, EvPart part, uint64_t *chg, Counters *cnt, int32_t *arrived) {
   constexpr int NW = 4;
   __shared__ float sv[NW][kWave * 4], ss[NW][kWave * 4];
   __shared__ int si[NW][kWave * 4], sf[NW][kWave * 4];
-  const int l = lane_id(), w = threadIdx.x / kWave;
+  const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
-  const int total = cnt->v[C_NEVCH];
+  const int total = ARRIVE ? ieee_mode_off(cnt->v[C_NEVCH]) : cnt->v[C_NEVCH];      // exposed rows are gathered where the target is decided
   for (int ch = blockIdx.x; ch < total; ch += gridDim.x) {
     int e0, e1;
     const int v = targets[long_chunk(lng, ch, seg, e0, e1)];
@@ -305,59 +351,43 @@ __global__ __launch_bounds__(256) void k_ev_partial(AggArgs a, const int32_t *ta
       sv[w][l * 4 + k] = s.cv.v[k]; si[w][l * 4 + k] = s.ci.v[k]; ss[w][l * 4 + k] = s.cs.v[k]; sf[w][l * 4 + k] = fl[k];
     }
     __syncthreads();
-    if (w == 0 && lane_on && l < LPR) {
-      for (int ww = 1; ww < NW; ww++)
+    if (w == 0) {
+      if (lane_on && l < LPR) {
+        for (int ww = 1; ww < NW; ww++)
+#pragma unroll
+          for (int k = 0; k < 4; k++) {
+            merge2<IS_MIN>(sv[ww][l * 4 + k], si[ww][l * 4 + k], ss[ww][l * 4 + k], s.cv.v[k], s.ci.v[k], s.cs.v[k]);
+            fl[k] |= sf[ww][l * 4 + k];
+          }
+        const int64_t o = (int64_t)ch * a.wd + 4 * q;
 #pragma unroll
         for (int k = 0; k < 4; k++) {
-          merge2<IS_MIN>(sv[ww][l * 4 + k], si[ww][l * 4 + k], ss[ww][l * 4 + k], s.cv.v[k], s.ci.v[k], s.cs.v[k]);
-          fl[k] |= sf[ww][l * 4 + k];
+          put_part<ARRIVE>(part.v + o + k, s.cv.v[k]); put_part<ARRIVE>(part.i + o + k, s.ci.v[k]);
+          put_part<ARRIVE>(part.s + o + k, s.cs.v[k]); put_part<ARRIVE>(part.f + o + k, fl[k]);
         }
-      const int64_t o = (int64_t)ch * a.wd + 4 * q;
-      *reinterpret_cast<float4 *>(part.v + o) = make_float4(s.cv.v[0], s.cv.v[1], s.cv.v[2], s.cv.v[3]);
-      *reinterpret_cast<int4 *>(part.i + o) = make_int4(s.ci.v[0], s.ci.v[1], s.ci.v[2], s.ci.v[3]);
-      *reinterpret_cast<float4 *>(part.s + o) = make_float4(s.cs.v[0], s.cs.v[1], s.cs.v[2], s.cs.v[3]);
-      *reinterpret_cast<int4 *>(part.f + o) = make_int4(fl[0], fl[1], fl[2], fl[3]);
+      }
+      if constexpr (ARRIVE) {
+        const int i = lng.owner[ch];
+        const LongSeg L = lng.list[i];
+        const int n_ev = seg[L.target + 1] - seg[L.target];
+        RowSink exp;
+        if (last_to_arrive(arrived + i, long_seg_chunks(lng, n_ev)))
+          combine_segment<IS_MIN, LPR, true, true>(a, targets, lng, L, n_ev, part, chg, nullptr, exp, cnt);
+      }
     }
     __syncthreads();
   }
 }
 
-// One wave per long segment: its lane groups take the chunks in turn, then the target is decided.
 template <bool IS_MIN, int LPR, bool INLINE>
 __global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targets, const int32_t *seg, LongEvents lng,
                                                  EvPart part, uint64_t *chg, int32_t *exp_list,
                                                  Counters *cnt) {
-  constexpr int G = kWave / LPR;
   RowSink exp;
-  const int l = lane_id(), q = l % LPR, g = l / LPR;
-  const bool lane_on = 4 * q < a.wd;
   const int n = INLINE ? ieee_mode_off(cnt->v[C_NEVL]) : cnt->v[C_NEVL];
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const LongSeg L = lng.list[i];
-    const int v = targets[L.target];
-    const int nch = (seg[L.target + 1] - seg[L.target] + lng.chunk - 1) / lng.chunk;
-    Cached<IS_MIN> c;
-    load_cached<IS_MIN>(a, v, lane_on, q, c);
-    EvAcc<IS_MIN> s;
-    s.init();
-    int fl = 0;
-    if (lane_on)
-      for (int p = g; p < nch; p += G) {
-        const int64_t o = (int64_t)(L.base + p) * a.wd + 4 * q;
-        const float4 pv = ld4(part.v + o), ps = ld4(part.s + o);
-        const int4 pi = *reinterpret_cast<const int4 *>(part.i + o), pf = *reinterpret_cast<const int4 *>(part.f + o);
-        const float xv[4] = {pv.x, pv.y, pv.z, pv.w}, xs[4] = {ps.x, ps.y, ps.z, ps.w};
-        const int xi[4] = {pi.x, pi.y, pi.z, pi.w}, xf[4] = {pf.x, pf.y, pf.z, pf.w};
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-          merge2<IS_MIN>(xv[k], xi[k], xs[k], s.cv.v[k], s.ci.v[k], s.cs.v[k]);
-          s.reset[k] |= (xf[k] & 1) != 0;
-          s.inv2[k] |= (xf[k] & 2) != 0;
-          fl |= xf[k];
-        }
-      }
-    s.any_del = __ballot((fl & 4) != 0) != 0ull;
-    finish_target<IS_MIN, LPR, INLINE>(a, v, c, s, lane_on, q, BitMark{chg}, exp_list, exp, cnt);
+    combine_segment<IS_MIN, LPR, INLINE, false>(a, targets, lng, L, seg[L.target + 1] - seg[L.target], part, chg, exp_list, exp, cnt);
   }
   if constexpr (!INLINE) exp.flush(exp_list, &cnt->v[C_NEXP]);
 }
@@ -367,16 +397,15 @@ static int lanes_per_row(int ld) { return ld <= 64 ? 16 : (ld <= 128 ? 32 : 64);
 
 template <bool IS_MIN, int LPR>
 static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compare, int64_t n_rows_max) {
-  const Counters *cnt = c->d_cnt;
   const BigParts part{c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>()};
   if (latency_mode(n_rows_max)) {
     const int slices = big_slices(a.wd);
-    hipLaunchKernelGGL((k_big_short<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part);
-  } else
-    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, cnt, part);
-  hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)c->big_part_v.as<float>(),
-                     (const int32_t *)c->big_part_i.as<int32_t>(), (const float *)c->big_part_s.as<float>(),
-                     (const int32_t *)c->big_part_j.as<int32_t>(), chg, compare, c->d_cnt);
+    hipLaunchKernelGGL((k_big_short<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, c->d_cnt, slices, part, chg,
+                       compare, c->arrived);
+  } else {
+    hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, (const Counters *)c->d_cnt, part);
+    hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, part, chg, compare, c->d_cnt);
+  }
   return hipGetLastError();
 }
 
@@ -422,10 +451,13 @@ static hipError_t launch_events(ink_ctx *c, const AggArgs &a, const int32_t *tar
                      n_targets_dev, ev, chg, exp_list, c->d_cnt, ev_block, lng);
   if (eb.max_seg > lng.limit) {      // otherwise no segment can be long
     EvPart part{c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>()};
-    hipLaunchKernelGGL((k_ev_partial<IS_MIN, LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(lng, eb.n_events), 8192)),
-                       dim3(256), 0, c->stream, a, targets, seg, ev, lng, part, (const Counters *)c->d_cnt);
-    hipLaunchKernelGGL((k_ev_final<IS_MIN, LPR, INLINE>), dim3((unsigned)std::min<int64_t>(long_ev_rows(lng, eb.n_events), 8192)),
-                       dim3(64), 0, c->stream, a, targets, seg, lng, part, chg, exp_list, c->d_cnt);
+    const dim3 chunks((unsigned)std::min<int64_t>(long_ev_chunks(lng, eb.n_events), 8192)), rows((unsigned)std::min<int64_t>(long_ev_rows(lng, eb.n_events), 8192));
+    if (latency) {                   // its exposed rows are recomputed on the spot (events_t)
+      hipLaunchKernelGGL((k_ev_partial<IS_MIN, LPR, true>), chunks, dim3(256), 0, c->stream, a, targets, seg, ev, lng, part, chg, c->d_cnt, c->arrived);
+    } else {
+      hipLaunchKernelGGL((k_ev_partial<IS_MIN, LPR, false>), chunks, dim3(256), 0, c->stream, a, targets, seg, ev, lng, part, chg, c->d_cnt, c->arrived);
+      hipLaunchKernelGGL((k_ev_final<IS_MIN, LPR, INLINE>), rows, dim3(64), 0, c->stream, a, targets, seg, lng, part, chg, exp_list, c->d_cnt);
+    }
   }
   return hipGetLastError();
 }

@@ -132,9 +132,10 @@ __global__ __launch_bounds__(256) void k_sum_full(AggArgs a, const int32_t *targ
 }
 
 // Chunks of long rows of at most 48 floats, of a table too large for slices to pay (kSlicedTableBytes), or of a short launch with many
-// (kSlicedItems), as they are: the NW waves of a workgroup take a part of a chunk each
-template <int LPR, int NW>
-__device__ __forceinline__ void whole_sum_chunks(const AggArgs &a, int total, int n_big, float (*sv)[kWave * 4], float *part) {
+// (kSlicedItems), as they are: the NW waves of a workgroup take a part of a chunk each; the wave that has stored a part calls
+// stored(place of its row in the list, node)
+template <int LPR, int NW, bool COHERENT, class Stored>
+__device__ __forceinline__ void whole_sum_chunks(const AggArgs &a, int total, int n_big, float (*sv)[kWave * 4], float *part, const Stored &stored) {
   const int l = lane_id(), w = threadIdx.x / kWave;
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
@@ -157,8 +158,9 @@ __device__ __forceinline__ void whole_sum_chunks(const AggArgs &a, int total, in
       if (lane_on && l < LPR) {
         int64_t o = (int64_t)cg * a.wd + 4 * q;
 #pragma unroll
-        for (int c = 0; c < 4; c++) part[o + c] = acc.v[c];
+        for (int c = 0; c < 4; c++) put_part<COHERENT>(part + o + c, acc.v[c]);
       }
+      stored(i, v);
     }
     __syncthreads();
   }
@@ -168,7 +170,7 @@ template <int LPR>
 __global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const Counters *cnt, float *part) {
   constexpr int NW = 4;
   __shared__ float sv[NW][kWave * 4];
-  whole_sum_chunks<LPR, NW>(a, cnt->v[C_NCHUNK], cnt->v[C_NBIG], sv, part);
+  whole_sum_chunks<LPR, NW, false>(a, cnt->v[C_NCHUNK], cnt->v[C_NBIG], sv, part, [](int, int) {});
 }
 
 // Chunks of the other rows, in slices (bigrows.h).  Whole rows came from beyond the L2 as often as not (GCN of 256 columns
@@ -176,8 +178,8 @@ __global__ __launch_bounds__(256) void k_sum_big_partial(AggArgs a, const Counte
 // in an XCD's L2 (4.4M of 97M lines, 661 us, 18.8 TB/s out of the L2s, of which the narrow rows above reach 17 to 24).
 // Inferences: that one 1.43 -> 1.22 ms, 100k nodes with 200 neighbours each and 256 columns 2.50 -> 2.27, GIN of 128
 // columns on 20k, 100k, 400k and 1M nodes 1.02, 1.0, 1.04 and 1.01 times as fast.
-template <int NW>
-__device__ __forceinline__ void sum_slices(const AggArgs &a, int total, int n_big, int slices, float (*sv)[kSliceCols], float *part) {
+template <int NW, bool COHERENT, class Stored>
+__device__ __forceinline__ void sum_slices(const AggArgs &a, int total, int n_big, int slices, float (*sv)[kSliceCols], float *part, const Stored &stored) {
   constexpr int LPR = kSliceLanes;
   const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = l % LPR, items = slice_items(total, slices);
@@ -199,61 +201,73 @@ __device__ __forceinline__ void sum_slices(const AggArgs &a, int total, int n_bi
     if (col < kSliceCols && c0 + col < a.wd) {
       float x = sv[0][col];
       for (int ww = 1; ww < NW; ww++) x = __fadd_rn(x, sv[ww][col]);
-      part[(int64_t)cg * a.wd + c0 + col] = x;
+      put_part<COHERENT>(part + (int64_t)cg * a.wd + c0 + col, x);
     }
+    if (w == 0) stored(i, v);
     __syncthreads();
   }
 }
 
 __global__ __launch_bounds__(256) void k_sum_big_slices(AggArgs a, const Counters *cnt, int slices, float *part) {
   __shared__ float sv[4][kSliceCols];
-  sum_slices<4>(a, cnt->v[C_NCHUNK], cnt->v[C_NBIG], slices, sv, part);
+  sum_slices<4, false>(a, cnt->v[C_NCHUNK], cnt->v[C_NBIG], slices, sv, part, [](int, int) {});
 }
 
-// Launches of few targets: 16 waves a chunk, and its slices in workgroups of their own unless they are many (kSlicedItems).  64
-// registers, so that a CU holds two.
+// One wave combines the parts [p0, p1) of row v: its lane groups take them in turn, U of them in flight.
+template <int LPR, int U, bool COHERENT>
+__device__ __forceinline__ void combine_sum_row(const AggArgs &a, int v, int p0, int p1, const float *part, uint64_t *chg, int compare) {
+  const int l = lane_id();
+  const int q = l % LPR;
+  const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
+  constexpr int G = kWave / LPR;
+  const int g = l / LPR < G ? l / LPR : G - 1, qo = lane_on ? 4 * q : 0;
+  S4 acc;
+#pragma unroll
+  for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
+  for (int pb = p0; pb < p1; pb += G * U) {
+    float4 x[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int p = pb + u * G + g;
+      x[u] = get_part<COHERENT, float4>(part + (int64_t)(p < p1 ? p : p1 - 1) * a.wd + qo);
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const bool on = pb + u * G + g < p1;
+      const float y[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+      for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], on ? y[c] : 0.f);
+    }
+  }
+  sum_groups<LPR>(acc);
+  const bool ch = store_sum<LPR>(a.A, a.ld, a.d, v, lane_on, q, acc, compare != 0);
+  if (ch && chg && l == 0) mark_bit_s(chg, v);
+}
+
+// Launches of few targets: 16 waves a chunk, and its slices in workgroups of their own unless they are many (kSlicedItems); a row's
+// last part combines it.  64 registers, so that a CU holds two.
 template <int LPR>
-__global__ __launch_bounds__(1024, 8) void k_sum_big_short(AggArgs a, const Counters *cnt, int slices, float *part) {
+__global__ __launch_bounds__(1024, 8) void k_sum_big_short(AggArgs a, const Counters *cnt, int slices, float *part, uint64_t *chg, int compare,
+                                                           int32_t *arrived) {
   constexpr int NW = 16;
   __shared__ float whole[NW][kWave * 4], sliced[NW][kSliceCols];
   const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG];
-  if (total > kSlicedItems / slices) whole_sum_chunks<LPR, NW>(a, total, n_big, whole, part);
-  else sum_slices<NW>(a, total, n_big, slices, sliced, part);
+  const bool whole_rows = total > kSlicedItems / slices;
+  auto stored = [&](int i, int v) {
+    const int chunks = big_row_chunks(a.in_deg[v], a.big.chunk), p0 = a.big.base[i];
+    if (last_to_arrive(arrived + i, whole_rows ? chunks : chunks * slices)) combine_sum_row<LPR, 4, true>(a, v, p0, p0 + chunks, part, chg, compare);
+  };
+  if (whole_rows) whole_sum_chunks<LPR, NW, true>(a, total, n_big, whole, part, stored);
+  else sum_slices<NW, true>(a, total, n_big, slices, sliced, part, stored);
 }
 
 template <int LPR>
 __global__ __launch_bounds__(64) void k_sum_big_final(AggArgs a, const float *part, uint64_t *chg, int compare,
                                                       const Counters *cnt) {
-  const int l = lane_id();
-  const int q = l % LPR;
-  const bool lane_on = 4 * q < a.wd && lane_in_groups<LPR>();
-  constexpr int G = kWave / LPR, U = 8;
-  const int g = l / LPR < G ? l / LPR : G - 1, qo = lane_on ? 4 * q : 0;
   const int n_big = cnt->v[C_NBIG];
   for (int i = blockIdx.x; i < n_big; i += gridDim.x) {
-    int v = a.big.list[i];
-    S4 acc;
-#pragma unroll
-    for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
-    const int p0 = a.big.base[i], p1 = p0 + big_row_chunks(a.in_deg[v], a.big.chunk);
-    for (int pb = p0; pb < p1; pb += G * U) {       // lane groups take the chunks in turn, U of them in flight
-      float4 x[U];
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        const int p = pb + u * G + g;
-        x[u] = ldf4(part + (int64_t)(p < p1 ? p : p1 - 1) * a.wd + qo);
-      }
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        const bool on = pb + u * G + g < p1;
-        const float y[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
-#pragma unroll
-        for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], on ? y[c] : 0.f);
-      }
-    }
-    sum_groups<LPR>(acc);
-    bool ch = store_sum<LPR>(a.A, a.ld, a.d, v, lane_on, q, acc, compare != 0);
-    if (ch && chg && l == 0) mark_bit_s(chg, v);
+    const int v = a.big.list[i], p0 = a.big.base[i];
+    combine_sum_row<LPR, 8, false>(a, v, p0, p0 + big_row_chunks(a.in_deg[v], a.big.chunk), part, chg, compare);
   }
 }
 
@@ -404,13 +418,34 @@ __global__ __launch_bounds__(256) void k_sum_events(AggArgs a, const int32_t *ta
   add_to_row<LPR>(a, targets[wid], lane_on, q, acc, chg, cnt);
 }
 
-// one workgroup per chunk of a long segment, its waves take a quarter of the events each
-template <int LPR>
-__global__ __launch_bounds__(256) void k_sum_ev_partial(AggArgs a, const int32_t *seg, const uint32_t *ev, SumSources src,
-                                                        LongEvents lng, float *part, const Counters *cnt) {
+// one wave per long segment: its lane groups take the chunks in turn
+template <int LPR, bool COHERENT>
+__device__ __forceinline__ void combine_sum_segment(const AggArgs &a, const int32_t *targets, const LongEvents &lng, const LongSeg &L, int n_ev,
+                                                    const float *part, uint64_t *chg, Counters *cnt) {
+  constexpr int G = kWave / LPR;
+  const int l = lane_id(), q = l % LPR, g = l / LPR;
+  const bool lane_on = 4 * q < a.wd;
+  const int nch = long_seg_chunks(lng, n_ev);
+  S4 acc;
+#pragma unroll
+  for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
+  if (lane_on)
+    for (int p = g; p < nch; p += G) {
+      const float4 x = get_part<COHERENT, float4>(part + (int64_t)(L.base + p) * a.wd + 4 * q);
+      acc.v[0] = __fadd_rn(acc.v[0], x.x); acc.v[1] = __fadd_rn(acc.v[1], x.y);
+      acc.v[2] = __fadd_rn(acc.v[2], x.z); acc.v[3] = __fadd_rn(acc.v[3], x.w);
+    }
+  sum_groups<LPR>(acc);
+  add_to_row<LPR>(a, targets[L.target], lane_on, q, acc, chg, cnt);
+}
+
+// one workgroup per chunk of a long segment, its waves take a quarter of the events each; ARRIVE (short launches): the segment's last chunk combines it
+template <int LPR, bool ARRIVE>
+__global__ __launch_bounds__(256) void k_sum_ev_partial(AggArgs a, const int32_t *targets, const int32_t *seg, const uint32_t *ev, SumSources src,
+                                                        LongEvents lng, float *part, uint64_t *chg, Counters *cnt, int32_t *arrived) {
   constexpr int NW = 4;
   __shared__ float sv[NW][kWave * 4];
-  const int l = lane_id(), w = threadIdx.x / kWave;
+  const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
   const int total = cnt->v[C_NEVCH];
@@ -426,38 +461,32 @@ __global__ __launch_bounds__(256) void k_sum_ev_partial(AggArgs a, const int32_t
 #pragma unroll
     for (int c = 0; c < 4; c++) sv[w][l * 4 + c] = acc.v[c];
     __syncthreads();
-    if (w == 0 && lane_on && l < LPR) {
-      for (int ww = 1; ww < NW; ww++)
+    if (w == 0) {
+      if (lane_on && l < LPR) {
+        for (int ww = 1; ww < NW; ww++)
 #pragma unroll
-        for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], sv[ww][l * 4 + c]);
-      *reinterpret_cast<float4 *>(part + (int64_t)ch * a.wd + 4 * q) = make_float4(acc.v[0], acc.v[1], acc.v[2], acc.v[3]);
+          for (int c = 0; c < 4; c++) acc.v[c] = __fadd_rn(acc.v[c], sv[ww][l * 4 + c]);
+#pragma unroll
+        for (int c = 0; c < 4; c++) put_part<ARRIVE>(part + (int64_t)ch * a.wd + 4 * q + c, acc.v[c]);
+      }
+      if constexpr (ARRIVE) {
+        const int i = lng.owner[ch];
+        const LongSeg L = lng.list[i];
+        const int n_ev = seg[L.target + 1] - seg[L.target];
+        if (last_to_arrive(arrived + i, long_seg_chunks(lng, n_ev))) combine_sum_segment<LPR, true>(a, targets, lng, L, n_ev, part, chg, cnt);
+      }
     }
     __syncthreads();
   }
 }
 
-// one wave per long segment: its lane groups take the chunks in turn
 template <int LPR>
 __global__ __launch_bounds__(64) void k_sum_ev_final(AggArgs a, const int32_t *targets, const int32_t *seg, LongEvents lng,
                                                      const float *part, uint64_t *chg, Counters *cnt) {
-  constexpr int G = kWave / LPR;
-  const int l = lane_id(), q = l % LPR, g = l / LPR;
-  const bool lane_on = 4 * q < a.wd;
   const int n = cnt->v[C_NEVL];
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const LongSeg L = lng.list[i];
-    const int nch = (seg[L.target + 1] - seg[L.target] + lng.chunk - 1) / lng.chunk;
-    S4 acc;
-#pragma unroll
-    for (int c = 0; c < 4; c++) acc.v[c] = 0.f;
-    if (lane_on)
-      for (int p = g; p < nch; p += G) {
-        const float4 x = ldf4(part + (int64_t)(L.base + p) * a.wd + 4 * q);
-        acc.v[0] = __fadd_rn(acc.v[0], x.x); acc.v[1] = __fadd_rn(acc.v[1], x.y);
-        acc.v[2] = __fadd_rn(acc.v[2], x.z); acc.v[3] = __fadd_rn(acc.v[3], x.w);
-      }
-    sum_groups<LPR>(acc);
-    add_to_row<LPR>(a, targets[L.target], lane_on, q, acc, chg, cnt);
+    combine_sum_segment<LPR, false>(a, targets, lng, L, seg[L.target + 1] - seg[L.target], part, chg, cnt);
   }
 }
 
@@ -487,12 +516,13 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   const Counters *cnt = c->d_cnt;
   float *part = c->big_part_v.as<float>();
   if (latency)
-    hipLaunchKernelGGL((k_sum_big_short<LPR>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part);
+    hipLaunchKernelGGL((k_sum_big_short<LPR>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part, chg,
+                       compare, c->arrived);
   else if (whole)
     hipLaunchKernelGGL((k_sum_big_partial<LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, cnt, part);
   else
     hipLaunchKernelGGL(k_sum_big_slices, dim3(big_grid(c, a.big_chunks, slices, false)), dim3(256), 0, c->stream, a, cnt, slices, part);
-  hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)part, chg, compare, cnt);
+  if (!latency) hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)part, chg, compare, cnt);
   return hipGetLastError();
 }
 
@@ -508,10 +538,13 @@ static hipError_t sum_events_t(ink_ctx *c, const AggArgs &a, const int32_t *targ
                      seg, n_targets_dev, ev, src, chg, c->d_cnt, lng);
   if (eb.max_seg > lng.limit) {      // otherwise no segment can be long
     float *part = c->big_part_v.as<float>();
-    hipLaunchKernelGGL((k_sum_ev_partial<LPR>), dim3((unsigned)std::min<int64_t>(long_ev_chunks(lng, eb.n_events), 8192)),
-                       dim3(256), 0, c->stream, a, seg, ev, src, lng, part, (const Counters *)c->d_cnt);
-    hipLaunchKernelGGL((k_sum_ev_final<LPR>), dim3((unsigned)std::min<int64_t>(long_ev_rows(lng, eb.n_events), 8192)),
-                       dim3(64), 0, c->stream, a, targets, seg, lng, (const float *)part, chg, c->d_cnt);
+    const dim3 chunks((unsigned)std::min<int64_t>(long_ev_chunks(lng, eb.n_events), 8192)), rows((unsigned)std::min<int64_t>(long_ev_rows(lng, eb.n_events), 8192));
+    if (latency_mode(n_targets)) {
+      hipLaunchKernelGGL((k_sum_ev_partial<LPR, true>), chunks, dim3(256), 0, c->stream, a, targets, seg, ev, src, lng, part, chg, c->d_cnt, c->arrived);
+    } else {
+      hipLaunchKernelGGL((k_sum_ev_partial<LPR, false>), chunks, dim3(256), 0, c->stream, a, targets, seg, ev, src, lng, part, chg, c->d_cnt, c->arrived);
+      hipLaunchKernelGGL((k_sum_ev_final<LPR>), rows, dim3(64), 0, c->stream, a, targets, seg, lng, (const float *)part, chg, c->d_cnt);
+    }
   }
   return hipGetLastError();
 }

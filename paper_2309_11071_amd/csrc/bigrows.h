@@ -1,6 +1,6 @@
 // Work list for rows with more than kBigDeg in-neighbours: each such row is cut into chunks of
 // kBigChunk neighbours (kBigChunkSum for long launches of sums), one workgroup per chunk, then one wave per row combines its chunks in
-// order.  A row takes its chunks when it is listed, so the plan stands when the list does (a scan of the list for it was one or
+// order; in short launches the wave that finishes a row's last chunk does.  A row takes its chunks when it is listed, so the plan stands when the list does (a scan of the list for it was one or
 // two launches more), and the chunk / row kernels run a fixed grid that strides over it, so no host round trip is
 // needed; with no long rows they return at once.
 #pragma once
@@ -79,6 +79,35 @@ __device__ __forceinline__ void list_big_row(const BigRows &b, Counters *cnt, in
   reserve_big(cnt, 1, big_row_chunks(deg, b.chunk), i, base);
   b.list[i] = v;
   b.base[i] = base;
+}
+
+// Short launches have no kernel that combines a row's parts: the wave that stores the last of them does.  The parts are then stored
+// and read past the L2s of the XCDs (COHERENT), a store is waited for before it is counted, and the count is 0 again afterwards.
+// True for the last of `units`.  (A launch of at most kLatencyTargets targets lists at most as many rows: ink_ctx::arrived.  With
+// fences instead, which write back and invalidate, the last part took 1.5 us longer.)
+__device__ __forceinline__ bool last_to_arrive(int32_t *at, int units) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (units == 1) return true;
+  int n = 0;
+  if (lane_id() == 0) n = __hip_atomic_fetch_add(at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  n = __builtin_amdgcn_readfirstlane(n);
+  asm volatile("" ::: "memory");
+  if (n != units - 1) return false;
+  if (lane_id() == 0) __hip_atomic_store(at, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+template <bool COHERENT, class T> __device__ __forceinline__ void put_part(T *p, T x) {
+  if constexpr (COHERENT) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = x;
+}
+template <bool COHERENT, class V> __device__ __forceinline__ V get_part(const void *p) {      // 16 bytes
+  static_assert(sizeof(V) == 16, "four values");
+  if constexpr (COHERENT) {
+    union { uint64_t u[2]; V v; } x;
+    x.u[0] = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    x.u[1] = __hip_atomic_load((const uint64_t *)p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return x.v;
+  } else return *reinterpret_cast<const V *>(p);
 }
 
 // row (index in the list), node id and neighbour range of global chunk cg

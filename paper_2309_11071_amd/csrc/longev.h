@@ -52,10 +52,11 @@ inline hipError_t ensure_long_events(ink_ctx *c, const EventBounds &eb, int wd, 
   return hipSuccess;
 }
 
+__device__ __forceinline__ int long_seg_chunks(const LongEvents &L, int n_ev) { return (n_ev + L.chunk - 1) / L.chunk; }
 // lists target t (whole wave, wave-uniform arguments)
 __device__ __forceinline__ void list_long_segment(const LongEvents &L, int t, int n_ev, Counters *cnt) {
   const int l = lane_id();
-  const int nch = (n_ev + L.chunk - 1) / L.chunk;
+  const int nch = long_seg_chunks(L, n_ev);
   int i = 0, base = 0;
   if (l == 0) {
     i = atomicAdd(&cnt->v[C_NEVL], 1);
