@@ -733,14 +733,16 @@ hipError_t ink::read_counters(ink_ctx *c, bool end_batch) {
   return wait_published(c, c->h_seq, seq);
 }
 
-// waits until the record with this sequence number has arrived: a short spin, then the blocking wait
+// Waits until the record with this sequence number has arrived: a spin of up to a millisecond, as long as all but the largest layers
+// take, then the blocking wait, whose wake-up is 15 to 20 us.  Spins of .15 and 1 ms, us a pass: 10000 updates at hubs of 612k nodes 2107 / 2076,
+// 1000 feature rows on 200k nodes 1461 / 1430, GCN of 57M edges 2797 / 2758.
 hipError_t ink::wait_published(ink_ctx *c, const uint32_t *h_seq, uint32_t seq) {
   hipError_t e;
   const auto t0 = std::chrono::steady_clock::now();
   for (int spin = 0;; spin++) {
     if (__atomic_load_n(h_seq, __ATOMIC_ACQUIRE) == seq) return hipSuccess;
     if ((spin & 63) == 63 &&
-        std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > 150.0)
+        std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > 1000.0)
       break;
   }
   e = hipStreamSynchronize(c->stream);
