@@ -1323,9 +1323,12 @@ static ink_status layer_aggregate(ink_ctx *c, int l, const int32_t *F, int64_t n
       API_TRY(radix_sort_planned(c->ws, sp, key, val, c->ws.tmpk.as<uint32_t>(), c->ws.tmpv.as<uint32_t>(), nE, true, s));
       if (sp.passes & 1) { std::swap(c->ev_key, c->ws.tmpk); std::swap(c->ev_val, c->ws.tmpv); }     // the sorted pair stays where it is
     }
-    API_TRY(segment_heads(c->ws, key, nE, c->t_list.as<int32_t>(), c->t_seg.as<int32_t>(), &dc->v[C_NT], s));
-    if (nE > kNoSyncEvents) {
-      API_TRY(read_counters(c));
+    const bool count = nE > kNoSyncEvents;
+    const RecordTo rec{dc, c->h_cnt, c->h_seq, count ? ++c->pub_seq : 0};
+    bool given = false;
+    API_TRY(segment_heads(c->ws, key, nE, c->t_list.as<int32_t>(), c->t_seg.as<int32_t>(), &dc->v[C_NT], s, nullptr, count ? &rec : nullptr, &given));
+    if (count) {
+      API_TRY(given ? wait_published(c, rec.h_seq, rec.seq) : read_counters(c));
       nT = c->h_cnt->v[C_NT];
     }
   }
@@ -1399,6 +1402,8 @@ static ink_status collect_rows(ink_ctx *c, const int32_t *extra0, int64_t n0, co
   hipStream_t s = c->stream;
   Prof p(c, INK_T_COMPACT);
   API_TRY(c->c_list.reserve((size_t)c->n * 4));
+  const RecordTo rec{c->d_cnt, c->h_cnt, c->h_seq, bound < 0 ? ++c->pub_seq : 0};
+  bool given = false;
   const int64_t M = n_t_bound + n0 + n1;
   if (n_t_bound >= 0 && M <= kSmallLayer && c->n > kBitmapOneLaunch) {
     const int64_t n_flags = std::min<int64_t>(M, c->n);
@@ -1417,10 +1422,10 @@ static ink_status collect_rows(ink_ctx *c, const int32_t *extra0, int64_t n0, co
     if (flags_cleared) *flags_cleared = true;
   } else {
     if (n0 + n1 > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n0 + n1), dim3(256), 0, s, extra0, (int)n0, extra1, (int)n1, c->bm_a, (const int32_t *)nullptr);
-    API_TRY(bitmap_to_list(c->ws, c->bm_a, c->n, c->c_list.as<int32_t>(), &c->d_cnt->v[C_NC], 1, s));
+    API_TRY(bitmap_to_list(c->ws, c->bm_a, c->n, c->c_list.as<int32_t>(), &c->d_cnt->v[C_NC], 1, s, bound < 0 ? &rec : nullptr, &given));
   }
   if (bound >= 0) { *nC = bound; return INK_OK; }
-  API_TRY(read_counters(c));
+  API_TRY(given ? wait_published(c, rec.h_seq, rec.seq) : read_counters(c));
   *nC = c->h_cnt->v[C_NC];
   return INK_OK;
 }

@@ -223,9 +223,12 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_blk(int32_t *blk, int nb,
   if (threadIdx.x == 0 && total) *total = carry;
 }
 
-template <class F, class W, int ITEMS>
+// Functor D: __device__ void operator()() const -> called by the whole workgroup that stores a scan's total, after it has
+struct NothingThen { __device__ __forceinline__ void operator()() const {} };
+
+template <class F, class W, int ITEMS, class D = NothingThen>
 __global__ __launch_bounds__(kScanThreads) void k_tile_apply(F f, W w, int64_t n, const int32_t *blk,
-                                                              int32_t *total_single) {
+                                                              int32_t *total_single, D then = D()) {
   __shared__ int sm[kScanThreads / kWave + 1];
   int64_t base = (int64_t)blockIdx.x * (kScanThreads * ITEMS) + (int64_t)threadIdx.x * ITEMS;
   int v[ITEMS];
@@ -246,14 +249,15 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_apply(F f, W w, int64_t n
     ex += v[k];
   }
   if (total_single && threadIdx.x == 0) *total_single = tot;   // only used when gridDim.x == 1
+  if (total_single) then();
 }
 
 // short inputs: the whole scan in one workgroup and one launch, tile after tile with a carry
 constexpr int kOneWgThreads = 1024;
 constexpr int kOneWgItems = 4;
 constexpr int64_t kOneWgLimit = 16384;
-template <class F, class W>
-__global__ __launch_bounds__(kOneWgThreads) void k_tile_scan_one(F f, W w, int64_t n, int32_t *total) {
+template <class F, class W, class D>
+__global__ __launch_bounds__(kOneWgThreads) void k_tile_scan_one(F f, W w, int64_t n, int32_t *total, D then) {
   __shared__ int sm[kOneWgThreads / kWave + 1];
   int carry = 0;
   for (int64_t t0 = 0; t0 < n; t0 += kOneWgThreads * kOneWgItems) {
@@ -278,13 +282,14 @@ __global__ __launch_bounds__(kOneWgThreads) void k_tile_scan_one(F f, W w, int64
     __syncthreads();
   }
   if (total && threadIdx.x == 0) *total = carry;
+  then();
 }
 
 // Second launch of a scan of up to kSumOwnLimit tiles: every workgroup adds up the sums of the tiles before
 // it (at most 16 k words from the caches), so the block sums need no scan launch of their own.
 constexpr int kSumOwnLimit = 16384;
-template <class F, class W, int ITEMS>
-__global__ __launch_bounds__(kScanThreads) void k_tile_apply_sum(F f, W w, int64_t n, const int32_t *blk, int32_t *total) {
+template <class F, class W, int ITEMS, class D>
+__global__ __launch_bounds__(kScanThreads) void k_tile_apply_sum(F f, W w, int64_t n, const int32_t *blk, int32_t *total, D then) {
   __shared__ int sm[kScanThreads / kWave + 1];
   int before = 0;
   for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanThreads) before += blk[i];
@@ -307,38 +312,48 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_apply_sum(F f, W w, int64
     if (i < n) w(i, v[k], ex);
     ex += v[k];
   }
-  if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = base_sum + tot;
+  if (blockIdx.x != gridDim.x - 1) return;
+  if (total && threadIdx.x == 0) *total = base_sum + tot;
+  then();
 }
 
-// ONE_WG: only for functors that do O(1) work per item
-template <class F, class W, int ITEMS = kScanItems, bool ONE_WG = false>
-inline hipError_t tile_scan(PrimWorkspace &ws, F f, W w, int64_t n, int32_t *total, hipStream_t s) {
+// ONE_WG: only for functors that do O(1) work per item.  *called: whether `then` will be called (not for no items or very many)
+template <class F, class W, int ITEMS = kScanItems, bool ONE_WG = false, class D = NothingThen>
+inline hipError_t tile_scan(PrimWorkspace &ws, F f, W w, int64_t n, int32_t *total, hipStream_t s, D then = D(), bool *called = nullptr) {
+  if (called) *called = false;
   if (n <= 0) {
     if (total) INK_TRY(hipMemsetAsync(total, 0, sizeof(int32_t), s));
     return hipSuccess;
   }
   int nb = nblocks(n, kScanThreads * ITEMS);
+  if (called) *called = nb <= kSumOwnLimit;
   if (nb == 1) {
-    hipLaunchKernelGGL((k_tile_apply<F, W, ITEMS>), dim3(1), dim3(kScanThreads), 0, s, f, w, n,
-                       (const int32_t *)nullptr, total);
+    hipLaunchKernelGGL((k_tile_apply<F, W, ITEMS, D>), dim3(1), dim3(kScanThreads), 0, s, f, w, n,
+                       (const int32_t *)nullptr, total, then);
     return hipGetLastError();
   }
   if (ONE_WG && n <= kOneWgLimit) {
-    hipLaunchKernelGGL((k_tile_scan_one<F, W>), dim3(1), dim3(kOneWgThreads), 0, s, f, w, n, total);
+    hipLaunchKernelGGL((k_tile_scan_one<F, W, D>), dim3(1), dim3(kOneWgThreads), 0, s, f, w, n, total, then);
     return hipGetLastError();
   }
   INK_TRY(ws.blk.reserve((size_t)nb * sizeof(int32_t)));
   int32_t *blk = ws.blk.as<int32_t>();
   hipLaunchKernelGGL((k_tile_reduce<F, ITEMS>), dim3(nb), dim3(kScanThreads), 0, s, f, n, blk);
   if (nb <= kSumOwnLimit) {
-    hipLaunchKernelGGL((k_tile_apply_sum<F, W, ITEMS>), dim3(nb), dim3(kScanThreads), 0, s, f, w, n, (const int32_t *)blk, total);
+    hipLaunchKernelGGL((k_tile_apply_sum<F, W, ITEMS, D>), dim3(nb), dim3(kScanThreads), 0, s, f, w, n, (const int32_t *)blk, total, then);
     return hipGetLastError();
   }
   hipLaunchKernelGGL((k_scan_blk<0>), dim3(1), dim3(kScanThreads), 0, s, blk, nb, total);
   hipLaunchKernelGGL((k_tile_apply<F, W, ITEMS>), dim3(nb), dim3(kScanThreads), 0, s, f, w, n,
-                     (const int32_t *)blk, (int32_t *)nullptr);
+                     (const int32_t *)blk, (int32_t *)nullptr, NothingThen());
   return hipGetLastError();
 }
+
+// Where the counters go once a scan's total is among them (publish_wave): the host waits for the record only, and its launch and
+// the gap in front of it are 5 us.  *given: the record will come, otherwise (see tile_scan) it is the caller's to ask for.
+struct Counters;
+struct HostCounters;
+struct RecordTo { const Counters *d = nullptr; HostCounters *h = nullptr; uint32_t *h_seq = nullptr; uint32_t seq = 0; };
 
 // out[i] = sum_{j<i} in[j] for i < n, *total = sum of all (device pointers; total may alias nothing)
 hipError_t scan_excl_i32(PrimWorkspace &ws, const int32_t *in, int32_t *out, int64_t n,
@@ -351,13 +366,14 @@ hipError_t compact_flags_u8(PrimWorkspace &ws, const uint8_t *flags, int64_t n, 
 // set bits of a bitmap of n_bits bits (uint64 words, bit b of word w = item 64 w + b) as an
 // ascending list; words are cleared to zero afterwards if clear != 0
 hipError_t bitmap_to_list(PrimWorkspace &ws, uint64_t *words, int64_t n_bits, int32_t *out_idx,
-                          int32_t *count, int clear, hipStream_t s);
+                          int32_t *count, int clear, hipStream_t s, const RecordTo *record = nullptr, bool *given = nullptr);
 
 // segment heads of a sorted key array: uniq[j] = j-th distinct key, seg[j] = first index of its
 // run, seg[*count] = n
 // n_dev (optional): device-side number of valid keys, n is then an upper bound
 hipError_t segment_heads(PrimWorkspace &ws, const uint32_t *keys, int64_t n, int32_t *uniq,
-                         int32_t *seg, int32_t *count, hipStream_t s, const int32_t *n_dev = nullptr);
+                         int32_t *seg, int32_t *count, hipStream_t s, const int32_t *n_dev = nullptr, const RecordTo *record = nullptr,
+                         bool *given = nullptr);
 
 // The passes of a device-wide sort of n pairs by the low `bits` bits of their keys.
 constexpr int kSortThreads = 256;

@@ -1,7 +1,7 @@
 // Scan, compaction and radix sort kernels (gfx950, wave64).
 #include <algorithm>
 
-#include "prim.h"
+#include "ctx.h"
 
 namespace ink {
 
@@ -43,10 +43,22 @@ struct StoreBits {
   }
 };
 
+struct PublishThen {
+  RecordTo r;
+  __device__ __forceinline__ void operator()() const {
+    if (threadIdx.x == 0) __threadfence();
+    __syncthreads();
+    if (threadIdx.x < kWave) publish_wave(r.d, r.h, r.h_seq, r.seq);
+  }
+};
+
 hipError_t bitmap_to_list(PrimWorkspace &ws, uint64_t *words, int64_t n_bits, int32_t *out_idx,
-                          int32_t *count, int clear, hipStream_t s) {
+                          int32_t *count, int clear, hipStream_t s, const RecordTo *record, bool *given) {
   int64_t nw = (n_bits + 63) / 64;
-  return tile_scan<LoadPop, StoreBits, 1>(ws, LoadPop{words}, StoreBits{words, out_idx, clear}, nw, count, s);
+  const LoadPop f{words};
+  const StoreBits w{words, out_idx, clear};
+  if (record) return tile_scan<LoadPop, StoreBits, 1, false, PublishThen>(ws, f, w, nw, count, s, PublishThen{*record}, given);
+  return tile_scan<LoadPop, StoreBits, 1>(ws, f, w, nw, count, s);
 }
 
 // ---------------------------------------------------------------- segment heads of sorted keys
@@ -67,9 +79,11 @@ struct StoreHead {
 };
 
 hipError_t segment_heads(PrimWorkspace &ws, const uint32_t *keys, int64_t n, int32_t *uniq,
-                         int32_t *seg, int32_t *count, hipStream_t s, const int32_t *n_dev) {
-  return tile_scan<LoadHead, StoreHead, kScanItems, true>(ws, LoadHead{keys, n_dev}, StoreHead{keys, uniq, seg, n, n_dev}, n, count,
-                                                             s);
+                         int32_t *seg, int32_t *count, hipStream_t s, const int32_t *n_dev, const RecordTo *record, bool *given) {
+  const LoadHead f{keys, n_dev};
+  const StoreHead w{keys, uniq, seg, n, n_dev};
+  if (record) return tile_scan<LoadHead, StoreHead, kScanItems, true, PublishThen>(ws, f, w, n, count, s, PublishThen{*record}, given);
+  return tile_scan<LoadHead, StoreHead, kScanItems, true>(ws, f, w, n, count, s);
 }
 
 // ---------------------------------------------------------------- stable LSD radix sort
