@@ -948,8 +948,8 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
     memset(h, 0, kRecords);
     c->h_cnt = reinterpret_cast<HostCounters *>(h);
     c->h_seq = reinterpret_cast<uint32_t *>(h + 192);
-    c->h_gcnt = reinterpret_cast<HostCounters *>(h + 256);
-    c->h_gseq = reinterpret_cast<uint32_t *>(h + 448);
+    c->h_gcnt = reinterpret_cast<HostCounters *>(h + kRecordBytes);
+    c->h_gseq = reinterpret_cast<uint32_t *>(h + kRecordBytes + sizeof(HostCounters));
     for (int l = 1; l <= INK_MAX_LAYERS; l++) {
       c->h_one[l] = reinterpret_cast<HostCounters *>(h + kRecordBytes * (l + 1));
       c->h_oseq[l] = reinterpret_cast<uint32_t *>(h + kRecordBytes * (l + 1) + sizeof(HostCounters));
@@ -1620,8 +1620,8 @@ static bool layer_one_possible(const ink_ctx *c, int64_t n_batch) {
   return true;
 }
 
-// Behind the graph stage, before its record is awaited.
-static hipError_t layers_one_begin(ink_ctx *c) {
+// The graph stage and the layers, before the stage's record is awaited.
+static hipError_t layers_one_begin(ink_ctx *c, const OneGraph &graph, uint32_t graph_seq) {
   const size_t rows = 2 * kOneEvents;
   for (DevBuf *b : {&c->f_list[0], &c->f_list[1], &c->t_list, &c->f_pref}) INK_TRY(b->reserve((rows + 2) * 4));
   INK_TRY(c->res_emb.reserve(rows * c->H[c->n_layers].d * 4));
@@ -1644,8 +1644,8 @@ static hipError_t layers_one_begin(ink_ctx *c) {
     q.out = c->H[l].f(); q.ld_out = c->H[l].ld;
     c->one_seq[l] = ++c->pub_seq;
   }
+  p.graph = graph; p.h_graph = reinterpret_cast<char *>(c->h_gcnt); p.graph_seq = graph_seq;
   p.g = c->d_gcnt; p.cnt = c->d_cnt;
-  p.del_s = c->del_src; p.del_d = c->del_dst; p.ins_s = c->ins_src; p.ins_d = c->ins_dst;
   p.f_list[0] = c->f_list[0].as<int32_t>(); p.f_list[1] = c->f_list[1].as<int32_t>(); p.pref = c->f_pref.as<int32_t>();
   p.out_off = c->gout.off; p.out_ids = c->gout.ids; p.out_deg = c->gout.deg; p.new_out = c->new_out;
   p.touched_src = c->b_uniq.as<int32_t>();

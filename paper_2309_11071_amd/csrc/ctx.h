@@ -261,9 +261,17 @@ struct KernelTimer : Prof {
 // ---- graph store (graph.hip)
 hipError_t graph_build(ink_ctx *c, const int64_t *rowptr_h, const int32_t *col_h);
 // applies a batch in memory the device can read (ink_edge_update records); fills Delta E lists and counts
-// `queued` is called once its launch is enqueued and before it waits for the record, if the batch may take the one-workgroup form
+// `queued`, if given, launches the one-workgroup form of the stage with the layers behind it (layer_one.hip); its record has the number it gets
+struct RawUpdate { uint8_t op; uint8_t pad[3]; int32_t src, dst; };
+struct OneSide { int64_t *off; int32_t *deg, *cap, *ids; uint8_t *asc; int32_t *new_cnt, *uniq; long long pool_base, room; };
+struct OneGraph {
+  const RawUpdate *raw; int n, n_nodes;
+  OneSide in, out;
+  int32_t *ins_s, *ins_d, *del_s, *del_d;          // applied edge changes
+  float slack;
+};
 ink_status graph_apply_batch(ink_ctx *c, const void *raw, int64_t n, int64_t *n_ins, int64_t *n_del,
-                             hipError_t (*queued)(ink_ctx *) = nullptr);
+                             hipError_t (*queued)(ink_ctx *, const OneGraph &, uint32_t) = nullptr);
 hipError_t graph_reserve(ink_ctx *c, int64_t max_batch);   // batch buffers for that many entries
 ink_status graph_add_nodes(ink_ctx *c, int64_t n_new);   // empty edge blocks for nodes n .. n + n_new - 1 (before n grows)
 hipError_t read_counters(ink_ctx *c, bool end_batch = false);   // device counters -> c->h_cnt, waits for them; with end_batch as graph_end_batch on the way
@@ -357,14 +365,15 @@ struct OneLayer {
   float *out; int ld_out;
 };
 struct OneUpdate {
-  const Counters *g; Counters *cnt;                // graph stage's counters; where a layer that is not finished leaves its own
-  const int32_t *del_s, *del_d, *ins_s, *ins_d;    // applied edge changes
+  OneGraph graph;
+  Counters *g, *cnt;                               // graph stage's counters; where a layer that is not finished leaves its own
   int32_t *f_list[2], *pref;                       // changed sources that layer l leaves: [l & 1]; prefix of their kept out-edges
   const int64_t *out_off; const int32_t *out_ids, *out_deg; int32_t *new_out; const int32_t *touched_src;
   int32_t *t_list; uint64_t *bm;
   float *res;                                      // the changed rows of the last layer, packed
   int32_t *h_ids; float *h_emb;                    // ... and ids and rows in pinned memory (null: not wanted there)
   char *h; uint32_t seq;                           // record of layer 1, the others behind it; its sequence number, those of the others follow
+  char *h_graph; uint32_t graph_seq;               // record of the graph stage
   int n_layers;
   OneLayer layer[INK_MAX_LAYERS];
 };

@@ -7,7 +7,7 @@
 #include <algorithm>
 #include <vector>
 
-#include "ctx.h"
+#include "graph_one.h"
 
 namespace ink {
 
@@ -96,15 +96,6 @@ hipError_t graph_export(ink_ctx *c, int64_t *rowptr, int32_t *col) {
 }
 
 // ------------------------------------------------------------------------------- batch kernels
-struct RawUpdate { uint8_t op; uint8_t pad[3]; int32_t src, dst; };
-
-// what is wrong with a list entry: bit 0 = op is neither insert nor delete, bit 1 = id out of range
-__device__ __forceinline__ int entry_error(const RawUpdate &a, int n_nodes) {
-  int e = a.op > 1 ? 1 : 0;
-  if (a.src < 0 || a.src >= n_nodes || a.dst < 0 || a.dst >= n_nodes) e |= 2;
-  return e;
-}
-
 // Also validates the batch: a bad entry sets *err, and no kernel uses an id as an index before
 // k_mark_last has seen *err and dropped every entry.
 __global__ void k_unpack(const RawUpdate *raw, int64_t n, int n_nodes, uint32_t *src, uint32_t *dst, uint32_t *pos,
@@ -151,8 +142,7 @@ __global__ void k_take_ops(const RawUpdate *raw, const uint32_t *perm, const int
   pos[k] = -1;
 }
 
-// chunks of 2048 block slots per touched node
-constexpr int kChunk = 2048;
+
 __global__ void k_chunk_counts(const int32_t *nodes, const int32_t *n_nodes, int64_t n_max, const int32_t *deg,
                                int32_t *chunks) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -190,8 +180,6 @@ __global__ __launch_bounds__(256) void k_classify(const int32_t *nodes, const in
     }
   }
 }
-
-__device__ __forceinline__ long long relocated_cap(int deg, int cap, float slack);
 
 // per touched node: effective op flags, counts and the pool space a relocation would need.
 // eff: 0 no-op, 1 insert, 2 delete.  One wave per node.
@@ -235,40 +223,6 @@ struct ApplySide {              // op lists and store of one direction (device p
   int32_t *fill;                // one slot per op
   int32_t *new_cnt;             // per node: ids appended by this batch (out side), or null
 };
-// 0 no-op, 1 insert, 2 delete, from the op (0 insert, 1 delete, 2 dead) and the slot where its edge was found
-__device__ __forceinline__ int effect_of(int op, int pos) { return op == 0 ? (pos < 0 ? 1 : 0) : (op == 1 && pos >= 0 ? 2 : 0); }
-
-__device__ __forceinline__ long long relocated_cap(int deg, int cap, float slack) {
-  long long want = 2ll * cap;
-  long long extra = (long long)(deg * (double)slack + 0.999);
-  if (extra < 4) extra = 4;
-  if (want < deg + extra) want = deg + extra;
-  return (want + 3) & ~3ll;
-}
-
-// Deletes up to 64 slots of a block, one per lane (pos, if del), whole wave: [0, d1) survives, its holes take the
-// survivors of the tail [d1, d1 + nd) in slot order, holes in op order.
-__device__ __forceinline__ void fill_holes(int32_t *ids, int d1, int nd, int pos, bool del) {
-  const int l = lane_id();
-  const bool hole = del && pos < d1;
-  // the tail has nd <= 64 slots; those that are deleted themselves do not survive
-  uint64_t gone = del && pos >= d1 ? 1ull << (pos - d1) : 0ull;
-  for (int o = 32; o > 0; o >>= 1) gone |= __shfl_xor((unsigned long long)gone, o, kWave);
-  const uint64_t live = (nd < kWave ? (1ull << nd) - 1 : ~0ull) & ~gone;
-  const uint64_t holes = __ballot(hole);
-  const int rank = __popcll(holes & ((1ull << l) - 1));
-  const int tail_id = l < nd ? ids[d1 + l] : 0;
-  uint64_t m = live;
-  int src = 0;
-  for (int r = 0; r < __popcll(holes); r++) {       // slot of the r-th survivor, for the lane whose hole it fills
-    const int b = __ffsll((unsigned long long)m) - 1;
-    if (hole && rank == r) src = b;
-    m &= m - 1;
-  }
-  const int id = __shfl(tail_id, src, kWave);
-  if (hole) ids[pos] = id;
-}
-
 // One workgroup per touched node and side: workgroups [0, n_max) take the in side, the next n_max the out
 // side; those past a side's device-side node count leave.  A node with at most 64 ops (nearly all) is
 // handled by one wave without a barrier, the other waves only help to move its block.
@@ -553,7 +507,7 @@ static ink_status apply_side(ink_ctx *c, GraphSide &g, SideBufs &b, int64_t n_op
 // 18 (205 with a workgroup a side for heads and finish that took 1024 entries a turn, 149 when it took all at once).
 constexpr int kOneChunk = 1024;        // entries that one workgroup sorts
 constexpr int kMaxChunks = (int)(kShortBatch / kOneChunk);
-constexpr uint64_t kNoKey = ~0ull;     // sorts behind every (node, other) pair
+
 
 struct ShortSide {           // op lists of one direction (device pointers), in (node, other) order
   int32_t *node, *other; uint8_t *op; int32_t *pos;
@@ -601,9 +555,6 @@ __device__ __forceinline__ int block_sort(SortLds<THREADS> &S, uint64_t key, int
   return cur;
 }
 
-__device__ __forceinline__ uint64_t update_key(const RawUpdate &a, int side) {
-  return side ? ((uint64_t)(uint32_t)a.src << 32) | (uint32_t)a.dst : ((uint64_t)(uint32_t)a.dst << 32) | (uint32_t)a.src;
-}
 // slots 0 .. 31 from zero, except the four that the two sides' workgroups set themselves
 __device__ __forceinline__ void clear_graph_slots(Counters *g, int err) {
   const int i = threadIdx.x;
@@ -954,181 +905,17 @@ __global__ __launch_bounds__(kOneChunk) void k_short_finish(int n, int n_chunks,
   if (s_last && t < kWave) publish_wave(g, h, h_seq, seq);
 }
 
-// ---- the whole graph stage of a few entries in one workgroup
-// A wave sorts one side's entries in registers and finds their nodes; all waves walk the blocks of both sides' nodes;
-// then, if the batch is valid, the pools have room and the sides agree, a wave per node applies its ops.  The four
-// launches of the short form take 26 us for a single entry, nearly all of it launches and barriers; this one takes 9.
-// Limits: kOneEvents entries (a wave holds a side's list), kOneGraphChunks chunks of ids to walk (256 = half a million
-// ids, two rounds of the workgroup take about as long as the launches saved); a batch beyond them, or one
-// that needs larger pools, is left untouched (C_ONE stays 0) and takes the short form.
-constexpr int kOneGraphChunks = 256;
-struct OneSide { int64_t *off; int32_t *deg, *cap, *ids; uint8_t *asc; int32_t *new_cnt, *uniq; long long pool_base, room; };
-struct OneGraphLds {
-  int node[2][kOneEvents], other[2][kOneEvents], op[2][kOneEvents], pos[2][kOneEvents];
-  int uniq[2][kOneEvents], seg[2][kOneEvents + 1], n_uniq[2];
-  int deg[2 * kOneEvents], cap[2 * kOneEvents], chunk[2 * kOneEvents + 1];     // touched nodes of both sides behind each other
-  int64_t off[2 * kOneEvents];
-  int n_ins[2 * kOneEvents], n_del[2 * kOneEvents], want[2 * kOneEvents];      // want: new capacity if the block moves, else 0
-  int64_t new_off[2 * kOneEvents];
-  int tot_ins[2], tot_del[2];
-  long long need[2];
-  int err;
-};
-static_assert(kOneEvents <= kWave, "a lane per entry");
-
-__global__ __launch_bounds__(1024) void k_graph_one(const RawUpdate *raw, int n, int n_nodes, OneSide in, OneSide out, int32_t *ins_s,
-                                                    int32_t *ins_d, int32_t *del_s, int32_t *del_d, float slack, Counters *g,
-                                                    HostCounters *h, uint32_t *h_seq, uint32_t seq) {
-  constexpr int NW = 1024 / kWave;
+// The stage by itself: batches of models whose layers do not take the one-workgroup form.
+__global__ __launch_bounds__(1024) void k_graph_one(OneGraph p, Counters *g, HostCounters *h, uint32_t *h_seq, uint32_t seq) {
   __shared__ OneGraphLds S;
-  const int t = threadIdx.x, l = lane_id(), w = __builtin_amdgcn_readfirstlane(t / kWave);
-  if (w < 2) {                        // wave s: the op list of side s in (node, other) order, equal pairs in batch order
-    const int side = w;
-    RawUpdate a{};
-    int bad = 0;
-    if (l < n) { a = raw[l]; bad = entry_error(a, n_nodes); }
-    const int err = (__ballot(bad & 1) ? 1 : 0) | (__ballot(bad & 2) ? 2 : 0);
-    if (t == 0) S.err = err;
-    const OneSide &o = side ? out : in;
-    const uint64_t key = l < n ? update_key(a, side) : kNoKey;
-    int rank = 0;
-    for (int j = 0; j < n; j++) {
-      const uint64_t kj = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(key >> 32), j) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, j);
-      rank += (kj < key) | ((kj == key) & (j < l));
-    }
-    if (l < n) { S.node[side][rank] = (int)(key >> 32); S.other[side][rank] = (int)(uint32_t)key; S.op[side][rank] = a.op; S.pos[side][rank] = -1; }
-    __builtin_amdgcn_wave_barrier();
-    const int v = l < n ? S.node[side][l] : -1, x = l < n ? S.other[side][l] : -1;
-    const int pv = l > 0 && l < n ? S.node[side][l - 1] : -1;
-    const int nv = l + 1 < n ? S.node[side][l + 1] : -1, nx = l + 1 < n ? S.other[side][l + 1] : -1;
-    const bool head = l < n && v != pv;
-    const uint64_t heads = __ballot(head);
-    if (l < n && ((nv == v && nx == x) || v == x)) S.op[side][l] = 2;          // overridden by a later entry, or a self loop
-    const int at = __popcll(heads & ((1ull << l) - 1));
-    if (head) { S.uniq[side][at] = v; S.seg[side][at] = l; }
-    if (l == 0) { S.n_uniq[side] = err ? 0 : __popcll(heads); S.seg[side][__popcll(heads)] = n; }
-    if (!err && head) o.uniq[at] = v;
-  }
-  __syncthreads();
-  const int n0 = S.n_uniq[0], n_all = n0 + S.n_uniq[1];
-  if (t < n_all) {
-    const OneSide &o = t < n0 ? in : out;
-    const int v = t < n0 ? S.uniq[0][t] : S.uniq[1][t - n0];
-    S.deg[t] = o.deg[v]; S.cap[t] = o.cap[v]; S.off[t] = o.off[v];
-  }
-  if (w == 0) {                       // prefix of the chunk counts (n_all <= kWave)
-    const int ch = l < n_all ? (S.deg[l] + kChunk - 1) / kChunk : 0;
-    const int inc = wave_incl_scan(ch);
-    if (l < n_all) S.chunk[l] = inc - ch;
-    if (l == kWave - 1) S.chunk[n_all] = inc;
-  }
-  __syncthreads();
-  const int total = S.chunk[n_all];
-  const bool walk = total <= kOneGraphChunks;
-  if (walk)
-    for (int c = w; c < total; c += NW) {
-      int i = 0;
-      for (int j = 1; j < n_all; j++) i = S.chunk[j] <= c ? j : i;      // empty blocks have no chunk: the last one that starts here owns it
-      i = __builtin_amdgcn_readfirstlane(i);
-      const int side = i >= n0, k = side ? i - n0 : i;
-      const int s0 = S.seg[side][k], s1 = S.seg[side][k + 1], d = S.deg[i];
-      const int32_t *ids = (side ? out.ids : in.ids) + S.off[i];
-      const int p_begin = (c - S.chunk[i]) * kChunk, p_end = p_begin + kChunk < d ? p_begin + kChunk : d;
-      for (int p = p_begin + 4 * l; p < p_end; p += 4 * kWave) {
-        const int4 e4 = *reinterpret_cast<const int4 *>(ids + p);
-        const int e[4] = {e4.x, e4.y, e4.z, e4.w};
-        for (int m = s0; m < s1; m++)
-#pragma unroll
-          for (int j = 0; j < 4; j++)
-            if (e[j] == S.other[side][m] && p + j < d) S.pos[side][m] = p + j;
-      }
-    }
-  __syncthreads();
-  if (w < 2) {                        // effective ops of side w, what they do to each node, and the pool space they need
-    const int side = w;
-    const int e = l < n && !S.err ? effect_of(S.op[side][l], S.pos[side][l]) : 0;
-    const uint64_t mi = __ballot(e == 1), md = __ballot(e == 2);
-    const uint64_t below = (1ull << l) - 1;
-    if (side == 0 && e == 1) { ins_s[__popcll(mi & below)] = S.other[0][l]; ins_d[__popcll(mi & below)] = S.node[0][l]; }
-    if (side == 0 && e == 2) { del_s[__popcll(md & below)] = S.other[0][l]; del_d[__popcll(md & below)] = S.node[0][l]; }
-    int want = 0;
-    if (l < S.n_uniq[side]) {
-      const int i = side * n0 + l;
-      const uint64_t seg = ((S.seg[side][l + 1] < kWave ? 1ull << S.seg[side][l + 1] : 0ull) - 1) & ~((1ull << S.seg[side][l]) - 1);
-      const int ni = __popcll(mi & seg), nd = __popcll(md & seg);
-      const int d2 = S.deg[i] - nd + ni;
-      S.n_ins[i] = ni; S.n_del[i] = nd;
-      if (d2 > S.cap[i]) want = (int)relocated_cap(d2, S.cap[i], slack);
-      S.want[i] = want;
-    }
-    const int inc = wave_incl_scan(want);
-    if (l < S.n_uniq[side]) S.new_off[side * n0 + l] = (side ? out : in).pool_base + inc - want;
-    if (l == kWave - 1) S.need[side] = inc;
-    if (l == 0) { S.tot_ins[side] = __popcll(mi); S.tot_del[side] = __popcll(md); }
-  }
-  __syncthreads();
-  const bool agree = S.tot_ins[0] == S.tot_ins[1] && S.tot_del[0] == S.tot_del[1];
-  const bool room = S.need[0] <= in.room && S.need[1] <= out.room;
-  const bool ok = !S.err && walk && agree && room;
-  if (ok) {
-    // holes in the surviving part of a block are filled from its tail, in op order
-    for (int i = w; i < n_all; i += NW) {
-      const int nd = S.n_del[i];
-      if (nd == 0) continue;
-      const int side = i >= n0, k0 = S.seg[side][side ? i - n0 : i], k1 = S.seg[side][(side ? i - n0 : i) + 1];
-      int32_t *ids = (side ? out.ids : in.ids) + S.off[i];
-      const int d1 = S.deg[i] - nd, k = k0 + l;
-      const int pos = k < k1 ? S.pos[side][k] : -1;
-      fill_holes(ids, d1, nd, pos, k < k1 && effect_of(S.op[side][k], pos) == 2);
-    }
-    __threadfence_block();
-    __syncthreads();
-    for (int i = 0; i < n_all; i++) {               // blocks that outgrow their slots
-      if (S.want[i] == 0) continue;
-      int32_t *pool = i >= n0 ? out.ids : in.ids;
-      const int d1 = S.deg[i] - S.n_del[i];
-      for (int p = t; p < d1; p += 1024) pool[S.new_off[i] + p] = pool[S.off[i] + p];
-    }
-    for (int i = w; i < n_all; i += NW) {
-      const int ni = S.n_ins[i], nd = S.n_del[i];
-      if (ni == 0 && nd == 0) continue;
-      const int side = i >= n0, j = side ? i - n0 : i, k = S.seg[side][j] + l;
-      const OneSide &o = side ? out : in;
-      const int d1 = S.deg[i] - nd, v = S.uniq[side][j];
-      const bool move = S.want[i] > 0;
-      int32_t *ids = o.ids + (move ? S.new_off[i] : S.off[i]);
-      const bool ins = k < S.seg[side][j + 1] && effect_of(S.op[side][k], S.pos[side][k]) == 1;
-      const uint64_t m = __ballot(ins);
-      if (ins) ids[d1 + __popcll(m & ((1ull << l) - 1))] = S.other[side][k];
-      if (l == 0) {
-        if (move) { o.cap[v] = S.want[i]; o.off[v] = S.new_off[i]; }
-        o.deg[v] = d1 + ni;
-        o.asc[v] = 0;
-        if (o.new_cnt) o.new_cnt[v] = ni;
-      }
-    }
-  }
-  __threadfence_block();
-  __syncthreads();
-  if (w == 0) {                       // the record, on the device for the layers and in pinned memory for the host
-    int x = 0;
-    const int slot = l;
-    if (slot == C_ERR) x = S.err;
-    if (slot == C_TMP0) x = n0;
-    if (slot == C_OT) x = n_all - n0;
-    if (slot == C_GINS) x = S.tot_ins[0];
-    if (slot == C_GDEL) x = S.tot_del[0];
-    if (slot == C_OINS) x = S.tot_ins[1];
-    if (slot == C_ODEL) x = S.tot_del[1];
-    if (slot == C_OK) x = ok;
-    if (slot == C_TMP2) x = ok ? S.tot_ins[0] : 0;
-    if (slot == C_TMP3) x = ok ? S.tot_del[0] : 0;
-    if (slot == C_ONE) x = S.err || !agree || ok;            // otherwise: walk the long way
-    if (l < 32) { g->v[l] = x; h->v[l] = x; }
-    if (l < 2) h->total[l] = (unsigned long long)S.need[l];
-    __threadfence_system();
-    if (l == 0) __hip_atomic_store(h_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
+  __shared__ HostCounters record;
+  graph_one(S, p, record);
+  const int l = threadIdx.x;
+  if (l >= kWave) return;
+  if (l < 32) { g->v[l] = record.v[l]; h->v[l] = record.v[l]; }
+  if (l < ST_N) h->total[l] = record.total[l];
+  __threadfence_system();
+  if (l == 0) __hip_atomic_store(h_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 static size_t short_bytes(int64_t n) {
@@ -1173,7 +960,7 @@ static void short_result(ink_ctx *c, const int64_t need[2], int64_t *n_ins_out, 
 
 // *done: the batch was within the limits of the one-workgroup form (or is in error)
 static ink_status graph_apply_one(ink_ctx *c, const RawUpdate *raw, int64_t n, int64_t *n_ins_out, int64_t *n_del_out,
-                                  hipError_t (*queued)(ink_ctx *), bool *done) {
+                                  hipError_t (*queued)(ink_ctx *, const OneGraph &, uint32_t), bool *done) {
   const size_t per = ((size_t)(n + 64) * 4 + 255) & ~(size_t)255;
   for (DevBuf *b : {&c->b_del_s, &c->b_del_d, &c->b_ins_s, &c->b_ins_d, &c->b_touch_in, &c->b_uniq}) INK_TRYS(b->reserve(per));
   c->del_src = c->b_del_s.as<int32_t>(); c->del_dst = c->b_del_d.as<int32_t>();
@@ -1181,12 +968,14 @@ static ink_status graph_apply_one(ink_ctx *c, const RawUpdate *raw, int64_t n, i
   auto side = [](GraphSide &g, int32_t *new_cnt, DevBuf &uniq) {
     return OneSide{g.off, g.deg, g.cap, g.ids, g.asc, new_cnt, uniq.as<int32_t>(), (long long)g.pool_top, (long long)(g.pool_cap - g.pool_top)};
   };
+  const OneGraph p{raw, (int)n, c->n, side(c->gin, nullptr, c->b_touch_in), side(c->gout, c->new_out, c->b_uniq),
+                   c->ins_src, c->ins_dst, c->del_src, c->del_dst, c->slack};
   const uint32_t seq = ++c->pub_seq;
-  hipLaunchKernelGGL(k_graph_one, dim3(1), dim3(1024), 0, c->stream, raw, (int)n, c->n, side(c->gin, nullptr, c->b_touch_in),
-                     side(c->gout, c->new_out, c->b_uniq), c->ins_src, c->ins_dst, c->del_src, c->del_dst, c->slack, c->d_gcnt,
-                     c->h_gcnt, c->h_gseq, seq);
-  INK_TRYS(hipGetLastError());
-  if (queued) INK_TRYS(queued(c));
+  if (queued) INK_TRYS(queued(c, p, seq));
+  else {
+    hipLaunchKernelGGL(k_graph_one, dim3(1), dim3(1024), 0, c->stream, p, c->d_gcnt, c->h_gcnt, c->h_gseq, seq);
+    INK_TRYS(hipGetLastError());
+  }
   INK_TRYS(wait_published(c, c->h_gseq, seq));
   const int32_t *v = c->h_gcnt->v;
   *done = v[C_ONE] != 0;
@@ -1268,7 +1057,7 @@ static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n6
 }
 
 ink_status graph_apply_batch(ink_ctx *c, const void *raw_v, int64_t n, int64_t *n_ins_out, int64_t *n_del_out,
-                             hipError_t (*queued)(ink_ctx *)) {
+                             hipError_t (*queued)(ink_ctx *, const OneGraph &, uint32_t)) {
   hipStream_t s = c->stream;
   *n_ins_out = *n_del_out = 0;
   c->n_ins = c->n_del = 0;
@@ -1278,7 +1067,7 @@ ink_status graph_apply_batch(ink_ctx *c, const void *raw_v, int64_t n, int64_t *
   if (n <= kOneEvents && n <= c->small_batch) {
     bool done = false;
     ink_status st = graph_apply_one(c, raw, n, n_ins_out, n_del_out, queued, &done);
-    if (st != INK_OK || done) return st;      // otherwise what `queued` enqueued did nothing
+    if (st != INK_OK || done) return st;      // otherwise the layers behind it did nothing
   }
   if (n <= c->small_batch) return graph_apply_short(c, raw, n, n_ins_out, n_del_out);
   size_t per = ((size_t)(n + 64) * 4 + 255) & ~(size_t)255;

@@ -1,5 +1,5 @@
-// The layers of a small update in one launch of one workgroup: events, grouping, aggregation, row collection, transform
-// and emission, the stages that otherwise take eight to ten launches and a host round trip a layer.  For SAGE layers with
+// A small update in one launch of one workgroup: the graph stage (graph_one.h), then layer by layer events, grouping, aggregation, row
+// collection, transform and emission, the stages that otherwise take eight to ten launches and a host round trip a layer.  For SAGE layers with
 // max or min aggregation.
 //
 // A single inserted edge has a handful of events a layer; a launch costs about 5 us and a round trip 10 to 15, whatever
@@ -14,16 +14,19 @@
 // One edge on 1.25M vertices, three layers of one event each, rows of 128 floats: 18.4 us a layer as launches of workgroup-wide
 // stages (transform 6.3, order 1.6, row collection 1.8, emission 1.6, the event 2.3 to 3.7), now 10 (weights, inputs and products 5.4, the
 // event as before, arguments .6, order .35, emission .5); a pass of two updates 208 -> 174 us, on 10k vertices, rows of 64, 126 -> 100.
-// The launch is enqueued behind the graph stage without waiting for the host: a layer finds its size on the device, and the
-// first one that is too large ends it.
+// Nothing waits for the host: a layer finds its size on the device, and the first one that is too large ends the launch, as does a
+// batch that the graph stage leaves to its longer forms.  (The graph stage as a launch in front: 2 us more an update, a pass of two
+// 129 -> 125 us on 1.25M vertices, 99.4 -> 97.2 on 10k.)
 //   * at most kOneEvents events: 16 waves take 4 us for 16 targets, most of it instructions that the CU's four SIMDs
 //     share, so 100 targets (28 us, and 18 to transform them) are no faster than the launches of the general path
 //   * exposed rows with many neighbours are recomputed here while they are at most kOneGather floats (2 MB, about
 //     20 us at what one CU reads); beyond, the layer stops after its events (kOneEventsDone) and the host continues
 //     it with the launches of the general path, which finds the targets, the bitmap and the list of long rows
 //     where its own event kernel leaves them
+#include <stddef.h>
 #define INK_LANE_ANEW      // the loop over the layers, below
 #include "events.h"
+#include "graph_one.h"
 #include "select.h"
 
 namespace ink {
@@ -56,7 +59,9 @@ struct OneLds {
     float x[kTileK / 32][kOneRows][kTileStride];
     float xf[kMaxK / 32 * kFewStride];
     struct { float v[kMergeFloats]; int i[kMergeFloats]; float s[kMergeFloats]; int j[kMergeFloats]; } m;
+    OneGraphLds graph;
   };
+  HostCounters graph_rec;
   f4v acc[kOneWaves / 2][kWave];                  // tiles of a product on their way from one wave to the next
 };
 
@@ -461,17 +466,18 @@ __global__ __launch_bounds__(kOneThreads) void k_layers_one(OneUpdate) {
   // the arguments where the launch has put them: a layer's are found by a running index
   const OneUpdate *K = (const OneUpdate *)__builtin_amdgcn_kernarg_segment_ptr();
   const int l = lane_id(), w = wave_id(), t = w * kWave + l;
+  // which are in host memory: the waves bring a line of 64 bytes each; a stage whose first look there is its own takes .7 us longer
   const int n_layers = K->n_layers;
-  // which are in host memory: the waves bring a line of 64 bytes each; a layer whose first look there is its own takes .7 us longer
-  for (int i = w * 16; i < n_layers * (int)(sizeof(OneLayer) / 4); i += kOneWaves * 16) {
-    const int seen = reinterpret_cast<const int *>(K->layer)[i];
+  for (int i = w * 16; i < (int)(offsetof(OneUpdate, layer) / 4) + n_layers * (int)(sizeof(OneLayer) / 4); i += kOneWaves * 16) {
+    const int seen = reinterpret_cast<const int *>(K)[i];
     asm volatile("" : : "s"(seen));
   }
-  const int n_ins = K->g->v[C_TMP2], n_del = K->g->v[C_TMP3];     // 0 unless the batch was applied
-  const bool ok = K->g->v[C_OK] != 0 && n_ins + n_del <= kOneEvents;
   for (int i = t; i < (int)(sizeof(Counters) / sizeof(int32_t)); i += kOneThreads) ((int32_t *)&S.cnt)[i] = 0;
-  if (t < n_ins + n_del && ok) seed_event(t, K->del_s, K->del_d, K->ins_s, K->ins_d, n_del, &S.seed_k[t], &S.seed_v[t]);
-  if (t == 0) { S.n_f = 0; S.n_ev = 0; S.n_del = n_del; S.n_seed = ok ? n_ins + n_del : 0; }
+  graph_one(S.graph, K->graph, S.graph_rec);
+  const int n_ins = __builtin_amdgcn_readfirstlane(S.graph_rec.v[C_TMP2]), n_del = __builtin_amdgcn_readfirstlane(S.graph_rec.v[C_TMP3]);     // 0 unless the batch was applied
+  if (t < 32) K->g->v[t] = S.graph_rec.v[t];
+  if (t < n_ins + n_del) seed_event(t, K->graph.del_s, K->graph.del_d, K->graph.ins_s, K->graph.ins_d, n_del, &S.seed_k[t], &S.seed_v[t]);
+  if (t == 0) { S.n_f = 0; S.n_ev = 0; S.n_del = n_del; S.n_seed = n_ins + n_del; }
   __syncthreads();
   int layer = 1, status;
   while ((status = one_layer<IS_MIN>(K, layer)) == kOneDone && layer < n_layers) layer++;
@@ -485,7 +491,7 @@ __global__ __launch_bounds__(kOneThreads) void k_layers_one(OneUpdate) {
       if (K->h_emb) K->h_emb[i] = x;
     }
     if (K->h_ids && t < nF) K->h_ids[t] = S.F[t];
-    const int n_src = K->g->v[C_OT];
+    const int n_src = S.graph_rec.v[C_OT];
     for (int i = t; i < n_src; i += kOneThreads) K->new_out[K->touched_src[i]] = 0;
   } else {
     if (status == kOneEventsDone) {       // what the general path goes on from
@@ -501,11 +507,13 @@ __global__ __launch_bounds__(kOneThreads) void k_layers_one(OneUpdate) {
   __syncthreads();
   if (w == 0) {
     constexpr int N = sizeof(HostCounters) / sizeof(int32_t);
+    if (l < N) reinterpret_cast<int32_t *>(K->h_graph)[l] = reinterpret_cast<const int32_t *>(&S.graph_rec)[l];
     for (int i = l; i < layer * N; i += kWave) {
       const int r = i / N;
       reinterpret_cast<int32_t *>(K->h + r * kRecordBytes)[i - r * N] = reinterpret_cast<const int32_t *>(S.rec)[i];
     }
     __threadfence_system();
+    if (l == 0) __hip_atomic_store(reinterpret_cast<uint32_t *>(K->h_graph + sizeof(HostCounters)), K->graph_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     if (l < layer) __hip_atomic_store(reinterpret_cast<uint32_t *>(K->h + l * kRecordBytes + sizeof(HostCounters)), K->seq + l, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
