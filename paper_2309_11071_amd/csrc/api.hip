@@ -934,12 +934,12 @@ extern "C" ink_status ink_create(const ink_csr *g, const float *features, int32_
   const int64_t nc = c->n_cap;     // every per-node array is allocated for the capacity
   CREATE_TRY(hipMalloc(&c->new_out, (size_t)nc * 4));
   CREATE_TRY(hipMemset(c->new_out, 0, (size_t)nc * 4));
-  CREATE_TRY(hipMalloc(&c->arrived, kLatencyTargets * sizeof(int32_t)));
-  CREATE_TRY(hipMemset(c->arrived, 0, kLatencyTargets * sizeof(int32_t)));
   CREATE_TRY(hipMalloc(&c->d_cnt, sizeof(Counters)));
   CREATE_TRY(hipMemset(c->d_cnt, 0, sizeof(Counters)));
-  CREATE_TRY(hipMalloc(&c->d_gcnt, sizeof(Counters)));
-  CREATE_TRY(hipMemset(c->d_gcnt, 0, sizeof(Counters)));
+  constexpr size_t kGraphCounters = sizeof(Counters) + kLatencyTargets * sizeof(int32_t);      // and `arrived`
+  CREATE_TRY(hipMalloc(&c->d_gcnt, kGraphCounters));
+  CREATE_TRY(hipMemset(c->d_gcnt, 0, kGraphCounters));
+  c->arrived = reinterpret_cast<int32_t *>(c->d_gcnt + 1);
   {   // one pinned allocation: layer record + sequence number, graph record + sequence number, one more per layer, batch staging
     static_assert(sizeof(HostCounters) == 192, "records and sequence numbers on their own cache lines");
     char *h = nullptr;
@@ -1043,7 +1043,6 @@ extern "C" void ink_destroy(ink_ctx *c) {
   if (c->cnorm) (void)hipFree(c->cnorm);
   if (c->d_cnt) (void)hipFree(c->d_cnt);
   if (c->d_gcnt) (void)hipFree(c->d_gcnt);
-  if (c->arrived) (void)hipFree(c->arrived);
   if (c->h_cnt) (void)hipHostFree(c->h_cnt);
   if (c->h_res) (void)hipHostFree(c->h_res);
   if (c->bm_a) (void)hipFree(c->bm_a);

@@ -212,7 +212,7 @@ struct ink_ctx {
   int64_t n_touched_in = 0;
   ink::DevBuf exp_list;              // exposed rows of moderate length, listed by the event kernel
   ink::DevBuf evl_list, evl_owner;   // targets with long event segments, and the owner of each chunk of them
-  int32_t *arrived = nullptr;        // [kLatencyTargets] parts of a row or segment that are there, in a launch that combines them itself; 0 between launches
+  int32_t *arrived = nullptr;        // [kLatencyTargets] parts of a row or segment that are there, in a launch that combines them itself; 0 between launches (behind d_gcnt)
   ink::DevBuf big_list, big_part_v, big_part_i, big_part_s, big_part_j, big_pref;   // cooperative re-gather of long rows
   ink::DevBuf stage0, stage1;        // transform staging
   ink::DevBuf res_ids, res_emb;      // result of the last batch
