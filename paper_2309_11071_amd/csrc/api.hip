@@ -1419,6 +1419,9 @@ static ink_status collect_rows(ink_ctx *c, const int32_t *extra0, int64_t n0, co
 #undef INK_SMALL_COLLECT
     API_TRY(hipGetLastError());
     if (flags_cleared) *flags_cleared = true;
+  } else if (c->n <= kOneTileBits && n0 + n1 <= kSmallLayer) {
+    given = bound < 0;
+    API_TRY(bitmap_one(c->bm_a, c->n, extra0, n0, extra1, n1, c->c_list.as<int32_t>(), &c->d_cnt->v[C_NC], s, given ? &rec : nullptr));
   } else {
     if (n0 + n1 > 0) hipLaunchKernelGGL(k_mark_nodes, grid1(n0 + n1), dim3(256), 0, s, extra0, (int)n0, extra1, (int)n1, c->bm_a, (const int32_t *)nullptr);
     API_TRY(bitmap_to_list(c->ws, c->bm_a, c->n, c->c_list.as<int32_t>(), &c->d_cnt->v[C_NC], 1, s, bound < 0 ? &rec : nullptr, &given));

@@ -368,6 +368,11 @@ hipError_t compact_flags_u8(PrimWorkspace &ws, const uint8_t *flags, int64_t n, 
 hipError_t bitmap_to_list(PrimWorkspace &ws, uint64_t *words, int64_t n_bits, int32_t *out_idx,
                           int32_t *count, int clear, hipStream_t s, const RecordTo *record = nullptr, bool *given = nullptr);
 
+// the same for at most kOneTileBits bits, cleared, with the bits of two lists set first; the record, if asked for, always comes
+constexpr int64_t kOneTileBits = 64 * kScanThreads;
+hipError_t bitmap_one(uint64_t *words, int64_t n_bits, const int32_t *a, int64_t na, const int32_t *b, int64_t nb, int32_t *out_idx, int32_t *count,
+                      hipStream_t s, const RecordTo *record);
+
 // segment heads of a sorted key array: uniq[j] = j-th distinct key, seg[j] = first index of its
 // run, seg[*count] = n
 // n_dev (optional): device-side number of valid keys, n is then an upper bound

@@ -52,6 +52,35 @@ struct PublishThen {
   }
 };
 
+// A bitmap of one tile, with the items of two short lists set in it first: 256 threads, a word each.  (A launch for the marks in front
+// took 4 us: 100 updates on 10k nodes 316 -> 311 us a pass.)
+__global__ __launch_bounds__(kScanThreads) void k_bitmap_one(uint64_t *words, int nw, const int32_t *a, int na, const int32_t *b, int nb, int32_t *out,
+                                                             int32_t *count, RecordTo record) {
+  __shared__ int sm[kScanThreads / kWave + 1];
+  __shared__ unsigned long long set[kScanThreads];
+  const int t = threadIdx.x;
+  set[t] = t < nw ? words[t] : 0;
+  __syncthreads();
+  for (int i = t; i < na + nb; i += kScanThreads) {
+    const int v = i < na ? a[i] : b[i - na];
+    atomicOr(&set[v >> 6], 1ull << (v & 63));
+  }
+  __syncthreads();
+  unsigned long long w = set[t];
+  int tot;
+  int at = block_excl_scan(__popcll(w), sm, &tot);
+  if (t < nw) words[t] = 0;
+  for (; w; w &= w - 1) out[at++] = t * 64 + __builtin_ctzll(w);
+  if (t == 0) *count = tot;
+  if (record.d) PublishThen{record}();
+}
+hipError_t bitmap_one(uint64_t *words, int64_t n_bits, const int32_t *a, int64_t na, const int32_t *b, int64_t nb, int32_t *out_idx, int32_t *count,
+                      hipStream_t s, const RecordTo *record) {
+  hipLaunchKernelGGL(k_bitmap_one, dim3(1), dim3(kScanThreads), 0, s, words, (int)((n_bits + 63) / 64), a, (int)na, b, (int)nb, out_idx, count,
+                     record ? *record : RecordTo());
+  return hipGetLastError();
+}
+
 hipError_t bitmap_to_list(PrimWorkspace &ws, uint64_t *words, int64_t n_bits, int32_t *out_idx,
                           int32_t *count, int clear, hipStream_t s, const RecordTo *record, bool *given) {
   int64_t nw = (n_bits + 63) / 64;
