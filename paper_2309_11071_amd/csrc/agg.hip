@@ -444,7 +444,7 @@ static hipError_t launch_events(ink_ctx *c, const AggArgs &a, const int32_t *tar
   // few targets per wave visit while the launch has fewer blocks than the chip has waves to spread them over
   const int ev_block = (int)std::max<int64_t>(1, std::min<int64_t>(kEvBlock, n_targets / 32768));
   int64_t blocks = std::min<int64_t>(((n_targets + ev_block - 1) / ev_block + 3) / 4, INK_EVENT_GRID);
-  LongEvents lng = long_events(eb.n_events, latency);
+  LongEvents lng = long_events(eb, n_targets);
   INK_TRY(ensure_long_events(c, eb, a.wd, true, &lng));
   int32_t *exp_list = c->exp_list.as<int32_t>();
   hipLaunchKernelGGL((k_agg_events<IS_MIN, LPR, INLINE>), dim3((unsigned)blocks), dim3(256), 0, c->stream, a, targets, seg,

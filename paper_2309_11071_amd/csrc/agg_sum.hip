@@ -532,7 +532,7 @@ static hipError_t sum_events_t(ink_ctx *c, const AggArgs &a, const int32_t *targ
                                const SumSources &src, uint64_t *chg) {
   if (n_targets <= 0) return hipSuccess;
   KernelTimer kt(c, a.layer, INK_K_AGG_EVENTS);
-  LongEvents lng = long_events(eb.n_events, latency_mode(n_targets));
+  LongEvents lng = long_events(eb, n_targets);
   INK_TRY(ensure_long_events(c, eb, a.wd, false, &lng));
   hipLaunchKernelGGL((k_sum_events<LPR>), dim3((unsigned)((n_targets + 3) / 4)), dim3(256), 0, c->stream, a, targets,
                      seg, n_targets_dev, ev, src, chg, c->d_cnt, lng);

@@ -22,12 +22,20 @@ struct LongEvents {                            // device buffers of the list
 // less than a wave's work for every wave the chip holds; a large launch pays for the partial rows instead, and one that
 // does not wait for its target count pays two launches as soon as a segment may be long.  Event stage, us, limit and chunk
 // 64, 128 / 128, 256 / 256, 256: max over rows of 128 floats, 37k events 48 / 37 / 37, 57k 64 / 52 / 52, 312k 140 / 154 / 166,
-// 589k 212 / 215 / 236, 5.3M 826 / 751 / 786, 6.4M 1251 / 877 / 912, 17M - / 2000 / 1750; rows of 256 floats 56k 95 / 82 / 79,
-// 495k 317 / 322 / 348; sums over rows of 128 floats 159k 68 / 65 / 63, 18M 2133 / 1262 / 1021.
-inline LongEvents long_events(int64_t n_events, bool latency) {
-  if (latency) return LongEvents{nullptr, nullptr, 128, 256};
-  if (n_events <= (1 << 18) || n_events > (1 << 23)) return LongEvents{nullptr, nullptr, 256, 256};
-  if (n_events <= (1 << 20)) return LongEvents{nullptr, nullptr, 64, 128};
+// 605k 220 / 223 / 244, 3.7M 667 / 638 / 648, 17M - / 2000 / 1750; rows of 256 floats 56k 95 / 82 / 79, 537k 302 / 365 / 338; sums
+// over 128 floats 159k 68 / 65 / 63, 296k 81 / 86 / 95, 725k 146 / 147 / 149, 2.05M 246 / 244 / 248, 18M 2133 / 1262 / 1021; over 256
+// 494k 99 / 102 / 103, 1.6M 189 / 186 / 191, 5.8M 732 / 470 / 477; over 64 282k 70 / 72 / 75, 4.4M 278 / 273 / 273.
+// Those have 2 to 5 events a target, up to 13 beyond 2M.  Where targets have many, nearly every event is in a segment above a low limit, and
+// their lists and partial rows cost more than the chains (events a target in brackets): sums over 128 floats 301k
+// (7) 47 / 50 / 54, 357k (8) 49 / 55 / 60, 525k (13) 77 / 57 / 61, 869k (13) 111 / 80 / 84, 1.34M (10) 154 / 112 / 120, 1.86M (23) 270 / 123 / 115, 3.5M (41)
+// 309 / 253 / 154, 1.28M (67) 177 / 137 / 76; over 64 869k (13) 103 / 65 / 67, 1.23M (19) 108 / 77 / 73, 1.86M (23) 257 / 109 / 88; max over 128
+// 1.23M (33) 510 / 459 / 444, 2.3M (30) 790 / 650 / 540.  And segments of at most 500 to 600 events have no chain worth cutting: sums over
+// 256 floats 341k 46 / 48 / 43, 558k 73 / 74 / 67, 866k 101 / 92 / 87; of at most 1000, 526k 77 / 57 / 60, 1.31M 120 / 110 / 118.
+inline LongEvents long_events(const EventBounds &eb, int64_t n_targets) {
+  const int64_t n = eb.n_events;
+  if (latency_mode(n_targets)) return LongEvents{nullptr, nullptr, 128, 256};
+  if (n <= (1 << 18) || n > (1 << 23) || n > 16 * n_targets || eb.max_seg <= 768) return LongEvents{nullptr, nullptr, 256, 256};
+  if (n <= (1 << 20) && n <= 8 * n_targets) return LongEvents{nullptr, nullptr, 64, 128};
   return LongEvents{nullptr, nullptr, 128, 256};
 }
 

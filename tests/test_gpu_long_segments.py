@@ -1,6 +1,6 @@
-"""Targets whose event segment is reduced by many waves: lengths around the limits (128 in short
-launches, 256 in large ones), around multiples of a chunk (256), and a hub with thousands, with
-every lane width and with events of all three kinds in one segment."""
+"""Targets whose event segment is reduced by many waves: lengths around the limits (128 in short launches, 64, 128 or 256 in
+larger ones), around multiples of a chunk (128 or 256), and a hub with thousands, with every lane width and with events of
+all three kinds in one segment."""
 import numpy as np
 import pytest
 
@@ -46,11 +46,9 @@ def test_hub_segments(kind, agg, d, n_src, fan):
     h.ink.close()
 
 
-@pytest.mark.parametrize("kind,agg,d", [("sage", "max", 100), ("sage", "min", 20), ("gin", "sum", 40)])
-@pytest.mark.parametrize("n_src,fan", [(1500, 190), (6000, 190)])     # 285 000 and 1 140 000 events in one layer
-def test_limits_of_mid_size_launches(kind, agg, d, n_src, fan):
-    """Targets with 63 to 300 events, around every limit and chunk that a launch of that many events may take."""
-    n, lengths = n_src + 12000, (63, 64, 65, 127, 128, 129, 192, 193, 255, 256, 257, 300)
+def check_lengths(kind, agg, d, n_src, fan, n_dst):
+    """Targets with 63 to 300 events, around every limit and chunk, among n_src * fan events on n_dst nodes."""
+    n, lengths = n_src + n_dst, (63, 64, 65, 127, 128, 129, 192, 193, 255, 256, 257, 300)
     rng = np.random.default_rng(n_src + d)
     s = np.arange(n_src)
     src = [np.repeat(s, fan)] + [rng.choice(s, size=k, replace=False) for k in lengths]
@@ -65,3 +63,20 @@ def test_limits_of_mid_size_launches(kind, agg, d, n_src, fan):
     assert h.ink.stats()["layers"][0]["n_events"] == len(src)
     h.check_state(exact=exact)
     h.ink.close()
+
+
+SELECT_AND_SUM = [("sage", "max", 100), ("sage", "min", 20), ("gin", "sum", 40)]
+
+
+@pytest.mark.parametrize("kind,agg,d", SELECT_AND_SUM)
+@pytest.mark.parametrize("n_src,fan", [(1500, 190), (6000, 190)])     # 285 000 and 1 140 000 events in one layer
+def test_limits_of_mid_size_launches(kind, agg, d, n_src, fan):
+    """Many events a target: cut from 257 on."""
+    check_lengths(kind, agg, d, n_src, fan, 12000)
+
+
+@pytest.mark.parametrize("kind,agg,d", SELECT_AND_SUM)
+@pytest.mark.parametrize("n_src,n_dst", [(1500, 60000), (1500, 30000), (6000, 120000)])
+def test_low_limits_of_mid_size_launches(kind, agg, d, n_src, n_dst):
+    """5 events a target, up to a million of them: cut from 65 on; 10: from 129 on."""
+    check_lengths(kind, agg, d, n_src, 190, n_dst)

@@ -24,13 +24,16 @@ int main() {
 '''
 
 
-def test_grids_of_the_long_row_kernels(tmp_path):
-    src = tmp_path / "grids.cpp"
-    src.write_text(PROGRAM)
-    exe = tmp_path / "grids"
+def run_program(tmp_path, text):
+    src, exe = tmp_path / "sizes.cpp", tmp_path / "sizes"
+    src.write_text(text)
     subprocess.check_call(["hipcc", "-std=c++17", "-O0", "--offload-arch=gfx950", "-x", "hip", "-I", os.path.join(ROOT, "paper_2309_11071_amd", "csrc"),
                            str(src), "-o", str(exe)], stderr=subprocess.DEVNULL)
-    rows = [tuple(map(int, line.split())) for line in subprocess.check_output([str(exe)], text=True).splitlines()]
+    return [tuple(map(int, line.split())) for line in subprocess.check_output([str(exe)], text=True).splitlines()]
+
+
+def test_grids_of_the_long_row_kernels(tmp_path):
+    rows = run_program(tmp_path, PROGRAM)
     assert len(rows) > 1000
     for chunks, groups, threads in rows:
         assert 0 < groups and groups % 8 == 0 and groups * threads < 2 ** 32
@@ -39,3 +42,36 @@ def test_grids_of_the_long_row_kernels(tmp_path):
         if chunks == 0:                                    # usually there are none: nothing but an empty launch
             assert groups * threads <= 2 ** 20
     assert max(g for _, g, _ in rows) > 2 ** 19               # the bound does not touch what graphs of usual sizes launch
+
+
+SEGMENTS = r'''
+#include <cstdio>
+#include "longev.h"
+int main() {
+  const int64_t events[] = {262144, 262145, 500000, 1000000, 1100000, 2000000, 8000000, 8388609, 20000000};
+  for (int64_t n : events)
+    for (int64_t per : {1, 2, 5, 7, 10, 15, 17, 25, 67, 500})
+      for (int64_t longest : {500, 700, 2000, 100000}) {
+        if (longest < per) continue;
+        const ink::LongEvents L = ink::long_events(ink::EventBounds{n, longest}, n / per);
+        printf("%lld %lld %lld %d %d\n", (long long)n, (long long)(n / per), (long long)longest, L.limit, L.chunk);
+      }
+}
+'''
+
+
+def test_limits_of_long_segments(tmp_path):
+    """Low limits only where few segments are above them: with many events a target, or none that is long, a list of nearly
+    all segments costs more than the chains it cuts."""
+    seen = set()
+    for events, targets, longest, limit, chunk in run_program(tmp_path, SEGMENTS):
+        seen.add((limit, chunk))
+        if targets <= 8192:                                   # short launches
+            assert (limit, chunk) == (128, 256)
+        elif events <= 1 << 18 or events > 1 << 23 or events / targets > 16 or longest <= 700:
+            assert (limit, chunk) == (256, 256), (events, targets, longest)
+        elif events > 1 << 20 or events / targets > 8.1:
+            assert (limit, chunk) == (128, 256), (events, targets, longest)
+        else:
+            assert (limit, chunk) == (64, 128), (events, targets, longest)
+    assert len(seen) == 3
