@@ -40,7 +40,10 @@ inline LongEvents long_events(const EventBounds &eb, int64_t n_targets) {
 }
 
 inline int64_t long_ev_rows(const LongEvents &L, int64_t n_events) { return n_events / L.limit + 1; }
-inline int64_t long_ev_chunks(const LongEvents &L, int64_t n_events) { return n_events / L.chunk + long_ev_rows(L, n_events); }
+// A segment of e > limit events has at most e / chunk + 1 chunks, and at most e / limit if a chunk is two limits or more.
+inline int64_t long_ev_chunks(const LongEvents &L, int64_t n_events) {
+  return (L.chunk >= 2 * L.limit ? 0 : n_events / L.chunk) + long_ev_rows(L, n_events);
+}
 
 // room for every segment and chunk that n_events events can hold, and for the chunks' partial rows
 // (with_ids: value, id, runner-up and flags; else one value); nothing if no segment can be long

@@ -75,3 +75,26 @@ def test_limits_of_long_segments(tmp_path):
         else:
             assert (limit, chunk) == (64, 128), (events, targets, longest)
     assert len(seen) == 3
+
+
+CHUNKS = r'''
+#include <cstdio>
+#include "longev.h"
+int main() {
+  for (int64_t n : {0, 64, 65, 129, 257, 513, 100000, 262145, 1000000, 8000000, 20000000})
+    for (ink::LongEvents L : {ink::LongEvents{nullptr, nullptr, 64, 128}, ink::LongEvents{nullptr, nullptr, 128, 256}, ink::LongEvents{nullptr, nullptr, 256, 256}})
+      printf("%lld %d %d %lld %lld\n", (long long)n, L.limit, L.chunk, (long long)ink::long_ev_rows(L, n), (long long)ink::long_ev_chunks(L, n));
+}
+'''
+
+
+def test_room_for_the_chunks_of_long_segments(tmp_path):
+    """Room for the chunks of any division of the events into segments, and hardly more: at 8M events and 256 columns a
+    chunk too many for every 256 events is a quarter of a gigabyte of partial rows."""
+    for n, limit, chunk, rows, chunks in run_program(tmp_path, CHUNKS):
+        most_rows, most_chunks = n // (limit + 1), 0
+        for s in range(limit + 1, min(n, 4 * chunk) + 1):          # as many segments of s events as there can be, the rest in one more
+            rest = n % s
+            most_chunks = max(most_chunks, n // s * -(-s // chunk) + (-(-rest // chunk) if rest > limit else 0))
+        assert most_rows <= rows <= 1.02 * most_rows + 2
+        assert most_chunks <= chunks <= 1.02 * most_chunks + 3, (n, limit, chunk, chunks, most_chunks)
