@@ -24,7 +24,6 @@
 //     it with the launches of the general path, which finds the targets, the bitmap and the list of long rows
 //     where its own event kernel leaves them
 #include <stddef.h>
-#define INK_LANE_ANEW      // the loop over the layers, below
 #include "events.h"
 #include "graph_one.h"
 #include "select.h"
@@ -67,6 +66,12 @@ struct OneLds {
 
 template <bool IS_MIN> static __shared__ OneLds one_lds;
 
+// A lane's number found anew at every use, and the place in LDS likewise (one_layer, below).
+__device__ __forceinline__ int lane_anew() {
+  int l = lane_id();
+  asm volatile("" : "+v"(l));
+  return l;
+}
 __device__ __forceinline__ OneLds *lds_anew(OneLds *p) {
   typedef __attribute__((address_space(3))) OneLds Lds;
   uint32_t at = (uint32_t)(uint64_t)(Lds *)p;
@@ -81,12 +86,12 @@ struct OneMark {
   __device__ __forceinline__ void operator()(int) const { *flag = 1; }
 };
 
-__device__ __forceinline__ int lanes_before(uint64_t mask) { return __popcll(mask & ((1ull << lane_id()) - 1)); }
+__device__ __forceinline__ int lanes_before(uint64_t mask) { return __popcll(mask & ((1ull << lane_anew()) - 1)); }
 
 // One wave: the layer's nE events in the order of their targets (equal targets in creation order), the distinct targets and
 // where each one's events start.
 __device__ __forceinline__ void order_events(OneLds &S, const OneUpdate *K, int nE, int n_del, int n_chg, int nF) {
-  const int l = lane_id();
+  const int l = lane_anew();
   uint32_t k = 0, v = 0;
   if (l < nE) {
     if (l >= n_del && l < n_del + n_chg) {
@@ -117,7 +122,7 @@ __device__ __forceinline__ void order_events(OneLds &S, const OneUpdate *K, int 
 // Lane i < kOneEvents has target i, the other half the sources; both are ascending and distinct.
 __device__ __forceinline__ void collect_rows_one(OneLds &S, int nT, int nF) {
   static_assert(2 * kOneEvents == kWave, "a lane per candidate");
-  const int l = lane_id(), f = l - kOneEvents;
+  const int l = lane_anew(), f = l - kOneEvents;
   const bool target = l < nT && S.t_chg[l] != 0, source = f >= 0 && f < nF;
   const int id = f < 0 ? (l < nT ? S.t_list[l] : 0) : (source ? S.F[f] : 0);
   const uint64_t targets = __ballot(target);
@@ -140,7 +145,7 @@ __device__ __forceinline__ void collect_rows_one(OneLds &S, int nT, int nF) {
 template <bool IS_MIN, int LPR>
 __device__ __forceinline__ void recompute_long_row(OneLds &S, const AggArgs &a, int v, int nT) {
   constexpr int SLOTS = kMergeFloats / (LPR * 4) < kOneWaves ? kMergeFloats / (LPR * 4) : kOneWaves;
-  const int l = lane_id(), w = wave_id(), t = w * kWave + l, q = l % LPR;
+  const int l = lane_anew(), w = wave_id(), t = w * kWave + l, q = l % LPR;
   const bool lane_on = 4 * q < a.wd;
   const int64_t deg = a.in_deg[v];
   F4 bv; I4 bi; F4 sv; I4 si;
@@ -206,7 +211,7 @@ struct FewRows {
   bool mine;
   f4v b[4][4];
   __device__ __forceinline__ void issue(const OneLayer &p, int c, int ch) {
-    const int l = lane_id(), kq = l >> 4;                            // kq: which of a step's four k
+    const int l = lane_anew(), kq = l >> 4;                            // kq: which of a step's four k
     const int wl = (kq & 1) * 32 + (ct & 1) * 16 + (l & 15);         // the lane of a weight tile that holds this lane's operands
     const f4v *wp = reinterpret_cast<const f4v *>(p.W) + (int64_t)(ch < n_ch ? ch : n_ch - 1) * 8 * p.Np + (ct / 2) * 256 + wl;
 #pragma unroll
@@ -222,7 +227,7 @@ struct FewRows {
       for (int c = 0; c < 4; c++) issue(p, c, 4 * g + c);
   }
   __device__ __forceinline__ void run(OneLds &S, const OneLayer &p, int w, int n_c) {
-    const int l = lane_id(), kq = l >> 4, col = ct * 16 + (l & 15), d4 = xform_self_row(p.d_in);
+    const int l = lane_anew(), kq = l >> 4, col = ct * 16 + (l & 15), d4 = xform_self_row(p.d_in);
     const bool ends = mine && g == (n_blk - 1) % G && col < p.n_out;
     // wave w stages row w
     const int64_t row = w < n_c ? S.rows[w] : 0;
@@ -285,7 +290,7 @@ struct FewRows {
 // products have just released.
 __device__ __forceinline__ void transform_rows(OneLds &S, const OneLayer &p, int n_c) {
   constexpr int NCH = kTileK / 32, XPT = kOneRows * kTileK / 4 / kOneThreads, NR = 16;
-  const int l = lane_id(), w = wave_id(), t = w * kWave + l;
+  const int l = lane_anew(), w = wave_id(), t = w * kWave + l;
   const int rt = w / 8, ct = w % 8;                                  // waves w, w + 4, .. share a SIMD: neighbours in ct do not
   const int d4 = xform_self_row(p.d_in), n_ch = p.Kp / 32;
   const int col = ct * 32 + (l & 31);
@@ -362,7 +367,7 @@ __device__ __forceinline__ void transform_rows(OneLds &S, const OneLayer &p, int
 // The targets, one per wave at a time; exposed rows of moderate length on the spot.
 template <bool IS_MIN, int LPR>
 __device__ __forceinline__ void aggregate_targets(OneLds &S, const AggArgs &a, int w, int nT) {
-  const int q = lane_id() % LPR;
+  const int q = lane_anew() % LPR;
   const bool lane_on = 4 * q < a.wd;
   RowSink exp;
   for (int i = w; i < nT; i += kOneWaves) {
@@ -381,7 +386,7 @@ template <bool IS_MIN>
 __device__ __forceinline__ int one_layer(const OneUpdate *K, int layer) {
   OneLds &S = *lds_anew(&one_lds<IS_MIN>);
   const OneLayer p = K->layer[layer - 1];
-  const int l = lane_id(), w = wave_id(), t = w * kWave + l;
+  const int l = lane_anew(), w = wave_id(), t = w * kWave + l;
   const int n_del = __builtin_amdgcn_readfirstlane(S.n_del), n_seed = __builtin_amdgcn_readfirstlane(S.n_seed);
   const int nF = __builtin_amdgcn_readfirstlane(S.n_f), n_chg = __builtin_amdgcn_readfirstlane(S.n_ev);
   const int nE = ieee_mode_off(__builtin_amdgcn_readfirstlane(n_seed + n_chg));
@@ -465,7 +470,7 @@ __global__ __launch_bounds__(kOneThreads) void k_layers_one(OneUpdate) {
   OneLds &S = one_lds<IS_MIN>;
   // the arguments where the launch has put them: a layer's are found by a running index
   const OneUpdate *K = (const OneUpdate *)__builtin_amdgcn_kernarg_segment_ptr();
-  const int l = lane_id(), w = wave_id(), t = w * kWave + l;
+  const int l = lane_anew(), w = wave_id(), t = w * kWave + l;
   // which are in host memory: the waves bring a line of 64 bytes each; a stage whose first look there is its own takes .7 us longer
   const int n_layers = K->n_layers;
   for (int i = w * 16; i < (int)(offsetof(OneUpdate, layer) / 4) + n_layers * (int)(sizeof(OneLayer) / 4); i += kOneWaves * 16) {

@@ -36,15 +36,7 @@ struct PrimWorkspace {     // scratch shared by scan / compaction / sort calls o
   DevBuf tmpk, tmpv;       // radix ping-pong
 };
 
-#ifdef INK_LANE_ANEW      // (layer_one.hip) found anew at every use: nothing computed from it can be moved out of a loop
-__device__ __forceinline__ int lane_id() {
-  int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  asm volatile("" : "+v"(l));
-  return l;
-}
-#else
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
-#endif
 
 // inclusive scan across the 64 lanes of a wave
 __device__ __forceinline__ int wave_incl_scan(int x) {
