@@ -309,8 +309,9 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_apply_sum(F f, W w, int64
   then();
 }
 
-// ONE_WG: only for functors that do O(1) work per item.  *called: whether `then` will be called (not for no items or very many)
-template <class F, class W, int ITEMS = kScanItems, bool ONE_WG = false, class D = NothingThen>
+// ONE_WG: only for functors that do O(1) work per item.  SHORT: inputs may be of one tile.  *called: whether `then` will be called
+// (not for no items or very many)
+template <class F, class W, int ITEMS = kScanItems, bool ONE_WG = false, class D = NothingThen, bool SHORT = true>
 inline hipError_t tile_scan(PrimWorkspace &ws, F f, W w, int64_t n, int32_t *total, hipStream_t s, D then = D(), bool *called = nullptr) {
   if (called) *called = false;
   if (n <= 0) {
@@ -319,15 +320,17 @@ inline hipError_t tile_scan(PrimWorkspace &ws, F f, W w, int64_t n, int32_t *tot
   }
   int nb = nblocks(n, kScanThreads * ITEMS);
   if (called) *called = nb <= kSumOwnLimit;
-  if (nb == 1) {
-    hipLaunchKernelGGL((k_tile_apply<F, W, ITEMS, D>), dim3(1), dim3(kScanThreads), 0, s, f, w, n,
-                       (const int32_t *)nullptr, total, then);
-    return hipGetLastError();
-  }
-  if (ONE_WG && n <= kOneWgLimit) {
-    hipLaunchKernelGGL((k_tile_scan_one<F, W, D>), dim3(1), dim3(kOneWgThreads), 0, s, f, w, n, total, then);
-    return hipGetLastError();
-  }
+  if constexpr (SHORT)
+    if (nb == 1) {
+      hipLaunchKernelGGL((k_tile_apply<F, W, ITEMS, D>), dim3(1), dim3(kScanThreads), 0, s, f, w, n,
+                         (const int32_t *)nullptr, total, then);
+      return hipGetLastError();
+    }
+  if constexpr (ONE_WG)
+    if (n <= kOneWgLimit) {
+      hipLaunchKernelGGL((k_tile_scan_one<F, W, D>), dim3(1), dim3(kOneWgThreads), 0, s, f, w, n, total, then);
+      return hipGetLastError();
+    }
   INK_TRY(ws.blk.reserve((size_t)nb * sizeof(int32_t)));
   int32_t *blk = ws.blk.as<int32_t>();
   hipLaunchKernelGGL((k_tile_reduce<F, ITEMS>), dim3(nb), dim3(kScanThreads), 0, s, f, n, blk);

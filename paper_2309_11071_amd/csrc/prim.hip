@@ -111,7 +111,8 @@ hipError_t segment_heads(PrimWorkspace &ws, const uint32_t *keys, int64_t n, int
                          int32_t *seg, int32_t *count, hipStream_t s, const int32_t *n_dev, const RecordTo *record, bool *given) {
   const LoadHead f{keys, n_dev};
   const StoreHead w{keys, uniq, seg, n, n_dev};
-  if (record) return tile_scan<LoadHead, StoreHead, kScanItems, true, PublishThen>(ws, f, w, n, count, s, PublishThen{*record}, given);
+  // a record is for lists whose count the host waits for, which are long
+  if (record) return tile_scan<LoadHead, StoreHead, kScanItems, false, PublishThen, false>(ws, f, w, n, count, s, PublishThen{*record}, given);
   return tile_scan<LoadHead, StoreHead, kScanItems, true>(ws, f, w, n, count, s);
 }
 
