@@ -189,18 +189,21 @@ __device__ __forceinline__ void combine_row(const AggArgs &a, int v, int p0, int
 // Long launches stay with whole rows: the slices leave a third of the reads beyond the L2 out (16.6M -> 10.8M of 128
 // bytes, 625k nodes and rows of 128 floats), but the chunks' fixed costs four times over take as much (10 to 600k nodes,
 // rows of 128 and 256 floats: 0.94 to 1.0 of the speed).
-template <bool IS_MIN, int ROW>
+template <bool IS_MIN, int ROW, bool ARRIVE>
 __global__ __launch_bounds__(1024) void k_big_short(AggArgs a, Counters *cnt, int slices, BigParts part, uint64_t *chg, int compare, int32_t *arrived) {
   constexpr int LPR = kSliceLanes, NW = 16;
   __shared__ float sv[NW][kWave * 4], ss[NW][kWave * 4];
   __shared__ int si[NW][kWave * 4], sj[NW][kWave * 4];
   const int total = ieee_mode_off(cnt->v[C_NCHUNK]), n_big = cnt->v[C_NBIG];
   const bool whole = slices > 2 && total > kSlicedItems / slices;
-  auto stored = [&](int i, int v) {          // a row's last part combines it: a launch of its own took 6 to 7 us, this 4 to 5 (100 updates on 10k nodes 338 -> 324 us a pass)
-    const int chunks = big_row_chunks(a.in_deg[v], a.big.chunk), p0 = a.big.base[i];
-    if (last_to_arrive(arrived + i, whole ? chunks : chunks * slices)) combine_row<IS_MIN, ROW, 2, true>(a, v, p0, p0 + chunks, part, chg, compare, cnt);
+  // ARRIVE (few chunks): a row's last part combines it; a launch of its own took 6 to 7 us, this 4 to 5 (100 updates on 10k nodes 338 -> 324 us a pass)
+  auto stored = [&](int i, int v) {
+    if constexpr (ARRIVE) {
+      const int chunks = big_row_chunks(a.in_deg[v], a.big.chunk), p0 = a.big.base[i];
+      if (last_to_arrive(arrived + i, whole ? chunks : chunks * slices)) combine_row<IS_MIN, ROW, 2, true>(a, v, p0, p0 + chunks, part, chg, compare, cnt);
+    }
   };
-  if (whole) { whole_chunks<IS_MIN, ROW, NW, true>(a, total, n_big, sv, si, ss, sj, part, stored); return; }
+  if (whole) { whole_chunks<IS_MIN, ROW, NW, ARRIVE>(a, total, n_big, sv, si, ss, sj, part, stored); return; }
   const int l = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int q = l % LPR, items = slice_items(total, slices);
   for (int b = blockIdx.x; b < items; b += gridDim.x) {
@@ -225,14 +228,14 @@ __global__ __launch_bounds__(1024) void k_big_short(AggArgs a, Counters *cnt, in
       int xi = si[0][col], xj = sj[0][col];
       for (int ww = 1; ww < NW; ww++) merge2i<IS_MIN>(sv[ww][col], si[ww][col], ss[ww][col], sj[ww][col], xv, xi, xs, xj);
       const int64_t o = (int64_t)cg * a.wd + c0 + col;
-      put_part<true>(part.v + o, xv); put_part<true>(part.i + o, xi); put_part<true>(part.s + o, xs); put_part<true>(part.j + o, xj);
+      put_part<ARRIVE>(part.v + o, xv); put_part<ARRIVE>(part.i + o, xi); put_part<ARRIVE>(part.s + o, xs); put_part<ARRIVE>(part.j + o, xj);
     }
     if (w == 0) stored(i, v);
     __syncthreads();
   }
 }
 
-// A kernel for long launches, whose rows are many.  (In theirs the chunk kernel's registers would suffer from the combination: 80 -> 126.)
+// A kernel for launches whose rows are many.  (In theirs the chunk kernel's registers would suffer from the combination: 80 -> 126.)
 template <bool IS_MIN, int LPR>
 __global__ __launch_bounds__(64) void k_big_final(AggArgs a, BigParts part, uint64_t *chg, int compare, Counters *cnt) {
   const int n_big = cnt->v[C_NBIG];
@@ -396,16 +399,17 @@ __global__ __launch_bounds__(64) void k_ev_final(AggArgs a, const int32_t *targe
 static int lanes_per_row(int ld) { return ld <= 64 ? 16 : (ld <= 128 ? 32 : 64); }
 
 template <bool IS_MIN, int LPR>
-static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compare, int64_t n_rows_max) {
+static hipError_t run_big(ink_ctx *c, const AggArgs &a, uint64_t *chg, int compare, int64_t n_rows_max, bool few) {
   const BigParts part{c->big_part_v.as<float>(), c->big_part_i.as<int32_t>(), c->big_part_s.as<float>(), c->big_part_j.as<int32_t>()};
-  if (latency_mode(n_rows_max)) {
+  const bool latency = latency_mode(n_rows_max), arrive = latency && few;
+  if (latency) {
     const int slices = big_slices(a.wd);
-    hipLaunchKernelGGL((k_big_short<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, c->d_cnt, slices, part, chg,
-                       compare, c->arrived);
-  } else {
+    const dim3 grid(big_grid(c, a.big_chunks, slices, true));
+    if (arrive) hipLaunchKernelGGL((k_big_short<IS_MIN, LPR, true>), grid, dim3(1024), 0, c->stream, a, c->d_cnt, slices, part, chg, compare, c->arrived);
+    else hipLaunchKernelGGL((k_big_short<IS_MIN, LPR, false>), grid, dim3(1024), 0, c->stream, a, c->d_cnt, slices, part, chg, compare, c->arrived);
+  } else
     hipLaunchKernelGGL((k_big_partial<IS_MIN, LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, (const Counters *)c->d_cnt, part);
-    hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, part, chg, compare, c->d_cnt);
-  }
+  if (!arrive) hipLaunchKernelGGL((k_big_final<IS_MIN, LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, part, chg, compare, c->d_cnt);
   return hipGetLastError();
 }
 
@@ -433,7 +437,7 @@ static hipError_t full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targets
     INK_TRY(hipGetLastError());
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
-  return run_big<IS_MIN, LPR>(c, a, chg, compare, n_targets);
+  return run_big<IS_MIN, LPR>(c, a, chg, compare, n_targets, combine_on_arrival(a, false));
 }
 
 template <bool IS_MIN, int LPR, bool INLINE>
@@ -486,7 +490,7 @@ static hipError_t events_t(ink_ctx *c, const AggArgs &a_in, const int32_t *targe
     INK_TRY(hipGetLastError());
   }
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
-  return run_big<IS_MIN, LPR>(c, a, chg, 1, n_targets);
+  return run_big<IS_MIN, LPR>(c, a, chg, 1, n_targets, a.big_chunks <= kArriveChunksEvents);
 }
 
 #define DISPATCH(fn, ...)                                                         \
@@ -512,7 +516,7 @@ static hipError_t long_rows_t(ink_ctx *c, const AggArgs &a_in, int64_t n_targets
   AggArgs a = a_in;
   a.big = big_rows_of(c, kBigChunk);
   KernelTimer kt(c, a.layer, INK_K_AGG_LONG);
-  return run_big<IS_MIN, LPR>(c, a, chg, 1, n_targets);
+  return run_big<IS_MIN, LPR>(c, a, chg, 1, n_targets, a.big_chunks <= kArriveChunksEvents);
 }
 
 hipError_t agg_select_long_rows(ink_ctx *c, const AggArgs &a, int64_t n_targets, uint64_t *chg) {

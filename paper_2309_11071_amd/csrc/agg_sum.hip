@@ -245,8 +245,9 @@ __device__ __forceinline__ void combine_sum_row(const AggArgs &a, int v, int p0,
 }
 
 // Launches of few targets: 16 waves a chunk, and its slices in workgroups of their own unless they are many (kSlicedItems); a row's
-// last part combines it.  64 registers, so that a CU holds two.
-template <int LPR>
+// last part combines it if there are few (combine_on_arrival).  64 registers, so that a CU holds two, which leaves 12 or 20
+// bytes a lane of half of the forms to scratch.
+template <int LPR, bool ARRIVE>
 __global__ __launch_bounds__(1024, 8) void k_sum_big_short(AggArgs a, const Counters *cnt, int slices, float *part, uint64_t *chg, int compare,
                                                            int32_t *arrived) {
   constexpr int NW = 16;
@@ -254,11 +255,13 @@ __global__ __launch_bounds__(1024, 8) void k_sum_big_short(AggArgs a, const Coun
   const int total = cnt->v[C_NCHUNK], n_big = cnt->v[C_NBIG];
   const bool whole_rows = total > kSlicedItems / slices;
   auto stored = [&](int i, int v) {
-    const int chunks = big_row_chunks(a.in_deg[v], a.big.chunk), p0 = a.big.base[i];
-    if (last_to_arrive(arrived + i, whole_rows ? chunks : chunks * slices)) combine_sum_row<LPR, 4, true>(a, v, p0, p0 + chunks, part, chg, compare);
+    if constexpr (ARRIVE) {
+      const int chunks = big_row_chunks(a.in_deg[v], a.big.chunk), p0 = a.big.base[i];
+      if (last_to_arrive(arrived + i, whole_rows ? chunks : chunks * slices)) combine_sum_row<LPR, 4, true>(a, v, p0, p0 + chunks, part, chg, compare);
+    }
   };
-  if (whole_rows) whole_sum_chunks<LPR, NW, true>(a, total, n_big, whole, part, stored);
-  else sum_slices<NW, true>(a, total, n_big, slices, sliced, part, stored);
+  if (whole_rows) whole_sum_chunks<LPR, NW, ARRIVE>(a, total, n_big, whole, part, stored);
+  else sum_slices<NW, ARRIVE>(a, total, n_big, slices, sliced, part, stored);
 }
 
 template <int LPR>
@@ -515,14 +518,18 @@ static hipError_t sum_full_t(ink_ctx *c, const AggArgs &a_in, const int32_t *tar
   const int slices = big_slices(a.wd);
   const Counters *cnt = c->d_cnt;
   float *part = c->big_part_v.as<float>();
-  if (latency)
-    hipLaunchKernelGGL((k_sum_big_short<LPR>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part, chg,
+  const bool arrive = latency && combine_on_arrival(a, true);
+  if (arrive)
+    hipLaunchKernelGGL((k_sum_big_short<LPR, true>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part, chg,
+                       compare, c->arrived);
+  else if (latency)
+    hipLaunchKernelGGL((k_sum_big_short<LPR, false>), dim3(big_grid(c, a.big_chunks, slices, true)), dim3(1024), 0, c->stream, a, cnt, slices, part, chg,
                        compare, c->arrived);
   else if (whole)
     hipLaunchKernelGGL((k_sum_big_partial<LPR>), dim3(big_grid(c, a.big_chunks, 1, false)), dim3(256), 0, c->stream, a, cnt, part);
   else
     hipLaunchKernelGGL(k_sum_big_slices, dim3(big_grid(c, a.big_chunks, slices, false)), dim3(256), 0, c->stream, a, cnt, slices, part);
-  if (!latency) hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)part, chg, compare, cnt);
+  if (!arrive) hipLaunchKernelGGL((k_sum_big_final<LPR>), dim3(kBigGrid), dim3(64), 0, c->stream, a, (const float *)part, chg, compare, cnt);
   return hipGetLastError();
 }
 

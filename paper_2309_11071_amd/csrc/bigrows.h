@@ -1,6 +1,6 @@
 // Work list for rows with more than kBigDeg in-neighbours: each such row is cut into chunks of
 // kBigChunk neighbours (kBigChunkSum for long launches of sums), one workgroup per chunk, then one wave per row combines its chunks in
-// order; in short launches the wave that finishes a row's last chunk does.  A row takes its chunks when it is listed, so the plan stands when the list does (a scan of the list for it was one or
+// order; in short launches of few chunks the wave that finishes a row's last chunk does.  A row takes its chunks when it is listed, so the plan stands when the list does (a scan of the list for it was one or
 // two launches more), and the chunk / row kernels run a fixed grid that strides over it, so no host round trip is
 // needed; with no long rows they return at once.
 #pragma once
@@ -81,7 +81,7 @@ __device__ __forceinline__ void list_big_row(const BigRows &b, Counters *cnt, in
   b.base[i] = base;
 }
 
-// Short launches have no kernel that combines a row's parts: the wave that stores the last of them does.  The parts are then stored
+// Short launches of few chunks have no kernel that combines a row's parts: the wave that stores the last of them does.  The parts are then stored
 // and read past the L2s of the XCDs (COHERENT), a store is waited for before it is counted, and the count is 0 again afterwards.
 // True for the last of `units`.  (A launch of at most kLatencyTargets targets lists at most as many rows: ink_ctx::arrived.  With
 // fences instead, which write back and invalidate, the last part took 1.5 us longer.)
@@ -96,6 +96,16 @@ __device__ __forceinline__ bool last_to_arrive(int32_t *at, int units) {
   if (lane_id() == 0) __hip_atomic_store(at, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
 }
+// That pays while there are few of them: a launch saved is 2 to 6 us, but every part is stored and read past the caches and waited for
+// while the rest of its workgroup stands.  Inferences of 1500 to 8000 nodes, two layers, at the expected chunks in brackets (of an R-MAT graph
+// half to one and a half times as many are there), us, with a kernel that combines / by the last to arrive: max of 128 columns 120 / 114 (219),
+// 176 / 176 (391), 294 / 315 (1172), 687 / 753 (5859); of 64 88 / 86 (219), 107 / 113 (366), 144 / 160 (782), 475 / 650 (5859); min of 250
+// 182 / 174 (98), 205 / 210 (366), 383 / 397 (977); GCN of 250 118 / 116 (98), 153 / 157 (586), 371 / 405 (5859).  Sums of at most 128
+// columns, a quarter of the stores and fewer rows above the limit, longer: GIN of 128 110 / 105 (391), 152 / 149 (1953), 206 / 207 (3126),
+// 261 / 265 (5859), mean of 64 123 / 120 (1953), 190 / 192 (5859).  Behind the events of an update, at twice the chunks of the last
+// one: 100 updates of max on 8000 nodes with 20 neighbours each 334 / 326, 500 with 150 each, some 600 chunks, 556 / 561.
+constexpr int64_t kArriveChunks = 256, kArriveChunksSum = 2048, kArriveChunksEvents = 1024;
+inline bool combine_on_arrival(const AggArgs &a, bool sums) { return a.big_chunks <= (sums && a.wd <= 128 ? kArriveChunksSum : kArriveChunks); }
 template <bool COHERENT, class T> __device__ __forceinline__ void put_part(T *p, T x) {
   if constexpr (COHERENT) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   else *p = x;

@@ -98,3 +98,23 @@ def test_room_for_the_chunks_of_long_segments(tmp_path):
             most_chunks = max(most_chunks, n // s * -(-s // chunk) + (-(-rest // chunk) if rest > limit else 0))
         assert most_rows <= rows <= 1.02 * most_rows + 2
         assert most_chunks <= chunks <= 1.02 * most_chunks + 3, (n, limit, chunk, chunks, most_chunks)
+
+
+COMBINE = r'''
+#include <cstdio>
+#include "bigrows.h"
+int main() {
+  for (int64_t chunks : {0, 1, 200, 366, 782, 1953, 3126, 5859})
+    for (int wd : {4, 64, 128, 132, 256})
+      for (int sums = 0; sums < 2; sums++) {
+        ink::AggArgs a{};
+        a.big_chunks = chunks; a.wd = wd;
+        printf("%lld %d %d %d\n", (long long)chunks, wd, sums, (int)ink::combine_on_arrival(a, sums != 0));
+      }
+}
+'''
+
+
+def test_many_parts_of_long_rows_have_a_kernel_that_combines_them(tmp_path):
+    for chunks, wd, sums, arrive in run_program(tmp_path, COMBINE):
+        assert arrive == (chunks <= (1953 if sums and wd <= 128 else 200)), (chunks, wd, sums)
