@@ -28,6 +28,8 @@
  *     can be used on any stream.  A successful update ends with a record that the device writes to the
  *     host when everything else is done: its last kernel, which writes nothing after that record, may for
  *     a moment still show as running on the stream.  A call that returns an error leaves nothing running.
+ *     The calling thread polls for such records: it keeps a host core busy for up to a millisecond per record
+ *     and blocks only then.  A layer of an update has one to three records, small updates have one for all.
  *   - Node ids are int32 in [0, n_nodes); the graph is a simple directed graph without self
  *     loops.  Edge batches never change n_nodes (the paper's update stream holds edges only,
  *     Sec. 2.1); it grows only through ink_add_nodes, up to ink_options.node_capacity.

@@ -328,7 +328,8 @@ __device__ __forceinline__ void combine_segment(const AggArgs &a, const int32_t 
 }
 
 // One workgroup per chunk of a long segment: its waves take a quarter of the events each.  ARRIVE (short launches): the segment's last chunk
-// combines it; a launch of its own took 4 to 5 us, most often for nothing.
+// combines it; a launch of its own took 4 to 5 us, most often for nothing.  (With the decision of a target in it the kernel has 105 registers
+// instead of 79, four waves a SIMD instead of six; a short launch has a wave or two.)
 template <bool IS_MIN, int LPR, bool ARRIVE>
 __global__ __launch_bounds__(256) void k_ev_partial(AggArgs a, const int32_t *targets, const int32_t *seg, const uint32_t *ev,
                                                     LongEvents lng, EvPart part, uint64_t *chg, Counters *cnt, int32_t *arrived) {

@@ -734,7 +734,7 @@ hipError_t ink::read_counters(ink_ctx *c, bool end_batch) {
 }
 
 // Waits until the record with this sequence number has arrived: a spin of up to a millisecond, as long as all but the largest layers
-// take, then the blocking wait, whose wake-up is 15 to 20 us.  Spins of .15 and 1 ms, us a pass: 10000 updates at hubs of 612k nodes 2107 / 2076,
+// take and a host core's time until then (ink.h), then the blocking wait, whose wake-up is 15 to 20 us.  Spins of .15 and 1 ms, us a pass: 10000 updates at hubs of 612k nodes 2107 / 2076,
 // 1000 feature rows on 200k nodes 1461 / 1430, GCN of 57M edges 2797 / 2758.
 hipError_t ink::wait_published(ink_ctx *c, const uint32_t *h_seq, uint32_t seq) {
   hipError_t e;
@@ -1727,7 +1727,7 @@ static ink_status apply_updates_impl(ink_ctx *c, const ink_edge_update *upd, int
   memset(&c->stats, 0, sizeof(c->stats));
   c->stats.n_layers = c->n_layers;
   int64_t n_ins = 0, n_del = 0;
-  bool one = false;            // the first layers may have run in one workgroup each
+  bool one = false;            // graph stage and first layers may have run in one launch (layers_one_begin)
   if (n > 0) {
     Prof p(c, INK_T_GRAPH);
     // a device batch is read where it is; a short host batch from pinned memory, by the one kernel that reads it

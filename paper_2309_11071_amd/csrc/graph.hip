@@ -640,6 +640,9 @@ __device__ __forceinline__ int batch_bad(const int32_t *chunk_err, int n_chunks)
 // reads took 31 us out of the L2, 10 chunks) and finds the places of 256 of them: the searches are what takes the time, and with
 // 1024 a workgroup four times as many of them share a CU's LDS (10000 entries 26 -> 12 us, with the reads of a step asked for together).
 constexpr int kMergeThreads = 256, kMergeParts = kOneChunk / kMergeThreads;
+// Chunks a kernel is built for: the searches of a thread advance through all of them, and a chunk is 8 KB of a CU's 160, so up to ten leave
+// room for two workgroups.  3 chunks, us, built for 4 / 10 / 16: 5.8 / 8.6 / 11.0; 4 6.0 / 8.2 / 11.1; 5 - / 8.6 / 11.2; 10 - / 9.0 / 11.7; 16 12.2.
+constexpr int kMergeFew = 4, kMergeTwoOnCu = 160 * 1024 / 2 / (kOneChunk * (int)sizeof(uint64_t));
 template <int C>               // at least n_chunks: chunks past them repeat the first, and what is found there is not used
 __global__ __launch_bounds__(kMergeThreads) void k_short_merge(int n, int n_chunks, ShortSide in, ShortSide out, const int32_t *chunk_err) {
   const int part = (int)blockIdx.x % kMergeParts, b = (int)blockIdx.x / kMergeParts;
@@ -1021,8 +1024,8 @@ static ink_status graph_apply_short(ink_ctx *c, const RawUpdate *raw, int64_t n6
     hipLaunchKernelGGL(k_short_sort, dim3(2 * n_chunks), dim3(kOneChunk), 0, s, raw, n, c->n, n_chunks, sd[0], sd[1], chunk_err);
 #define INK_MERGE(C) \
   hipLaunchKernelGGL(k_short_merge<C>, dim3(2 * n_chunks * kMergeParts), dim3(kMergeThreads), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err)
-    if (n_chunks <= 4) INK_MERGE(4);
-    else if (n_chunks <= 10) INK_MERGE(10);
+    if (n_chunks <= kMergeFew) INK_MERGE(kMergeFew);
+    else if (n_chunks <= kMergeTwoOnCu) INK_MERGE(kMergeTwoOnCu);
     else INK_MERGE(kMaxChunks);
 #undef INK_MERGE
     hipLaunchKernelGGL(k_short_heads, dim3(2 * n_chunks), dim3(kOneChunk), 0, s, n, n_chunks, sd[0], sd[1], (const int32_t *)chunk_err, g);
