@@ -12,8 +12,10 @@
 //   * all layers are in one launch, so that the code is in the instruction cache from the second on: a layer of its own launch
 //     cost 2.2 us between the launches and 1.6 until its first event.
 // One edge on 1.25M vertices, three layers of one event each, rows of 128 floats: 18.4 us a layer as launches of workgroup-wide
-// stages (transform 6.3, order 1.6, row collection 1.8, emission 1.6, the event 2.3 to 3.7), now 10 (weights, inputs and products 5.4, the
-// event as before, arguments .6, order .35, emission .5); a pass of two updates 208 -> 174 us, on 10k vertices, rows of 64, 126 -> 100.
+// stages (transform 6.3, order 1.6, row collection 1.8, emission 1.6, the event 2.3 to 3.7), now 10.8 by the clock in here (event
+// 3.0, weights asked for 2.0, rows known .5, inputs, products and stores 3.8, emission .7, order .5, from the layer before .5; rows of 64 floats
+// 8.0: 3.5, 1.0, .4, 1.6, .7, .5, .5; graph stage 4.7, records 1.7); a pass of two updates 208 -> 174 us, on 10k vertices, rows of 64, 126 -> 100; of
+// 200 distinct updates the median call 96 -> 72 and 48 -> 33.
 // Nothing waits for the host: a layer finds its size on the device, and the first one that is too large ends the launch, as does a
 // batch that the graph stage leaves to its longer forms.  (The graph stage as a launch in front: 2 us more an update, a pass of two
 // 129 -> 125 us on 1.25M vertices, 99.4 -> 97.2 on 10k.)
